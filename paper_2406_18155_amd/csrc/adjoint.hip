@@ -60,7 +60,7 @@ __device__ __forceinline__ void zero(Mat<d>& m) {
 // Adjoint pair item: ybar += W(at PJ) T + c T with T = O(at PI) kb, and the
 // local sensitivities G (along PJ, left factor T) and H (along PI, left
 // factor X' = W(at PJ) kb), both against y.
-template <int d, int NR, int PI, int PJ, int RB>
+template <int d, int NR, int PI, int PJ, bool PAR, int RB>
 __device__ __forceinline__ void group_pair_adj(const Op<d>& O, const Op<d>& W, float c,
                                                const Vec<RB>& kb, const Vec<RB>& y,
                                                Vec<RB>& yb, Mat<d>& G, Mat<d>& H) {
@@ -77,6 +77,7 @@ __device__ __forceinline__ void group_pair_adj(const Op<d>& O, const Op<d>& W, f
         float sr = 0.f, sim = 0.f;
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(ai, b)) continue;
           const float orr = O.re[ai * d + b], oi = O.im[ai * d + b];
           const float xr = kb.re[r0 + b * si_ + aj * sj_], xi = kb.im[r0 + b * si_ + aj * sj_];
           sr = fmaf(orr, xr, sr);
@@ -96,6 +97,7 @@ __device__ __forceinline__ void group_pair_adj(const Op<d>& O, const Op<d>& W, f
         float sim = fmaf(c, ti[ai][aj], yb.im[r0 + ai * si_ + aj * sj_]);
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(aj, b)) continue;
           const float wr = W.re[aj * d + b], wi = W.im[aj * d + b];
           sr = fmaf(wr, tr[ai][b], sr);
           sr = fmaf(-wi, ti[ai][b], sr);
@@ -110,6 +112,7 @@ __device__ __forceinline__ void group_pair_adj(const Op<d>& O, const Op<d>& W, f
     for (int a = 0; a < d; ++a)
 #pragma unroll
       for (int b = 0; b < d; ++b) {
+        if (!entry<PAR>(a, b)) continue;
         float gr = G.re[a * d + b], gi = G.im[a * d + b];
 #pragma unroll
         for (int ai = 0; ai < d; ++ai) {
@@ -130,6 +133,7 @@ __device__ __forceinline__ void group_pair_adj(const Op<d>& O, const Op<d>& W, f
         float sr = 0.f, sim = 0.f;
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(aj, b)) continue;
           const float wr = W.re[aj * d + b], wi = W.im[aj * d + b];
           const float xr = kb.re[r0 + ai * si_ + b * sj_], xi = kb.im[r0 + ai * si_ + b * sj_];
           sr = fmaf(wr, xr, sr);
@@ -144,6 +148,7 @@ __device__ __forceinline__ void group_pair_adj(const Op<d>& O, const Op<d>& W, f
     for (int a = 0; a < d; ++a)
 #pragma unroll
       for (int b = 0; b < d; ++b) {
+        if (!entry<PAR>(a, b)) continue;
         float hr = H.re[a * d + b], hi = H.im[a * d + b];
 #pragma unroll
         for (int aj = 0; aj < d; ++aj) {
@@ -160,7 +165,7 @@ __device__ __forceinline__ void group_pair_adj(const Op<d>& O, const Op<d>& W, f
 }
 
 // K_ab += sum over fibers along P of conj(kb[a]) y[b]
-template <int d, int NR, int P, int RB>
+template <int d, int NR, int P, bool PAR, int RB>
 __device__ __forceinline__ void mode_reduce(const Vec<RB>& kb, const Vec<RB>& y, Mat<d>& K) {
   using C = Cfg<d, NR>;
   constexpr int st = C::stride(P);
@@ -170,6 +175,7 @@ __device__ __forceinline__ void mode_reduce(const Vec<RB>& kb, const Vec<RB>& y,
     for (int a = 0; a < d; ++a)
 #pragma unroll
       for (int b = 0; b < d; ++b) {
+        if (a != b && !entry<PAR>(a, b)) continue;   // the diagonal serves d eps
         const float kr = kb.re[r0 + a * st], ki = kb.im[r0 + a * st];
         const float yr = y.re[r0 + b * st], yi = y.im[r0 + b * st];
         K.re[a * d + b] = fmaf(kr, yr, fmaf(ki, yi, K.re[a * d + b]));
@@ -180,7 +186,7 @@ __device__ __forceinline__ void mode_reduce(const Vec<RB>& kb, const Vec<RB>& y,
 
 // Real frame (real operators, vectors rotated by D(t)^dag): the same items
 // with real O and W; the folds with real tables need only Im G, Im H, Im K.
-template <int d, int NR, int PI, int PJ, int RB>
+template <int d, int NR, int PI, int PJ, bool PAR, int RB>
 __device__ __forceinline__ void group_pair_adj_real(const ROp<d>& O, const ROp<d>& W, float c,
                                                     const Vec<RB>& kb, const Vec<RB>& y,
                                                     Vec<RB>& yb, Mat<d>& G, Mat<d>& H) {
@@ -197,6 +203,7 @@ __device__ __forceinline__ void group_pair_adj_real(const ROp<d>& O, const ROp<d
         float sr = 0.f, sim = 0.f;
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(ai, b)) continue;
           const float o = O.v[ai * d + b];
           sr = fmaf(o, kb.re[r0 + b * si_ + aj * sj_], sr);
           sim = fmaf(o, kb.im[r0 + b * si_ + aj * sj_], sim);
@@ -212,6 +219,7 @@ __device__ __forceinline__ void group_pair_adj_real(const ROp<d>& O, const ROp<d
         float sim = fmaf(c, ti[ai][aj], yb.im[r0 + ai * si_ + aj * sj_]);
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(aj, b)) continue;
           const float w = W.v[aj * d + b];
           sr = fmaf(w, tr[ai][b], sr);
           sim = fmaf(w, ti[ai][b], sim);
@@ -224,6 +232,7 @@ __device__ __forceinline__ void group_pair_adj_real(const ROp<d>& O, const ROp<d
     for (int a = 0; a < d; ++a)
 #pragma unroll
       for (int b = 0; b < d; ++b) {
+        if (!entry<PAR>(a, b)) continue;
         float gi = G.im[a * d + b];
 #pragma unroll
         for (int ai = 0; ai < d; ++ai) {
@@ -240,6 +249,7 @@ __device__ __forceinline__ void group_pair_adj_real(const ROp<d>& O, const ROp<d
         float sr = 0.f, sim = 0.f;
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(aj, b)) continue;
           const float w = W.v[aj * d + b];
           sr = fmaf(w, kb.re[r0 + ai * si_ + b * sj_], sr);
           sim = fmaf(w, kb.im[r0 + ai * si_ + b * sj_], sim);
@@ -251,6 +261,7 @@ __device__ __forceinline__ void group_pair_adj_real(const ROp<d>& O, const ROp<d
     for (int a = 0; a < d; ++a)
 #pragma unroll
       for (int b = 0; b < d; ++b) {
+        if (!entry<PAR>(a, b)) continue;
         float hi = H.im[a * d + b];
 #pragma unroll
         for (int aj = 0; aj < d; ++aj) {
@@ -263,7 +274,7 @@ __device__ __forceinline__ void group_pair_adj_real(const ROp<d>& O, const ROp<d
 }
 
 // Im K_ab += sum over fibers along P of Im(conj(kb[a]) y[b])
-template <int d, int NR, int P, int RB>
+template <int d, int NR, int P, bool PAR, int RB>
 __device__ __forceinline__ void mode_reduce_real(const Vec<RB>& kb, const Vec<RB>& y, Mat<d>& K) {
   using C = Cfg<d, NR>;
   constexpr int st = C::stride(P);
@@ -272,18 +283,21 @@ __device__ __forceinline__ void mode_reduce_real(const Vec<RB>& kb, const Vec<RB
 #pragma unroll
     for (int a = 0; a < d; ++a)
 #pragma unroll
-      for (int b = 0; b < d; ++b)
+      for (int b = 0; b < d; ++b) {
+        if (a != b && !entry<PAR>(a, b)) continue;
         K.im[a * d + b] = fmaf(kb.re[r0 + a * st], y.im[r0 + b * st],
                                fmaf(-kb.im[r0 + a * st], y.re[r0 + b * st], K.im[a * d + b]));
+      }
   });
 }
 
 // Im( sum_ab X_ab M_ab ) for a uniform operator X from the table
-template <int d>
+template <int d, bool PAR>
 __device__ __forceinline__ float im_dot(kptr<c32> X, const Mat<d>& M) {
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < d * d; ++i) {
+    if (!entry<PAR>(i / d, i % d)) continue;
     s = fmaf(X[i].x, M.im[i], fmaf(X[i].y, M.re[i], s));
   }
   return s;
@@ -291,15 +305,16 @@ __device__ __forceinline__ float im_dot(kptr<c32> X, const Mat<d>& M) {
 
 // Im( sum_ab X_ab M_ab ) with X at element offset off of the stage's complex
 // table, or (real frame) of the real table.
-template <int d, bool RF>
+template <int d, int EV>
 __device__ __forceinline__ float tdot(kptr<c32> ops, kptr<float> rops, int off, const Mat<d>& M) {
-  if constexpr (RF) {
+  if constexpr (ev_real(EV)) {
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < d * d; ++i) s = fmaf(rops[off + i], M.im[i], s);
+    for (int i = 0; i < d * d; ++i)
+      if (entry<ev_parity(EV)>(i / d, i % d)) s = fmaf(rops[off + i], M.im[i], s);
     return s;
   } else {
-    return im_dot<d>(ops + off, M);
+    return im_dot<d, ev_parity(EV)>(ops + off, M);
   }
 }
 
@@ -364,12 +379,13 @@ __device__ __forceinline__ gptr<T> fresh(T* p) {
 // (read only during the stage), and every layout gathers its elements from
 // there; yb accumulates layout by layout and passes to the next layout in
 // natural order through region 2.
-template <int d, int NR, int MP, int RB, bool RF>
+template <int d, int NR, int MP, int RB, int EV>
 __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
                                           int vstride, bool lds_ok, int tc, int lane,
                                           LaneAcc& A, double* accw, kptr<c32> ops,
                                           kptr<float> rops, kptr<float> cq,
                                           kptr<float> dcq, Vec<RB>& yb) {
+  constexpr bool RF = ev_real(EV), PAR = ev_parity(EV);
   constexpr int dd = d * d;
   const int L = P->L;
   const int npulse = P->npulse, N = P->N;
@@ -412,14 +428,14 @@ __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
         zero(H);
         if constexpr (RF) {
           ROp<d> O, W;
-          load_rop<d>(rops + c_slot * dd, O);
-          load_rop<d>(rops + uni(P->off_pair + c_pair * dd), W);
-          group_pair_adj_real<d, NR, p, p + 1>(O, W, coef(cq, uni(C.cidx)), kb, y, yb, G, H);
+          load_rop<d, PAR>(rops + c_slot * dd, O);
+          load_rop<d, PAR>(rops + uni(P->off_pair + c_pair * dd), W);
+          group_pair_adj_real<d, NR, p, p + 1, PAR>(O, W, coef(cq, uni(C.cidx)), kb, y, yb, G, H);
         } else {
           Op<d> O, W;
-          load_op<d>(ops + c_slot * dd, O);
-          load_op<d>(ops + uni(P->off_pair + c_pair * dd), W);
-          group_pair_adj<d, NR, p, p + 1>(O, W, coef(cq, uni(C.cidx)), kb, y, yb, G, H);
+          load_op<d, PAR>(ops + c_slot * dd, O);
+          load_op<d, PAR>(ops + uni(P->off_pair + c_pair * dd), W);
+          group_pair_adj<d, NR, p, p + 1, PAR>(O, W, coef(cq, uni(C.cidx)), kb, y, yb, G, H);
         }
         const int mi = uni(C.mode_i);
         if (mi >= 0) {
@@ -431,17 +447,17 @@ __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
           for (int q = 0; q < nq; ++q) {
             const int e = uni(P->pair_coup[pr][q]);
             const int sj = uni(P->pair_pslot[pr][q]);
-            fold(A, accw, npulse + 3 * N + e, tdot<d, RF>(ops, rops, sj * dd, G), lane);
+            fold(A, accw, npulse + 3 * N + e, tdot<d, EV>(ops, rops, sj * dd, G), lane);
             const float ge = unif(P->coup_g[e]);
 #pragma unroll
             for (int th = 0; th < 3; ++th)
-              dacc[(p + 1) * 3 + th] += ge * tdot<d, RF>(ops, rops, offd + (sj * 3 + th) * dd, G);
+              dacc[(p + 1) * 3 + th] += ge * tdot<d, EV>(ops, rops, offd + (sj * 3 + th) * dd, G);
           }
           // real frame, first factor i times real: its folds change sign (i^2)
           const float hs = RF ? (float)uni(C.hsign) : 1.f;
 #pragma unroll
           for (int th = 0; th < 3; ++th)
-            dacc[p * 3 + th] += hs * tdot<d, RF>(ops, rops, offd + (c_slot * 3 + th) * dd, H);
+            dacc[p * 3 + th] += hs * tdot<d, EV>(ops, rops, offd + (c_slot * 3 + th) * dd, H);
         }
       });
     });
@@ -452,19 +468,21 @@ __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
         const float c = coef(cq, uni(C1.cidx));
         if constexpr (RF) {
           ROp<d> O;
-          load_rop<d>(rops + uni(C1.slot) * dd, O);
+          load_rop<d, PAR>(rops + uni(C1.slot) * dd, O);
 #pragma unroll
-          for (int i = 0; i < dd; ++i) O.v[i] *= c;
-          contract_acc_real<d, NR, p>(O, kb, yb);
+          for (int i = 0; i < dd; ++i)
+            if (entry<PAR>(i / d, i % d)) O.v[i] *= c;
+          contract_acc_real<d, NR, p, PAR>(O, kb, yb);
         } else {
           Op<d> O;
-          load_op<d>(ops + uni(C1.slot) * dd, O);
+          load_op<d, PAR>(ops + uni(C1.slot) * dd, O);
 #pragma unroll
           for (int i = 0; i < dd; ++i) {
+            if (!entry<PAR>(i / d, i % d)) continue;
             O.re[i] *= c;
             O.im[i] *= c;
           }
-          contract_acc<d, NR, p>(O, kb, yb);
+          contract_acc<d, NR, p, PAR>(O, kb, yb);
         }
       });
     }
@@ -486,9 +504,9 @@ __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
           Mat<d> K;
           zero(K);
           if constexpr (RF)
-            mode_reduce_real<d, NR, p>(kb, y, K);
+            mode_reduce_real<d, NR, p, PAR>(kb, y, K);
           else
-            mode_reduce<d, NR, p>(kb, y, K);
+            mode_reduce<d, NR, p, PAR>(kb, y, K);
           float dev[3] = {0.f, 0.f, 0.f};
 #pragma unroll
           for (int th = 0; th < 3; ++th)
@@ -499,7 +517,7 @@ __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
           for (int kk = k0; kk < k1; ++kk) {
             const auto& R = P->drives[uni(P->mdrv[kk])];
             const int rslot = uni(R.slot);
-            const float s_im = wave_sum(tdot<d, RF>(ops, rops, rslot * dd, K));
+            const float s_im = wave_sum(tdot<d, EV>(ops, rops, rslot * dd, K));
             const int par0 = uni(R.par0), npar = uni(R.npar);
             for (int q = 0; q < npar; ++q)
               acc_add(A, accw, par0 + q, (double)dcq[par0 + q] * (double)s_im, lane);
@@ -507,7 +525,7 @@ __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
               const float c = cq[uni(R.cidx)];
 #pragma unroll
               for (int th = 0; th < 3; ++th)
-                dev[th] = fmaf(c, tdot<d, RF>(ops, rops, offd + (rslot * 3 + th) * dd, K), dev[th]);
+                dev[th] = fmaf(c, tdot<d, EV>(ops, rops, offd + (rslot * 3 + th) * dd, K), dev[th]);
             }
           }
 #pragma unroll
@@ -545,10 +563,11 @@ __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
 // costate starts from the cotangent and the accumulators from zero; else both
 // continue from lamstate / part exactly (chunked runs are bitwise identical to
 // one launch).
-// RF: the real frame (vectors rotated by D(t)^dag at every stage, real
-// operator and derivative tables; yb rotated back).
-template <int d, int NR, int MP, bool RF>
+// EV: the evaluation (real frame: vectors rotated by D(t)^dag at every stage, real
+// operator and derivative tables, yb rotated back; parity).
+template <int d, int NR, int MP, int EV>
 __device__ __forceinline__ void adjoint_block(const AdjItem& I) {
+  constexpr bool RF = ev_real(EV);
   constexpr int RB = Cfg<d, NR>::RB;
   extern __shared__ c32 lds[];
   kptr<Plan> P = kconst(I.P);
@@ -680,7 +699,7 @@ __device__ __forceinline__ void adjoint_block(const AdjItem& I) {
           const int qn = s > 0 ? stage_q(n, s - 1) : stage_q(n - 1, 3);   // >= 0
           pf = ((const float*)(uintptr_t)(pf_base + (size_t)qn * pf_stride))[tc * 16];
         }
-        adj_stage<d, NR, MP, RB, RF>(P, lds, cbase, vstride, lds_ok, tc, lane, A, accw, ops, rops,
+        adj_stage<d, NR, MP, RB, EV>(P, lds, cbase, vstride, lds_ok, tc, lane, A, accw, ops, rops,
                                      cq, dcq, yb);
         if constexpr (RF) {
           // back to the interaction picture: yb <- D yb
@@ -735,15 +754,15 @@ __device__ __forceinline__ void adjoint_block(const AdjItem& I) {
   for (int i = threadIdx.x; i < 4 * nacc; i += blockDim.x) partb[i] = i < nwaves * nacc ? acc[i] : 0.0;
 }
 
-template <int d, int NR, int MP, bool RF>
+template <int d, int NR, int MP, int EV>
 __global__ void __launch_bounds__(WG_THREADS) adjoint_kernel(AdjItem I) {
   I.cb = blockIdx.x;
-  adjoint_block<d, NR, MP, RF>(I);
+  adjoint_block<d, NR, MP, EV>(I);
 }
 
-template <int d, int NR, int MP, bool RF>
+template <int d, int NR, int MP, int EV>
 __global__ void __launch_bounds__(WG_THREADS) adjoint_batched_kernel(const AdjItem* __restrict__ items) {
-  adjoint_block<d, NR, MP, RF>(items[blockIdx.x]);
+  adjoint_block<d, NR, MP, EV>(items[blockIdx.x]);
 }
 
 namespace {
@@ -752,35 +771,43 @@ size_t adj_lds_bytes(const Plan& P) {
   return sizeof(c32) * 3 * (size_t)P.CPW * P.D + sizeof(double) * 4 * (size_t)P.nacc;
 }
 
-template <int d, int NR, int MP, bool RF>
+template <int d, int NR, int MP, int EV>
 hipError_t run_adj1(const AdjItem& I0, int nwg, int wg, size_t sh, hipStream_t s) {
-  hipFuncSetAttribute((const void*)adjoint_kernel<d, NR, MP, RF>,
+  hipFuncSetAttribute((const void*)adjoint_kernel<d, NR, MP, EV>,
                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-  hipLaunchKernelGGL((adjoint_kernel<d, NR, MP, RF>), dim3(nwg), dim3(wg), sh, s, I0);
+  hipLaunchKernelGGL((adjoint_kernel<d, NR, MP, EV>), dim3(nwg), dim3(wg), sh, s, I0);
   return hipGetLastError();
 }
 
 template <int d, int NR, int MP>
-hipError_t run_adj(const AdjItem& I0, int nwg, int wg, size_t sh, bool rf, hipStream_t s) {
+hipError_t run_adj(const AdjItem& I0, int nwg, int wg, size_t sh, int ev, hipStream_t s) {
   if (sh > 160 * 1024) return hipErrorInvalidValue;
-  if (rf) return run_adj1<d, NR, MP, true>(I0, nwg, wg, sh, s);
-  return run_adj1<d, NR, MP, false>(I0, nwg, wg, sh, s);
+  switch (ev) {
+    case 0: return run_adj1<d, NR, MP, 0>(I0, nwg, wg, sh, s);
+    case 1: return run_adj1<d, NR, MP, 1>(I0, nwg, wg, sh, s);
+    case 2: return run_adj1<d, NR, MP, 2>(I0, nwg, wg, sh, s);
+    default: return run_adj1<d, NR, MP, 3>(I0, nwg, wg, sh, s);
+  }
 }
 
-template <int d, int NR, int MP, bool RF>
+template <int d, int NR, int MP, int EV>
 hipError_t run_adj_batched1(const AdjItem* items, int nitems, int wg, size_t sh, hipStream_t s) {
-  hipFuncSetAttribute((const void*)adjoint_batched_kernel<d, NR, MP, RF>,
+  hipFuncSetAttribute((const void*)adjoint_batched_kernel<d, NR, MP, EV>,
                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-  hipLaunchKernelGGL((adjoint_batched_kernel<d, NR, MP, RF>), dim3(nitems), dim3(wg), sh, s, items);
+  hipLaunchKernelGGL((adjoint_batched_kernel<d, NR, MP, EV>), dim3(nitems), dim3(wg), sh, s, items);
   return hipGetLastError();
 }
 
 template <int d, int NR, int MP>
-hipError_t run_adj_batched(const AdjItem* items, int nitems, int wg, size_t sh, bool rf,
+hipError_t run_adj_batched(const AdjItem* items, int nitems, int wg, size_t sh, int ev,
                            hipStream_t s) {
   if (sh > 160 * 1024) return hipErrorInvalidValue;
-  if (rf) return run_adj_batched1<d, NR, MP, true>(items, nitems, wg, sh, s);
-  return run_adj_batched1<d, NR, MP, false>(items, nitems, wg, sh, s);
+  switch (ev) {
+    case 0: return run_adj_batched1<d, NR, MP, 0>(items, nitems, wg, sh, s);
+    case 1: return run_adj_batched1<d, NR, MP, 1>(items, nitems, wg, sh, s);
+    case 2: return run_adj_batched1<d, NR, MP, 2>(items, nitems, wg, sh, s);
+    default: return run_adj_batched1<d, NR, MP, 3>(items, nitems, wg, sh, s);
+  }
 }
 
 }  // namespace
@@ -813,9 +840,9 @@ scp_status launch_adjoint_impl(const scp_system* sys, const void* ckpt, const vo
               (float2*)lamstate, part, sys->d_ph, sys->d_rops, ce, nckpt, S, 0, seg, seg,
               seg == nckpt - 1 ? 1 : 0, 0};
     hipError_t e = hipErrorInvalidValue;
-    const bool rf = P.real_frame != 0;
+    const int ev = plan_eval(P);
 #define X(D_, NR_, MP_) \
-  if (d == D_ && NR == NR_ && MP == MP_) e = run_adj<D_, NR_, MP_>(I, nwg, P.WG, sh, rf, s);
+  if (d == D_ && NR == NR_ && MP == MP_) e = run_adj<D_, NR_, MP_>(I, nwg, P.WG, sh, ev, s);
     SCP_ADJ_ALL(X)
 #undef X
     if (e != hipSuccess) return fail(SCP_EHIP, std::string("adjoint launch: ") + hipGetErrorString(e));
@@ -824,11 +851,11 @@ scp_status launch_adjoint_impl(const scp_system* sys, const void* ckpt, const vo
   return SCP_OK;
 }
 
-scp_status launch_adjoint_batched(int d, int NR, int MP, bool rf, const AdjItem* items, int nitems,
+scp_status launch_adjoint_batched(int d, int NR, int MP, int ev, const AdjItem* items, int nitems,
                                   int wg, size_t sh, hipStream_t s) {
   hipError_t e = hipErrorInvalidValue;
 #define X(D_, NR_, MP_) \
-  if (d == D_ && NR == NR_ && MP == MP_) e = run_adj_batched<D_, NR_, MP_>(items, nitems, wg, sh, rf, s);
+  if (d == D_ && NR == NR_ && MP == MP_) e = run_adj_batched<D_, NR_, MP_>(items, nitems, wg, sh, ev, s);
   SCP_ADJ_ALL(X)
 #undef X
   if (e != hipSuccess)

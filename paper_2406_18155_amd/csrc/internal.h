@@ -82,7 +82,14 @@ struct Plan {
   // layout, then from ph_thr the NT * d thread-position phases.
   int32_t real_frame;
   int32_t ph_row, ph_thr;
+  // Parity: every operator in use and every derivative of one connects levels
+  // of unlike parity only (transmons at n_g = 0, fluxoniums at half flux: n and
+  // phi are odd under the reflection that the Hamiltonian keeps).
+  int32_t parity;
 };
+
+// The evaluation of a plan, as the kernels' template parameter EV has it.
+inline int plan_eval(const Plan& P) { return (P.real_frame ? 1 : 0) | (P.parity ? 2 : 0); }
 
 // Work descriptor of one workgroup of a (possibly batched) forward launch:
 // CPW columns (column block cb) of one system for steps [n0, n1).

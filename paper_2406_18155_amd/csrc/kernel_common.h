@@ -34,6 +34,19 @@ __device__ __forceinline__ float unif(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
+// Evaluation of a kernel instance (template parameter EV): bit 0, the real
+// frame; bit 1, parity: every operator, pair operator and derivative operator
+// connects levels of unlike parity only, so its entries (a, b) with a + b even
+// are zero and their multiply-adds, loads and sensitivities are left out.
+constexpr int EV_REAL = 1, EV_PARITY = 2;
+constexpr bool ev_real(int ev) { return (ev & EV_REAL) != 0; }
+constexpr bool ev_parity(int ev) { return (ev & EV_PARITY) != 0; }
+// Entry (a, b) of an operator may be non-zero.
+template <bool PAR>
+__device__ __forceinline__ constexpr bool entry(int a, int b) {
+  return !PAR || ((a + b) & 1) != 0;
+}
+
 template <int d, int NR>
 struct Cfg {
   static constexpr int RB = (NR == 1) ? d : (NR == 2) ? d * d : (NR == 3) ? d * d * d
@@ -121,10 +134,11 @@ struct Op {
   float im[d * d];
 };
 
-template <int d>
+template <int d, bool PAR = false>
 __device__ __forceinline__ void load_op(kptr<c32> p, Op<d>& o) {
 #pragma unroll
   for (int i = 0; i < d * d; ++i) {
+    if (!entry<PAR>(i / d, i % d)) continue;
     o.re[i] = p[i].x;
     o.im[i] = p[i].y;
   }
@@ -153,7 +167,7 @@ constexpr int fiber_base(int b) {
 }
 
 // out += (O at position P) in, for all fibers along P
-template <int d, int NR, int P, int RB>
+template <int d, int NR, int P, bool PAR = false, int RB>
 __device__ __forceinline__ void contract_acc(const Op<d>& O, const Vec<RB>& in, Vec<RB>& out) {
   using C = Cfg<d, NR>;
   constexpr int st = C::stride(P);
@@ -164,6 +178,7 @@ __device__ __forceinline__ void contract_acc(const Op<d>& O, const Vec<RB>& in, 
       float sr = out.re[r0 + a * st], si = out.im[r0 + a * st];
 #pragma unroll
       for (int b = 0; b < d; ++b) {
+        if (!entry<PAR>(a, b)) continue;
         const float orr = O.re[a * d + b], oi = O.im[a * d + b];
         const float xr = in.re[r0 + b * st], xi = in.im[r0 + b * st];
         sr = fmaf(orr, xr, sr);
@@ -179,7 +194,7 @@ __device__ __forceinline__ void contract_acc(const Op<d>& O, const Vec<RB>& in, 
 
 // Group item with one partner: out += W(at PJ) O(at PI) in + c O(at PI) in,
 // evaluated block by block over the (PI, PJ) plane to keep temporaries small.
-template <int d, int NR, int PI, int PJ, int RB>
+template <int d, int NR, int PI, int PJ, bool PAR, int RB>
 __device__ __forceinline__ void group_pair(const Op<d>& O, const Op<d>& W, float c,
                                            const Vec<RB>& in, Vec<RB>& out) {
   using C = Cfg<d, NR>;
@@ -195,6 +210,7 @@ __device__ __forceinline__ void group_pair(const Op<d>& O, const Op<d>& W, float
         float sr = 0.f, sim = 0.f;
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(ai, b)) continue;
           const float orr = O.re[ai * d + b], oi = O.im[ai * d + b];
           const float xr = in.re[r0 + b * si_ + aj * sj_], xi = in.im[r0 + b * si_ + aj * sj_];
           sr = fmaf(orr, xr, sr);
@@ -214,6 +230,7 @@ __device__ __forceinline__ void group_pair(const Op<d>& O, const Op<d>& W, float
         float sim = fmaf(c, ti[ai][aj], out.im[r0 + ai * si_ + aj * sj_]);
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(aj, b)) continue;
           const float wr = W.re[aj * d + b], wi = W.im[aj * d + b];
           sr = fmaf(wr, tr[ai][b], sr);
           sr = fmaf(-wi, ti[ai][b], sr);
@@ -248,7 +265,7 @@ __device__ __forceinline__ float coef(kptr<float> cq, int cidx) {
 // Apply all terms of layout l: out += V_l(t) in.  Positions are compile-time:
 // pair terms at (p, p+1), MP of them per position pair; drive-only and
 // diagonal terms behind one per-layout flag each.
-template <int d, int NR, int MP, int RB>
+template <int d, int NR, int MP, bool PAR, int RB>
 __device__ __forceinline__ void apply_layout(kptr<Plan> P, int l,
                                              kptr<c32> ops,
                                              kptr<float> cq, const Vec<RB>& in,
@@ -260,9 +277,9 @@ __device__ __forceinline__ void apply_layout(kptr<Plan> P, int l,
       constexpr int m = decltype(Mm)::value;
       const auto& C = P->cpair[l][p][m];
       Op<d> O, W;
-      load_op<d>(ops + uni(C.slot) * dd, O);
-      load_op<d>(ops + uni(P->off_pair + C.pair * dd), W);
-      group_pair<d, NR, p, p + 1>(O, W, coef(cq, uni(C.cidx)), in, out);
+      load_op<d, PAR>(ops + uni(C.slot) * dd, O);
+      load_op<d, PAR>(ops + uni(P->off_pair + C.pair * dd), W);
+      group_pair<d, NR, p, p + 1, PAR>(O, W, coef(cq, uni(C.cidx)), in, out);
     });
   });
   if (uni(P->has_single[l])) {
@@ -270,14 +287,15 @@ __device__ __forceinline__ void apply_layout(kptr<Plan> P, int l,
       constexpr int p = decltype(Pp)::value;
       const auto& C1 = P->csingle[l][p];
       Op<d> O;
-      load_op<d>(ops + uni(C1.slot) * dd, O);
+      load_op<d, PAR>(ops + uni(C1.slot) * dd, O);
       const float c = coef(cq, uni(C1.cidx));
 #pragma unroll
       for (int i = 0; i < dd; ++i) {
+        if (!entry<PAR>(i / d, i % d)) continue;
         O.re[i] *= c;
         O.im[i] *= c;
       }
-      contract_acc<d, NR, p>(O, in, out);
+      contract_acc<d, NR, p, PAR>(O, in, out);
     });
   }
   if (uni(P->has_diag[l])) {
@@ -299,14 +317,15 @@ struct ROp {
   float v[d * d];
 };
 
-template <int d>
+template <int d, bool PAR = false>
 __device__ __forceinline__ void load_rop(kptr<float> p, ROp<d>& o) {
 #pragma unroll
-  for (int i = 0; i < d * d; ++i) o.v[i] = p[i];
+  for (int i = 0; i < d * d; ++i)
+    if (entry<PAR>(i / d, i % d)) o.v[i] = p[i];
 }
 
 // out += (O at position P) in, O real
-template <int d, int NR, int P, int RB>
+template <int d, int NR, int P, bool PAR = false, int RB>
 __device__ __forceinline__ void contract_acc_real(const ROp<d>& O, const Vec<RB>& in, Vec<RB>& out) {
   using C = Cfg<d, NR>;
   constexpr int st = C::stride(P);
@@ -317,6 +336,7 @@ __device__ __forceinline__ void contract_acc_real(const ROp<d>& O, const Vec<RB>
       float sr = out.re[r0 + a * st], si = out.im[r0 + a * st];
 #pragma unroll
       for (int b = 0; b < d; ++b) {
+        if (!entry<PAR>(a, b)) continue;
         const float o = O.v[a * d + b];
         sr = fmaf(o, in.re[r0 + b * st], sr);
         si = fmaf(o, in.im[r0 + b * st], si);
@@ -328,7 +348,7 @@ __device__ __forceinline__ void contract_acc_real(const ROp<d>& O, const Vec<RB>
 }
 
 // out += W(at PJ) O(at PI) in + c O(at PI) in, O and W real
-template <int d, int NR, int PI, int PJ, int RB>
+template <int d, int NR, int PI, int PJ, bool PAR, int RB>
 __device__ __forceinline__ void group_pair_real(const ROp<d>& O, const ROp<d>& W, float c,
                                                 const Vec<RB>& in, Vec<RB>& out) {
   using C = Cfg<d, NR>;
@@ -344,6 +364,7 @@ __device__ __forceinline__ void group_pair_real(const ROp<d>& O, const ROp<d>& W
         float sr = 0.f, sim = 0.f;
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(ai, b)) continue;
           const float o = O.v[ai * d + b];
           sr = fmaf(o, in.re[r0 + b * si_ + aj * sj_], sr);
           sim = fmaf(o, in.im[r0 + b * si_ + aj * sj_], sim);
@@ -359,6 +380,7 @@ __device__ __forceinline__ void group_pair_real(const ROp<d>& O, const ROp<d>& W
         float sim = fmaf(c, ti[ai][aj], out.im[r0 + ai * si_ + aj * sj_]);
 #pragma unroll
         for (int b = 0; b < d; ++b) {
+          if (!entry<PAR>(aj, b)) continue;
           const float w = W.v[aj * d + b];
           sr = fmaf(w, tr[ai][b], sr);
           sim = fmaf(w, ti[ai][b], sim);
@@ -370,7 +392,7 @@ __device__ __forceinline__ void group_pair_real(const ROp<d>& O, const ROp<d>& W
 }
 
 // apply_layout with the un-rotated (real) operators
-template <int d, int NR, int MP, int RB>
+template <int d, int NR, int MP, bool PAR, int RB>
 __device__ __forceinline__ void apply_layout_real(kptr<Plan> P, int l, kptr<float> ops,
                                                   kptr<float> cq, const Vec<RB>& in,
                                                   Vec<RB>& out) {
@@ -381,9 +403,9 @@ __device__ __forceinline__ void apply_layout_real(kptr<Plan> P, int l, kptr<floa
       constexpr int m = decltype(Mm)::value;
       const auto& C = P->cpair[l][p][m];
       ROp<d> O, W;
-      load_rop<d>(ops + uni(C.slot) * dd, O);
-      load_rop<d>(ops + uni(P->off_pair + C.pair * dd), W);
-      group_pair_real<d, NR, p, p + 1>(O, W, coef(cq, uni(C.cidx)), in, out);
+      load_rop<d, PAR>(ops + uni(C.slot) * dd, O);
+      load_rop<d, PAR>(ops + uni(P->off_pair + C.pair * dd), W);
+      group_pair_real<d, NR, p, p + 1, PAR>(O, W, coef(cq, uni(C.cidx)), in, out);
     });
   });
   if (uni(P->has_single[l])) {
@@ -391,11 +413,12 @@ __device__ __forceinline__ void apply_layout_real(kptr<Plan> P, int l, kptr<floa
       constexpr int p = decltype(Pp)::value;
       const auto& C1 = P->csingle[l][p];
       ROp<d> O;
-      load_rop<d>(ops + uni(C1.slot) * dd, O);
+      load_rop<d, PAR>(ops + uni(C1.slot) * dd, O);
       const float c = coef(cq, uni(C1.cidx));
 #pragma unroll
-      for (int i = 0; i < dd; ++i) O.v[i] *= c;
-      contract_acc_real<d, NR, p>(O, in, out);
+      for (int i = 0; i < dd; ++i)
+        if (entry<PAR>(i / d, i % d)) O.v[i] *= c;
+      contract_acc_real<d, NR, p, PAR>(O, in, out);
     });
   }
   if (uni(P->has_diag[l])) {
@@ -488,7 +511,7 @@ __device__ __forceinline__ int thread_base(kptr<Plan> P, int l, int tc) {
 // before the previous barrier; y's region is never written during a stage).
 // k leaves in the base layout (L-1).  On return ka is the region that the
 // last move did not use, which may be written next without a barrier.
-template <int d, int NR, int MP, int RB, bool RF = false>
+template <int d, int NR, int MP, int RB, int EV = 0>
 __device__ __forceinline__ void stage_apply(kptr<Plan> P, c32* lds, int cbase, int rstride,
                                             bool lds_ok, int tc, kptr<c32> ops, kptr<float> rops,
                                             kptr<float> cq, int iy, int& ka, int& kb, Vec<RB>& k) {
@@ -517,10 +540,10 @@ __device__ __forceinline__ void stage_apply(kptr<Plan> P, c32* lds, int cbase, i
 #pragma unroll
       for (int r = 0; r < RB; ++r) y.re[r] = y.im[r] = 0.f;
     }
-    if constexpr (RF)
-      apply_layout_real<d, NR, MP, RB>(P, l, rops, cq, y, k);
+    if constexpr (ev_real(EV))
+      apply_layout_real<d, NR, MP, ev_parity(EV), RB>(P, l, rops, cq, y, k);
     else
-      apply_layout<d, NR, MP, RB>(P, l, ops, cq, y, k);
+      apply_layout<d, NR, MP, ev_parity(EV), RB>(P, l, ops, cq, y, k);
   }
 }
 
@@ -547,10 +570,10 @@ __device__ __forceinline__ void comp_add(float& hi, float& lo, float dx) {
 // the dropped lo is below their rounding).  If ystore != nullptr the four
 // stage inputs are also written there in natural order (ystore is the
 // column's base; stride ystride between stages) for the adjoint.
-// RF (real frame): LDS receives D(t_s)^dag y_s, the layouts apply the
+// Real frame (EV): LDS receives D(t_s)^dag y_s, the layouts apply the
 // un-rotated real operators (table block 0), and k_s = D(t_s) (R y'_s); the
 // phases come from the half-step rows of ph.  ystore still receives y_s.
-template <int d, int NR, int MP, int RB, bool RF = false>
+template <int d, int NR, int MP, int RB, int EV = 0>
 __device__ __forceinline__ void rk4_step(kptr<Plan> P, c32* lds, int cbase, int rstride,
                                          bool lds_ok, bool active, int tc, int TPC,
                                          kptr<c32> optab, kptr<float> rops, kptr<float> ctab,
@@ -558,6 +581,7 @@ __device__ __forceinline__ void rk4_step(kptr<Plan> P, c32* lds, int cbase, int 
                                          Vec<RB>& hi, Vec<RB>& lo, int& iy, int& ka, int& kb,
                                          c32* __restrict__ ystore, size_t ystride,
                                          int& pq, c32& pt_q) {
+  constexpr bool RF = ev_real(EV);
   const float h = P->h;
   const int ng = uni(P->ngroups);
   const int bq = uni(P->block_q);
@@ -622,7 +646,7 @@ __device__ __forceinline__ void rk4_step(kptr<Plan> P, c32* lds, int cbase, int 
       const int qn = s < 3 ? stage_q(n, s + 1) : stage_q(n + 1, 0);   // <= 2 N
       pf = ((const float*)(uintptr_t)(pf_base + (size_t)qn * pf_stride))[tc * 16];
     }
-    stage_apply<d, NR, MP, RB, RF>(P, lds, cbase, rstride, lds_ok, tc, ops, rops, cq, iy, ka, kb,
+    stage_apply<d, NR, MP, RB, EV>(P, lds, cbase, rstride, lds_ok, tc, ops, rops, cq, iy, ka, kb,
                                    k);
     pf_sink += pf;
     if (RF) {

@@ -28,8 +28,8 @@ namespace scp {
 // register-order slices, touched only at the start and the end of a run.
 // REC: the adjoint's recompute of one segment: start from the checkpoint slab
 // ckin and write the four stage inputs of every step to ystore.
-// RF: the real-frame stepper (all terms real; frame phases from I.ph).
-template <int d, int NR, int MP, bool REC, bool RF>
+// EV: the evaluation (real frame: all terms real, frame phases from I.ph; parity).
+template <int d, int NR, int MP, bool REC, int EV>
 __device__ __forceinline__ void rk4_block(const FwdItem& I) {
   constexpr int RB = Cfg<d, NR>::RB;
   extern __shared__ c32 lds[];
@@ -107,13 +107,13 @@ __device__ __forceinline__ void rk4_block(const FwdItem& I) {
       }
     }
     if (REC)
-      rk4_step<d, NR, MP, RB, RF>(P, lds, cbase, vstride, lds_ok, active, tc, TPC, optab, rops,
+      rk4_step<d, NR, MP, RB, EV>(P, lds, cbase, vstride, lds_ok, active, tc, TPC, optab, rops,
                                   ctab, ph, n, hi, lo, iy, ka, kb,
                                   (c32*)I.ystore + (size_t)(active ? col : 0) * D +
                                       (size_t)(n - n0) * 4 * S * D,
                                   (size_t)S * D, pq, pt_q);
     else
-      rk4_step<d, NR, MP, RB, RF>(P, lds, cbase, vstride, lds_ok, active, tc, TPC, optab, rops,
+      rk4_step<d, NR, MP, RB, EV>(P, lds, cbase, vstride, lds_ok, active, tc, TPC, optab, rops,
                                   ctab, ph, n, hi, lo, iy, ka, kb, nullptr, 0, pq, pt_q);
   }
   if (!active) return;
@@ -142,16 +142,16 @@ __device__ __forceinline__ void rk4_block(const FwdItem& I) {
   }
 }
 
-template <int d, int NR, int MP, bool REC, bool RF>
+template <int d, int NR, int MP, bool REC, int EV>
 __global__ void __launch_bounds__(WG_THREADS) rk4_kernel(FwdItem I) {
   I.cb = blockIdx.x;
-  rk4_block<d, NR, MP, REC, RF>(I);
+  rk4_block<d, NR, MP, REC, EV>(I);
 }
 
 // Batched launch: workgroup b runs items[b] (requests of one size class).
-template <int d, int NR, int MP, bool REC, bool RF>
+template <int d, int NR, int MP, bool REC, int EV>
 __global__ void __launch_bounds__(WG_THREADS) rk4_batched_kernel(const FwdItem* __restrict__ items) {
-  rk4_block<d, NR, MP, REC, RF>(items[blockIdx.x]);
+  rk4_block<d, NR, MP, REC, EV>(items[blockIdx.x]);
 }
 
 // out = V(t) y at one stage time, through the same stage_apply as the stepper.
@@ -213,20 +213,24 @@ namespace {
 
 template <int d, int NR, int MP>
 struct Launch {
-  template <bool REC, bool RF>
+  template <bool REC, int EV>
   static hipError_t run1(const scp_system* sys, const FwdItem& I, int S, hipStream_t s) {
     const Plan& P = sys->plan;
     const int nwg = (S + P.CPW - 1) / P.CPW;
     const size_t sh = sizeof(c32) * 3 * (size_t)P.CPW * P.D;
-    hipFuncSetAttribute((const void*)rk4_kernel<d, NR, MP, REC, RF>,
+    hipFuncSetAttribute((const void*)rk4_kernel<d, NR, MP, REC, EV>,
                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    hipLaunchKernelGGL((rk4_kernel<d, NR, MP, REC, RF>), dim3(nwg), dim3(P.WG), sh, s, I);
+    hipLaunchKernelGGL((rk4_kernel<d, NR, MP, REC, EV>), dim3(nwg), dim3(P.WG), sh, s, I);
     return hipGetLastError();
   }
   template <bool REC>
   static hipError_t run(const scp_system* sys, const FwdItem& I, int S, hipStream_t s) {
-    if (sys->plan.real_frame) return run1<REC, true>(sys, I, S, s);
-    return run1<REC, false>(sys, I, S, s);
+    switch (plan_eval(sys->plan)) {
+      case 0: return run1<REC, 0>(sys, I, S, s);
+      case 1: return run1<REC, 1>(sys, I, S, s);
+      case 2: return run1<REC, 2>(sys, I, S, s);
+      default: return run1<REC, 3>(sys, I, S, s);
+    }
   }
   static hipError_t rk4(const scp_system* sys, const float2* psi0, float2* psiT, float2* state,
                         float2* lo, float4* ckpt, int ce, int S, int n0, int n1, hipStream_t s) {
@@ -240,26 +244,22 @@ struct Launch {
               ystore, sys->d_ph, sys->d_rops, 1, S, 0, n0, n1, 0};
     return run<true>(sys, I, S, s);
   }
-  template <bool REC, bool RF>
+  template <bool REC, int EV>
   static void batched1(const FwdItem* items, int nitems, int wg, size_t sh, hipStream_t s) {
-    hipFuncSetAttribute((const void*)rk4_batched_kernel<d, NR, MP, REC, RF>,
+    hipFuncSetAttribute((const void*)rk4_batched_kernel<d, NR, MP, REC, EV>,
                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    hipLaunchKernelGGL((rk4_batched_kernel<d, NR, MP, REC, RF>), dim3(nitems), dim3(wg), sh, s,
+    hipLaunchKernelGGL((rk4_batched_kernel<d, NR, MP, REC, EV>), dim3(nitems), dim3(wg), sh, s,
                        items);
   }
-  static hipError_t batched(const FwdItem* items, int nitems, int wg, size_t sh, bool rec,
-                            bool rf, hipStream_t s) {
-    if (rf) {
-      if (rec)
-        batched1<true, true>(items, nitems, wg, sh, s);
-      else
-        batched1<false, true>(items, nitems, wg, sh, s);
-      return hipGetLastError();
+  template <bool REC>
+  static hipError_t batched(const FwdItem* items, int nitems, int wg, size_t sh, int ev,
+                            hipStream_t s) {
+    switch (ev) {
+      case 0: batched1<REC, 0>(items, nitems, wg, sh, s); break;
+      case 1: batched1<REC, 1>(items, nitems, wg, sh, s); break;
+      case 2: batched1<REC, 2>(items, nitems, wg, sh, s); break;
+      default: batched1<REC, 3>(items, nitems, wg, sh, s); break;
     }
-    if (rec)
-      batched1<true, false>(items, nitems, wg, sh, s);
-    else
-      batched1<false, false>(items, nitems, wg, sh, s);
     return hipGetLastError();
   }
   static hipError_t apply(const scp_system* sys, const float2* ops, const float* cq,
@@ -333,10 +333,11 @@ scp_status launch_apply(const scp_system* sys, int step, int stage, const float2
 }  // namespace scp
 
 namespace scp {
-scp_status launch_rk4_batched(int d, int NR, int MP, bool rf, const FwdItem* items, int nitems,
+scp_status launch_rk4_batched(int d, int NR, int MP, int ev, const FwdItem* items, int nitems,
                               int wg, size_t sh, bool recompute, hipStream_t s) {
   hipError_t e = dispatch(d, NR, MP, [&](auto L) {
-    return decltype(L)::batched(items, nitems, wg, sh, recompute, rf, s);
+    return recompute ? decltype(L)::template batched<true>(items, nitems, wg, sh, ev, s)
+                     : decltype(L)::template batched<false>(items, nitems, wg, sh, ev, s);
   });
   if (e != hipSuccess) return fail(SCP_EHIP, std::string("batched rk4 launch: ") + hipGetErrorString(e));
   return SCP_OK;

@@ -36,9 +36,9 @@
 
 namespace scp {
 
-scp_status launch_rk4_batched(int d, int NR, int MP, bool rf, const FwdItem* items, int nitems, int wg,
+scp_status launch_rk4_batched(int d, int NR, int MP, int ev, const FwdItem* items, int nitems, int wg,
                               size_t sh, bool recompute, hipStream_t s);
-scp_status launch_adjoint_batched(int d, int NR, int MP, bool rf, const AdjItem* items, int nitems, int wg,
+scp_status launch_adjoint_batched(int d, int NR, int MP, int ev, const AdjItem* items, int nitems, int wg,
                                   size_t sh, hipStream_t s);
 size_t adjoint_lds_bytes(const Plan& P);
 
@@ -382,11 +382,11 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
       const int steps = std::max(8, (int)(sv->chunk_work / per_wg_step));
       if (r->phase == 0) {
         const int n0 = r->n_done, n1 = std::min(r->sys->n_steps, n0 + steps);
-        classes[{0, P.d, P.NR, P.MP, P.real_frame}].push_back({r, n0, n1, 0, 0});
+        classes[{0, P.d, P.NR, P.MP, plan_eval(P)}].push_back({r, n0, n1, 0, 0});
       } else {
         const int segs = std::max(1, steps / (4 * r->ce));
         const int s_hi = r->seg_next, s_lo = std::max(0, s_hi - segs + 1);
-        classes[{1, P.d, P.NR, P.MP, P.real_frame}].push_back({r, 0, 0, s_hi, s_lo});
+        classes[{1, P.d, P.NR, P.MP, plan_eval(P)}].push_back({r, 0, 0, s_hi, s_lo});
       }
     }
     // staging: per class, the forward items, or per adjoint round (one segment
@@ -423,7 +423,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
       hipStream_t st = sv->work[ci++ % scp_server::kWork];
       const int kind = std::get<0>(kv.first), d = std::get<1>(kv.first), NR = std::get<2>(kv.first),
                 MP = std::get<3>(kv.first);
-      const bool rf = std::get<4>(kv.first) != 0;
+      const int ev = std::get<4>(kv.first);
       int wg = 64;
       size_t sh_f = 0, sh_a = 0;
       for (auto& w : kv.second) {
@@ -446,7 +446,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
         }
         void* dptr = nullptr;
         if (!stage(it, (size_t)nit * sizeof(FwdItem), st, &dptr)) return fail(SCP_EHIP, "item upload");
-        s = launch_rk4_batched(d, NR, MP, rf, (const FwdItem*)dptr, nit, wg, sh_f, false, st);
+        s = launch_rk4_batched(d, NR, MP, ev, (const FwdItem*)dptr, nit, wg, sh_f, false, st);
         if (s != SCP_OK) return s;
       } else {
         // round j: segment s_hi - j of every request that still has one this tick
@@ -468,7 +468,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
           }
           void* dptr = nullptr;
           if (!stage(fi, (size_t)nf * sizeof(FwdItem), st, &dptr)) return fail(SCP_EHIP, "item upload");
-          s = launch_rk4_batched(d, NR, MP, rf, (const FwdItem*)dptr, nf, wg, sh_f, true, st);
+          s = launch_rk4_batched(d, NR, MP, ev, (const FwdItem*)dptr, nf, wg, sh_f, true, st);
           if (s != SCP_OK) return s;
           AdjItem* ai = (AdjItem*)((char*)sv->h_items + off);
           int na = 0;
@@ -483,7 +483,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
                                  seg == r->nckpt - 1 ? 1 : 0, 0};
           }
           if (!stage(ai, (size_t)na * sizeof(AdjItem), st, &dptr)) return fail(SCP_EHIP, "item upload");
-          s = launch_adjoint_batched(d, NR, MP, rf, (const AdjItem*)dptr, na, wg, sh_a, st);
+          s = launch_adjoint_batched(d, NR, MP, ev, (const AdjItem*)dptr, na, wg, sh_a, st);
           if (s != SCP_OK) return s;
         }
       }
