@@ -50,7 +50,7 @@
 namespace scp {
 
 constexpr int GA_MAXM = 10;      // modes (three-bit digits, 2N (open) or N in one word)
-constexpr int GA_MAXDM = 5;      // driven modes
+constexpr int GA_MAXDM = 10;     // driven modes
 constexpr int GA_MAXPR = 10;     // coupled mode pairs
 constexpr int GA_MAXC = 4;       // operators summed into one table entry
 constexpr int GA_MAXTAB = 4096;  // complex entries of a stage table
@@ -75,8 +75,12 @@ struct GArgs {
   int block_q, ngroups, nsteps, S;
   float h;
   int ndm, npr, ntab, has_jump, off_p, off_j;
-  int prow;   // stride of a pair-operator row: d^2 rounded up to even
-  int orow;   // stride of a driven-mode operator row: d rounded up to even
+  int par;    // operators connect levels of unlike parity only (see Nb)
+  int nn;     // entries of an operator row
+  int prow;   // stride of a pair-operator row: nn^2 rounded up to even
+  int orow;   // stride of a driven-mode operator row: nn rounded up to even
+  int srow;   // stride of a slot-operator row (gradient)
+  int mrow;   // stride of a row of a mode's derivative operator (gradient)
   int kst[GA_MAXM], bst[GA_MAXM];                    // strides of ket / bra digits in a column
   int dm_mode[GA_MAXDM], dm_n[GA_MAXDM];
   int dm_slot[GA_MAXDM][GA_MAXC], dm_cidx[GA_MAXDM][GA_MAXC];
@@ -138,6 +142,35 @@ struct GShape {
   static constexpr int st(int m) { return cpow(d, N - 1 - m); }       // stride in A or B
 };
 
+// The levels along one mode that an operator row connects to level a: all d of
+// them or, where every operator is odd (PAR), those of the other parity: at
+// most (d + 1) / 2 entries.  With d odd an even level has one neighbour fewer;
+// its last entry repeats the first neighbour with a zero coefficient, so the
+// gather stays inside the column.  A pair term gathers 4 (d = 3, 4) or 9
+// (d = 5) neighbours instead of d^2, with as many table entries.  Measured:
+// 4-fluxonium chain (d = 5, 16 columns) forward 11.8 -> 8.4 us per step, open
+// 4-fluxonium chain (d = 3, 256 matrices) forward + gradient 583 -> 426.
+template <int d, bool PAR>
+struct Nb {
+  static constexpr int n = PAR ? (d + 1) / 2 : d;
+  static constexpr int orow = n + (n & 1);
+  static constexpr int prow = n * n + ((n * n) & 1);
+  static constexpr int srow = PAR ? orow : d;
+  static constexpr int mrow = PAR ? (n + 1) + ((n + 1) & 1) : d;
+  // offset of entry k's element from the row's own (digit a, stride st)
+  static __device__ __forceinline__ int off(int k, int a, int st) {
+    if (!PAR) return (k - a) * st;
+    const int b0 = (a & 1) ^ 1;
+    const int b = ((d & 1) && k == n - 1 && b0) ? b0 : b0 + 2 * k;
+    return (b - a) * st;
+  }
+};
+// Level of entry k of row a (-1: padding), as Nb<d, par> has it.
+__host__ __device__ inline int nb_level(int d, int par, int k, int a) {
+  const int b = par ? ((a & 1) ^ 1) + 2 * k : k;
+  return b < d ? b : -1;
+}
+
 __device__ __forceinline__ int ket_digit(uint32_t pk, int m) { return (pk >> (3 * m)) & 7; }
 __device__ __forceinline__ int bra_digit(uint32_t pk, int m, int N) {
   return (pk >> (3 * (N + m))) & 7;
@@ -175,12 +208,15 @@ __global__ void gtab_kernel(const GArgs* __restrict__ Ag, int d, int N, float2* 
   for (int t = threadIdx.x; t < ntot; t += blockDim.x) {
     float vr = 0.f, vi = 0.f;
     if (t >= A.ntab) {
-      if (t < A.off_s + A.nsl * dd) {   // rotated slot operator
+      if (t < A.off_s + A.nsl * d * A.srow) {   // rotated slot operator
         const int u = t - A.off_s;
-        const int k = u / dd, ab = u - k * dd;
-        const c32 o = ops[A.sl_slot[k] * dd + ab];
-        vr = o.x;
-        vi = o.y;
+        const int k = u / (d * A.srow), a = (u / A.srow) % d, kb = u % A.srow;
+        const int b = kb < A.nn ? nb_level(d, A.par, kb, a) : -1;
+        if (b >= 0) {
+          const c32 o = ops[A.sl_slot[k] * dd + a * d + b];
+          vr = o.x;
+          vi = o.y;
+        }
       } else if (A.grad == 1) {         // unit-rate relaxation band (then row padding)
         if (t - A.off_u < N * dd) {
           const c32 j = ((const c32*)A.jtab)[((size_t)q * N) * dd + (t - A.off_u)];
@@ -188,30 +224,36 @@ __global__ void gtab_kernel(const GArgs* __restrict__ Ag, int d, int N, float2* 
           vi = j.y;
         }
       } else if (t < A.off_d) {         // d/dtheta of mode m's one-mode terms
-        const int u = t - A.off_m;
-        const int m = u / (3 * dd), th = (u / dd) % 3, ab = u % dd;
-        const int a = ab / d, b = ab - a * d;
-        if (a == b) vr = A.deps[m][th][a];
+        const int u = t - A.off_m, dr = d * A.mrow;
+        const int m = u / (3 * dr), th = (u / dr) % 3, a = (u / A.mrow) % d, kb = u % A.mrow;
+        // parity: the diagonal sits behind the row's entries
+        const int b = kb < A.nn ? nb_level(d, A.par, kb, a) : (A.par && kb == A.nn ? a : -1);
+        const int ab = a * d + b;
+        if (b == a) vr = A.deps[m][th][a];
         const int dm = A.mdm[m];
-        if (dm >= 0)
+        if (dm >= 0 && b >= 0 && kb < A.nn)
           for (int k = 0; k < A.dm_n[dm]; ++k) {
             const float c = cq[A.dm_cidx[dm][k]];
             const c32 o = ops[A.off_dslot + (A.dm_slot[dm][k] * 3 + th) * dd + ab];
             vr = fmaf(c, o.x, vr);
             vi = fmaf(c, o.y, vi);
           }
-      } else if (t < A.off_d + 3 * A.nsl * dd) {   // derivative slot operator
-        const int u = t - A.off_d;
-        const int k = u / (3 * dd), th = (u / dd) % 3, ab = u % dd;
-        const c32 o = ops[A.off_dslot + (A.sl_slot[k] * 3 + th) * dd + ab];
-        vr = o.x;
-        vi = o.y;
+      } else if (t < A.off_d + 3 * A.nsl * d * A.srow) {   // derivative slot operator
+        const int u = t - A.off_d, dr = d * A.srow;
+        const int k = u / (3 * dr), th = (u / dr) % 3, a = (u / A.srow) % d, kb = u % A.srow;
+        const int b = kb < A.nn ? nb_level(d, A.par, kb, a) : -1;
+        if (b >= 0) {
+          const c32 o = ops[A.off_dslot + (A.sl_slot[k] * 3 + th) * dd + a * d + b];
+          vr = o.x;
+          vi = o.y;
+        }
       }
     } else if (t < A.off_p) {
       const int dm = t / (d * A.orow), rr = t - dm * d * A.orow;
-      const int ra = rr / A.orow, rb = rr - ra * A.orow;   // rb >= d: row padding
+      const int ra = rr / A.orow, kb = rr - ra * A.orow;   // kb >= nn: row padding
+      const int rb = kb < A.nn ? nb_level(d, A.par, kb, ra) : -1;
       const int ab = ra * d + rb;
-      for (int k = 0; k < (dm < A.ndm && rb < d ? A.dm_n[dm] : 0); ++k) {
+      for (int k = 0; k < (dm < A.ndm && rb >= 0 ? A.dm_n[dm] : 0); ++k) {
         const float c = cq[A.dm_cidx[dm][k]];
         const c32 o = ops[A.dm_slot[dm][k] * dd + ab];
         vr = fmaf(c, o.x, vr);
@@ -220,9 +262,11 @@ __global__ void gtab_kernel(const GArgs* __restrict__ Ag, int d, int N, float2* 
     } else if (t < A.off_j) {
       const int u = t - A.off_p;
       const int p = u / (dd * A.prow), rr = u - p * dd * A.prow;
-      const int row = rr / A.prow, col = rr - row * A.prow;   // col >= dd: row padding
-      const int ai = row / d, aj = row - ai * d, x = col / d, z = col - x * d;
-      for (int k = 0; k < (col < dd ? A.pr_n[p] : 0); ++k) {
+      const int row = rr / A.prow, col = rr - row * A.prow;   // col >= nn^2: row padding
+      const int ai = row / d, aj = row - ai * d, kx = col / A.nn, kz = col - kx * A.nn;
+      const int x = kx < A.nn ? nb_level(d, A.par, kx, ai) : -1;
+      const int z = nb_level(d, A.par, kz, aj);
+      for (int k = 0; k < (x >= 0 && z >= 0 ? A.pr_n[p] : 0); ++k) {
         const c32 oi = ops[A.pr_si[p][k] * dd + ai * d + x];
         const c32 oj = ops[A.pr_sj[p][k] * dd + aj * d + z];
         const float g = A.pr_g[p][k];
@@ -240,81 +284,61 @@ __global__ void gtab_kernel(const GArgs* __restrict__ Ag, int d, int N, float2* 
   }
 }
 
-// Stride of a pair-operator row in the stage table: the d^2 entries padded to
-// an even count so that a row starts 16-byte aligned and is read two entries
+// sum_k row[k] y_k (CONJ: conj(row[k])) over one driven-mode operator row of an
+// element at `y` with digit a on a mode of stride st.  Operator rows are padded
+// to an even length, so a row starts 16-byte aligned and is read two entries
 // per LDS instruction.
-template <int d, bool OPEN>
-__host__ __device__ constexpr int pair_row() {
-  return d * d + ((d * d) & 1);
-}
-
-template <int d, bool OPEN>
-__host__ __device__ constexpr int one_row() {
-  return d + (d & 1);
-}
-
-// sum_x row[x] y0[x sm] (CONJ: conj(row[x])) over one driven-mode operator
-// row; the row is 16-byte aligned and read two entries at a time
-template <int d, bool CONJ>
-__device__ __forceinline__ void one_dot(const c32* __restrict__ row, const c32* __restrict__ y0,
-                                        int sm, float& sr, float& si) {
+template <int d, bool PAR, bool CONJ>
+__device__ __forceinline__ void one_dot(const c32* __restrict__ row, const c32* __restrict__ y,
+                                        int a, int st, float& sr, float& si) {
+  using B = Nb<d, PAR>;
   const float4* r4 = reinterpret_cast<const float4*>(row);
 #pragma unroll
-  for (int k = 0; k < (d + 1) / 2; ++k) {
+  for (int k = 0; k < (B::n + 1) / 2; ++k) {
     const float4 q = r4[k];
-    c32 a;
-    a.x = q.x;
-    a.y = q.y;
-    if (CONJ)
-      cmac_conj(sr, si, a, y0[(2 * k) * sm]);
-    else
-      cmac(sr, si, a, y0[(2 * k) * sm]);
-    if (2 * k + 1 < d) {
-      c32 b;
-      b.x = q.z;
-      b.y = q.w;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (2 * k + u >= B::n) continue;
+      c32 o;
+      o.x = u ? q.z : q.x;
+      o.y = u ? q.w : q.y;
       if (CONJ)
-        cmac_conj(sr, si, b, y0[(2 * k + 1) * sm]);
+        cmac_conj(sr, si, o, y[B::off(2 * k + u, a, st)]);
       else
-        cmac(sr, si, b, y0[(2 * k + 1) * sm]);
+        cmac(sr, si, o, y[B::off(2 * k + u, a, st)]);
     }
   }
 }
 
-// sum_{x,z} row[x d + z] y0[x si + z sj] (CONJ: conj(row[...])) over one
-// pair-operator row, read two entries at a time
-template <int d, bool CONJ>
-__device__ __forceinline__ void pair_dot(const c32* __restrict__ row, const c32* __restrict__ y0,
-                                         int si_, int sj_, float& sr, float& si) {
-  constexpr int dd = d * d;
+// The same over one pair-operator row, entry (x, z) of modes (i, j).
+template <int d, bool PAR, bool CONJ>
+__device__ __forceinline__ void pair_dot(const c32* __restrict__ row, const c32* __restrict__ y,
+                                         int ai, int aj, int si_, int sj_, float& sr, float& si) {
+  using B = Nb<d, PAR>;
+  constexpr int nn = B::n * B::n;
   const float4* r4 = reinterpret_cast<const float4*>(row);
 #pragma unroll
-  for (int k = 0; k < (dd + 1) / 2; ++k) {
+  for (int k = 0; k < (nn + 1) / 2; ++k) {
     const float4 q = r4[k];
-    c32 a;
-    a.x = q.x;
-    a.y = q.y;
-    const c32 ya = y0[((2 * k) / d) * si_ + ((2 * k) % d) * sj_];
-    if (CONJ)
-      cmac_conj(sr, si, a, ya);
-    else
-      cmac(sr, si, a, ya);
-    if (2 * k + 1 < dd) {
-      c32 b;
-      b.x = q.z;
-      b.y = q.w;
-      const c32 yb_ = y0[((2 * k + 1) / d) * si_ + ((2 * k + 1) % d) * sj_];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int t = 2 * k + u;
+      if (t >= nn) continue;
+      c32 o;
+      o.x = u ? q.z : q.x;
+      o.y = u ? q.w : q.y;
+      const c32 v = y[B::off(t / B::n, ai, si_) + B::off(t % B::n, aj, sj_)];
       if (CONJ)
-        cmac_conj(sr, si, b, yb_);
+        cmac_conj(sr, si, o, v);
       else
-        cmac(sr, si, b, yb_);
+        cmac(sr, si, o, v);
     }
   }
 }
 
 // k = G(t) y for one element; y read from LDS (neighbours), the own value
 // from the caller.
-template <int d, int N, bool OPEN>
+template <int d, int N, bool OPEN, bool PAR>
 __device__ __forceinline__ void g_apply(kptr<GArgs> A, const c32* __restrict__ yb,
                                         const c32* __restrict__ tab, int e, uint32_t pk,
                                         float dgr, float dgi, float yr, float yi, float& kr,
@@ -342,22 +366,18 @@ __device__ __forceinline__ void g_apply(kptr<GArgs> A, const c32* __restrict__ y
     {
       const int sm = uni(A->kst[m]);
       const int am = ket_digit(pk, m);
-      constexpr int RD = one_row<d, OPEN>();
-      const c32* row = tab + dm * d * RD + am * RD;
-      const c32* y0 = yb + e - am * sm;
+      const c32* row = tab + (dm * d + am) * Nb<d, PAR>::orow;
       float sr = 0.f, si = 0.f;
-      one_dot<d, false>(row, y0, sm, sr, si);
+      one_dot<d, PAR, false>(row, yb + e, am, sm, sr, si);
       kr += si;
       ki -= sr;
     }
     if (OPEN) {
       const int sm = uni(A->bst[m]);
       const int bm = bra_digit(pk, m, N);
-      constexpr int RD = one_row<d, OPEN>();
-      const c32* row = tab + dm * d * RD + bm * RD;
-      const c32* y0 = yb + e - bm * sm;
+      const c32* row = tab + (dm * d + bm) * Nb<d, PAR>::orow;
       float sr = 0.f, si = 0.f;
-      one_dot<d, true>(row, y0, sm, sr, si);
+      one_dot<d, PAR, true>(row, yb + e, bm, sm, sr, si);
       kr -= si;
       ki += sr;
     }
@@ -367,15 +387,14 @@ __device__ __forceinline__ void g_apply(kptr<GArgs> A, const c32* __restrict__ y
   for (int pv = 0; pv < npr; ++pv) {
     const int p = uni(pv);
     const int i = uni(A->pr_i[p]), j = uni(A->pr_j[p]);
-    constexpr int PR = pair_row<d, OPEN>();
+    constexpr int PR = Nb<d, PAR>::prow;
     const c32* P = tab + A->off_p + p * dd * PR;
     {
       const int si_ = uni(A->kst[i]), sj_ = uni(A->kst[j]);
       const int ai = ket_digit(pk, i), aj = ket_digit(pk, j);
       const c32* row = P + (ai * d + aj) * PR;
-      const c32* y0 = yb + e - (ai * si_ + aj * sj_);
       float sr = 0.f, si = 0.f;
-      pair_dot<d, false>(row, y0, si_, sj_, sr, si);
+      pair_dot<d, PAR, false>(row, yb + e, ai, aj, si_, sj_, sr, si);
       kr += si;
       ki -= sr;
     }
@@ -383,9 +402,8 @@ __device__ __forceinline__ void g_apply(kptr<GArgs> A, const c32* __restrict__ y
       const int si_ = uni(A->bst[i]), sj_ = uni(A->bst[j]);
       const int bi = bra_digit(pk, i, N), bj = bra_digit(pk, j, N);
       const c32* row = P + (bi * d + bj) * PR;
-      const c32* y0 = yb + e - (bi * si_ + bj * sj_);
       float sr = 0.f, si = 0.f;
-      pair_dot<d, true>(row, y0, si_, sj_, sr, si);
+      pair_dot<d, PAR, true>(row, yb + e, bi, bj, si_, sj_, sr, si);
       kr -= si;
       ki += sr;
     }
@@ -393,7 +411,7 @@ __device__ __forceinline__ void g_apply(kptr<GArgs> A, const c32* __restrict__ y
 }
 
 // One column (col) of a propagation: the body of the stepper kernels.
-template <int d, int N, bool OPEN, bool CK>
+template <int d, int N, bool OPEN, bool PAR, bool CK>
 __device__ __forceinline__ void g_rk4_body(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg,
                                            int col, int n_lo, int n_hi,
                                            const float4* __restrict__ st_in,
@@ -533,7 +551,7 @@ __device__ __forceinline__ void g_rk4_body(const GArgs* __restrict__ Ag, const G
           }
           const c32 ye = yc[e];
           float kr, ki;
-          g_apply<d, N, OPEN>(A, yc, tc, e, p, g.x, g.y, ye.x, ye.y, kr, ki);
+          g_apply<d, N, OPEN, PAR>(A, yc, tc, e, p, g.x, g.y, ye.x, ye.y, kr, ki);
           if (s == 0) {
             ar[r] = kr;
             am_[r] = ki;
@@ -602,20 +620,20 @@ __device__ __forceinline__ void g_rk4_body(const GArgs* __restrict__ Ag, const G
   }
 }
 
-template <int d, int N, bool OPEN, bool CK>
+template <int d, int N, bool OPEN, bool PAR, bool CK>
 __global__ void __launch_bounds__((GShape<d, N, OPEN>::T))
 g_rk4_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg, int n_lo, int n_hi,
              const float4* __restrict__ st_in, float4* __restrict__ st_out) {
-  g_rk4_body<d, N, OPEN, CK>(Ag, Bg, blockIdx.x, n_lo, n_hi, st_in, st_out);
+  g_rk4_body<d, N, OPEN, PAR, CK>(Ag, Bg, blockIdx.x, n_lo, n_hi, st_in, st_out);
 }
 
 // Batched (serving): every workgroup reads its own work item -- its request's
 // description, column, step range and state buffers.
-template <int d, int N, bool CK>
+template <int d, int N, bool PAR, bool CK>
 __global__ void __launch_bounds__((GShape<d, N, false>::T))
 g_rk4_batched_kernel(const GItem* __restrict__ items) {
   kptr<GItem> it = kconst(items) + blockIdx.x;
-  g_rk4_body<d, N, false, CK>((const GArgs*)it->A, (const GAdj*)it->B, it->col, it->n_lo,
+  g_rk4_body<d, N, false, PAR, CK>((const GArgs*)it->A, (const GAdj*)it->B, it->col, it->n_lo,
                               it->n_hi, it->st_in, it->st_out);
 }
 
@@ -630,7 +648,7 @@ g_rk4_batched_kernel(const GItem* __restrict__ items) {
 // L^dag x for one element: the Hamiltonian part with the opposite sign, the
 // static diagonal conjugated, the relaxation jump transposed
 // (conj(J[a-1][b-1]) x_{A-e_m, B-e_m}).  Closed systems: G^dag = i (delta + H).
-template <int d, int N, bool OPEN>
+template <int d, int N, bool OPEN, bool PAR>
 __device__ __forceinline__ void g_apply_adj(kptr<GArgs> A, const c32* __restrict__ xb,
                                             const c32* __restrict__ tab, int e, uint32_t pk,
                                             float dgr, float dgi, float xr, float xi, float& yr,
@@ -657,22 +675,18 @@ __device__ __forceinline__ void g_apply_adj(kptr<GArgs> A, const c32* __restrict
     {
       const int sm = uni(A->kst[m]);
       const int am = ket_digit(pk, m);
-      constexpr int RD = one_row<d, OPEN>();
-      const c32* row = tab + dm * d * RD + am * RD;
-      const c32* x0 = xb + e - am * sm;
+      const c32* row = tab + (dm * d + am) * Nb<d, PAR>::orow;
       float sr = 0.f, si = 0.f;
-      one_dot<d, false>(row, x0, sm, sr, si);
+      one_dot<d, PAR, false>(row, xb + e, am, sm, sr, si);
       yr -= si;
       yi += sr;
     }
     if (OPEN) {
       const int sm = uni(A->bst[m]);
       const int bm = bra_digit(pk, m, N);
-      constexpr int RD = one_row<d, OPEN>();
-      const c32* row = tab + dm * d * RD + bm * RD;
-      const c32* x0 = xb + e - bm * sm;
+      const c32* row = tab + (dm * d + bm) * Nb<d, PAR>::orow;
       float sr = 0.f, si = 0.f;
-      one_dot<d, true>(row, x0, sm, sr, si);
+      one_dot<d, PAR, true>(row, xb + e, bm, sm, sr, si);
       yr += si;
       yi -= sr;
     }
@@ -681,15 +695,14 @@ __device__ __forceinline__ void g_apply_adj(kptr<GArgs> A, const c32* __restrict
   for (int pv = 0; pv < npr; ++pv) {
     const int p = uni(pv);
     const int i = uni(A->pr_i[p]), j = uni(A->pr_j[p]);
-    constexpr int PR = pair_row<d, OPEN>();
+    constexpr int PR = Nb<d, PAR>::prow;
     const c32* P = tab + A->off_p + p * dd * PR;
     {
       const int si_ = uni(A->kst[i]), sj_ = uni(A->kst[j]);
       const int ai = ket_digit(pk, i), aj = ket_digit(pk, j);
       const c32* row = P + (ai * d + aj) * PR;
-      const c32* x0 = xb + e - (ai * si_ + aj * sj_);
       float sr = 0.f, si = 0.f;
-      pair_dot<d, false>(row, x0, si_, sj_, sr, si);
+      pair_dot<d, PAR, false>(row, xb + e, ai, aj, si_, sj_, sr, si);
       yr -= si;
       yi += sr;
     }
@@ -697,9 +710,8 @@ __device__ __forceinline__ void g_apply_adj(kptr<GArgs> A, const c32* __restrict
       const int si_ = uni(A->bst[i]), sj_ = uni(A->bst[j]);
       const int bi = bra_digit(pk, i, N), bj = bra_digit(pk, j, N);
       const c32* row = P + (bi * d + bj) * PR;
-      const c32* x0 = xb + e - (bi * si_ + bj * sj_);
       float sr = 0.f, si = 0.f;
-      pair_dot<d, true>(row, x0, si_, sj_, sr, si);
+      pair_dot<d, PAR, true>(row, xb + e, bi, bj, si_, sj_, sr, si);
       yr += si;
       yi -= sr;
     }
@@ -708,16 +720,15 @@ __device__ __forceinline__ void g_apply_adj(kptr<GArgs> A, const c32* __restrict
 
 // z = (O kb - kb O) at one element for a one-mode operator O (table rows at
 // `rows`, O Hermitian): the commutator's ket gather minus its bra gather.
-template <int d, int N>
+template <int d, int N, bool PAR>
 __device__ __forceinline__ c32 comm1(const c32* __restrict__ kb, const c32* __restrict__ rows,
                                      int e, int am, int bm, int ks, int bs) {
+  using B = Nb<d, PAR>;
   float kr = 0.f, ki = 0.f, br = 0.f, bi = 0.f;
-  const c32* k0 = kb + e - am * ks;
-  const c32* b0 = kb + e - bm * bs;
 #pragma unroll
-  for (int x = 0; x < d; ++x) {
-    cmac(kr, ki, rows[am * d + x], k0[x * ks]);
-    cmac_conj(br, bi, rows[bm * d + x], b0[x * bs]);
+  for (int x = 0; x < B::n; ++x) {
+    cmac(kr, ki, rows[am * B::srow + x], kb[e + B::off(x, am, ks)]);
+    cmac_conj(br, bi, rows[bm * B::srow + x], kb[e + B::off(x, bm, bs)]);
   }
   c32 z;
   z.x = kr - br;
@@ -726,28 +737,27 @@ __device__ __forceinline__ c32 comm1(const c32* __restrict__ kb, const c32* __re
 }
 
 // z = (P kb - kb P) at one element for P = Oi (x) Oj on modes (i, j).
-template <int d, int N>
+template <int d, int N, bool PAR>
 __device__ __forceinline__ c32 comm2(const c32* __restrict__ kb, const c32* __restrict__ Ri,
                                      const c32* __restrict__ Rj, int e, int ai, int aj, int bi,
                                      int bj, int ksi, int ksj, int bsi, int bsj) {
+  using B = Nb<d, PAR>;
   float kr = 0.f, ki = 0.f, br = 0.f, bim = 0.f;
-  const c32* k0 = kb + e - ai * ksi - aj * ksj;
-  const c32* b0 = kb + e - bi * bsi - bj * bsj;
 #pragma unroll
-  for (int x = 0; x < d; ++x) {
+  for (int x = 0; x < B::n; ++x) {
     float ir = 0.f, ii = 0.f, jr = 0.f, ji = 0.f;
 #pragma unroll
-    for (int z = 0; z < d; ++z) {
-      cmac(ir, ii, Rj[aj * d + z], k0[x * ksi + z * ksj]);
-      cmac_conj(jr, ji, Rj[bj * d + z], b0[x * bsi + z * bsj]);
+    for (int z = 0; z < B::n; ++z) {
+      cmac(ir, ii, Rj[aj * B::srow + z], kb[e + B::off(x, ai, ksi) + B::off(z, aj, ksj)]);
+      cmac_conj(jr, ji, Rj[bj * B::srow + z], kb[e + B::off(x, bi, bsi) + B::off(z, bj, bsj)]);
     }
     c32 u, w;
     u.x = ir;
     u.y = ii;
     w.x = jr;
     w.y = ji;
-    cmac(kr, ki, Ri[ai * d + x], u);
-    cmac_conj(br, bim, Ri[bi * d + x], w);
+    cmac(kr, ki, Ri[ai * B::srow + x], u);
+    cmac_conj(br, bim, Ri[bi * B::srow + x], w);
   }
   c32 z;
   z.x = kr - br;
@@ -776,11 +786,11 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // s = sum_x row[x] v[x]
-template <int d>
-__device__ __forceinline__ c32 rowdot(const c32* __restrict__ row, const c32 (&v)[d]) {
+template <int n>
+__device__ __forceinline__ c32 rowdot(const c32* __restrict__ row, const c32 (&v)[n]) {
   float sr = 0.f, si = 0.f;
 #pragma unroll
-  for (int x = 0; x < d; ++x) cmac(sr, si, row[x], v[x]);
+  for (int x = 0; x < n; ++x) cmac(sr, si, row[x], v[x]);
   c32 z;
   z.x = sr;
   z.y = si;
@@ -791,21 +801,21 @@ __device__ __forceinline__ c32 rowdot(const c32* __restrict__ row, const c32 (&v
 __device__ __forceinline__ float im_conj(c32 a, c32 b) { return a.x * b.y - a.y * b.x; }
 
 // w[x] = conj(v[x]) b
-template <int d>
-__device__ __forceinline__ void conj_scale(const c32 (&v)[d], c32 b, c32 (&w)[d]) {
+template <int n>
+__device__ __forceinline__ void conj_scale(const c32 (&v)[n], c32 b, c32 (&w)[n]) {
 #pragma unroll
-  for (int x = 0; x < d; ++x) {
+  for (int x = 0; x < n; ++x) {
     w[x].x = fmaf(v[x].x, b.x, v[x].y * b.y);
     w[x].y = fmaf(v[x].x, b.y, -v[x].y * b.x);
   }
 }
 
 // Im(conj(sum_x row[x] v[x]) b) = sum_x Im(conj(row[x]) w[x]) with w = conj(v) b
-template <int d>
-__device__ __forceinline__ float im_rowdot(const c32* __restrict__ row, const c32 (&w)[d]) {
+template <int n>
+__device__ __forceinline__ float im_rowdot(const c32* __restrict__ row, const c32 (&w)[n]) {
   float s = 0.f;
 #pragma unroll
-  for (int x = 0; x < d; ++x) {
+  for (int x = 0; x < n; ++x) {
     s = fmaf(row[x].x, w[x].y, s);
     s = fmaf(-row[x].y, w[x].x, s);
   }
@@ -813,11 +823,13 @@ __device__ __forceinline__ float im_rowdot(const c32* __restrict__ row, const c3
 }
 
 // Block blk of a reverse-walk launch for segment gseg (see g_adj_kernel).
-template <int d, int N, bool OPEN>
+template <int d, int N, bool OPEN, bool PAR>
 __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg,
                                            int gseg, int blk) {
   using Sh = GShape<d, N, OPEN>;
+  using B_ = Nb<d, PAR>;
   constexpr int L = Sh::L, T = Sh::T, E = Sh::E, D = Sh::D, dd = d * d;
+  constexpr int nb = B_::n, SR = B_::srow, MR = B_::mrow;   // gathered levels; operator row strides
   constexpr int NW = T / 64;
   constexpr int WS = OPEN ? GA_MAXDS : GA_NV;   // per-wave sums of one stage
   extern __shared__ __align__(16) c32 lds[];
@@ -963,7 +975,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
               const c32 ye = yc[e];
               ys[e] = ye;
               float kr, ki;
-              g_apply<d, N, OPEN>(A, yc, tc, e, p, gr, gi, ye.x, ye.y, kr, ki);
+              g_apply<d, N, OPEN, PAR>(A, yc, tc, e, p, gr, gi, ye.x, ye.y, kr, ki);
               if (s == 0) {
                 ar[r] = kr;
                 am_[r] = ki;
@@ -1120,7 +1132,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
             }
             const c32 kbe = kbw[e];
             float yr_, yi_;
-            g_apply_adj<d, N, OPEN>(A, kbw, tw, e, p, gr, gi, kbe.x, kbe.y, yr_, yi_);
+            g_apply_adj<d, N, OPEN, PAR>(A, kbw, tw, e, p, gr, gi, kbe.x, kbe.y, yr_, yi_);
             ybr[r] = yr_;
             ybm[r] = yi_;
             llr[r] += yr_;
@@ -1133,7 +1145,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
 #pragma unroll 1
           for (int k = 0; k < nds; ++k) {
             const int m = uni(A->ds_mode[k]);
-            const c32* rows = tw + A->off_s + uni(A->ds_sl[k]) * dd;
+            const c32* rows = tw + A->off_s + uni(A->ds_sl[k]) * d * SR;
             const int ks = uni(A->kst[m]), bs = uni(A->bst[m]);
             float v = 0.f;
 #pragma unroll
@@ -1141,7 +1153,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
               const int e = tid + r * T;
               if (e < L) {
                 const c32 z =
-                    comm1<d, N>(kbw, rows, e, ket_digit(pk[r], m), bra_digit(pk[r], m, N), ks, bs);
+                    comm1<d, N, PAR>(kbw, rows, e, ket_digit(pk[r], m), bra_digit(pk[r], m, N), ks, bs);
                 v += 2.f * im_conj(z, ys[e]);
               }
             }
@@ -1152,8 +1164,8 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
 #pragma unroll 1
           for (int c = 0; c < ncp; ++c) {
             const int i = uni(A->cp_i[c]), j = uni(A->cp_j[c]);
-            const c32* Ri = tw + A->off_s + uni(A->cp_si[c]) * dd;
-            const c32* Rj = tw + A->off_s + uni(A->cp_sj[c]) * dd;
+            const c32* Ri = tw + A->off_s + uni(A->cp_si[c]) * d * SR;
+            const c32* Rj = tw + A->off_s + uni(A->cp_sj[c]) * d * SR;
             const int ksi = uni(A->kst[i]), ksj = uni(A->kst[j]);
             const int bsi = uni(A->bst[i]), bsj = uni(A->bst[j]);
             float v = 0.f;
@@ -1162,7 +1174,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
               const int e = tid + r * T;
               if (e < L) {
                 const uint32_t p = pk[r];
-                const c32 z = comm2<d, N>(kbw, Ri, Rj, e, ket_digit(p, i), ket_digit(p, j),
+                const c32 z = comm2<d, N, PAR>(kbw, Ri, Rj, e, ket_digit(p, i), ket_digit(p, j),
                                           bra_digit(p, i, N), bra_digit(p, j, N), ksi, ksj, bsi,
                                           bsj);
                 const c32 y = ys[e];
@@ -1209,12 +1221,12 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
           for (int mv = 0; mv < N; ++mv) {
             const int m = uni(mv);
             const int ks = uni(A->kst[m]);
-            const c32* Dm = tw + uni(A->off_m) + m * 3 * dd;
+            const c32* Dm = tw + uni(A->off_m) + m * 3 * d * MR;
             // kb along m: kept in registers for the whole mode when small,
             // else gathered again at each use (keeps the E = 4 shapes out of
             // scratch)
-            constexpr bool KC = E * d <= 12;
-            c32 kv[KC ? E : 1][d];
+            constexpr bool KC = E * nb <= 12;
+            c32 kv[KC ? E : 1][nb];
             c32 C[E];
             float v0 = 0.f, v1 = 0.f, v2 = 0.f;
 #pragma unroll
@@ -1223,29 +1235,36 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
               C[r].x = C[r].y = 0.f;
               if (e < L) {
                 const int am = ket_digit(pk[r], m);
-                c32 kt[d];
+                c32 kt[nb];
 #pragma unroll
-                for (int x = 0; x < d; ++x) kt[x] = kbw[e + (x - am) * ks];
+                for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::off(x, am, ks)];
                 if constexpr (KC) {
 #pragma unroll
-                  for (int x = 0; x < d; ++x) kv[r][x] = kt[x];
+                  for (int x = 0; x < nb; ++x) kv[r][x] = kt[x];
                 }
-                c32 w[d];
-                conj_scale<d>(kt, ybw[e], w);
-                v0 += 2.f * im_rowdot<d>(Dm + am * d, w);
-                v1 += 2.f * im_rowdot<d>(Dm + dd + am * d, w);
-                v2 += 2.f * im_rowdot<d>(Dm + 2 * dd + am * d, w);
+                c32 w[nb];
+                conj_scale<nb>(kt, ybw[e], w);
+                const c32* Dr = Dm + am * MR;
+                v0 += 2.f * im_rowdot<nb>(Dr, w);
+                v1 += 2.f * im_rowdot<nb>(Dr + d * MR, w);
+                v2 += 2.f * im_rowdot<nb>(Dr + 2 * d * MR, w);
+                if constexpr (PAR) {   // the diagonal (real), behind the row's entries
+                  const float dg = 2.f * im_conj(kbw[e], ybw[e]);
+                  v0 = fmaf(dg, Dr[nb].x, v0);
+                  v1 = fmaf(dg, Dr[d * MR + nb].x, v1);
+                  v2 = fmaf(dg, Dr[2 * d * MR + nb].x, v2);
+                }
               }
               __builtin_amdgcn_sched_barrier(0);
             }
             // kb along m of element r (registers or LDS)
-            auto kb_of = [&](int r, int e, int am, c32(&kt)[d]) {
+            auto kb_of = [&](int r, int e, int am, c32(&kt)[nb]) {
               if constexpr (KC) {
 #pragma unroll
-                for (int x = 0; x < d; ++x) kt[x] = kv[KC ? r : 0][x];
+                for (int x = 0; x < nb; ++x) kt[x] = kv[KC ? r : 0][x];
               } else {
 #pragma unroll
-                for (int x = 0; x < d; ++x) kt[x] = kbw[e + (x - am) * ks];
+                for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::off(x, am, ks)];
               }
             };
             // drive slots on this mode: 2 Im <O kb, y>, one sum per wave (the
@@ -1253,16 +1272,16 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
 #pragma unroll 1
             for (int k = 0; k < (KC ? nds : 0); ++k) {
               if (uni(A->ds_mode[k]) != m) continue;
-              const c32* rows = tw + A->off_s + uni(A->ds_sl[k]) * dd;
+              const c32* rows = tw + A->off_s + uni(A->ds_sl[k]) * d * SR;
               float v = 0.f;
 #pragma unroll
               for (int r = 0; r < E; ++r) {
                 const int e = tid + r * T;
                 if (e < L) {
                   const int am = ket_digit(pk[r], m);
-                  c32 kt[d];
+                  c32 kt[nb];
                   kb_of(r, e, am, kt);
-                  v += 2.f * im_conj(rowdot<d>(rows + am * d, kt), ybw[e]);
+                  v += 2.f * im_conj(rowdot<nb>(rows + am * SR, kt), ybw[e]);
                 }
               }
               v = wave_sum(v);
@@ -1277,31 +1296,32 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
               const bool first = (pkd >> 20) & 1, last = (pkd >> 21) & 1;
               const float gc = unif(A->cp_g[c]);
               const int ps = uni(A->kst[pm]);
-              const c32* Ro = tw + A->off_s + own * dd;
-              const c32* Rp = tw + A->off_s + psl * dd;
-              const c32* dR = tw + A->off_d + own * 3 * dd;
+              const c32* Ro = tw + A->off_s + own * d * SR;
+              const c32* Rp = tw + A->off_s + psl * d * SR;
+              const c32* dR = tw + A->off_d + own * 3 * d * SR;
               float vc = 0.f;
 #pragma unroll
               for (int r = 0; r < E; ++r) {
                 const int e = tid + r * T;
                 if (e < L) {
                   const int am = ket_digit(pk[r], m), ap = ket_digit(pk[r], pm);
-                  c32 yv[d];
+                  c32 yv[nb];
 #pragma unroll
-                  for (int z = 0; z < d; ++z) yv[z] = ybw[e + (z - ap) * ps];
-                  const c32 cp = rowdot<d>(Rp + ap * d, yv);
+                  for (int z = 0; z < nb; ++z) yv[z] = ybw[e + B_::off(z, ap, ps)];
+                  const c32 cp = rowdot<nb>(Rp + ap * SR, yv);
                   C[r].x = fmaf(gc, cp.x, C[r].x);
                   C[r].y = fmaf(gc, cp.y, C[r].y);
                   if (first || last) {
-                    c32 kt[d];
+                    c32 kt[nb];
                     kb_of(r, e, am, kt);
-                    if (first) vc += 2.f * im_conj(rowdot<d>(Ro + am * d, kt), cp);
+                    if (first) vc += 2.f * im_conj(rowdot<nb>(Ro + am * SR, kt), cp);
                     if (last) {
-                      c32 w[d];
-                      conj_scale<d>(kt, C[r], w);
-                      v0 += 2.f * im_rowdot<d>(dR + am * d, w);
-                      v1 += 2.f * im_rowdot<d>(dR + dd + am * d, w);
-                      v2 += 2.f * im_rowdot<d>(dR + 2 * dd + am * d, w);
+                      c32 w[nb];
+                      conj_scale<nb>(kt, C[r], w);
+                      const c32* dr_ = dR + am * SR;
+                      v0 += 2.f * im_rowdot<nb>(dr_, w);
+                      v1 += 2.f * im_rowdot<nb>(dr_ + d * SR, w);
+                      v2 += 2.f * im_rowdot<nb>(dr_ + 2 * d * SR, w);
                       C[r].x = C[r].y = 0.f;
                     }
                   }
@@ -1322,22 +1342,22 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
               wv[2] = v2;
             }
           }
-          if constexpr (E * d > 12) {
+          if constexpr (E * nb > 12) {
 #pragma unroll 1
             for (int k = 0; k < nds; ++k) {
               const int m = uni(A->ds_mode[k]);
               const int ks = uni(A->kst[m]);
-              const c32* rows = tw + A->off_s + uni(A->ds_sl[k]) * dd;
+              const c32* rows = tw + A->off_s + uni(A->ds_sl[k]) * d * SR;
               float v = 0.f;
 #pragma unroll
               for (int r = 0; r < E; ++r) {
                 const int e = tid + r * T;
                 if (e < L) {
                   const int am = ket_digit(pk[r], m);
-                  c32 kt[d];
+                  c32 kt[nb];
 #pragma unroll
-                  for (int x = 0; x < d; ++x) kt[x] = kbw[e + (x - am) * ks];
-                  v += 2.f * im_conj(rowdot<d>(rows + am * d, kt), ybw[e]);
+                  for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::off(x, am, ks)];
+                  v += 2.f * im_conj(rowdot<nb>(rows + am * SR, kt), ybw[e]);
                 }
               }
               v = wave_sum(v);
@@ -1376,19 +1396,19 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
   for (int t = tid; t < nacc; t += T) B->part[(size_t)col * nacc + t] = acc[t];
 }
 
-template <int d, int N, bool OPEN>
+template <int d, int N, bool OPEN, bool PAR>
 __global__ void __launch_bounds__((GShape<d, N, OPEN>::T))
 g_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg, int gseg) {
-  g_adj_body<d, N, OPEN>(Ag, Bg, gseg, blockIdx.x);
+  g_adj_body<d, N, OPEN, PAR>(Ag, Bg, gseg, blockIdx.x);
 }
 
 // Batched (serving, closed systems): item.col is the block of the request's
 // 2S-block launch, item.gseg its segment.
-template <int d, int N>
+template <int d, int N, bool PAR>
 __global__ void __launch_bounds__((GShape<d, N, false>::T))
 g_adj_batched_kernel(const GItem* __restrict__ items) {
   kptr<GItem> it = kconst(items) + blockIdx.x;
-  g_adj_body<d, N, false>((const GArgs*)it->A, (const GAdj*)it->B, it->gseg, it->col);
+  g_adj_body<d, N, false, PAR>((const GArgs*)it->A, (const GAdj*)it->B, it->gseg, it->col);
 }
 
 // Unit-rate relaxation band of every mode at every half-step q (t = q h/2):
@@ -1430,27 +1450,32 @@ size_t g_lds_bytes(int ntab) {
   return sizeof(c32) * (3 * L + ((3 * L) & 1) + 2 * (size_t)ntab);
 }
 
+template <typename K>
+hipError_t g_lds(K* kernel, size_t sh) {
+  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+}
+
 // Steps [n_lo, n_hi) with the state from st_in / to st_out (nullable; see the
 // kernel); dadj != nullptr also writes the checkpoints.
-template <int d, int N, bool OPEN>
-hipError_t g_launch(const GArgs* dargs, const GAdj* dadj, int S, int ntab, int n_lo, int n_hi,
-                    const float4* st_in, float4* st_out, hipStream_t s) {
+template <int d, int N, bool OPEN, bool PAR, bool CK>
+hipError_t g_launch1(const GArgs* dargs, const GAdj* dadj, int S, int ntab, int n_lo, int n_hi,
+                     const float4* st_in, float4* st_out, hipStream_t s) {
   using Sh = GShape<d, N, OPEN>;
   const size_t sh = g_lds_bytes<d, N, OPEN>(ntab);
-  if (dadj != nullptr) {
-    (void)hipFuncSetAttribute((const void*)g_rk4_kernel<d, N, OPEN, true>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    hipLaunchKernelGGL((g_rk4_kernel<d, N, OPEN, true>), dim3(S), dim3(Sh::T), sh, s, dargs, dadj,
-                       n_lo, n_hi, st_in, st_out);
-    return hipGetLastError();
-  }
-  {
-    (void)hipFuncSetAttribute((const void*)g_rk4_kernel<d, N, OPEN, false>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    hipLaunchKernelGGL((g_rk4_kernel<d, N, OPEN, false>), dim3(S), dim3(Sh::T), sh, s, dargs, dadj,
-                       n_lo, n_hi, st_in, st_out);
-  }
+  (void)g_lds(g_rk4_kernel<d, N, OPEN, PAR, CK>, sh);
+  hipLaunchKernelGGL((g_rk4_kernel<d, N, OPEN, PAR, CK>), dim3(S), dim3(Sh::T), sh, s, dargs, dadj,
+                     n_lo, n_hi, st_in, st_out);
   return hipGetLastError();
+}
+
+template <int d, int N, bool OPEN>
+hipError_t g_launch(bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntab, int n_lo,
+                    int n_hi, const float4* st_in, float4* st_out, hipStream_t s) {
+  if (dadj != nullptr)
+    return par ? g_launch1<d, N, OPEN, true, true>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s)
+               : g_launch1<d, N, OPEN, false, true>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
+  return par ? g_launch1<d, N, OPEN, true, false>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s)
+             : g_launch1<d, N, OPEN, false, false>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
 }
 
 // Shapes with a compiled stepper: open systems D^2 <= 6561, closed systems
@@ -1460,14 +1485,14 @@ hipError_t g_launch(const GArgs* dargs, const GAdj* dadj, int S, int ntab, int n
 #define GA_CLOSED_SHAPES(X) X(2, 6) X(2, 7) X(2, 8) X(2, 9) X(2, 10) X(3, 4) X(3, 5) X(3, 6) \
   X(3, 7) X(4, 3) X(4, 4) X(4, 5) X(4, 6) X(5, 3) X(5, 4) X(5, 5)
 
-hipError_t g_dispatch(int d, int N, bool open, const GArgs* dargs, const GAdj* dadj, int S, int ntab,
+hipError_t g_dispatch(int d, int N, bool open, bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntab,
                       int n_lo, int n_hi, const float4* st_in, float4* st_out, hipStream_t s) {
 #define GA_CASE_O(dd_, nn_)          \
   if (open && d == dd_ && N == nn_) \
-    return g_launch<dd_, nn_, true>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
+    return g_launch<dd_, nn_, true>(par, dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
 #define GA_CASE_C(dd_, nn_)           \
   if (!open && d == dd_ && N == nn_) \
-    return g_launch<dd_, nn_, false>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
+    return g_launch<dd_, nn_, false>(par, dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
   GA_OPEN_SHAPES(GA_CASE_O)
   GA_CLOSED_SHAPES(GA_CASE_C)
 #undef GA_CASE_O
@@ -1500,15 +1525,19 @@ size_t g_adj_lds_bytes(int ntabg, int nacc) {
 // Open systems: one launch (gseg unused).  Closed systems: launch gseg = nck
 // down to 0 in order on one stream, 2S workgroups each (see the kernel).
 template <int d, int N, bool OPEN>
-hipError_t g_adj_launch(const GArgs* dargs, const GAdj* dadj, int S, int ntabg, int nacc,
+hipError_t g_adj_launch(bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntabg, int nacc,
                         int gseg, hipStream_t s) {
   using Sh = GShape<d, N, OPEN>;
   const size_t sh = g_adj_lds_bytes<d, N, OPEN>(ntabg, nacc);
   if (sh > 163840) return hipErrorInvalidValue;
-  (void)hipFuncSetAttribute((const void*)g_adj_kernel<d, N, OPEN>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-  hipLaunchKernelGGL((g_adj_kernel<d, N, OPEN>), dim3(OPEN ? S : 2 * S), dim3(Sh::T), sh, s,
-                     dargs, dadj, gseg);
+  auto run = [&](auto* kernel) {
+    (void)g_lds(kernel, sh);
+    hipLaunchKernelGGL(kernel, dim3(OPEN ? S : 2 * S), dim3(Sh::T), sh, s, dargs, dadj, gseg);
+  };
+  if (par)
+    run(g_adj_kernel<d, N, OPEN, true>);
+  else
+    run(g_adj_kernel<d, N, OPEN, false>);
   return hipGetLastError();
 }
 
@@ -1524,14 +1553,14 @@ size_t g_adj_lds(int d, int N, bool open, int ntabg, int nacc) {
   return ~(size_t)0;
 }
 
-hipError_t g_adj_dispatch(int d, int N, bool open, const GArgs* dargs, const GAdj* dadj, int S,
+hipError_t g_adj_dispatch(int d, int N, bool open, bool par, const GArgs* dargs, const GAdj* dadj, int S,
                           int ntabg, int nacc, int gseg, hipStream_t s) {
 #define GA_ADJ_CASE_O(dd_, nn_) \
   if (open && d == dd_ && N == nn_)  \
-    return g_adj_launch<dd_, nn_, true>(dargs, dadj, S, ntabg, nacc, gseg, s);
+    return g_adj_launch<dd_, nn_, true>(par, dargs, dadj, S, ntabg, nacc, gseg, s);
 #define GA_ADJ_CASE_C(dd_, nn_) \
   if (!open && d == dd_ && N == nn_)   \
-    return g_adj_launch<dd_, nn_, false>(dargs, dadj, S, ntabg, nacc, gseg, s);
+    return g_adj_launch<dd_, nn_, false>(par, dargs, dadj, S, ntabg, nacc, gseg, s);
   GA_OPEN_SHAPES(GA_ADJ_CASE_O)
   GA_CLOSED_SHAPES(GA_ADJ_CASE_C)
 #undef GA_ADJ_CASE_O
@@ -1615,8 +1644,12 @@ static scp_status g_args(const scp_system* sys, bool open, const double* gamma1,
   // operator rows padded to an even length, the pair block and
   // the table starting at even entries (16-byte aligned rows)
   auto even = [](int x) { return x + (x & 1); };
-  A.prow = even(dd);
-  A.orow = even(d);
+  A.par = P.parity;
+  A.nn = A.par ? (d + 1) / 2 : d;
+  A.prow = even(A.nn * A.nn);
+  A.orow = even(A.nn);
+  A.srow = A.par ? A.orow : d;
+  A.mrow = A.par ? even(A.nn + 1) : d;
   A.off_p = even(A.ndm * d * A.orow);
   A.off_j = A.off_p + A.npr * dd * A.prow;
   A.ntab = even(A.off_j + (A.has_jump ? N * dd : 0));
@@ -1678,7 +1711,7 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
   A.off_s = A.ntab;
   if (open) {
     A.grad = 1;
-    A.off_u = A.off_s + A.nsl * dd;
+    A.off_u = A.off_s + A.nsl * d * A.srow;
     A.ntabg = A.off_u + N * dd;
     A.ntabg += A.ntabg & 1;   // the second table buffer starts 16-byte aligned
   } else {
@@ -1710,10 +1743,10 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
       }
     }
     A.me_beg[N] = k;
-    A.off_m = A.off_s + A.nsl * dd;
-    A.off_d = A.off_m + 3 * N * dd;
+    A.off_m = A.off_s + A.nsl * d * A.srow;
+    A.off_d = A.off_m + 3 * N * d * A.mrow;
     A.off_u = A.off_m;
-    A.ntabg = A.off_d + 3 * A.nsl * dd;
+    A.ntabg = A.off_d + 3 * A.nsl * d * A.srow;
     A.ntabg += A.ntabg & 1;   // the second table buffer starts 16-byte aligned
   }
   if (A.ntabg > GA_MAXTAB) return fail(SCP_EINVAL, "gather-engine gradient: stage table too large");
@@ -1766,7 +1799,7 @@ static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const 
   HIPCHK(hipGetLastError());
   if (S == 0) return SCP_OK;
   hipEvent_t t0 = timing_start(sys, st);
-  HIPCHK(g_dispatch(d, N, open, dargs, nullptr, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
+  HIPCHK(g_dispatch(d, N, open, A.par != 0, dargs, nullptr, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
   timing_stop(sys, t0, 0, st);
   return SCP_OK;
 }
@@ -1900,10 +1933,10 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
   hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
   HIPCHK(hipGetLastError());
   hipEvent_t t0 = timing_start(sys, st);
-  HIPCHK(g_dispatch(d, N, true, dargs, dadj, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
+  HIPCHK(g_dispatch(d, N, true, A.par != 0, dargs, dadj, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
   timing_stop(sys, t0, 0, st);
   t0 = timing_start(sys, st);
-  HIPCHK(g_adj_dispatch(d, N, true, dargs, dadj, S, A.ntabg, w.nacc, -1, st));
+  HIPCHK(g_adj_dispatch(d, N, true, A.par != 0, dargs, dadj, S, A.ntabg, w.nacc, -1, st));
   timing_stop(sys, t0, 2, st);
   std::vector<double> part((size_t)S * w.nacc);
   HIPCHK(hipMemcpyAsync(part.data(), base + w.part, part.size() * sizeof(double),
@@ -2066,7 +2099,7 @@ scp_status launch_gather_ckpt_forward(scp_system* sys, int S, int ce, void* ws, 
   GArgs A;
   SCP_TRY(gc_prepare(sys, S, ce, false, base, ws_bytes, psi0, psiT, nullptr, true, w, A, st));
   hipEvent_t t0 = timing_start(sys, st);
-  HIPCHK(g_dispatch(sys->d, sys->n_modes, false, reinterpret_cast<GArgs*>(base + w.args),
+  HIPCHK(g_dispatch(sys->d, sys->n_modes, false, A.par != 0, reinterpret_cast<GArgs*>(base + w.args),
                     reinterpret_cast<GAdj*>(base + w.adj), S, A.ntab, 0, sys->n_steps, nullptr,
                     nullptr, st));
   timing_stop(sys, t0, 0, st);
@@ -2084,7 +2117,7 @@ scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, void* ws, size_
   SCP_TRY(gc_prepare(sys, S, ce, true, base, ws_bytes, nullptr, nullptr, cot, false, w, A, st));
   for (int gs = w.nck; gs >= 0; --gs) {
     hipEvent_t t0 = timing_start(sys, st);
-    HIPCHK(g_adj_dispatch(sys->d, sys->n_modes, false, reinterpret_cast<GArgs*>(base + w.args),
+    HIPCHK(g_adj_dispatch(sys->d, sys->n_modes, false, A.par != 0, reinterpret_cast<GArgs*>(base + w.args),
                           reinterpret_cast<GAdj*>(base + w.adj), S, A.ntabg, w.nacc, gs, st));
     timing_stop(sys, t0, 2, st);
   }
@@ -2131,7 +2164,7 @@ scp_status gather_serve_forward(scp_system* sys, int S, int ce, bool grad, void*
   SCP_TRY(gc_layout(sys, S, ce, grad, w, &A));
   char* base = static_cast<char*>(ws);
   float4* state = reinterpret_cast<float4*>(base + w.total);
-  HIPCHK(g_dispatch(sys->d, sys->n_modes, false, reinterpret_cast<GArgs*>(base + w.args),
+  HIPCHK(g_dispatch(sys->d, sys->n_modes, false, A.par != 0, reinterpret_cast<GArgs*>(base + w.args),
                     grad ? reinterpret_cast<GAdj*>(base + w.adj) : nullptr, S, A.ntab, n0, n1,
                     n0 == 0 ? nullptr : state, state, st));
   return SCP_OK;
@@ -2143,7 +2176,7 @@ scp_status gather_serve_adjoint(scp_system* sys, int S, int ce, void* ws, int gs
   GArgs A;
   SCP_TRY(gc_layout(sys, S, ce, true, w, &A));
   char* base = static_cast<char*>(ws);
-  HIPCHK(g_adj_dispatch(sys->d, sys->n_modes, false, reinterpret_cast<GArgs*>(base + w.args),
+  HIPCHK(g_adj_dispatch(sys->d, sys->n_modes, false, A.par != 0, reinterpret_cast<GArgs*>(base + w.args),
                         reinterpret_cast<GAdj*>(base + w.adj), S, A.ntabg, w.nacc, gs, st));
   return SCP_OK;
 }
@@ -2168,38 +2201,42 @@ scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, vo
 namespace {
 
 template <int d, int N>
-hipError_t g_fwd_batched_launch(bool ck, const GItem* items, int n, size_t sh, hipStream_t s) {
-  using Sh = GShape<d, N, false>;
+hipError_t g_fwd_batched_launch(bool par, bool ck, const GItem* items, int n, size_t sh,
+                                hipStream_t s) {
   if (sh > 163840) return hipErrorInvalidValue;
-  if (ck) {
-    (void)hipFuncSetAttribute((const void*)g_rk4_batched_kernel<d, N, true>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    hipLaunchKernelGGL((g_rk4_batched_kernel<d, N, true>), dim3(n), dim3(Sh::T), sh, s, items);
+  auto run = [&](auto* kernel) {
+    (void)g_lds(kernel, sh);
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(GShape<d, N, false>::T), sh, s, items);
+  };
+  if (par) {
+    if (ck) run(g_rk4_batched_kernel<d, N, true, true>);
+    else run(g_rk4_batched_kernel<d, N, true, false>);
   } else {
-    (void)hipFuncSetAttribute((const void*)g_rk4_batched_kernel<d, N, false>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    hipLaunchKernelGGL((g_rk4_batched_kernel<d, N, false>), dim3(n), dim3(Sh::T), sh, s, items);
+    if (ck) run(g_rk4_batched_kernel<d, N, false, true>);
+    else run(g_rk4_batched_kernel<d, N, false, false>);
   }
   return hipGetLastError();
 }
 
 template <int d, int N>
-hipError_t g_adj_batched_launch(const GItem* items, int n, size_t sh, hipStream_t s) {
-  using Sh = GShape<d, N, false>;
+hipError_t g_adj_batched_launch(bool par, const GItem* items, int n, size_t sh, hipStream_t s) {
   if (sh > 163840) return hipErrorInvalidValue;
-  (void)hipFuncSetAttribute((const void*)g_adj_batched_kernel<d, N>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-  hipLaunchKernelGGL((g_adj_batched_kernel<d, N>), dim3(n), dim3(Sh::T), sh, s, items);
+  auto run = [&](auto* kernel) {
+    (void)g_lds(kernel, sh);
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(GShape<d, N, false>::T), sh, s, items);
+  };
+  if (par) run(g_adj_batched_kernel<d, N, true>);
+  else run(g_adj_batched_kernel<d, N, false>);
   return hipGetLastError();
 }
 
 }  // namespace
 
-scp_status gather_launch_fwd_batched(int d, int N, bool ck, const GItem* items, int n, size_t lds,
+scp_status gather_launch_fwd_batched(int d, int N, bool par, bool ck, const GItem* items, int n, size_t lds,
                                      hipStream_t st) {
 #define GA_FWD_B(dd_, nn_) \
   if (d == dd_ && N == nn_) {                                                  \
-    HIPCHK((g_fwd_batched_launch<dd_, nn_>(ck, items, n, lds, st)));          \
+    HIPCHK((g_fwd_batched_launch<dd_, nn_>(par, ck, items, n, lds, st)));          \
     return SCP_OK;                                                            \
   }
   GA_CLOSED_SHAPES(GA_FWD_B)
@@ -2207,11 +2244,11 @@ scp_status gather_launch_fwd_batched(int d, int N, bool ck, const GItem* items, 
   return fail(SCP_EINVAL, "gather engine: no compiled stepper for this shape");
 }
 
-scp_status gather_launch_adj_batched(int d, int N, const GItem* items, int n, size_t lds,
+scp_status gather_launch_adj_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
                                      hipStream_t st) {
 #define GA_ADJ_B(dd_, nn_) \
   if (d == dd_ && N == nn_) {                                                  \
-    HIPCHK((g_adj_batched_launch<dd_, nn_>(items, n, lds, st)));              \
+    HIPCHK((g_adj_batched_launch<dd_, nn_>(par, items, n, lds, st)));              \
     return SCP_OK;                                                            \
   }
   GA_CLOSED_SHAPES(GA_ADJ_B)

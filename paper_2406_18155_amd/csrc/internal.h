@@ -308,9 +308,9 @@ struct GServeInfo {
 };
 scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, void* ws,
                              GServeInfo& out);
-scp_status gather_launch_fwd_batched(int d, int N, bool ck, const GItem* items, int n, size_t lds,
+scp_status gather_launch_fwd_batched(int d, int N, bool par, bool ck, const GItem* items, int n, size_t lds,
                                      hipStream_t st);
-scp_status gather_launch_adj_batched(int d, int N, const GItem* items, int n, size_t lds,
+scp_status gather_launch_adj_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
                                      hipStream_t st);
 size_t gather_serve_bytes(const scp_system* sys, int S, int ce, bool grad);
 scp_status gather_serve_prepare(scp_system* sys, int S, int ce, bool grad, void* ws, size_t bytes,
