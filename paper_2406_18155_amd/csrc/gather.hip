@@ -110,15 +110,17 @@ struct GArgs {
   int me[GA_MAXME];
 };
 
-// Checkpoints, costate and gradient buffers of an open-system adjoint.
+// Checkpoints, costate and gradient buffers of an adjoint.
 struct GAdj {
   float4* ck;            // [S][nck][L] (hi re, hi im, lo re, lo im) at steps g * ce
   const float2* cot;     // [S][L] cotangent of the final columns
-  float2* seg;           // [S][ce][4][L] stage inputs of the current segment
+  float2* seg;           // stage inputs, [ce][4][L] per column (open) or per slot (closed)
   const double* dctab;   // [3N][npulse] dc/dpar
-  double* part;          // [S][nacc] gradient partial sums
-  float4* lam;           // [S][L] costate (hi, lo) between reverse walks
-  int ce, nck, npulse, nacc;
+  double* part;          // open: [S][nacc] gradient partial sums
+  float4* lam;           // costate (hi, lo): open [S][L] between reverse walks,
+                         // closed [S][nck][L] at the end of every segment
+  double* gs;            // closed: [S][N][gw] sums of every step (see g_fold_kernel)
+  int ce, nck, npulse, nacc, gw;
 };
 
 #define SCP_TRY(expr)                  \
@@ -822,10 +824,221 @@ __device__ __forceinline__ float im_rowdot(const c32* __restrict__ row, const c3
   return s;
 }
 
-// Block blk of a reverse-walk launch for segment gseg (see g_adj_kernel).
+// Closed systems, costate sweep of one column over the segments g_hi down to
+// g_lo: only the costate is carried (the step map's adjoint needs no forward
+// state: kb_s = c_s lambda + c'_s yb_{s+1}, yb_s = i V_s kb_s), and its value at
+// the end of every segment is kept.  The segments' own walks, with their
+// sensitivities, then run side by side instead of one after the other: they
+// are the larger part of a gradient, and a device of few columns leaves most
+// of the chip idle.  Forward + gradient, one segment after the other -> side by
+// side: 4-fluxonium chain (16 columns) 62 -> 29 us per step, 5-transmon ring
+// (32 columns) 49 -> 21.  Entered with the costate at the end of g_hi in lam (the
+// last segment: from the cotangent); leaves it at the end of g_lo - 1.
+template <int d, int N, bool PAR>
+__device__ __forceinline__ void g_cos_body(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg,
+                                           int col, int g_hi, int g_lo) {
+  using Sh = GShape<d, N, false>;
+  constexpr int L = Sh::L, T = Sh::T, E = Sh::E;
+  extern __shared__ __align__(16) c32 lds[];
+  kptr<GArgs> A = kconst(Ag);
+  kptr<GAdj> B = kconst(Bg);
+  const int ntab = A->ntab, nrow = A->ntabg;
+  const c32* gtab = (const c32*)A->gtab;
+  const int tid = threadIdx.x;
+  const float h = A->h;
+  const int nsteps = A->nsteps, ce = B->ce, nck = B->nck;
+  float4* lam = B->lam + (size_t)col * nck * L;
+  uint32_t pk[E];
+  float lhr[E], lhm[E], llr[E], llm[E], dg[E];
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const int e = tid + r * T;
+    uint32_t p = 0;
+    float g = 0.f;
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+      const int a = (e / Sh::st(m)) % d;
+      p |= (uint32_t)a << (3 * m);
+      g -= A->delta[m][a];
+    }
+    pk[r] = p;
+    dg[r] = g;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (e < L) {
+      if (g_hi == nck - 1) {
+        const c32 c = ((const c32*)B->cot)[(size_t)col * L + e];
+        v = make_float4(c.x, c.y, 0.f, 0.f);
+        lam[(size_t)g_hi * L + e] = v;
+      } else {
+        v = lam[(size_t)g_hi * L + e];
+      }
+    }
+    lhr[r] = v.x;
+    lhm[r] = v.y;
+    llr[r] = v.z;
+    llm[r] = v.w;
+  }
+  if (g_hi <= 0) return;   // the first segment's start is not needed
+  constexpr int TB = 2 * L;   // two kb buffers, then two stage tables (16-byte aligned)
+  constexpr int GP4 = GA_PRE / 2;
+  const int n_hi = min(nsteps, (g_hi + 1) * ce), n_lo = max(g_lo, 1) * ce;
+  {
+    const c32* g0 = gtab + (size_t)stage_c(n_hi - 1, 3) * nrow;
+    for (int t = tid; t < ntab; t += T) lds[TB + t] = g0[t];
+  }
+  int cur = 0;
+#pragma unroll 1
+  for (int n = n_hi - 1; n >= n_lo; --n) {
+    float ybr[E], ybm[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) ybr[r] = ybm[r] = 0.f;
+#pragma unroll 1
+    for (int s = 3; s >= 0; --s) {
+      const float cs = (s == 0 || s == 3) ? h * (1.0f / 6.0f) : h * (1.0f / 3.0f);
+      const float cy = (s == 3) ? 0.f : (s == 2 ? h : 0.5f * h);
+      c32* kbw = lds + cur * L;
+      const c32* tw = lds + TB + cur * ntab;
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        const int e = tid + r * T;
+        if (e < L) {
+          c32 v;
+          v.x = fmaf(cs, lhr[r], cy * ybr[r]);
+          v.y = fmaf(cs, lhm[r], cy * ybm[r]);
+          kbw[e] = v;
+        }
+      }
+      __syncthreads();
+      // the next (earlier) stage's table, loaded now and stored after this stage
+      const int nn = s > 0 ? n : n - 1, sn = s > 0 ? s - 1 : 3;
+      const bool more = nn >= n_lo;
+      const c32* gnext = gtab + (size_t)stage_c(more ? nn : n, more ? sn : s) * nrow;
+      float4 pre4[GP4];
+#pragma unroll
+      for (int k = 0; k < GP4; ++k) {
+        const int t = tid + k * T;
+        if (2 * t < ntab) pre4[k] = reinterpret_cast<const float4*>(gnext)[t];
+      }
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        int e = tid + r * T;
+        uint32_t p = pk[r];
+        asm volatile("" : "+v"(e), "+v"(p));
+        if (e < L) {
+          const c32 kbe = kbw[e];
+          float yr_, yi_;
+          g_apply_adj<d, N, false, PAR>(A, kbw, tw, e, p, 0.f, dg[r], kbe.x, kbe.y, yr_, yi_);
+          ybr[r] = yr_;
+          ybm[r] = yi_;
+          llr[r] += yr_;
+          llm[r] += yi_;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (more) {
+        float4* tn4 = reinterpret_cast<float4*>(lds + TB + (cur ^ 1) * ntab);
+#pragma unroll
+        for (int k = 0; k < GP4; ++k) {
+          const int t = tid + k * T;
+          if (2 * t < ntab) tn4[t] = pre4[k];
+        }
+        for (int t = tid + GP4 * T; 2 * t < ntab; t += T)
+          tn4[t] = reinterpret_cast<const float4*>(gnext)[t];
+      }
+      cur ^= 1;
+    }
+    // lambda_n (fast two-sum, as in the segments' walks)
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      float t = lhr[r] + llr[r];
+      llr[r] -= t - lhr[r];
+      lhr[r] = t;
+      t = lhm[r] + llm[r];
+      llm[r] -= t - lhm[r];
+      lhm[r] = t;
+    }
+    if (n % ce == 0) {
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        const int e = tid + r * T;
+        if (e < L) lam[(size_t)(n / ce - 1) * L + e] = make_float4(lhr[r], lhm[r], llr[r], llm[r]);
+      }
+    }
+  }
+}
+
+template <int d, int N, bool PAR>
+__global__ void __launch_bounds__((GShape<d, N, false>::T))
+g_cos_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg, int g_hi, int g_lo) {
+  g_cos_body<d, N, PAR>(Ag, Bg, blockIdx.x, g_hi, g_lo);
+}
+
+// Batched (serving): item.gseg the first segment, item.n_lo the last.
+template <int d, int N, bool PAR>
+__global__ void __launch_bounds__((GShape<d, N, false>::T))
+g_cos_batched_kernel(const GItem* __restrict__ items) {
+  kptr<GItem> it = kconst(items) + blockIdx.x;
+  g_cos_body<d, N, PAR>((const GArgs*)it->A, (const GAdj*)it->B, it->col, it->gseg, it->n_lo);
+}
+
+// Closed systems: the gradient from the steps' sums.  Block b of 64 steps of
+// a column, last step first: the pulse parameters take dc/dpar of every stage
+// times its drive-slot sum, the others the sums as they are.  The grouping is
+// by step, not by segment, so the gradient does not depend on the checkpoint
+// interval.
+constexpr int GF_STEPS = 64;
+__global__ void __launch_bounds__(256) g_fold_kernel(const GArgs* __restrict__ Ag,
+                                                     const GAdj* __restrict__ Bg, int nblk,
+                                                     double* __restrict__ out) {
+  const GArgs& A = *Ag;
+  const GAdj& B = *Bg;
+  const int col = blockIdx.x / nblk, b = blockIdx.x - col * nblk;
+  const int n0 = b * GF_STEPS, n1 = min(A.nsteps, n0 + GF_STEPS);
+  const double* gs = B.gs + (size_t)col * A.nsteps * B.gw;
+  const int nds = A.nds;
+  for (int k = threadIdx.x; k < B.nacc; k += blockDim.x) {
+    double v = 0.0;
+    if (k < B.npulse) {
+      int ds = -1;
+      for (int q = 0; q < A.ndr; ++q)
+        if (k >= A.dr_par0[q] && k < A.dr_par0[q] + A.dr_npar[q]) ds = A.dr_ds[q];
+      for (int n = n1 - 1; n >= n0; --n) {
+        const double* g = gs + (size_t)n * B.gw + ds;
+        const double* dc = B.dctab + (size_t)3 * n * B.npulse + k;
+        const double c0 = dc[0], c1 = dc[B.npulse], c2 = dc[2 * B.npulse];
+        const double x3 = g[3 * nds], x2 = g[2 * nds], x1 = g[nds], x0 = g[0];
+        v += c2 * x3;
+        v += c1 * x2;
+        v += c1 * x1;
+        v += c0 * x0;
+      }
+    } else {
+      const double* g = gs + 4 * nds + (k - B.npulse);
+      for (int n = n1 - 1; n >= n0; --n) v += g[(size_t)n * B.gw];
+    }
+    out[(size_t)blockIdx.x * B.nacc + k] = v;
+  }
+}
+// grad[k]: the blocks of a column from the last, columns in order.
+__global__ void __launch_bounds__(64) g_fold_sum_kernel(const double* __restrict__ part, int S,
+                                                        int nblk, int nacc,
+                                                        double* __restrict__ grad) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nacc) return;
+  double v = 0.0;
+  for (int c = 0; c < S; ++c) {
+    double u = 0.0;
+    for (int b = nblk - 1; b >= 0; --b) u += part[((size_t)c * nblk + b) * nacc + k];
+    v += u;
+  }
+  grad[k] = v;
+}
+
+// One workgroup's reverse walk: open systems column col over every segment;
+// closed systems segment gseg of column col, its stage inputs in buffer slot.
 template <int d, int N, bool OPEN, bool PAR>
 __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg,
-                                           int gseg, int blk) {
+                                           int gseg, int col, int slot) {
   using Sh = GShape<d, N, OPEN>;
   using B_ = Nb<d, PAR>;
   constexpr int L = Sh::L, T = Sh::T, E = Sh::E, D = Sh::D, dd = d * d;
@@ -849,21 +1062,15 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float h = A->h;
   const int nsteps = A->nsteps, ce = B->ce, nck = B->nck;
-  // Open systems: one launch walks every segment (recompute, then reverse).
-  // Closed systems: one launch per segment, 2S workgroups: the first S walk
-  // segment gseg back while the other S recompute segment gseg - 1 into the
-  // other stage-input buffer, so the recompute hides behind the reverse walk.
-  const int S = A->S;
-  const bool rev_role = OPEN || blk < S;
-  const int col = (OPEN || rev_role) ? blk : blk - S;
-  const int g_hi = OPEN ? nck - 1 : (rev_role ? gseg : gseg - 1);
+  // Open systems: one workgroup per column walks every segment (recompute,
+  // then reverse).  Closed systems: one workgroup per column and segment, the
+  // costate at the segment's end from the sweep before (g_cos_body).
+  const int g_hi = OPEN ? nck - 1 : gseg;
   const int g_lo = OPEN ? 0 : g_hi;
-  if (!OPEN && (g_hi < 0 || g_hi >= nck)) return;
   const int nds = uni(A->nds), ncp = uni(A->ncp), ndr = uni(A->ndr);
   const int nv = OPEN ? 0 : 3 * N + ncp;   // closed: device-parameter and coupling sums
-  // closed systems continue the accumulators of the later segments
-  const bool resume = !OPEN && rev_role && g_hi < nck - 1;
-  for (int t = tid; t < nacc; t += T) acc[t] = resume ? B->part[(size_t)col * nacc + t] : 0.0;
+  if (OPEN)
+    for (int t = tid; t < nacc; t += T) acc[t] = 0.0;
   uint32_t pk[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) {
@@ -879,25 +1086,34 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
   }
   // the costate lives in registers only during the reverse walks; between
   // them (while a segment is recomputed) it waits in device memory
-  float4* lsave = B->lam + (size_t)col * L;
-  int prev_row = -1;   // step-grid row of the stage whose sums wait in wsum
-  int par = 0;         // parity of the wsum buffer being filled
-  // fold the previous stage's per-wave sums in a fixed order: the drive slots
-  // into the pulse parameters (one thread per drive, times dc/dpar of that
-  // stage), closed systems' device-parameter and coupling sums as they are
+  float4* lsave = B->lam + (OPEN ? (size_t)col : (size_t)col * nck + gseg) * L;
+  int prev_n = -1, prev_s = 0;   // the stage whose sums wait in wsum
+  int par = 0;                   // parity of the wsum buffer being filled
+  double vstep = 0.0;            // closed: this thread's sum over the step's stages
+  // fold the previous stage's per-wave sums in a fixed order.  Open systems:
+  // the drive slots into the pulse parameters (one thread per drive, times
+  // dc/dpar of that stage).  Closed systems: into the step's row of gs, the
+  // drive slots of each stage, then the device-parameter and coupling sums
+  // over the four stages (at most GA_NV <= 64 sums: one thread each).
   auto fold_prev = [&]() {
-    for (int t = tid; t < ndr + nv; t += T) {
-      if (t < ndr) {
+    if constexpr (OPEN) {
+      for (int t = tid; t < ndr; t += T) {
         const int ds = A->dr_ds[t];
         double G = 0.0;
         for (int w = 0; w < NW; ++w) G += (double)wsum[((par ^ 1) * NW + w) * WS + ds];
-        const double* dct = B->dctab + (size_t)prev_row * npulse;
+        const double* dct = B->dctab + (size_t)stage_c(prev_n, prev_s) * npulse;
         for (int p = A->dr_par0[t]; p < A->dr_par0[t] + A->dr_npar[t]; ++p) acc[p] += dct[p] * G;
+      }
+    } else if (tid < nds + nv) {
+      const int k = tid < nds ? tid : GA_MAXDS + tid - nds;
+      double G = 0.0;
+      for (int w = 0; w < NW; ++w) G += (double)wsum[((par ^ 1) * NW + w) * WS + k];
+      double* row = B->gs + ((size_t)col * nsteps + prev_n) * B->gw;
+      if (tid < nds) {
+        row[prev_s * nds + tid] = G;
       } else {
-        const int k = t - ndr;
-        double G = 0.0;
-        for (int w = 0; w < NW; ++w) G += (double)wsum[((par ^ 1) * NW + w) * WS + GA_MAXDS + k];
-        acc[npulse + k] += G;
+        vstep = prev_s == 3 ? G : vstep + G;
+        if (prev_s == 0) row[3 * nds + tid] = vstep;
       }
     }
   };
@@ -905,11 +1121,11 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
 #pragma unroll 1
   for (int g = g_hi; g >= g_lo; --g) {
     const int n0 = g * ce, n1 = min(nsteps, n0 + ce);
-    // stage inputs of the segment: one buffer per column (open systems), two
-    // alternating by segment (closed systems)
-    c32* segc = (c32*)B->seg + ((size_t)col * (OPEN ? 1 : 2) + (OPEN ? 0 : (g & 1))) * ce * 4 * L;
+    // stage inputs of the segment: one buffer per column (open systems) or
+    // per workgroup in flight (closed systems)
+    c32* segc = (c32*)B->seg + (size_t)(OPEN ? col : slot) * ce * 4 * L;
     // ---- recompute the segment from its checkpoint, storing the stage inputs
-    if (OPEN || !rev_role) {
+    {
       float hr[E], hm[E], lr[E], lm[E], ar[E], am_[E];
       const float4* ck = B->ck + ((size_t)col * nck + g) * L;
 #pragma unroll
@@ -1012,7 +1228,6 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
         }
       }
     }
-    if (!OPEN && !rev_role) return;
     // ---- reverse walk of the segment
     float lhr[E], lhm[E], llr[E], llm[E];   // costate (hi, lo)
 #pragma unroll
@@ -1020,7 +1235,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
       const int e = tid + r * T;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (e < L) {
-        if (g == nck - 1) {
+        if (OPEN && g == nck - 1) {
           const c32 c = ((const c32*)B->cot)[(size_t)col * L + e];
           v = make_float4(c.x, c.y, 0.f, 0.f);
         } else {
@@ -1111,7 +1326,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
           }
         }
         // the previous stage's sums are complete
-        if (prev_row >= 0) fold_prev();
+        if (prev_n >= 0) fold_prev();
 #pragma unroll
         for (int r = 0; r < E; ++r) {
           int e = tid + r * T;
@@ -1365,7 +1580,8 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
             }
           }
         }
-        prev_row = row;
+        prev_n = n;
+        prev_s = s;
         par ^= 1;
         cur ^= 1;
       }
@@ -1381,7 +1597,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
         lhm[r] = t;
       }
     }
-    if (g > 0) {
+    if (OPEN && g > 0) {
 #pragma unroll
       for (int r = 0; r < E; ++r) {
         const int e = tid + r * T;
@@ -1391,7 +1607,8 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
     __syncthreads();
   }
   // the last stage's sums
-  if (prev_row >= 0) fold_prev();
+  if (prev_n >= 0) fold_prev();
+  if (!OPEN) return;
   __syncthreads();
   for (int t = tid; t < nacc; t += T) B->part[(size_t)col * nacc + t] = acc[t];
 }
@@ -1399,16 +1616,19 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
 template <int d, int N, bool OPEN, bool PAR>
 __global__ void __launch_bounds__((GShape<d, N, OPEN>::T))
 g_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg, int gseg) {
-  g_adj_body<d, N, OPEN, PAR>(Ag, Bg, gseg, blockIdx.x);
+  // closed: S workgroups per segment, from segment gseg down
+  const int S = OPEN ? (int)gridDim.x : Ag->S;
+  const int k = blockIdx.x / S, col = blockIdx.x - k * S;
+  g_adj_body<d, N, OPEN, PAR>(Ag, Bg, gseg - k, col, blockIdx.x);
 }
 
-// Batched (serving, closed systems): item.col is the block of the request's
-// 2S-block launch, item.gseg its segment.
+// Batched (serving, closed systems): item.gseg is the segment, item.n_lo the
+// stage-input buffer.
 template <int d, int N, bool PAR>
 __global__ void __launch_bounds__((GShape<d, N, false>::T))
 g_adj_batched_kernel(const GItem* __restrict__ items) {
   kptr<GItem> it = kconst(items) + blockIdx.x;
-  g_adj_body<d, N, false, PAR>((const GArgs*)it->A, (const GAdj*)it->B, it->gseg, it->col);
+  g_adj_body<d, N, false, PAR>((const GArgs*)it->A, (const GAdj*)it->B, it->gseg, it->col, it->n_lo);
 }
 
 // Unit-rate relaxation band of every mode at every half-step q (t = q h/2):
@@ -1522,17 +1742,17 @@ size_t g_adj_lds_bytes(int ntabg, int nacc) {
          sizeof(float) * 2 * (Sh::T / 64) * (OPEN ? GA_MAXDS : GA_NV);
 }
 
-// Open systems: one launch (gseg unused).  Closed systems: launch gseg = nck
-// down to 0 in order on one stream, 2S workgroups each (see the kernel).
+// Open systems: one launch (gseg, nseg unused).  Closed systems: nseg segments
+// from gseg down, S workgroups each, after the costate sweep over them.
 template <int d, int N, bool OPEN>
 hipError_t g_adj_launch(bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntabg, int nacc,
-                        int gseg, hipStream_t s) {
+                        int gseg, int nseg, hipStream_t s) {
   using Sh = GShape<d, N, OPEN>;
   const size_t sh = g_adj_lds_bytes<d, N, OPEN>(ntabg, nacc);
   if (sh > 163840) return hipErrorInvalidValue;
   auto run = [&](auto* kernel) {
     (void)g_lds(kernel, sh);
-    hipLaunchKernelGGL(kernel, dim3(OPEN ? S : 2 * S), dim3(Sh::T), sh, s, dargs, dadj, gseg);
+    hipLaunchKernelGGL(kernel, dim3(OPEN ? S : nseg * S), dim3(Sh::T), sh, s, dargs, dadj, gseg);
   };
   if (par)
     run(g_adj_kernel<d, N, OPEN, true>);
@@ -1554,17 +1774,47 @@ size_t g_adj_lds(int d, int N, bool open, int ntabg, int nacc) {
 }
 
 hipError_t g_adj_dispatch(int d, int N, bool open, bool par, const GArgs* dargs, const GAdj* dadj, int S,
-                          int ntabg, int nacc, int gseg, hipStream_t s) {
+                          int ntabg, int nacc, int gseg, int nseg, hipStream_t s) {
 #define GA_ADJ_CASE_O(dd_, nn_) \
   if (open && d == dd_ && N == nn_)  \
-    return g_adj_launch<dd_, nn_, true>(par, dargs, dadj, S, ntabg, nacc, gseg, s);
+    return g_adj_launch<dd_, nn_, true>(par, dargs, dadj, S, ntabg, nacc, gseg, nseg, s);
 #define GA_ADJ_CASE_C(dd_, nn_) \
   if (!open && d == dd_ && N == nn_)   \
-    return g_adj_launch<dd_, nn_, false>(par, dargs, dadj, S, ntabg, nacc, gseg, s);
+    return g_adj_launch<dd_, nn_, false>(par, dargs, dadj, S, ntabg, nacc, gseg, nseg, s);
   GA_OPEN_SHAPES(GA_ADJ_CASE_O)
   GA_CLOSED_SHAPES(GA_ADJ_CASE_C)
 #undef GA_ADJ_CASE_O
 #undef GA_ADJ_CASE_C
+  return hipErrorInvalidValue;
+}
+
+template <int d, int N>
+size_t g_cos_lds_bytes(int ntab) {
+  return sizeof(c32) * (2 * (size_t)GShape<d, N, false>::L + 2 * (size_t)ntab);
+}
+
+// Costate sweep of a closed system over the segments g_hi down to g_lo.
+template <int d, int N>
+hipError_t g_cos_launch(bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntab, int g_hi,
+                        int g_lo, hipStream_t s) {
+  const size_t sh = g_cos_lds_bytes<d, N>(ntab);
+  auto run = [&](auto* kernel) {
+    (void)g_lds(kernel, sh);
+    hipLaunchKernelGGL(kernel, dim3(S), dim3(GShape<d, N, false>::T), sh, s, dargs, dadj, g_hi, g_lo);
+  };
+  if (par)
+    run(g_cos_kernel<d, N, true>);
+  else
+    run(g_cos_kernel<d, N, false>);
+  return hipGetLastError();
+}
+
+hipError_t g_cos_dispatch(int d, int N, bool par, const GArgs* dargs, const GAdj* dadj, int S,
+                          int ntab, int g_hi, int g_lo, hipStream_t s) {
+#define GA_COS_CASE(dd_, nn_) \
+  if (d == dd_ && N == nn_) return g_cos_launch<dd_, nn_>(par, dargs, dadj, S, ntab, g_hi, g_lo, s);
+  GA_CLOSED_SHAPES(GA_COS_CASE)
+#undef GA_COS_CASE
   return hipErrorInvalidValue;
 }
 
@@ -1936,7 +2186,7 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
   HIPCHK(g_dispatch(d, N, true, A.par != 0, dargs, dadj, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
   timing_stop(sys, t0, 0, st);
   t0 = timing_start(sys, st);
-  HIPCHK(g_adj_dispatch(d, N, true, A.par != 0, dargs, dadj, S, A.ntabg, w.nacc, -1, st));
+  HIPCHK(g_adj_dispatch(d, N, true, A.par != 0, dargs, dadj, S, A.ntabg, w.nacc, 0, 1, st));
   timing_stop(sys, t0, 2, st);
   std::vector<double> part((size_t)S * w.nacc);
   HIPCHK(hipMemcpyAsync(part.data(), base + w.part, part.size() * sizeof(double),
@@ -1993,12 +2243,14 @@ scp_status launch_gather_forward(scp_system* sys, int S, void* ws, size_t ws_byt
 
 // Closed-system gradient on the gather engine.  Workspace: [GArgs][GAdj]
 // [stage tables [3N][ntabg]][checkpoints [S][nck][D] float4] and, for the
-// adjoint, [stage inputs [S][2][ce][4][D]][partial sums [S][nacc] double]
-// [costate [S][D] float4].  The forward with checkpoints and the adjoint
-// share the offsets of the first four.
+// adjoint, [stage inputs [S nseg][ce][4][D]][sums of the steps [S][N][gw]
+// double][their blocks [S][nblk][nacc] double][gradient [nacc] double][costate
+// at the segments' ends [S][nck][D] float4].  The forward with checkpoints and
+// the adjoint share the offsets of the first four.
 struct GcLayout {
-  size_t args, adj, gtab, ck, seg, part, lam, total;
-  int nck, nacc;
+  size_t args, adj, gtab, ck, seg, gs, part, grad, lam, total;
+  int nck, nacc, gw, nblk;
+  int nseg;   // segments walked side by side
 };
 
 static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad, GcLayout& w,
@@ -2012,6 +2264,12 @@ static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad
   const int N = sys->n_steps;
   w.nck = (N + ce - 1) / ce;
   w.nacc = sys->plan.npulse + 3 * sys->n_modes + sys->plan.ncoup;
+  w.gw = 4 * A.nds + 3 * sys->n_modes + A.ncp;
+  w.nblk = (N + GF_STEPS - 1) / GF_STEPS;
+  // two workgroups for every compute unit, where there are that many segments
+  // (each holds a buffer of stage inputs); two segments at least, as many
+  // buffers as a walk one segment after the other needs to hide its recompute
+  w.nseg = std::min(w.nck, std::max(2, (512 + S - 1) / S));
   size_t off = 0;
   w.args = off;
   off += align256(sizeof(GArgs));
@@ -2021,14 +2279,18 @@ static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad
   off += align256(3 * (size_t)N * A.ntabg * sizeof(float2));
   w.ck = off;
   off += align256((size_t)S * w.nck * L * sizeof(float4));
-  w.seg = w.part = w.lam = off;
+  w.seg = w.gs = w.part = w.grad = w.lam = off;
   if (with_grad) {
-    w.seg = off;   // two stage-input buffers per column (segments alternate)
-    off += align256((size_t)S * 2 * ce * 4 * L * sizeof(float2));
+    w.seg = off;
+    off += align256((size_t)S * w.nseg * std::min(ce, N) * 4 * L * sizeof(float2));
+    w.gs = off;
+    off += align256((size_t)S * N * w.gw * sizeof(double));
     w.part = off;
-    off += align256((size_t)S * w.nacc * sizeof(double));
+    off += align256((size_t)S * w.nblk * w.nacc * sizeof(double));
+    w.grad = off;
+    off += align256((size_t)w.nacc * sizeof(double));
     w.lam = off;
-    off += align256((size_t)S * L * sizeof(float4));
+    off += align256((size_t)S * w.nck * L * sizeof(float4));
   }
   w.total = off;
   if (g_adj_lds(sys->d, sys->n_modes, false, A.ntabg, w.nacc) > 163840)
@@ -2074,9 +2336,10 @@ static scp_status gc_prepare(scp_system* sys, int S, int ce, bool with_grad, cha
   B.cot = cot;
   B.seg = with_grad ? reinterpret_cast<float2*>(base + w.seg) : nullptr;
   B.dctab = sys->d_dctab64;
-  B.part = with_grad ? reinterpret_cast<double*>(base + w.part) : nullptr;
+  B.gs = with_grad ? reinterpret_cast<double*>(base + w.gs) : nullptr;
+  B.gw = w.gw;
   B.lam = with_grad ? reinterpret_cast<float4*>(base + w.lam) : nullptr;
-  B.ce = ce;
+  B.ce = std::min(ce, sys->n_steps);   // one segment: the same walk
   B.nck = w.nck;
   B.npulse = sys->plan.npulse;
   B.nacc = w.nacc;
@@ -2106,31 +2369,43 @@ scp_status launch_gather_ckpt_forward(scp_system* sys, int S, int ce, void* ws, 
   return SCP_OK;
 }
 
+// The gradient from the steps' sums, copied to the host (synchronises st).
+static scp_status gc_fold(scp_system* sys, int S, char* base, const GcLayout& w, double* grad,
+                          hipStream_t st) {
+  hipLaunchKernelGGL(g_fold_kernel, dim3(S * w.nblk), dim3(256), 0, st,
+                     reinterpret_cast<GArgs*>(base + w.args), reinterpret_cast<GAdj*>(base + w.adj),
+                     w.nblk, reinterpret_cast<double*>(base + w.part));
+  HIPCHK(hipGetLastError());
+  hipLaunchKernelGGL(g_fold_sum_kernel, dim3((w.nacc + 63) / 64), dim3(64), 0, st,
+                     reinterpret_cast<double*>(base + w.part), S, w.nblk, w.nacc,
+                     reinterpret_cast<double*>(base + w.grad));
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipMemcpyAsync(grad, base + w.grad, w.nacc * sizeof(double), hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  return SCP_OK;
+}
+
 // The reverse walk from the checkpoints (and stage tables) that
-// launch_gather_ckpt_forward left in the same workspace; the gradient is the
-// fixed-order sum of the columns' partial sums.
+// launch_gather_ckpt_forward left in the same workspace: the costate sweep,
+// then the segments side by side.
 scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, void* ws, size_t ws_bytes,
                                  const float2* cot, double* grad, hipStream_t st) {
   char* base = static_cast<char*>(ws);
   GcLayout w;
   GArgs A;
   SCP_TRY(gc_prepare(sys, S, ce, true, base, ws_bytes, nullptr, nullptr, cot, false, w, A, st));
-  for (int gs = w.nck; gs >= 0; --gs) {
-    hipEvent_t t0 = timing_start(sys, st);
-    HIPCHK(g_adj_dispatch(sys->d, sys->n_modes, false, A.par != 0, reinterpret_cast<GArgs*>(base + w.args),
-                          reinterpret_cast<GAdj*>(base + w.adj), S, A.ntabg, w.nacc, gs, st));
-    timing_stop(sys, t0, 2, st);
-  }
-  std::vector<double> part((size_t)S * w.nacc);
-  HIPCHK(hipMemcpyAsync(part.data(), base + w.part, part.size() * sizeof(double),
-                        hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  for (int k = 0; k < w.nacc; ++k) {
-    double v = 0.0;
-    for (int c = 0; c < S; ++c) v += part[(size_t)c * w.nacc + k];   // fixed order
-    if (!std::isfinite(v)) return fail(SCP_ENONFINITE, "gradient is not finite");
-    grad[k] = v;
-  }
+  const GArgs* dargs = reinterpret_cast<GArgs*>(base + w.args);
+  const GAdj* dadj = reinterpret_cast<GAdj*>(base + w.adj);
+  const int d = sys->d, N = sys->n_modes;
+  hipEvent_t t0 = timing_start(sys, st);
+  HIPCHK(g_cos_dispatch(d, N, A.par != 0, dargs, dadj, S, A.ntab, w.nck - 1, 0, st));
+  for (int gs = w.nck - 1; gs >= 0; gs -= w.nseg)
+    HIPCHK(g_adj_dispatch(d, N, false, A.par != 0, dargs, dadj, S, A.ntabg, w.nacc, gs,
+                          std::min(w.nseg, gs + 1), st));
+  timing_stop(sys, t0, 2, st);
+  SCP_TRY(gc_fold(sys, S, base, w, grad, st));
+  for (int k = 0; k < w.nacc; ++k)
+    if (!std::isfinite(grad[k])) return fail(SCP_ENONFINITE, "gradient is not finite");
   return SCP_OK;
 }
 
@@ -2154,33 +2429,6 @@ scp_status gather_serve_prepare(scp_system* sys, int S, int ce, bool grad, void*
                     st);
 }
 
-// Forward steps [n0, n1): from psi0 when n0 = 0, else from the saved state;
-// the state is saved after, psiT written when n1 = n_steps, checkpoints kept
-// when the gradient is wanted.
-scp_status gather_serve_forward(scp_system* sys, int S, int ce, bool grad, void* ws, int n0, int n1,
-                                hipStream_t st) {
-  GcLayout w;
-  GArgs A;
-  SCP_TRY(gc_layout(sys, S, ce, grad, w, &A));
-  char* base = static_cast<char*>(ws);
-  float4* state = reinterpret_cast<float4*>(base + w.total);
-  HIPCHK(g_dispatch(sys->d, sys->n_modes, false, A.par != 0, reinterpret_cast<GArgs*>(base + w.args),
-                    grad ? reinterpret_cast<GAdj*>(base + w.adj) : nullptr, S, A.ntab, n0, n1,
-                    n0 == 0 ? nullptr : state, state, st));
-  return SCP_OK;
-}
-
-// One launch of the reverse walk (gs = nckpt down to 0, in order).
-scp_status gather_serve_adjoint(scp_system* sys, int S, int ce, void* ws, int gs, hipStream_t st) {
-  GcLayout w;
-  GArgs A;
-  SCP_TRY(gc_layout(sys, S, ce, true, w, &A));
-  char* base = static_cast<char*>(ws);
-  HIPCHK(g_adj_dispatch(sys->d, sys->n_modes, false, A.par != 0, reinterpret_cast<GArgs*>(base + w.args),
-                        reinterpret_cast<GAdj*>(base + w.adj), S, A.ntabg, w.nacc, gs, st));
-  return SCP_OK;
-}
-
 int gather_serve_nckpt(const scp_system* sys, int ce) { return (sys->n_steps + ce - 1) / ce; }
 
 scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, void* ws,
@@ -2194,7 +2442,9 @@ scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, vo
   out.state = reinterpret_cast<float4*>(base + w.total);
   out.lds_fwd = sizeof(c32) * (3 * (size_t)sys->D + ((3 * (size_t)sys->D) & 1) + 2 * (size_t)A.ntab);
   out.lds_adj = g_adj_lds(sys->d, sys->n_modes, false, A.ntabg, w.nacc);
+  out.lds_cos = sizeof(c32) * (2 * (size_t)sys->D + 2 * (size_t)A.ntab);
   out.nck = w.nck;
+  out.nseg = w.nseg;
   return SCP_OK;
 }
 
@@ -2230,7 +2480,31 @@ hipError_t g_adj_batched_launch(bool par, const GItem* items, int n, size_t sh, 
   return hipGetLastError();
 }
 
+template <int d, int N>
+hipError_t g_cos_batched_launch(bool par, const GItem* items, int n, size_t sh, hipStream_t s) {
+  if (sh > 163840) return hipErrorInvalidValue;
+  auto run = [&](auto* kernel) {
+    (void)g_lds(kernel, sh);
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(GShape<d, N, false>::T), sh, s, items);
+  };
+  if (par) run(g_cos_batched_kernel<d, N, true>);
+  else run(g_cos_batched_kernel<d, N, false>);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+scp_status gather_launch_cos_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
+                                     hipStream_t st) {
+#define GA_COS_B(dd_, nn_) \
+  if (d == dd_ && N == nn_) {                                                  \
+    HIPCHK((g_cos_batched_launch<dd_, nn_>(par, items, n, lds, st)));         \
+    return SCP_OK;                                                            \
+  }
+  GA_CLOSED_SHAPES(GA_COS_B)
+#undef GA_COS_B
+  return fail(SCP_EINVAL, "gather engine: no compiled stepper for this shape");
+}
 
 scp_status gather_launch_fwd_batched(int d, int N, bool par, bool ck, const GItem* items, int n, size_t lds,
                                      hipStream_t st) {
@@ -2261,17 +2535,8 @@ scp_status gather_serve_gradient(scp_system* sys, int S, int ce, void* ws, std::
                                  hipStream_t st) {
   GcLayout w;
   SCP_TRY(gc_layout(sys, S, ce, true, w, nullptr));
-  std::vector<double> part((size_t)S * w.nacc);
-  HIPCHK(hipMemcpyAsync(part.data(), static_cast<char*>(ws) + w.part, part.size() * sizeof(double),
-                        hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
   grad.assign(w.nacc, 0.0);
-  for (int k = 0; k < w.nacc; ++k) {
-    double v = 0.0;
-    for (int c = 0; c < S; ++c) v += part[(size_t)c * w.nacc + k];   // fixed order
-    grad[k] = v;
-  }
-  return SCP_OK;
+  return gc_fold(sys, S, static_cast<char*>(ws), w, grad.data(), st);
 }
 
 // ---------------------------------------------------------------------------

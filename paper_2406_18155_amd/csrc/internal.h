@@ -295,16 +295,18 @@ struct GItem {
   const void* B;          // its adjoint description (device GAdj; nullptr: no checkpoints)
   const float4* st_in;    // forward: the saved state (nullptr: start from the columns)
   float4* st_out;         // forward: where the state is saved
-  int col, n_lo, n_hi;    // forward: column and step range; reverse: col = block of 2S
-  int gseg;               // reverse: segment
+  int col, n_lo, n_hi;    // column; forward: step range; costate sweep: n_lo the last
+                          // segment; segment walk: n_lo its stage-input buffer
+  int gseg;               // costate sweep: first segment; segment walk: the segment
 };
 // Device pointers and LDS needs of a request prepared by gather_serve_prepare.
 struct GServeInfo {
   const void* A;
   const void* B;
   float4* state;
-  size_t lds_fwd, lds_adj;
+  size_t lds_fwd, lds_adj, lds_cos;
   int nck;
+  int nseg;   // segments walked side by side (stage-input buffers: nseg per column)
 };
 scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, void* ws,
                              GServeInfo& out);
@@ -312,12 +314,11 @@ scp_status gather_launch_fwd_batched(int d, int N, bool par, bool ck, const GIte
                                      hipStream_t st);
 scp_status gather_launch_adj_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
                                      hipStream_t st);
+scp_status gather_launch_cos_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
+                                     hipStream_t st);
 size_t gather_serve_bytes(const scp_system* sys, int S, int ce, bool grad);
 scp_status gather_serve_prepare(scp_system* sys, int S, int ce, bool grad, void* ws, size_t bytes,
                                 const float2* psi0, float2* psiT, const float2* cot, hipStream_t st);
-scp_status gather_serve_forward(scp_system* sys, int S, int ce, bool grad, void* ws, int n0, int n1,
-                                hipStream_t st);
-scp_status gather_serve_adjoint(scp_system* sys, int S, int ce, void* ws, int gs, hipStream_t st);
 int gather_serve_nckpt(const scp_system* sys, int ce);
 scp_status gather_serve_gradient(scp_system* sys, int S, int ce, void* ws, std::vector<double>& grad,
                                  hipStream_t st);

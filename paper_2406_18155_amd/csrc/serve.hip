@@ -405,8 +405,8 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
     for (Request* r : sv->active)
       if (r->gather) {
         const int steps = std::max(8, (int)(sv->chunk_work / r->cost_step));
-        const size_t rounds = r->phase == 0 ? 1 : (size_t)std::max(1, steps / r->ce);
-        need += rounds * (2 * (size_t)r->S * sizeof(GItem) + 2 * 256);
+        const size_t segs = r->phase == 0 ? 1 : (size_t)std::max(1, steps / r->ce);
+        need += (segs + 1) * ((size_t)r->S * sizeof(GItem) + 2 * 256);
       }
     scp_status s = ensure_items(sv, need);
     if (s != SCP_OK) return s;
@@ -523,29 +523,41 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
           s = gather_launch_fwd_batched(d, N, par, ck, (const GItem*)dptr, nit, lds, st);
           if (s != SCP_OK) return s;
         } else {
-          // round j: launch seg_next - j of every request that still has one this tick
+          // this tick's segments of every request: the costate sweep over them,
+          // then rounds of at most nseg segments of each side by side
           int rounds = 0;
           std::vector<int> g_lo(kv.second.size());
+          GItem* it = (GItem*)((char*)sv->h_items + off);
+          int nit = 0;
+          size_t lds = 0;
           for (size_t q = 0; q < kv.second.size(); ++q) {
             Request* r = kv.second[q];
             const int steps = std::max(8, (int)(sv->chunk_work / r->cost_step));
-            const int launches = std::max(1, steps / r->ce);
-            g_lo[q] = std::max(0, r->seg_next - launches + 1);
-            rounds = std::max(rounds, r->seg_next - g_lo[q] + 1);
+            const int segs = std::max(1, steps / r->ce);
+            g_lo[q] = std::max(0, r->seg_next - segs + 1);
+            rounds = std::max(rounds, (r->seg_next - g_lo[q]) / r->gi.nseg + 1);
+            for (int c = 0; c < r->S; ++c)
+              it[nit++] = GItem{r->gi.A, r->gi.B, nullptr, nullptr, c, g_lo[q], 0, r->seg_next};
+            lds = std::max(lds, r->gi.lds_cos);
           }
+          void* dptr = nullptr;
+          if (!stage(it, (size_t)nit * sizeof(GItem), st, &dptr)) return fail(SCP_EHIP, "item upload");
+          s = gather_launch_cos_batched(d, N, par, (const GItem*)dptr, nit, lds, st);
+          if (s != SCP_OK) return s;
           for (int j = 0; j < rounds; ++j) {
-            GItem* it = (GItem*)((char*)sv->h_items + off);
-            int nit = 0;
-            size_t lds = 0;
+            it = (GItem*)((char*)sv->h_items + off);
+            nit = 0;
+            lds = 0;
             for (size_t q = 0; q < kv.second.size(); ++q) {
               Request* r = kv.second[q];
-              const int gs = r->seg_next - j;
-              if (gs < g_lo[q]) continue;
-              for (int b = 0; b < 2 * r->S; ++b)
-                it[nit++] = GItem{r->gi.A, r->gi.B, nullptr, nullptr, b, 0, 0, gs};
-              lds = std::max(lds, r->gi.lds_adj);
+              for (int k = 0; k < r->gi.nseg; ++k) {
+                const int gs = r->seg_next - j * r->gi.nseg - k;
+                if (gs < g_lo[q]) break;
+                for (int c = 0; c < r->S; ++c)
+                  it[nit++] = GItem{r->gi.A, r->gi.B, nullptr, nullptr, c, k * r->S + c, 0, gs};
+                lds = std::max(lds, r->gi.lds_adj);
+              }
             }
-            void* dptr = nullptr;
             if (!stage(it, (size_t)nit * sizeof(GItem), st, &dptr))
               return fail(SCP_EHIP, "item upload");
             s = gather_launch_adj_batched(d, N, par, (const GItem*)dptr, nit, lds, st);
@@ -578,9 +590,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
         r->F = (tau.x * tau.x + tau.y * tau.y) / ((double)r->d_c * r->d_c);
         if (r->want_grad) {
           r->phase = 1;
-          // the gather engine's reverse launches run nckpt down to 0 (the
-          // first recomputes the last segment only)
-          r->seg_next = r->gather ? gather_serve_nckpt(r->sys, r->ce) : r->nckpt - 1;
+          r->seg_next = r->gather ? gather_serve_nckpt(r->sys, r->ce) - 1 : r->nckpt - 1;
         } else {
           done = true;
         }
