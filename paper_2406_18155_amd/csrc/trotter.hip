@@ -572,9 +572,283 @@ hipError_t run_trotter(const TrRun& R, int S, const double2* psi0, double2* psiT
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// Phase form, where the couplings of every mode act through one operator of it
+// (n (x) n couplings alone: transmon chains and rings).  All two-body terms
+// then commute, and in the product of that operator's eigenbases (V_m on mode
+// m) the pair gates of a whole pass are one diagonal of phases,
+//   prod_e exp(-i a tau g_e A (x) B) = V diag(exp(-i a tau sum_e g_e alpha_i beta_j)) V^dag,
+// twice of it where the two passes of a symmetric piece meet.  What is left
+// between two diagonals is one d x d gate per mode: the single-mode gates of
+// the pass behind and the pass ahead with the basis change on either side,
+// multiplied once per step into a table (tr_merge_kernel).  The ring of 8
+// transmons (d = 3) executes 24 complex multiply-adds and one product per
+// amplitude and step instead of 192, in 4 passes over the column instead of
+// 16 (256 columns: 57 -> 9.6 us per step at Q2); the formula applied is the
+// same one, up to FP64 rounding.
+//
+// Bound: FP64 multiply-adds (4.1 us of a step of that ring at the vector peak,
+// 2.7 us of LDS traffic behind them).  A thread holds d^NQ amplitudes of NQ
+// consecutive modes in registers for one pass (d = 3: nine), so that a pass is
+// one read and one write of the column for NQ gates; the gates are uniform and
+// come by scalar loads.
+// ---------------------------------------------------------------------------
+struct TpRun {
+  int M, K, r, D, ngrp;
+  int nq[SCP_MAX_MODES], m0[SCP_MAX_MODES], s[SCP_MAX_MODES];   // groups: modes, first mode, stride
+  double fT[SCP_MAX_MODES][SCP_MAX_TRUNC];   // frame energy times T, reduced mod 2 pi
+};
+
+// modes per pass: d^Q amplitudes of a thread in registers
+constexpr int tp_q(int d) { return d == 2 ? 4 : (d == 5 ? 1 : 2); }
+constexpr int tp_pow(int b, int e) { return e == 0 ? 1 : b * tp_pow(b, e - 1); }
+
+// Place of element i in LDS.  Even d: a thread's amplitudes of the fastest
+// group are 16 in a row, which would put every lane on the same banks; one
+// element of padding per 16 spreads them.  Strides of at least 16 are
+// multiples of 16 there, so the map is additive along a group.
+template <int d>
+__host__ __device__ __forceinline__ int tp_at(int i) {
+  return d % 2 == 0 ? i + (i >> 4) : i;
+}
+
+// One pass: the gates G[k] (d x d each, k = 0 the most significant mode) of
+// NQ modes, then (ph not null) the phases ph[r * nf + f].
+template <int d, int NQ>
+__device__ __forceinline__ void tp_group(double2* L, int D, int s, const double2* __restrict__ G,
+                                         const double2* __restrict__ ph) {
+  constexpr int n = tp_pow(d, NQ), dd = d * d;
+  const int nf = D / n;
+  const double is = 1.0 / s;
+  const int sp = tp_at<d>(s);
+  for (int f = threadIdx.x; f < nf; f += blockDim.x) {
+    const int hi = qdiv(f, is);
+    const int base = tp_at<d>(hi * s * n + (f - hi * s));
+    double2 x[n];
+#pragma unroll
+    for (int r = 0; r < n; ++r) x[r] = L[base + r * sp];
+    double2 p[n];
+    if (ph != nullptr) {
+#pragma unroll
+      for (int r = 0; r < n; ++r) p[r] = ph[(size_t)r * nf + f];
+    }
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+      const int st = tp_pow(d, NQ - 1 - k);
+      const double2* g = G + k * dd;
+#pragma unroll
+      for (int q = 0; q < n / d; ++q) {
+        const int r0 = (q / st) * st * d + q % st;
+        double2 t[d];
+#pragma unroll
+        for (int a = 0; a < d; ++a) {
+          double re = 0.0, im = 0.0;
+#pragma unroll
+          for (int b = 0; b < d; ++b) cmac(re, im, g[a * d + b], x[r0 + b * st]);
+          t[a] = make_double2(re, im);
+        }
+#pragma unroll
+        for (int a = 0; a < d; ++a) x[r0 + a * st] = t[a];
+      }
+    }
+    if (ph != nullptr) {
+#pragma unroll
+      for (int r = 0; r < n; ++r) x[r] = cmul(p[r], x[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < n; ++r) L[base + r * sp] = x[r];
+  }
+}
+
+// Workgroup = one column.  gk: [K][M][d*d], glast: [M][d*d] after the last
+// diagonal, ph: [r][D] in the order of the last group's pass.
+template <int d>
+__global__ void __launch_bounds__(1024) tr_phase_kernel(TpRun R, const double2* __restrict__ psi0,
+                                                        double2* __restrict__ psiT,
+                                                        const double2* __restrict__ gk,
+                                                        const double2* __restrict__ glast,
+                                                        const double2* __restrict__ ph) {
+  extern __shared__ double2 lds[];
+  constexpr int dd = d * d, Q = tp_q(d);
+  const size_t off = (size_t)blockIdx.x * R.D;
+  for (int i = threadIdx.x; i < R.D; i += blockDim.x) lds[tp_at<d>(i)] = psi0[off + i];
+  __syncthreads();
+  int j = 0;
+  for (int k = 0; k <= R.K; ++k) {
+    for (int g = 0; g < R.ngrp; ++g) {
+      const double2* G = (k < R.K ? gk + (size_t)k * R.M * dd : glast) + R.m0[g] * dd;
+      const double2* pj = (g + 1 == R.ngrp && k < R.K) ? ph + (size_t)j * R.D : nullptr;
+      if (R.nq[g] == Q) {
+        tp_group<d, Q>(lds, R.D, R.s[g], G, pj);
+      } else if constexpr (Q > 1) {
+        if (R.nq[g] == 1) tp_group<d, 1>(lds, R.D, R.s[g], G, pj);
+        if constexpr (Q > 2) {
+          if (R.nq[g] == 2) tp_group<d, 2>(lds, R.D, R.s[g], G, pj);
+          if (R.nq[g] == 3) tp_group<d, 3>(lds, R.D, R.s[g], G, pj);
+        }
+      }
+      __syncthreads();
+    }
+    j = j + 1 == R.r ? 0 : j + 1;
+  }
+  for (int i = threadIdx.x; i < R.D; i += blockDim.x) {
+    int r = i;
+    double th = 0.0;
+    for (int m = R.M - 1; m >= 0; --m) {
+      th += R.fT[m][r % d];
+      r /= d;
+    }
+    double sn, cs;
+    sincos(wrap_2pi(th), &sn, &cs);
+    const double2 v = lds[tp_at<d>(i)];
+    psiT[off + i] = make_double2(v.x * cs - v.y * sn, v.x * sn + v.y * cs);
+  }
+}
+
+// Gate of every mode before diagonal k (k = K, symmetric formulas: after the
+// last one; Q1 ends with V itself): the
+// single-mode gates of the pass behind (symmetric pieces) and the pass ahead,
+// V on the right of the first and V^dag on the left of the last.  sg: [K][M].
+__global__ void __launch_bounds__(256) tr_merge_kernel(int d, int M, int K, int sym,
+                                                       const double2* __restrict__ sg,
+                                                       const double2* __restrict__ V,
+                                                       double2* __restrict__ gk) {
+  extern __shared__ double2 sh[];
+  const int dd = d * d, n = M * dd, k = blockIdx.x;
+  double2 *A = sh, *B = sh + n;
+  const double2* Sb = sym && k > 0 ? sg + (size_t)(k - 1) * n : nullptr;
+  const double2* Sa = k < K ? sg + (size_t)k * n : nullptr;
+  auto times = [&](const double2* X, bool adj, const double2* Y, double2* out) {   // X Y per mode
+    for (int e = threadIdx.x; e < n; e += blockDim.x) {
+      const int m = e / dd, a = (e % dd) / d, b = e % d;
+      double re = 0.0, im = 0.0;
+      for (int x = 0; x < d; ++x) {
+        double2 u = adj ? X[m * dd + x * d + a] : X[m * dd + a * d + x];
+        if (adj) u.y = -u.y;
+        cmac(re, im, u, Y[m * dd + x * d + b]);
+      }
+      out[e] = make_double2(re, im);
+    }
+    __syncthreads();
+  };
+  for (int e = threadIdx.x; e < n; e += blockDim.x) {
+    const int ab = e % dd;
+    A[e] = k > 0 ? V[e] : make_double2(ab / d == ab % d ? 1.0 : 0.0, 0.0);
+  }
+  __syncthreads();
+  double2 *c = A, *o = B;
+  auto step = [&](const double2* X, bool adj) {
+    times(X, adj, c, o);
+    double2* t = c;
+    c = o;
+    o = t;
+  };
+  if (Sb) step(Sb, false);
+  if (Sa) {
+    step(Sa, false);
+    step(V, true);
+  }
+  for (int e = threadIdx.x; e < n; e += blockDim.x) gk[(size_t)k * n + e] = c[e];
+}
+
+// exp(w_j sum_e g_e alpha_i beta_j) of every element, in the order r * nf + f
+// of the last group's pass (stride s, n = d^NQ amplitudes per thread).
+__global__ void __launch_bounds__(256) tr_phase_table_kernel(TrGen G, int sym, int D, int s, int n,
+                                                             const double* __restrict__ alpha,
+                                                             double2* __restrict__ ph) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= D) return;
+  const int d = G.d, nf = D / n, r = i / nf, f = i - r * nf;
+  const int hi = f / s;
+  int e = hi * s * n + (f - hi * s) + r * s;
+  double al[SCP_MAX_MODES];
+  for (int m = G.M - 1; m >= 0; --m) {
+    al[m] = alpha[m * d + e % d];
+    e /= d;
+  }
+  double lam = 0.0;
+  for (int q = 0; q < G.E; ++q) lam += G.g[q] * al[G.ci[q]] * al[G.cj[q]];
+  for (int j = 0; j < G.r; ++j) {
+    const double2 w = gate_factor(G, j, sym ? 2.0 : 1.0);
+    double sn, cs;
+    sincos(w.y * lam, &sn, &cs);
+    const double a = exp(w.x * lam);
+    ph[(size_t)j * D + i] = make_double2(a * cs, a * sn);
+  }
+}
+
+template <int d>
+hipError_t run_phase(const TpRun& R, int S, const double2* psi0, double2* psiT, const double2* gk,
+                     const double2* glast, const double2* ph, hipStream_t st) {
+  const size_t sh = (size_t)(tp_at<d>(R.D - 1) + 1) * sizeof(double2);
+  int nf = 0, n = 1;
+  for (int g = 0; g < R.ngrp; ++g) {
+    n = 1;
+    for (int k = 0; k < R.nq[g]; ++k) n *= d;
+    nf = std::max(nf, R.D / n);
+  }
+  const int threads = std::min(1024, (nf + 63) / 64 * 64);
+  hipError_t e = hipFuncSetAttribute((const void*)tr_phase_kernel<d>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(tr_phase_kernel<d>, dim3(S), dim3(threads), sh, st, R, psi0, psiT, gk, glast, ph);
+  return hipGetLastError();
+}
+
+// Eigenvalues and eigenvectors (columns of V) of a Hermitian n x n matrix, by
+// cyclic complex Jacobi rotations.
+void herm_eig(int n, std::vector<cplx> A, double* w, cplx* V) {
+  for (int i = 0; i < n * n; ++i) V[i] = i / n == i % n ? 1.0 : 0.0;
+  for (int sweep = 0; sweep < 60; ++sweep) {
+    double off = 0.0, all = 0.0;
+    for (int i = 0; i < n * n; ++i) {
+      all += std::norm(A[i]);
+      if (i / n != i % n) off += std::norm(A[i]);
+    }
+    if (off <= 1e-34 * all) break;
+    for (int p = 0; p < n; ++p)
+      for (int q = p + 1; q < n; ++q) {
+        const double m = std::abs(A[p * n + q]);
+        if (m == 0.0) continue;
+        const cplx u = A[p * n + q] / m;   // A_pq = m u
+        const double th = 0.5 * std::atan2(2.0 * m, A[q * n + q].real() - A[p * n + p].real());
+        const double c = std::cos(th), s = std::sin(th);
+        // columns p, q <- (c p - s conj(u) q, s u p + c q), rows with the conjugate
+        for (int k = 0; k < n; ++k) {
+          const cplx x = A[k * n + p], y = A[k * n + q];
+          A[k * n + p] = c * x - s * std::conj(u) * y;
+          A[k * n + q] = s * u * x + c * y;
+          const cplx vx = V[k * n + p], vy = V[k * n + q];
+          V[k * n + p] = c * vx - s * std::conj(u) * vy;
+          V[k * n + q] = s * u * vx + c * vy;
+        }
+        for (int k = 0; k < n; ++k) {
+          const cplx x = A[p * n + k], y = A[q * n + k];
+          A[p * n + k] = c * x - s * u * y;
+          A[q * n + k] = s * std::conj(u) * x + c * y;
+        }
+        A[p * n + q] = A[q * n + p] = 0.0;
+      }
+  }
+  for (int i = 0; i < n; ++i) w[i] = A[i * n + i].real();
+}
+
+// The couplings of every mode act through one operator of it.
+bool couplings_commute(const scp_system* sys) {
+  int op[SCP_MAX_MODES];
+  for (int m = 0; m < SCP_MAX_MODES; ++m) op[m] = -1;
+  for (const Coupling& c : sys->coup) {
+    if ((op[c.i] >= 0 && op[c.i] != c.op_i) || (op[c.j] >= 0 && op[c.j] != c.op_j)) return false;
+    op[c.i] = c.op_i;
+    op[c.j] = c.op_j;
+  }
+  return true;
+}
+
 struct TrLayout {
-  size_t eps, ops, par, plan, pg, sg, fg, fs, total;
+  size_t eps, ops, par, plan, V, alpha, in_end, pg, sg, fg, fs, gk, ph, total;
   int r, sym, npar, H, nopmax, mode1, mode2;
+  bool phase;   // the phase form
   TrPlan P;
 };
 
@@ -713,7 +987,9 @@ TrLayout tr_layout(const scp_system* sys, int order) {
   L.r = order == SCP_TROTTER_Q4 ? 3 : (order == SCP_TROTTER_Q4J ? 2 : 1);
   L.sym = order != SCP_TROTTER_Q1;
   L.H = L.sym ? 2 : 1;
-  {
+  L.phase = couplings_commute(sys);
+  L.P = TrPlan{};
+  if (!L.phase) {
     // split forms need a second column buffer; single-mode gates are
     // absorbed into pair operations exactly when pair gates run split
     const int64_t D = sys->D, dg = sys->d, E0 = (int64_t)sys->coup.size();
@@ -723,7 +999,6 @@ TrLayout tr_layout(const scp_system* sys, int order) {
     // where pair gates run in place (large D, d <= 3) the single-mode gates
     // are absorbed in registers instead, next to static pair products
     const bool regs = L.mode2 == 0 && E0 > 0 && dg <= 3;
-    L.P = TrPlan{};
     build_plan(sys, L.H, L.mode2 != 0 || regs, regs, L.P);
     bool any_single = false;
     for (int h = 0; h < L.H; ++h)
@@ -734,7 +1009,7 @@ TrLayout tr_layout(const scp_system* sys, int order) {
   // the per-step fused-gate table holds only the pair operations with a
   // single-mode factor (the static ones are formed once)
   L.P.ndyn = 0;
-  for (int h = 0; h < L.H; ++h)
+  for (int h = 0; h < L.H && !L.phase; ++h)
     for (int o = 0; o < L.P.nop[h]; ++o) {
       TrOp& op = L.P.op[h][o];
       op.dix = (op.kind == 1 && !op.stat) ? L.P.ndyn++ : -1;
@@ -750,15 +1025,26 @@ TrLayout tr_layout(const scp_system* sys, int order) {
   L.par = o;
   o = align256(o + std::max(1, L.npar) * sizeof(double));
   L.plan = o;
-  o = align256(o + sizeof(TrPlan));
+  if (!L.phase) o = align256(o + sizeof(TrPlan));
+  L.V = o;
+  if (L.phase) o = align256(o + M * d * d * sizeof(double2));
+  L.alpha = o;
+  if (L.phase) o = align256(o + M * d * sizeof(double));
+  L.in_end = o;
   L.pg = o;
   o = align256(o + (size_t)L.r * std::max<size_t>(1, E) * d * d * d * d * sizeof(double2));
   L.sg = o;
   o = align256(o + (size_t)sys->n_steps * L.r * M * d * d * sizeof(double2));
-  L.fg = o;
-  o = align256(o + (size_t)sys->n_steps * L.r * L.P.ndyn * d * d * d * d * sizeof(double2));
-  L.fs = o;
-  o = align256(o + (size_t)L.r * std::max(1, L.P.nslot) * d * d * d * d * sizeof(double2));
+  L.fg = L.fs = L.gk = L.ph = o;
+  if (L.phase) {
+    o = align256(o + ((size_t)sys->n_steps * L.r + L.sym) * M * d * d * sizeof(double2));   // Q1: V is last
+    L.ph = o;
+    o = align256(o + (size_t)L.r * sys->D * sizeof(double2));
+  } else {
+    o = align256(o + (size_t)sys->n_steps * L.r * L.P.ndyn * d * d * d * d * sizeof(double2));
+    L.fs = o;
+    o = align256(o + (size_t)L.r * std::max(1, L.P.nslot) * d * d * d * d * sizeof(double2));
+  }
   L.total = o;
   return L;
 }
@@ -841,11 +1127,30 @@ scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const dou
   const int d = sys->d, M = sys->n_modes, E = (int)sys->coup.size(), N = sys->n_steps;
   char* base = static_cast<char*>(ws);
   // inputs: energies, dressed operators, pulse parameters
-  std::vector<char> in(W.pg, 0);
+  std::vector<char> in(W.in_end, 0);
   double* ieps = reinterpret_cast<double*>(in.data() + W.eps);
   double2* iops = reinterpret_cast<double2*>(in.data() + W.ops);
   double* ipar = reinterpret_cast<double*>(in.data() + W.par);
-  std::memcpy(in.data() + W.plan, &W.P, sizeof(TrPlan));
+  if (W.phase) {
+    double2* iV = reinterpret_cast<double2*>(in.data() + W.V);
+    double* ial = reinterpret_cast<double*>(in.data() + W.alpha);
+    std::vector<int> op(M, -1);
+    for (const Coupling& c : sys->coup) {
+      op[c.i] = c.op_i;
+      op[c.j] = c.op_j;
+    }
+    for (int m = 0; m < M; ++m) {
+      cplx V[TR_MAXD * TR_MAXD];
+      double w[TR_MAXD] = {0};
+      std::vector<cplx> A((size_t)d * d, 0.0);   // uncoupled modes keep their basis
+      if (op[m] >= 0) A.assign(sys->modes[m].ops[op[m]], sys->modes[m].ops[op[m]] + d * d);
+      herm_eig(d, A, w, V);
+      for (int i = 0; i < d * d; ++i) iV[m * d * d + i] = make_double2(V[i].real(), V[i].imag());
+      for (int a = 0; a < d; ++a) ial[m * d + a] = w[a];
+    }
+  } else {
+    std::memcpy(in.data() + W.plan, &W.P, sizeof(TrPlan));
+  }
   for (int m = 0; m < M; ++m) {
     for (int a = 0; a < d; ++a) ieps[m * d + a] = sys->modes[m].eps[a];
     for (int op = 0; op < 2; ++op)
@@ -874,6 +1179,45 @@ scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const dou
                      sg);
   HIPCHK(hipGetLastError());
   if (psi0 == nullptr) return SCP_OK;
+  const double twopi = 6.283185307179586476925286766559;
+  if (W.phase) {
+    TpRun R{};
+    R.M = M;
+    R.K = N * W.r;
+    R.r = W.r;
+    R.D = (int)sys->D;
+    // groups from the fastest mode up, so that only the slowest one is short
+    int n = 1, s = 1;
+    for (int m = M; m > 0;) {
+      const int nq = std::min(tp_q(d), m), g = R.ngrp++;
+      m -= nq;
+      R.nq[g] = nq;
+      R.m0[g] = m;
+      R.s[g] = s;
+      n = 1;
+      for (int k = 0; k < nq; ++k) n *= d;
+      s *= n;
+    }
+    for (int m = 0; m < M; ++m)
+      for (int a = 0; a < d; ++a) R.fT[m][a] = std::remainder(sys->modes[m].frame[a] * N * sys->h, twopi);
+    double2* gk = reinterpret_cast<double2*>(base + W.gk);
+    double2* ph = reinterpret_cast<double2*>(base + W.ph);
+    const double2* V = reinterpret_cast<const double2*>(base + W.V);
+    const double2* glast = W.sym ? gk + (size_t)R.K * M * d * d : V;
+    hipLaunchKernelGGL(tr_merge_kernel, dim3(R.K + W.sym), dim3(256), 2 * M * d * d * sizeof(double2), st,
+                       d, M, R.K, W.sym, sg, V, gk);
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL(tr_phase_table_kernel, dim3((R.D + 255) / 256), dim3(256), 0, st, G, W.sym, R.D,
+                       R.s[R.ngrp - 1], n, reinterpret_cast<const double*>(base + W.alpha), ph);
+    HIPCHK(hipGetLastError());
+    switch (d) {
+      case 2: HIPCHK(run_phase<2>(R, S, psi0, psiT, gk, glast, ph, st)); break;
+      case 3: HIPCHK(run_phase<3>(R, S, psi0, psiT, gk, glast, ph, st)); break;
+      case 4: HIPCHK(run_phase<4>(R, S, psi0, psiT, gk, glast, ph, st)); break;
+      default: HIPCHK(run_phase<5>(R, S, psi0, psiT, gk, glast, ph, st)); break;
+    }
+    return SCP_OK;
+  }
   double2* fg = reinterpret_cast<double2*>(base + W.fg);
   double2* fs = reinterpret_cast<double2*>(base + W.fs);
   {
@@ -912,7 +1256,6 @@ scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const dou
     R.stride[m] = s;
     s *= d;
   }
-  const double twopi = 6.283185307179586476925286766559;
   for (int m = 0; m < M; ++m)
     for (int a = 0; a < d; ++a) R.fT[m][a] = std::remainder(sys->modes[m].frame[a] * N * sys->h, twopi);
   hipError_t e;
