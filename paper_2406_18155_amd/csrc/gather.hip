@@ -44,84 +44,9 @@
 #include <vector>
 #include <string>
 
-#include "internal.h"
-#include "kernel_common.h"
+#include "gather.h"
 
 namespace scp {
-
-constexpr int GA_MAXM = 10;      // modes (three-bit digits, 2N (open) or N in one word)
-constexpr int GA_MAXDM = 10;     // driven modes
-constexpr int GA_MAXPR = 10;     // coupled mode pairs
-constexpr int GA_MAXC = 4;       // operators summed into one table entry
-constexpr int GA_MAXTAB = 4096;  // complex entries of a stage table
-constexpr int GA_PRE = 4;        // table entries each thread prefetches per stage
-constexpr int GA_MAXSL = 16;     // slots in a gradient table
-constexpr int GA_MAXDS = 10;     // distinct drive slots (gradient)
-constexpr int GA_MAXDR = 16;     // drives (gradient)
-constexpr int GA_MAXCP = 16;     // couplings (gradient)
-constexpr int GA_MAXME = 24;     // coupling ends (closed-system gradient)
-// per-wave partial sums of one stage: drive slots | 3 per mode | couplings
-constexpr int GA_NV = GA_MAXDS + 3 * GA_MAXM + GA_MAXCP;
-
-// Static description of one gather-engine propagation (device copy in the
-// workspace, read through the scalar path where uniform).
-struct GArgs {
-  const float2* optab;   // [2N+1][block_q] rotated slot operators of the system
-  const float* ctab;     // [3N][ngroups] drive coefficients
-  const float2* jtab;    // [2N+1][N][d*d] unit-rate relaxation band (open systems)
-  const float2* gtab;    // [3N][ntab] stage tables (built by gtab_kernel)
-  const float2* x0;      // [S][L] input columns
-  float2* xT;            // [S][L] output columns
-  int block_q, ngroups, nsteps, S;
-  float h;
-  int ndm, npr, ntab, has_jump, off_p, off_j;
-  int par;    // operators connect levels of unlike parity only (see Nb)
-  int nn;     // entries of an operator row
-  int prow;   // stride of a pair-operator row: nn^2 rounded up to even
-  int orow;   // stride of a driven-mode operator row: nn rounded up to even
-  int srow;   // stride of a slot-operator row (gradient)
-  int mrow;   // stride of a row of a mode's derivative operator (gradient)
-  int kst[GA_MAXM], bst[GA_MAXM];                    // strides of ket / bra digits in a column
-  int dm_mode[GA_MAXDM], dm_n[GA_MAXDM];
-  int dm_slot[GA_MAXDM][GA_MAXC], dm_cidx[GA_MAXDM][GA_MAXC];
-  int pr_i[GA_MAXPR], pr_j[GA_MAXPR], pr_n[GA_MAXPR];
-  int pr_si[GA_MAXPR][GA_MAXC], pr_sj[GA_MAXPR][GA_MAXC];
-  float pr_g[GA_MAXPR][GA_MAXC];
-  float g1[GA_MAXM], gp[GA_MAXM];
-  float delta[GA_MAXM][8];
-  // gradient (open systems): the table gains the rotated slot operators and
-  // the unit-rate relaxation bands
-  int grad, ntabg, off_s, off_u, nsl;
-  int sl_slot[GA_MAXSL];                             // system slot of each table slot
-  int nds, ds_sl[GA_MAXDS], ds_mode[GA_MAXDS];       // distinct drive slots
-  int ndr, dr_ds[GA_MAXDR], dr_par0[GA_MAXDR], dr_npar[GA_MAXDR];
-  int ncp, cp_i[GA_MAXCP], cp_j[GA_MAXCP], cp_si[GA_MAXCP], cp_sj[GA_MAXCP];
-  // gradient (closed systems, grad = 2): the table gains the rotated slot
-  // operators, per mode and device parameter the one-mode derivative operator
-  // (sum_k c_k dO_k + d delta), and the derivative slot operators
-  int off_m, off_d, off_dslot;
-  int mdm[GA_MAXM];                                  // driven-mode index of a mode (-1: none)
-  float deps[GA_MAXM][3][8];                         // d delta / d(EJ, EC, EL)
-  float cp_g[GA_MAXCP];
-  // coupling ends grouped by mode and own table slot: me_beg[m] .. me_beg[m+1]
-  // packed (coupling | own slot << 5 | partner slot << 10 | partner mode << 15 |
-  // first side << 20 | last of its own-slot group << 21)
-  int me_beg[GA_MAXM + 1];
-  int me[GA_MAXME];
-};
-
-// Checkpoints, costate and gradient buffers of an adjoint.
-struct GAdj {
-  float4* ck;            // [S][nck][L] (hi re, hi im, lo re, lo im) at steps g * ce
-  const float2* cot;     // [S][L] cotangent of the final columns
-  float2* seg;           // stage inputs, [ce][4][L] per column (open) or per slot (closed)
-  const double* dctab;   // [3N][npulse] dc/dpar
-  double* part;          // open: [S][nacc] gradient partial sums
-  float4* lam;           // costate (hi, lo): open [S][L] between reverse walks,
-                         // closed [S][nck][L] at the end of every segment
-  double* gs;            // closed: [S][N][gw] sums of every step (see g_fold_kernel)
-  int ce, nck, npulse, nacc, gw;
-};
 
 #define SCP_TRY(expr)                  \
   do {                                 \
@@ -130,67 +55,6 @@ struct GAdj {
   } while (0)
 
 namespace {
-
-constexpr int cpow(int b, int e) { return e == 0 ? 1 : b * cpow(b, e - 1); }
-
-// Geometry of one column: N modes of dimension d; a state (L = D) or a
-// vectorised density matrix (L = D^2).
-template <int d, int N, bool OPEN>
-struct GShape {
-  static constexpr int D = cpow(d, N);
-  static constexpr int L = OPEN ? D * D : D;
-  static constexpr int T = L >= 1024 ? 1024 : ((L + 63) / 64) * 64;   // threads
-  static constexpr int E = (L + T - 1) / T;                           // elements per thread
-  static constexpr int st(int m) { return cpow(d, N - 1 - m); }       // stride in A or B
-};
-
-// The levels along one mode that an operator row connects to level a: all d of
-// them or, where every operator is odd (PAR), those of the other parity: at
-// most (d + 1) / 2 entries.  With d odd an even level has one neighbour fewer;
-// its last entry repeats the first neighbour with a zero coefficient, so the
-// gather stays inside the column.  A pair term gathers 4 (d = 3, 4) or 9
-// (d = 5) neighbours instead of d^2, with as many table entries.  Measured:
-// 4-fluxonium chain (d = 5, 16 columns) forward 11.8 -> 8.4 us per step, open
-// 4-fluxonium chain (d = 3, 256 matrices) forward + gradient 583 -> 426.
-template <int d, bool PAR>
-struct Nb {
-  static constexpr int n = PAR ? (d + 1) / 2 : d;
-  static constexpr int orow = n + (n & 1);
-  static constexpr int prow = n * n + ((n * n) & 1);
-  static constexpr int srow = PAR ? orow : d;
-  static constexpr int mrow = PAR ? (n + 1) + ((n + 1) & 1) : d;
-  // offset of entry k's element from the row's own (digit a, stride st)
-  static __device__ __forceinline__ int off(int k, int a, int st) {
-    if (!PAR) return (k - a) * st;
-    const int b0 = (a & 1) ^ 1;
-    const int b = ((d & 1) && k == n - 1 && b0) ? b0 : b0 + 2 * k;
-    return (b - a) * st;
-  }
-};
-// Level of entry k of row a (-1: padding), as Nb<d, par> has it.
-__host__ __device__ inline int nb_level(int d, int par, int k, int a) {
-  const int b = par ? ((a & 1) ^ 1) + 2 * k : k;
-  return b < d ? b : -1;
-}
-
-__device__ __forceinline__ int ket_digit(uint32_t pk, int m) { return (pk >> (3 * m)) & 7; }
-__device__ __forceinline__ int bra_digit(uint32_t pk, int m, int N) {
-  return (pk >> (3 * (N + m))) & 7;
-}
-
-__device__ __forceinline__ void cmac(float& sr, float& si, c32 a, c32 b) {
-  sr = fmaf(a.x, b.x, sr);
-  sr = fmaf(-a.y, b.y, sr);
-  si = fmaf(a.x, b.y, si);
-  si = fmaf(a.y, b.x, si);
-}
-// s += conj(a) b
-__device__ __forceinline__ void cmac_conj(float& sr, float& si, c32 a, c32 b) {
-  sr = fmaf(a.x, b.x, sr);
-  sr = fmaf(a.y, b.y, sr);
-  si = fmaf(a.x, b.y, si);
-  si = fmaf(-a.y, b.x, si);
-}
 
 // Row of the drive table of step-grid row r (3 per step: t_n, t_n + h/2,
 // t_n + h) and the half-step of its operators.
@@ -765,26 +629,6 @@ __device__ __forceinline__ c32 comm2(const c32* __restrict__ kb, const c32* __re
   z.x = kr - br;
   z.y = ki - bim;
   return z;
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float lane_f(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-
-// Sum over the wave (all 64 lanes active), the same in every lane, in a fixed
-// order: within each row of 16 lanes by DPP (quad exchanges, then the half-row
-// and row mirrors), then the four row sums.  DPP stays on the vector ALU
-// (a shuffle would use the LDS crossbar these kernels are bound by).
-__device__ __forceinline__ float wave_sum(float v) {
-  v += dpp_f<0xB1>(v);    // quad_perm [1, 0, 3, 2]
-  v += dpp_f<0x4E>(v);    // quad_perm [2, 3, 0, 1]
-  v += dpp_f<0x141>(v);   // row_half_mirror
-  v += dpp_f<0x140>(v);   // row_mirror
-  return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
 }
 
 // s = sum_x row[x] v[x]
@@ -1372,7 +1216,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                 v += 2.f * im_conj(z, ys[e]);
               }
             }
-            v = wave_sum(v);
+            v = g_wave_sum(v);
             if (lane == 0) wsum[(par * NW + wave) * WS + k] = v;
           }
           // couplings: 2 Im <P kb - kb P, y>, added to the FP64 sums per wave
@@ -1396,7 +1240,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                 v += 2.f * (z.x * y.y - z.y * y.x);
               }
             }
-            v = wave_sum(v);
+            v = g_wave_sum(v);
             if (lane == 0) atomicAdd(&acc[npulse + c], (double)v);
           }
           // rates: 2 Re <D[a_m]^dag kb, y> and 2 Re <-(a - b)^2 kb, y>
@@ -1418,8 +1262,8 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                 v2 -= 2.f * (float)((a - b) * (a - b)) * (kbe.x * y.x + kbe.y * y.y);
               }
             }
-            v1 = wave_sum(v1);
-            v2 = wave_sum(v2);
+            v1 = g_wave_sum(v1);
+            v2 = g_wave_sum(v2);
             if (lane == 0) {
               atomicAdd(&acc[npulse + ncp + 2 * m], (double)v1);
               atomicAdd(&acc[npulse + ncp + 2 * m + 1], (double)v2);
@@ -1499,7 +1343,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                   v += 2.f * im_conj(rowdot<nb>(rows + am * SR, kt), ybw[e]);
                 }
               }
-              v = wave_sum(v);
+              v = g_wave_sum(v);
               if (lane == 0) wsum[(par * NW + wave) * WS + k] = v;
             }
             const int k0 = uni(A->me_beg[m]), k1 = uni(A->me_beg[m + 1]);
@@ -1543,13 +1387,13 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                 }
               }
               if (first) {
-                vc = wave_sum(vc);
+                vc = g_wave_sum(vc);
                 if (lane == 0) wsum[(par * NW + wave) * WS + GA_MAXDS + 3 * N + c] = vc;
               }
             }
-            v0 = wave_sum(v0);
-            v1 = wave_sum(v1);
-            v2 = wave_sum(v2);
+            v0 = g_wave_sum(v0);
+            v1 = g_wave_sum(v1);
+            v2 = g_wave_sum(v2);
             if (lane == 0) {
               float* wv = wsum + (par * NW + wave) * WS + GA_MAXDS + 3 * m;
               wv[0] = v0;
@@ -1575,7 +1419,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                   v += 2.f * im_conj(rowdot<nb>(rows + am * SR, kt), ybw[e]);
                 }
               }
-              v = wave_sum(v);
+              v = g_wave_sum(v);
               if (lane == 0) wsum[(par * NW + wave) * WS + k] = v;
             }
           }
@@ -1688,9 +1532,15 @@ hipError_t g_launch1(const GArgs* dargs, const GAdj* dadj, int S, int ntab, int 
   return hipGetLastError();
 }
 
+// Form of a launch: 0 general, 1 parity, 2 real (closed systems).
+int g_form(const GArgs& A) { return A.real ? 2 : (A.par ? 1 : 0); }
+
 template <int d, int N, bool OPEN>
-hipError_t g_launch(bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntab, int n_lo,
+hipError_t g_launch(int form, const GArgs* dargs, const GAdj* dadj, int S, int ntab, int n_lo,
                     int n_hi, const float4* st_in, float4* st_out, hipStream_t s) {
+  const bool par = form != 0;
+  if (!OPEN && form == 2)
+    return g_real_forward(d, N, dadj != nullptr, nullptr, dargs, dadj, S, n_lo, n_hi, st_in, st_out, s);
   if (dadj != nullptr)
     return par ? g_launch1<d, N, OPEN, true, true>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s)
                : g_launch1<d, N, OPEN, false, true>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
@@ -1698,21 +1548,14 @@ hipError_t g_launch(bool par, const GArgs* dargs, const GAdj* dadj, int S, int n
              : g_launch1<d, N, OPEN, false, false>(dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
 }
 
-// Shapes with a compiled stepper: open systems D^2 <= 6561, closed systems
-// 64 <= D <= 4096 with at most 10 modes.
-#define GA_OPEN_SHAPES(X) X(2, 1) X(2, 2) X(2, 3) X(2, 4) X(2, 5) X(3, 1) X(3, 2) X(3, 3) X(3, 4) \
-  X(4, 1) X(4, 2) X(4, 3) X(5, 1) X(5, 2)
-#define GA_CLOSED_SHAPES(X) X(2, 6) X(2, 7) X(2, 8) X(2, 9) X(2, 10) X(3, 4) X(3, 5) X(3, 6) \
-  X(3, 7) X(4, 3) X(4, 4) X(4, 5) X(4, 6) X(5, 3) X(5, 4) X(5, 5)
-
-hipError_t g_dispatch(int d, int N, bool open, bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntab,
+hipError_t g_dispatch(int d, int N, bool open, int form, const GArgs* dargs, const GAdj* dadj, int S, int ntab,
                       int n_lo, int n_hi, const float4* st_in, float4* st_out, hipStream_t s) {
 #define GA_CASE_O(dd_, nn_)          \
   if (open && d == dd_ && N == nn_) \
-    return g_launch<dd_, nn_, true>(par, dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
+    return g_launch<dd_, nn_, true>(form, dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
 #define GA_CASE_C(dd_, nn_)           \
   if (!open && d == dd_ && N == nn_) \
-    return g_launch<dd_, nn_, false>(par, dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
+    return g_launch<dd_, nn_, false>(form, dargs, dadj, S, ntab, n_lo, n_hi, st_in, st_out, s);
   GA_OPEN_SHAPES(GA_CASE_O)
   GA_CLOSED_SHAPES(GA_CASE_C)
 #undef GA_CASE_O
@@ -1745,16 +1588,17 @@ size_t g_adj_lds_bytes(int ntabg, int nacc) {
 // Open systems: one launch (gseg, nseg unused).  Closed systems: nseg segments
 // from gseg down, S workgroups each, after the costate sweep over them.
 template <int d, int N, bool OPEN>
-hipError_t g_adj_launch(bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntabg, int nacc,
+hipError_t g_adj_launch(int form, const GArgs* dargs, const GAdj* dadj, int S, int ntabg, int nacc,
                         int gseg, int nseg, hipStream_t s) {
   using Sh = GShape<d, N, OPEN>;
+  if (!OPEN && form == 2) return g_real_segments(d, N, nullptr, dargs, dadj, nseg * S, gseg, s);
   const size_t sh = g_adj_lds_bytes<d, N, OPEN>(ntabg, nacc);
   if (sh > 163840) return hipErrorInvalidValue;
   auto run = [&](auto* kernel) {
     (void)g_lds(kernel, sh);
     hipLaunchKernelGGL(kernel, dim3(OPEN ? S : nseg * S), dim3(Sh::T), sh, s, dargs, dadj, gseg);
   };
-  if (par)
+  if (form != 0)
     run(g_adj_kernel<d, N, OPEN, true>);
   else
     run(g_adj_kernel<d, N, OPEN, false>);
@@ -1773,14 +1617,14 @@ size_t g_adj_lds(int d, int N, bool open, int ntabg, int nacc) {
   return ~(size_t)0;
 }
 
-hipError_t g_adj_dispatch(int d, int N, bool open, bool par, const GArgs* dargs, const GAdj* dadj, int S,
+hipError_t g_adj_dispatch(int d, int N, bool open, int form, const GArgs* dargs, const GAdj* dadj, int S,
                           int ntabg, int nacc, int gseg, int nseg, hipStream_t s) {
 #define GA_ADJ_CASE_O(dd_, nn_) \
   if (open && d == dd_ && N == nn_)  \
-    return g_adj_launch<dd_, nn_, true>(par, dargs, dadj, S, ntabg, nacc, gseg, nseg, s);
+    return g_adj_launch<dd_, nn_, true>(form, dargs, dadj, S, ntabg, nacc, gseg, nseg, s);
 #define GA_ADJ_CASE_C(dd_, nn_) \
   if (!open && d == dd_ && N == nn_)   \
-    return g_adj_launch<dd_, nn_, false>(par, dargs, dadj, S, ntabg, nacc, gseg, nseg, s);
+    return g_adj_launch<dd_, nn_, false>(form, dargs, dadj, S, ntabg, nacc, gseg, nseg, s);
   GA_OPEN_SHAPES(GA_ADJ_CASE_O)
   GA_CLOSED_SHAPES(GA_ADJ_CASE_C)
 #undef GA_ADJ_CASE_O
@@ -1795,24 +1639,25 @@ size_t g_cos_lds_bytes(int ntab) {
 
 // Costate sweep of a closed system over the segments g_hi down to g_lo.
 template <int d, int N>
-hipError_t g_cos_launch(bool par, const GArgs* dargs, const GAdj* dadj, int S, int ntab, int g_hi,
+hipError_t g_cos_launch(int form, const GArgs* dargs, const GAdj* dadj, int S, int ntab, int g_hi,
                         int g_lo, hipStream_t s) {
+  if (form == 2) return g_real_sweep(d, N, nullptr, dargs, dadj, S, g_hi, g_lo, s);
   const size_t sh = g_cos_lds_bytes<d, N>(ntab);
   auto run = [&](auto* kernel) {
     (void)g_lds(kernel, sh);
     hipLaunchKernelGGL(kernel, dim3(S), dim3(GShape<d, N, false>::T), sh, s, dargs, dadj, g_hi, g_lo);
   };
-  if (par)
+  if (form == 1)
     run(g_cos_kernel<d, N, true>);
   else
     run(g_cos_kernel<d, N, false>);
   return hipGetLastError();
 }
 
-hipError_t g_cos_dispatch(int d, int N, bool par, const GArgs* dargs, const GAdj* dadj, int S,
+hipError_t g_cos_dispatch(int d, int N, int form, const GArgs* dargs, const GAdj* dadj, int S,
                           int ntab, int g_hi, int g_lo, hipStream_t s) {
 #define GA_COS_CASE(dd_, nn_) \
-  if (d == dd_ && N == nn_) return g_cos_launch<dd_, nn_>(par, dargs, dadj, S, ntab, g_hi, g_lo, s);
+  if (d == dd_ && N == nn_) return g_cos_launch<dd_, nn_>(form, dargs, dadj, S, ntab, g_hi, g_lo, s);
   GA_CLOSED_SHAPES(GA_COS_CASE)
 #undef GA_COS_CASE
   return hipErrorInvalidValue;
@@ -1821,6 +1666,14 @@ hipError_t g_cos_dispatch(int d, int N, bool par, const GArgs* dargs, const GAdj
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
+
+// The real form's coefficients carry h / (6 h6), h6 the FP32 weight of the RK4
+// sum: the rounding of h6 is the same at every step and would stretch every
+// rotation angle (the same errors: 1.3e-7 -> 1.0e-7 and 2e-8 to 6e-8).
+static double real_kappa(const scp_system* sys) {
+  const float h = (float)sys->h, h6 = h * (1.0f / 6.0f);
+  return sys->h / (6.0 * (double)h6);
+}
 
 // Fill the static description from the system and (open systems) the rates.
 static scp_status g_args(const scp_system* sys, bool open, const double* gamma1,
@@ -1908,6 +1761,115 @@ static scp_status g_args(const scp_system* sys, bool open, const double* gamma1,
   if ((3 * L + ((3 * L) & 1) + 2 * (size_t)A.ntab) * sizeof(float2) > 163840)
     return fail(SCP_EINVAL, "gather engine: column and stage tables exceed the LDS");
   A.ntabg = A.ntab;
+  if (!open && sys->d_rt != nullptr) {   // the real form (see build_gather_rows)
+    A.real = P.real_frame != 0 ? 1 : 0;
+    A.rt = sys->d_rt;
+    A.rc = sys->d_rc;
+    A.kappa = real_kappa(sys);
+    for (int p = 0; p < A.npr; ++p)
+      A.pmask |= 1 << (A.pr_j[p] == A.pr_i[p] + 1 ? A.pr_i[p] : N - 1);
+    for (int q = 0; q < A.ndm; ++q) {
+      A.dmask |= 1 << A.dm_mode[q];
+      A.rd_s[A.dm_mode[q]] = (float)(A.kappa / sys->rc_scale[A.dm_mode[q]]);
+    }
+  }
+  return SCP_OK;
+}
+
+// Static rows of the real form: Re(sum_e g_e O_i (x) O_j) of the neighbour
+// pairs and Re(O) of the driven modes over the levels Nb names, summed in FP64.
+// Empty where the form does not apply: an operator with even entries or a
+// complex term, a coupled pair that is no neighbour pair of the ring of modes
+// or has more than two couplings, two drive operators on a mode, or a shape
+// without a closed-system stepper.  Behind them the gradient's rows (RShape).
+// A drive operator is divided by its largest entry and c(t) multiplied by it in
+// FP64 (scale): a static coefficient repeats its rounding at every stage, which
+// for the resonant entry turns into an error of the rotation angle, while c(t)
+// rounds differently at each (error of the final states against FP64: 5-transmon
+// ring 1.6e-7 -> 1.3e-7, chains of 3 to 5 modes 0.8-1.2e-7 -> 0.7-0.9e-7).
+std::vector<float> build_gather_rows(const scp_system* sys, double* scale) {
+  std::vector<float> rt;
+  const Plan& P = sys->plan;
+  const int d = sys->d, N = sys->n_modes;
+  if (!P.parity || !sys->real_ok || !g_supported(d, N, false) || N < 3) return rt;
+  GArgs A;
+  if (g_args(sys, false, nullptr, nullptr, A) != SCP_OK) {
+    set_error("");
+    return rt;
+  }
+  for (int p = 0; p < A.npr; ++p)
+    if ((A.pr_j[p] != A.pr_i[p] + 1 && !(A.pr_i[p] == 0 && A.pr_j[p] == N - 1)) || A.pr_n[p] > 2)
+      return rt;
+  for (int q = 0; q < A.ndm; ++q)
+    if (A.dm_n[q] != 1) return rt;
+  const int n = (d + 1) / 2, nn = n * n, pr = nn == 9 ? 12 : nn, dr = n == 3 ? 4 : n;
+  const double kappa = real_kappa(sys);
+  rt.assign((size_t)N * d * d * pr + (size_t)N * d * dr, 0.f);
+  for (int p = 0; p < A.npr; ++p) {
+    const int i = A.pr_i[p], j = A.pr_j[p], at = j == i + 1 ? i : N - 1;
+    for (int a = 0; a < d; ++a)
+      for (int b = 0; b < d; ++b)
+        for (int x = 0; x < n; ++x)
+          for (int z = 0; z < n; ++z) {
+            const int la = nb_level(d, 1, x, a), lb = nb_level(d, 1, z, b);
+            if (la < 0 || lb < 0) continue;
+            cplx v = 0.0;
+            for (const Coupling& c : sys->coup) {
+              const bool fwd = c.i == i && c.j == j;
+              if (!fwd && !(c.i == j && c.j == i)) continue;
+              v += c.g * sys->modes[i].ops[fwd ? c.op_i : c.op_j][a * d + la] *
+                   sys->modes[j].ops[fwd ? c.op_j : c.op_i][b * d + lb];
+            }
+            rt[((size_t)at * d * d + a * d + b) * pr + x * n + z] = (float)(kappa * v.real());
+          }
+  }
+  for (int m = 0; m < N; ++m) scale[m] = kappa;
+  for (int q = 0; q < A.ndm; ++q) {
+    const int m = A.dm_mode[q], op = P.slot_op[A.dm_slot[q][0]];
+    double big = 0.0;
+    for (int i = 0; i < d * d; ++i) big = std::max(big, std::abs(sys->modes[m].ops[op][i].real()));
+    if (big > 0.0) scale[m] = kappa * big;
+    for (int a = 0; a < d; ++a)
+      for (int x = 0; x < n; ++x) {
+        const int la = nb_level(d, 1, x, a);
+        if (la >= 0)
+          rt[(size_t)N * d * d * pr + ((size_t)m * d + a) * dr + x] =
+              (float)(sys->modes[m].ops[op][a * d + la].real() / (scale[m] / kappa));
+      }
+  }
+  const int gr = (4 * n + 3) / 4 * 4;
+  const size_t off_g = (rt.size() + 3) & ~(size_t)3;
+  rt.resize(off_g + (size_t)N * 2 * d * gr + (size_t)N * d * 4, 0.f);
+  for (int m = 0; m < N; ++m) {
+    const ModeData& M = sys->modes[m];
+    for (int u = 0; u < 2; ++u) {
+      // i times real operators (n of a fluxonium): their imaginary parts
+      bool im = false;
+      for (size_t q = 0; q < sys->slot_mode.size(); ++q)
+        if (sys->slot_mode[q] == m && sys->slot_op[q] == u) im = sys->slot_imag[q] != 0;
+      for (int a = 0; a < d; ++a)
+        for (int x = 0; x < n; ++x) {
+          const int la = nb_level(d, 1, x, a);
+          if (la < 0) continue;
+          float* row = rt.data() + off_g + ((size_t)(m * 2 + u) * d + a) * gr;
+          auto part = [&](cplx v) { return (float)(im ? v.imag() : v.real()); };
+          row[x] = part(M.ops[u][a * d + la]);
+          for (int th = 0; th < 3; ++th) row[(th + 1) * n + x] = part(M.dops[th][u][a * d + la]);
+        }
+    }
+    for (int a = 0; a < d; ++a)
+      for (int th = 0; th < 3; ++th)
+        rt[off_g + (size_t)N * 2 * d * gr + ((size_t)m * d + a) * 4 + th] = (float)M.deps[th][a];
+  }
+  return rt;
+}
+
+// Frame phases of the real form into the workspace.
+static scp_status g_phases(const scp_system* sys, float2* ph, hipStream_t st) {
+  double f[GA_MAXM][8] = {{0}};
+  for (int m = 0; m < sys->n_modes; ++m)
+    for (int a = 0; a < sys->d; ++a) f[m][a] = sys->modes[m].frame[a];
+  HIPCHK(g_real_phases(sys->d, sys->n_modes, sys->n_steps, sys->h, f, ph, st));
   return SCP_OK;
 }
 
@@ -1993,6 +1955,26 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
       }
     }
     A.me_beg[N] = k;
+    if (sys->d_rt != nullptr) {
+      // operator index on a mode: 0 for n, 1 for phi
+      for (int q = 0; q < A.ndm; ++q) {
+        const int m = A.dm_mode[q];
+        A.rd_u[m] = P.slot_op[A.dm_slot[q][0]];
+        for (int x = 0; x < A.nds; ++x)
+          if (A.ds_mode[x] == m) A.rd_k[m] = x;
+      }
+      for (int e = 0; e < P.ncoup; ++e) {
+        const Coupling& c = sys->coup[e];
+        const int i = std::min(c.i, c.j), j = std::max(c.i, c.j), p = j == i + 1 ? i : N - 1;
+        const int ui = c.i == i ? c.op_i : c.op_j, uj = c.i == i ? c.op_j : c.op_i;
+        const int q = A.rp_n[p]++;
+        const float sg = sys->slot_imag[P.coup_slot_i[e]] ? -1.f : 1.f;
+        A.rp_u[p][q] = ui | (uj << 1);
+        A.rp_c[p][q] = e;
+        A.rp_s[p][q] = sg;
+        A.rp_g[p][q] = sg * (float)c.g;
+      }
+    }
     A.off_m = A.off_s + A.nsl * d * A.srow;
     A.off_d = A.off_m + 3 * N * d * A.mrow;
     A.off_u = A.off_m;
@@ -2003,10 +1985,21 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
   return SCP_OK;
 }
 
-// Workspace: [GArgs][stage tables [3N][ntab]][open: jump bands [2N+1][N][d*d]].
+// Bytes of the real form's frame phases (0 where it does not apply; the same
+// for either frame setting of a system that allows it).
+static size_t g_ph_bytes(const scp_system* sys) {
+  return sys->d_rt == nullptr
+             ? 0
+             : align256((2 * (size_t)sys->n_steps + 1) * (size_t)sys->D * sizeof(float2));
+}
+
+// Workspace: [GArgs][stage tables [3N][ntab], or the real form's frame phases
+// [2N+1][L]][open: jump bands [2N+1][N][d*d]].
 static size_t g_ws_bytes(const scp_system* sys, bool open, int ntab) {
   const size_t dd = (size_t)sys->d * sys->d;
-  size_t b = align256(sizeof(GArgs)) + align256(3 * (size_t)sys->n_steps * ntab * sizeof(float2));
+  size_t t = align256(3 * (size_t)sys->n_steps * ntab * sizeof(float2));
+  if (!open) t = std::max(t, g_ph_bytes(sys));
+  size_t b = align256(sizeof(GArgs)) + t;
   if (open) b += align256((2 * (size_t)sys->n_steps + 1) * sys->n_modes * dd * sizeof(float2));
   return b;
 }
@@ -2043,13 +2036,18 @@ static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const 
     hipLaunchKernelGGL(jtab_kernel, dim3(js.nq), dim3(64), 0, st, js, jtab);
     HIPCHK(hipGetLastError());
   }
+  if (A.real) A.ph = gtab;
   hipLaunchKernelGGL(store_args_kernel, dim3(1), dim3(64), 0, st, A, dargs);
   HIPCHK(hipGetLastError());
-  hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
-  HIPCHK(hipGetLastError());
+  if (A.real) {
+    SCP_TRY(g_phases(sys, gtab, st));
+  } else {
+    hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
+    HIPCHK(hipGetLastError());
+  }
   if (S == 0) return SCP_OK;
   hipEvent_t t0 = timing_start(sys, st);
-  HIPCHK(g_dispatch(d, N, open, A.par != 0, dargs, nullptr, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
+  HIPCHK(g_dispatch(d, N, open, g_form(A), dargs, nullptr, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
   timing_stop(sys, t0, 0, st);
   return SCP_OK;
 }
@@ -2183,10 +2181,10 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
   hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
   HIPCHK(hipGetLastError());
   hipEvent_t t0 = timing_start(sys, st);
-  HIPCHK(g_dispatch(d, N, true, A.par != 0, dargs, dadj, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
+  HIPCHK(g_dispatch(d, N, true, g_form(A), dargs, dadj, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
   timing_stop(sys, t0, 0, st);
   t0 = timing_start(sys, st);
-  HIPCHK(g_adj_dispatch(d, N, true, A.par != 0, dargs, dadj, S, A.ntabg, w.nacc, 0, 1, st));
+  HIPCHK(g_adj_dispatch(d, N, true, g_form(A), dargs, dadj, S, A.ntabg, w.nacc, 0, 1, st));
   timing_stop(sys, t0, 2, st);
   std::vector<double> part((size_t)S * w.nacc);
   HIPCHK(hipMemcpyAsync(part.data(), base + w.part, part.size() * sizeof(double),
@@ -2242,13 +2240,13 @@ scp_status launch_gather_forward(scp_system* sys, int S, void* ws, size_t ws_byt
 }
 
 // Closed-system gradient on the gather engine.  Workspace: [GArgs][GAdj]
-// [stage tables [3N][ntabg]][checkpoints [S][nck][D] float4] and, for the
-// adjoint, [stage inputs [S nseg][ce][4][D]][sums of the steps [S][N][gw]
+// [stage tables [3N][ntabg], or the real form's frame phases [2N+1][D]]
+// [checkpoints [S][nck][D] float4] and, for the adjoint, [stage inputs [S nseg][ce][4][D]][sums of the steps [S][N][gw]
 // double][their blocks [S][nblk][nacc] double][gradient [nacc] double][costate
 // at the segments' ends [S][nck][D] float4].  The forward with checkpoints and
 // the adjoint share the offsets of the first four.
 struct GcLayout {
-  size_t args, adj, gtab, ck, seg, gs, part, grad, lam, total;
+  size_t args, adj, gtab, ph, ck, seg, gs, part, grad, lam, total;
   int nck, nacc, gw, nblk;
   int nseg;   // segments walked side by side
 };
@@ -2276,7 +2274,8 @@ static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad
   w.adj = off;
   off += align256(sizeof(GAdj));
   w.gtab = off;
-  off += align256(3 * (size_t)N * A.ntabg * sizeof(float2));
+  w.ph = off;
+  off += std::max(align256(3 * (size_t)N * A.ntabg * sizeof(float2)), g_ph_bytes(sys));
   w.ck = off;
   off += align256((size_t)S * w.nck * L * sizeof(float4));
   w.seg = w.gs = w.part = w.grad = w.lam = off;
@@ -2330,6 +2329,7 @@ static scp_status gc_prepare(scp_system* sys, int S, int ce, bool with_grad, cha
   A.x0 = x0;
   A.xT = xT;
   A.S = S;
+  A.ph = reinterpret_cast<float2*>(base + w.ph);
   GAdj B;
   std::memset(&B, 0, sizeof(B));
   B.ck = reinterpret_cast<float4*>(base + w.ck);
@@ -2348,6 +2348,7 @@ static scp_status gc_prepare(scp_system* sys, int S, int ce, bool with_grad, cha
   hipLaunchKernelGGL(store_adj_kernel, dim3(1), dim3(64), 0, st, B, dadj);
   HIPCHK(hipGetLastError());
   if (tables) {
+    if (A.real) return g_phases(sys, reinterpret_cast<float2*>(base + w.ph), st);
     hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, sys->d,
                        sys->n_modes, gtab);
     HIPCHK(hipGetLastError());
@@ -2362,7 +2363,7 @@ scp_status launch_gather_ckpt_forward(scp_system* sys, int S, int ce, void* ws, 
   GArgs A;
   SCP_TRY(gc_prepare(sys, S, ce, false, base, ws_bytes, psi0, psiT, nullptr, true, w, A, st));
   hipEvent_t t0 = timing_start(sys, st);
-  HIPCHK(g_dispatch(sys->d, sys->n_modes, false, A.par != 0, reinterpret_cast<GArgs*>(base + w.args),
+  HIPCHK(g_dispatch(sys->d, sys->n_modes, false, g_form(A), reinterpret_cast<GArgs*>(base + w.args),
                     reinterpret_cast<GAdj*>(base + w.adj), S, A.ntab, 0, sys->n_steps, nullptr,
                     nullptr, st));
   timing_stop(sys, t0, 0, st);
@@ -2398,9 +2399,9 @@ scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, void* ws, size_
   const GAdj* dadj = reinterpret_cast<GAdj*>(base + w.adj);
   const int d = sys->d, N = sys->n_modes;
   hipEvent_t t0 = timing_start(sys, st);
-  HIPCHK(g_cos_dispatch(d, N, A.par != 0, dargs, dadj, S, A.ntab, w.nck - 1, 0, st));
+  HIPCHK(g_cos_dispatch(d, N, g_form(A), dargs, dadj, S, A.ntab, w.nck - 1, 0, st));
   for (int gs = w.nck - 1; gs >= 0; gs -= w.nseg)
-    HIPCHK(g_adj_dispatch(d, N, false, A.par != 0, dargs, dadj, S, A.ntabg, w.nacc, gs,
+    HIPCHK(g_adj_dispatch(d, N, false, g_form(A), dargs, dadj, S, A.ntabg, w.nacc, gs,
                           std::min(w.nseg, gs + 1), st));
   timing_stop(sys, t0, 2, st);
   SCP_TRY(gc_fold(sys, S, base, w, grad, st));
@@ -2440,9 +2441,14 @@ scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, vo
   out.A = base + w.args;
   out.B = base + w.adj;
   out.state = reinterpret_cast<float4*>(base + w.total);
+  out.form = g_form(A);
   out.lds_fwd = sizeof(c32) * (3 * (size_t)sys->D + ((3 * (size_t)sys->D) & 1) + 2 * (size_t)A.ntab);
   out.lds_adj = g_adj_lds(sys->d, sys->n_modes, false, A.ntabg, w.nacc);
   out.lds_cos = sizeof(c32) * (2 * (size_t)sys->D + 2 * (size_t)A.ntab);
+  if (A.real) {
+    out.lds_fwd = out.lds_cos = g_real_lds(sys->d, sys->n_modes, false);
+    out.lds_adj = g_real_lds(sys->d, sys->n_modes, true);
+  }
   out.nck = w.nck;
   out.nseg = w.nseg;
   return SCP_OK;
@@ -2451,14 +2457,16 @@ scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, vo
 namespace {
 
 template <int d, int N>
-hipError_t g_fwd_batched_launch(bool par, bool ck, const GItem* items, int n, size_t sh,
+hipError_t g_fwd_batched_launch(int form, bool ck, const GItem* items, int n, size_t sh,
                                 hipStream_t s) {
   if (sh > 163840) return hipErrorInvalidValue;
   auto run = [&](auto* kernel) {
     (void)g_lds(kernel, sh);
     hipLaunchKernelGGL(kernel, dim3(n), dim3(GShape<d, N, false>::T), sh, s, items);
   };
-  if (par) {
+  if (form == 2)
+    return g_real_forward(d, N, ck, items, nullptr, nullptr, n, 0, 0, nullptr, nullptr, s);
+  if (form == 1) {
     if (ck) run(g_rk4_batched_kernel<d, N, true, true>);
     else run(g_rk4_batched_kernel<d, N, true, false>);
   } else {
@@ -2469,36 +2477,38 @@ hipError_t g_fwd_batched_launch(bool par, bool ck, const GItem* items, int n, si
 }
 
 template <int d, int N>
-hipError_t g_adj_batched_launch(bool par, const GItem* items, int n, size_t sh, hipStream_t s) {
+hipError_t g_adj_batched_launch(int form, const GItem* items, int n, size_t sh, hipStream_t s) {
   if (sh > 163840) return hipErrorInvalidValue;
   auto run = [&](auto* kernel) {
     (void)g_lds(kernel, sh);
     hipLaunchKernelGGL(kernel, dim3(n), dim3(GShape<d, N, false>::T), sh, s, items);
   };
-  if (par) run(g_adj_batched_kernel<d, N, true>);
+  if (form == 2) return g_real_segments(d, N, items, nullptr, nullptr, n, 0, s);
+  if (form == 1) run(g_adj_batched_kernel<d, N, true>);
   else run(g_adj_batched_kernel<d, N, false>);
   return hipGetLastError();
 }
 
 template <int d, int N>
-hipError_t g_cos_batched_launch(bool par, const GItem* items, int n, size_t sh, hipStream_t s) {
+hipError_t g_cos_batched_launch(int form, const GItem* items, int n, size_t sh, hipStream_t s) {
   if (sh > 163840) return hipErrorInvalidValue;
   auto run = [&](auto* kernel) {
     (void)g_lds(kernel, sh);
     hipLaunchKernelGGL(kernel, dim3(n), dim3(GShape<d, N, false>::T), sh, s, items);
   };
-  if (par) run(g_cos_batched_kernel<d, N, true>);
+  if (form == 2) return g_real_sweep(d, N, items, nullptr, nullptr, n, 0, 0, s);
+  if (form == 1) run(g_cos_batched_kernel<d, N, true>);
   else run(g_cos_batched_kernel<d, N, false>);
   return hipGetLastError();
 }
 
 }  // namespace
 
-scp_status gather_launch_cos_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
+scp_status gather_launch_cos_batched(int d, int N, int form, const GItem* items, int n, size_t lds,
                                      hipStream_t st) {
 #define GA_COS_B(dd_, nn_) \
   if (d == dd_ && N == nn_) {                                                  \
-    HIPCHK((g_cos_batched_launch<dd_, nn_>(par, items, n, lds, st)));         \
+    HIPCHK((g_cos_batched_launch<dd_, nn_>(form, items, n, lds, st)));         \
     return SCP_OK;                                                            \
   }
   GA_CLOSED_SHAPES(GA_COS_B)
@@ -2506,11 +2516,11 @@ scp_status gather_launch_cos_batched(int d, int N, bool par, const GItem* items,
   return fail(SCP_EINVAL, "gather engine: no compiled stepper for this shape");
 }
 
-scp_status gather_launch_fwd_batched(int d, int N, bool par, bool ck, const GItem* items, int n, size_t lds,
+scp_status gather_launch_fwd_batched(int d, int N, int form, bool ck, const GItem* items, int n, size_t lds,
                                      hipStream_t st) {
 #define GA_FWD_B(dd_, nn_) \
   if (d == dd_ && N == nn_) {                                                  \
-    HIPCHK((g_fwd_batched_launch<dd_, nn_>(par, ck, items, n, lds, st)));          \
+    HIPCHK((g_fwd_batched_launch<dd_, nn_>(form, ck, items, n, lds, st)));          \
     return SCP_OK;                                                            \
   }
   GA_CLOSED_SHAPES(GA_FWD_B)
@@ -2518,11 +2528,11 @@ scp_status gather_launch_fwd_batched(int d, int N, bool par, bool ck, const GIte
   return fail(SCP_EINVAL, "gather engine: no compiled stepper for this shape");
 }
 
-scp_status gather_launch_adj_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
+scp_status gather_launch_adj_batched(int d, int N, int form, const GItem* items, int n, size_t lds,
                                      hipStream_t st) {
 #define GA_ADJ_B(dd_, nn_) \
   if (d == dd_ && N == nn_) {                                                  \
-    HIPCHK((g_adj_batched_launch<dd_, nn_>(par, items, n, lds, st)));              \
+    HIPCHK((g_adj_batched_launch<dd_, nn_>(form, items, n, lds, st)));              \
     return SCP_OK;                                                            \
   }
   GA_CLOSED_SHAPES(GA_ADJ_B)

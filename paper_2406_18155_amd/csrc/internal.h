@@ -194,6 +194,9 @@ struct scp_system {
   double* d_dctab64 = nullptr;
   double* d_ctab64 = nullptr;   // [3N][n_drives] c(t) per drive, FP64 (plain path)
   float2* d_ph = nullptr;       // real frame: [2N+1][ph_row] frame phases (cos, sin)
+  float* d_rt = nullptr;        // real form of the gather engine: static rows (else null)
+  float* d_rc = nullptr;        // its drive coefficients [3N][n_modes], scaled with the rows
+  double rc_scale[16] = {0};    // that scale (largest drive-operator entry of the mode)
   float* d_rops = nullptr;      // real frame: [block_q] un-rotated operators (real parts)
   void* d_scratch = nullptr;    // small per-system scratch (adjoint partial sums)
   size_t scratch_bytes = 0;
@@ -280,6 +283,7 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
                                    const float2* cot, double* grad, hipStream_t st);
 bool gather_preferred(const scp_system* sys, int S);
 bool gather_supported(const scp_system* sys);
+std::vector<float> build_gather_rows(const scp_system* sys, double* scale);
 size_t gather_workspace_bytes(const scp_system* sys);
 scp_status launch_gather_forward(scp_system* sys, int S, void* ws, size_t ws_bytes,
                                  const float2* psi0, float2* psiT, hipStream_t st);
@@ -305,16 +309,17 @@ struct GServeInfo {
   const void* B;
   float4* state;
   size_t lds_fwd, lds_adj, lds_cos;
+  int form;   // 0 general, 1 parity, 2 real (batched launches are of one form)
   int nck;
   int nseg;   // segments walked side by side (stage-input buffers: nseg per column)
 };
 scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, void* ws,
                              GServeInfo& out);
-scp_status gather_launch_fwd_batched(int d, int N, bool par, bool ck, const GItem* items, int n, size_t lds,
+scp_status gather_launch_fwd_batched(int d, int N, int form, bool ck, const GItem* items, int n, size_t lds,
                                      hipStream_t st);
-scp_status gather_launch_adj_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
+scp_status gather_launch_adj_batched(int d, int N, int form, const GItem* items, int n, size_t lds,
                                      hipStream_t st);
-scp_status gather_launch_cos_batched(int d, int N, bool par, const GItem* items, int n, size_t lds,
+scp_status gather_launch_cos_batched(int d, int N, int form, const GItem* items, int n, size_t lds,
                                      hipStream_t st);
 size_t gather_serve_bytes(const scp_system* sys, int S, int ce, bool grad);
 scp_status gather_serve_prepare(scp_system* sys, int S, int ce, bool grad, void* ws, size_t bytes,

@@ -109,6 +109,8 @@ hipError_t launch_phase_table(int d, int NT, int NR, int RB, int thr, int row, i
                               double h, const double* frames, const int* tmode, const int* rmode,
                               float2* ph, hipStream_t s);
 size_t drive_static_size();
+hipError_t launch_gather_drives(int npt, int ndrives, int N, const int* mode, const double* scale,
+                                const double* ctab64, float* out, hipStream_t s);
 void pack_drive_static(void* dst, int k, int env, int npar, int par0, int group, double omega,
                        double phase, double sigma);
 scp_status launch_rk4_range(const scp_system* sys, const float2* psi0, float2* psiT, float2* state,
@@ -679,6 +681,16 @@ scp_status build_tables(scp_system* sys, hipStream_t st) {
                             sys->d_ctab64, st));
   DevBuf bmodes;
   sys->real_ok = P.real_frame != 0;
+  const std::vector<float> rt = build_gather_rows(sys, sys->rc_scale);
+  if (!rt.empty()) {
+    HIPCHK(hipMalloc(&sys->d_rt, rt.size() * sizeof(float)));
+    HIPCHK(hipMemcpyAsync(sys->d_rt, rt.data(), rt.size() * sizeof(float), hipMemcpyHostToDevice, st));
+    HIPCHK(hipMalloc(&sys->d_rc, np3 * N * sizeof(float)));
+    std::vector<int> dm;
+    for (const Drive& R : sys->drives) dm.push_back(R.mode);
+    HIPCHK(launch_gather_drives((int)np3, (int)dm.size(), N, dm.data(), sys->rc_scale, sys->d_ctab64,
+                                sys->d_rc, st));
+  }
   if (P.real_frame) {
     // modes at the thread positions (by natural stride) and at the register
     // positions of the base layout
@@ -1452,6 +1464,8 @@ void scp_destroy(scp_system* sys) {
   if (sys->d_ctab64) (void)hipFree(sys->d_ctab64);
   if (sys->d_ph) (void)hipFree(sys->d_ph);
   if (sys->d_rops) (void)hipFree(sys->d_rops);
+  if (sys->d_rt) (void)hipFree(sys->d_rt);
+  if (sys->d_rc) (void)hipFree(sys->d_rc);
   if (sys->d_scratch) (void)hipFree(sys->d_scratch);
   delete sys;
 }

@@ -493,17 +493,18 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
         w.r->tick_stream = st;
       }
     }
-    // gather-engine requests, batched per (kind, d, modes, checkpoints, parity)
+    // gather-engine requests, batched per (kind, d, modes, checkpoints, form)
     {
       std::map<std::tuple<int, int, int, int, int>, std::vector<Request*>> gcls;
       for (Request* r : sv->active)
         if (r->gather)
-          gcls[{r->phase, r->sys->d, r->sys->n_modes, r->want_grad, r->sys->plan.parity}].push_back(r);
+          gcls[{r->phase, r->sys->d, r->sys->n_modes, r->want_grad, r->gi.form}].push_back(r);
       for (auto& kv : gcls) {
         hipStream_t st = sv->work[ci++ % scp_server::kWork];
         const int kind = std::get<0>(kv.first), d = std::get<1>(kv.first),
                   N = std::get<2>(kv.first);
-        const bool ck = std::get<3>(kv.first) != 0, par = std::get<4>(kv.first) != 0;
+        const bool ck = std::get<3>(kv.first) != 0;
+        const int form = std::get<4>(kv.first);
         if (kind == 0) {
           GItem* it = (GItem*)((char*)sv->h_items + off);
           int nit = 0;
@@ -520,7 +521,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
           }
           void* dptr = nullptr;
           if (!stage(it, (size_t)nit * sizeof(GItem), st, &dptr)) return fail(SCP_EHIP, "item upload");
-          s = gather_launch_fwd_batched(d, N, par, ck, (const GItem*)dptr, nit, lds, st);
+          s = gather_launch_fwd_batched(d, N, form, ck, (const GItem*)dptr, nit, lds, st);
           if (s != SCP_OK) return s;
         } else {
           // this tick's segments of every request: the costate sweep over them,
@@ -542,7 +543,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
           }
           void* dptr = nullptr;
           if (!stage(it, (size_t)nit * sizeof(GItem), st, &dptr)) return fail(SCP_EHIP, "item upload");
-          s = gather_launch_cos_batched(d, N, par, (const GItem*)dptr, nit, lds, st);
+          s = gather_launch_cos_batched(d, N, form, (const GItem*)dptr, nit, lds, st);
           if (s != SCP_OK) return s;
           for (int j = 0; j < rounds; ++j) {
             it = (GItem*)((char*)sv->h_items + off);
@@ -560,7 +561,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
             }
             if (!stage(it, (size_t)nit * sizeof(GItem), st, &dptr))
               return fail(SCP_EHIP, "item upload");
-            s = gather_launch_adj_batched(d, N, par, (const GItem*)dptr, nit, lds, st);
+            s = gather_launch_adj_batched(d, N, form, (const GItem*)dptr, nit, lds, st);
             if (s != SCP_OK) return s;
           }
           for (size_t q = 0; q < kv.second.size(); ++q) {

@@ -121,7 +121,35 @@ __global__ void ctable_kernel(TabStatic ts, const DriveStatic* __restrict__ dr,
   for (int g = 0; g < ts.ngroups && g < 64; ++g) ctab[(size_t)p * ts.ngroups + g] = (float)csum[g];
 }
 
+// out[p][m] = scale_m sum over mode m's drives of c(t_p), summed in FP64.
+struct RcStatic {
+  int npt, ndrives, N;
+  int mode[MAXGROUPS];
+  double scale[SCP_MAX_MODES];
+};
+__global__ void rc_kernel(RcStatic R, const double* __restrict__ ctab64, float* __restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= R.npt * R.N) return;
+  const int p = i / R.N, m = i - p * R.N;
+  double v = 0.0;
+  for (int k = 0; k < R.ndrives; ++k)
+    if (R.mode[k] == m) v += ctab64[(size_t)p * R.ndrives + k];
+  out[i] = (float)(R.scale[m] * v);
+}
+
 }  // namespace
+
+hipError_t launch_gather_drives(int npt, int ndrives, int N, const int* mode, const double* scale,
+                                const double* ctab64, float* out, hipStream_t s) {
+  RcStatic R{};
+  R.npt = npt;
+  R.ndrives = ndrives;
+  R.N = N;
+  for (int k = 0; k < ndrives; ++k) R.mode[k] = mode[k];
+  for (int m = 0; m < N; ++m) R.scale[m] = scale[m];
+  hipLaunchKernelGGL(rc_kernel, dim3((npt * N + 255) / 256), dim3(256), 0, s, R, ctab64, out);
+  return hipGetLastError();
+}
 
 hipError_t launch_tables_impl(int d, int nslots, int npairs, int ndrives, int ngroups, int npulse,
                               int nsteps, double h, double T, const double* frames,
