@@ -192,8 +192,14 @@ scp_status scp_system_set_frame(scp_system* sys, int32_t real_frame);
  * whose stage tables fit in LDS; its adjoint needs in addition at most 16
  * drives on 10 distinct operators, 16 couplings and 16 operator slots, else
  * that solve runs on engine 1.  engine 0 (the default): engine 2 where it
- * runs and the columns would occupy fewer than 64 of engine 1's workgroups,
- * else engine 1.  Both engines compute the same RK4 steps and the same
+ * runs and either the columns would occupy fewer than 64 of engine 1's
+ * workgroups, or the device is in the real frame with operators between levels
+ * of unlike parity only, coupled neighbours on a chain or ring of its modes
+ * and at most 256 columns (1024 for D <= 1024); else engine 1.  A forward
+ * without checkpoints of a device with D < 64 and at least 64 steps is split
+ * over time under engine 0: runs of steps propagate the identity side by side
+ * on engine 1's stepper and are multiplied onto the columns in FP64
+ * (scp_solve_engine reports 1).  Both engines compute the same RK4 steps and the same
  * discrete adjoint in FP32 with a compensated state; results differ by
  * rounding.  scp_system_set_engine: SCP_EINVAL for engine 2 on a device the
  * gather engine cannot run; a change forgets the recorded checkpoints.

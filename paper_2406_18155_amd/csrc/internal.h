@@ -282,6 +282,10 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
                                    int S, void* ws, size_t ws_bytes, const float2* rho0,
                                    const float2* cot, double* grad, hipStream_t st);
 bool gather_preferred(const scp_system* sys, int S);
+bool split_preferred(const scp_system* sys);
+size_t split_workspace_bytes(const scp_system* sys);
+scp_status launch_split_forward(scp_system* sys, int S, void* ws, const float2* psi0, float2* psiT,
+                                hipStream_t st);
 bool gather_supported(const scp_system* sys);
 std::vector<float> build_gather_rows(const scp_system* sys, double* scale);
 size_t gather_workspace_bytes(const scp_system* sys);

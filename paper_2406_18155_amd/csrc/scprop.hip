@@ -885,6 +885,7 @@ struct WsLayout {
   int nckpt = 0, ce = 0, nwg = 0;
   bool gather = false;        // a forward-only FP32 solve on the gather engine (workspace from 0)
   bool gather_grad = false;   // checkpoints / adjoint on the gather engine (its own layout)
+  bool split = false;         // a forward-only solve of a small device, split over time
 };
 
 // Which engine runs an FP32 solve: the system's choice, else (automatic) the
@@ -916,6 +917,10 @@ WsLayout ws_layout(const scp_system* sys, const scp_solve_opts* o, int with_grad
   } else if (o->precision == 0) {
     w.lo = off;
     off = align(off + S * D * sizeof(float2));
+    if (engine == 0 && !o->with_ckpt && !with_grad && split_preferred(sys)) {
+      w.split = true;
+      off = std::max(off, split_workspace_bytes(sys));
+    }
     if (o->with_ckpt || with_grad) {
       w.ckpt = off;
       off = align(off + (size_t)w.nckpt * S * D * sizeof(float4));
@@ -1122,6 +1127,10 @@ scp_status scp_propagate(scp_system* sys, const scp_solve_opts* opts, void* work
                                               (float2*)psiT, st);
     if (s == SCP_OK) ck_record(sys, workspace, opts->n_cols, w.ce);
     return s;
+  }
+  if (w.split) {
+    ck_clear(sys);
+    return launch_split_forward(sys, opts->n_cols, workspace, (const float2*)psi0, (float2*)psiT, st);
   }
   float4* ck = opts->with_ckpt ? (float4*)((char*)workspace + w.ckpt) : nullptr;
   ck_clear(sys);
