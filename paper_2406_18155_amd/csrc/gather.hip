@@ -2200,17 +2200,26 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
 }
 
 // --- closed systems ----------------------------------------------------------
-// The gather engine takes a closed-system forward (no checkpoints) when the
-// system has a compiled shape and its columns would leave most of the chip
-// idle in the register-layout stepper: fewer columns than 256 workgroups'
-// worth (each gather workgroup holds one column).
+// The gather engine (one workgroup per column) takes a closed system of a
+// compiled shape when its columns would leave most of the chip idle in the
+// register-layout stepper; in its real form, whenever the columns fill no more
+// than one round of workgroups, four where a thread has one element.  Measured,
+// register -> real form, us per step (forward; forward + gradient):
+//   6-fluxonium chain, d = 4, 64 columns       56 -> 26;  302 -> 107
+//   7-transmon ring, d = 3, 128 columns        47 -> 23;  244 -> 121
+//   5-fluxonium chain, d = 5, 32 columns       54 -> 40;  313 -> 111
+//   4-transmon chain, d = 4, 256 columns       35 -> 2.8; 163 -> 17
+//   6-transmon ring, d = 3, 64 / 729 columns   33 -> 4 / 33 -> 12;  147 -> 20 / 150 -> 136
+//   9-mode ring, d = 2, 512 columns            34 -> 4.3; 181 -> 89
 bool gather_preferred(const scp_system* sys, int S) {
-  if (!g_supported(sys->d, sys->n_modes, false) || S > 256) return false;
+  if (!g_supported(sys->d, sys->n_modes, false)) return false;
   GArgs A;
   if (g_args(sys, false, nullptr, nullptr, A) != SCP_OK) {
     set_error("");
     return false;
   }
+  if (A.real) return S <= (sys->D <= 1024 ? 1024 : 256);
+  if (S > 256) return false;
   const int fused_wg = (S + sys->plan.CPW - 1) / sys->plan.CPW;
   return fused_wg < 64;
 }
