@@ -1117,10 +1117,48 @@ TrGen make_gen(const scp_system* sys, int order, const TrLayout& W, double* ipar
 
 }  // namespace
 
+namespace {
+
+TrRun make_run(const scp_system* sys, const TrLayout& W) {
+  const int d = sys->d, M = sys->n_modes, N = sys->n_steps;
+  TrRun R{};
+  R.M = M;
+  R.N = N;
+  R.r = W.r;
+  R.H = W.H;
+  R.nopmax = W.nopmax;
+  R.nslot = W.P.nslot;
+  R.ndyn = W.P.ndyn;
+  for (int h = 0; h < W.H; ++h) {
+    R.nop[h] = W.P.nop[h];
+    for (int o = 0; o < W.P.nop[h]; ++o) {
+      R.opk[h][o] = W.P.op[h][o].kind;
+      R.opi[h][o] = W.P.op[h][o].mi;
+      R.opj[h][o] = W.P.op[h][o].mj;
+      R.ops[h][o] = W.P.op[h][o].stat ? W.P.op[h][o].sid + 1 : -(W.P.op[h][o].dix + 1);
+      R.opa[h][o] = W.P.op[h][o].s0 | (W.P.op[h][o].s1 << 8);
+    }
+  }
+  R.D = (int)sys->D;
+  R.mode1 = W.mode1;
+  R.mode2 = W.mode2;
+  int s = 1;
+  for (int m = M - 1; m >= 0; --m) {
+    R.stride[m] = s;
+    s *= d;
+  }
+  const double twopi = 6.283185307179586476925286766559;
+  for (int m = 0; m < M; ++m)
+    for (int a = 0; a < d; ++a) R.fT[m][a] = std::remainder(sys->modes[m].frame[a] * N * sys->h, twopi);
+  return R;
+}
+
+}  // namespace
+
 // psi0 == nullptr: the gate tables only (single-mode and pair gates, what
-// the adjoint reuses), no fusion and no propagation
-scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const double2* psi0,
-                          double2* psiT, hipStream_t st) {
+// the adjoint reuses; with ``fuse`` the fused operations too), no propagation
+static scp_status tr_launch(scp_system* sys, int order, int S, void* ws, const double2* psi0,
+                            double2* psiT, bool fuse, hipStream_t st) {
   scp_status chk = trotter_check(sys, order);
   if (chk != SCP_OK) return chk;
   const TrLayout W = tr_layout(sys, order);
@@ -1178,7 +1216,7 @@ scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const dou
                      4 * d * d * sizeof(double2) + TR_MAXDRV * sizeof(double), st, G, deps, dops, dpar,
                      sg);
   HIPCHK(hipGetLastError());
-  if (psi0 == nullptr) return SCP_OK;
+  if (psi0 == nullptr && !fuse) return SCP_OK;
   const double twopi = 6.283185307179586476925286766559;
   if (W.phase) {
     TpRun R{};
@@ -1230,34 +1268,8 @@ scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const dou
                        pg, fg, fs);
     HIPCHK(hipGetLastError());
   }
-  TrRun R{};
-  R.M = M;
-  R.N = N;
-  R.r = W.r;
-  R.H = W.H;
-  R.nopmax = W.nopmax;
-  R.nslot = W.P.nslot;
-  R.ndyn = W.P.ndyn;
-  for (int h = 0; h < W.H; ++h) {
-    R.nop[h] = W.P.nop[h];
-    for (int o = 0; o < W.P.nop[h]; ++o) {
-      R.opk[h][o] = W.P.op[h][o].kind;
-      R.opi[h][o] = W.P.op[h][o].mi;
-      R.opj[h][o] = W.P.op[h][o].mj;
-      R.ops[h][o] = W.P.op[h][o].stat ? W.P.op[h][o].sid + 1 : -(W.P.op[h][o].dix + 1);
-      R.opa[h][o] = W.P.op[h][o].s0 | (W.P.op[h][o].s1 << 8);
-    }
-  }
-  R.D = (int)sys->D;
-  R.mode1 = W.mode1;
-  R.mode2 = W.mode2;
-  int s = 1;
-  for (int m = M - 1; m >= 0; --m) {
-    R.stride[m] = s;
-    s *= d;
-  }
-  for (int m = 0; m < M; ++m)
-    for (int a = 0; a < d; ++a) R.fT[m][a] = std::remainder(sys->modes[m].frame[a] * N * sys->h, twopi);
+  if (psi0 == nullptr) return SCP_OK;
+  const TrRun R = make_run(sys, W);
   hipError_t e;
   switch (d) {
     case 2: e = run_trotter<2>(R, S, psi0, psiT, fg, fs, sg, st); break;
@@ -1269,6 +1281,10 @@ scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const dou
   return SCP_OK;
 }
 
+scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const double2* psi0,
+                          double2* psiT, hipStream_t st) {
+  return tr_launch(sys, order, S, ws, psi0, psiT, false, st);
+}
 
 // ---------------------------------------------------------------------------
 // Local continuous adjoint method (LCAM) of the product formulas (Sec. 2.5).
@@ -1303,6 +1319,16 @@ scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const dou
 // second kernel reduces over the visits and columns in a fixed order; the
 // pair sums accumulate per column.  No atomics: the result is bitwise
 // reproducible.
+//
+// Few columns leave most of the chip idle, and the walk is several times the
+// work of the propagation.  Where the gates are unitary (real coefficients) the
+// state and the costate go back alike: rounds of up to 256 / S slots of at most
+// 64 steps each are walked side by side, after a sweep (lc_sweep_kernel) that
+// takes psi and mu back over the round with the adjoints of the fused
+// operations, two workgroups per column, and leaves both at the top of every
+// slot.  Its memory does not grow with the number of steps.
+// 4-fluxonium chain (d = 5, 16 columns), Q2, forward + gradient: 121 us per
+// step with one walk, 69 with slots.
 // ---------------------------------------------------------------------------
 namespace {
 
@@ -1310,6 +1336,7 @@ constexpr int LC_CHUNK = 128;     // steps per walk launch
 
 struct LcRun {
   int M, E, N, r, H, D, S;
+  int len;   // steps of a slot; 0: one walk that carries its state between launches
   int stride[SCP_MAX_MODES];
   int ci[TR_MAXE], cj[TR_MAXE];
   double fT[SCP_MAX_MODES][SCP_MAX_TRUNC];   // frame energy times T, reduced mod 2 pi
@@ -1359,7 +1386,7 @@ __device__ __forceinline__ void lc_apply2(double2* L, int D, int si, int sj, con
 
 template <int d>
 __global__ void __launch_bounds__(TR_THREADS)
-lc_walk_kernel(LcRun R, int n_hi, int n_lo, int first, const double2* __restrict__ psiT,
+lc_walk_kernel(LcRun R, int n_top, int n_base, int first, const double2* __restrict__ psiT,
                const double2* __restrict__ lamT, double2* __restrict__ psi_st,
                double2* __restrict__ mu_st, const double2* __restrict__ sg_inv,
                const double2* __restrict__ sg_adj, const double2* __restrict__ pg_inv,
@@ -1367,18 +1394,21 @@ lc_walk_kernel(LcRun R, int n_hi, int n_lo, int first, const double2* __restrict
                double2* __restrict__ Mp) {
   extern __shared__ double2 lds[];
   constexpr int dd = d * d;
-  const int col = blockIdx.x;
-  const size_t off = (size_t)col * R.D;
+  const int slot = blockIdx.x / R.S, col = blockIdx.x - slot * R.S;
+  const int n_hi = n_top - slot * R.len, n_lo = R.len ? max(n_base, n_hi - R.len) : n_base;
+  const size_t off = (size_t)blockIdx.x * R.D;
   double2* L = lds;                   // psi (the state)
   double2* Lm = lds + R.D;            // mu (the costate)
   double2* scr = lds + 2 * R.D;       // TR_THREADS partial sums
   const size_t np_col = (size_t)R.r * R.E * dd * dd;
-  if (first) {
+  Mp += (size_t)slot * R.S * np_col;
+  if (first)
+    for (size_t e = threadIdx.x; e < np_col; e += blockDim.x) Mp[col * np_col + e] = make_double2(0, 0);
+  if (first && !R.len) {
     for (int i = threadIdx.x; i < R.D; i += blockDim.x) {
       L[i] = unrotate(R, d, i, psiT[off + i]);
       Lm[i] = unrotate(R, d, i, lamT[off + i]);
     }
-    for (size_t e = threadIdx.x; e < np_col; e += blockDim.x) Mp[col * np_col + e] = make_double2(0, 0);
   } else {
     for (int i = threadIdx.x; i < R.D; i += blockDim.x) {
       L[i] = psi_st[off + i];
@@ -1386,6 +1416,7 @@ lc_walk_kernel(LcRun R, int n_hi, int n_lo, int first, const double2* __restrict
     }
   }
   const int nq = (n_hi - n_lo) * R.r * R.M;
+  Ms += (size_t)(n_lo - n_base) * R.r * R.M * R.S * dd;   // this slot's steps
   for (int e = threadIdx.x; e < nq * dd; e += blockDim.x)
     Ms[((size_t)(e / dd) * R.S + col) * dd + e % dd] = make_double2(0, 0);
   __syncthreads();
@@ -1499,10 +1530,100 @@ lc_walk_kernel(LcRun R, int n_hi, int n_lo, int first, const double2* __restrict
       lc_apply2<d>(Lm, R.D, R.stride[R.ci[pend_t - R.M]], R.stride[R.cj[pend_t - R.M]], pend);
   }
   __syncthreads();
+  if (R.len) return;
   for (int i = threadIdx.x; i < R.D; i += blockDim.x) {
     psi_st[off + i] = L[i];
     mu_st[off + i] = Lm[i];
   }
+}
+
+// Both vectors back over the steps [n_base, n_top) with the adjoints of the
+// fused operations (fga, fsa, sga: the tables of trotter_kernel, every gate
+// conjugate-transposed), left at the top of every slot of R1.len steps and, in
+// psi_c / mu_c, at n_base.  first: from psi_I(T) and lambda_I(T).  Blocks
+// [0, S): psi, [S, 2 S): mu.
+template <int d>
+__global__ void __launch_bounds__(TR_THREADS)
+lc_sweep_kernel(TrRun R, LcRun R1, int n_top, int n_base, int first,
+                const double2* __restrict__ psiT, const double2* __restrict__ lamT,
+                double2* __restrict__ psi_c, double2* __restrict__ mu_c, double2* __restrict__ psi_st,
+                double2* __restrict__ mu_st, const double2* __restrict__ fga,
+                const double2* __restrict__ fsa, const double2* __restrict__ sga) {
+  extern __shared__ double2 lds[];
+  constexpr int dd = d * d;
+  const int S = R1.S, col = blockIdx.x % S;
+  const bool mu = (int)blockIdx.x >= S;
+  const double2* src = (mu ? lamT : psiT) + (size_t)col * R.D;
+  double2* carry = (mu ? mu_c : psi_c) + (size_t)col * R.D;
+  double2* top = (mu ? mu_st : psi_st) + (size_t)col * R.D;
+  double2 *L = lds, *Lo = lds + R.D;
+  for (int i = threadIdx.x; i < R.D; i += blockDim.x)
+    L[i] = first ? unrotate(R1, d, i, src[i]) : carry[i];
+  __syncthreads();
+  for (int n = n_top - 1; n >= n_base; --n) {
+    const int up = n_top - 1 - n;
+    if (up % R1.len == 0) {
+      double2* dst = top + (size_t)(up / R1.len) * S * R.D;
+      for (int i = threadIdx.x; i < R.D; i += blockDim.x) dst[i] = L[i];
+      __syncthreads();
+    }
+    for (int j = R.r - 1; j >= 0; --j)
+      for (int h = R.H - 1; h >= 0; --h) {
+        const double2* fgh = fga + ((size_t)n * R.r + j) * R.ndyn * dd * dd;
+        const double2* fsj = fsa + (size_t)j * R.nslot * dd * dd;
+        const double2* sgj = sga + ((size_t)n * R.r + j) * R.M * dd;
+        for (int o = R.nop[h] - 1; o >= 0; --o) {
+          const double2* gt = !R.opk[h][o]  ? sgj + (size_t)R.opi[h][o] * dd
+                              : R.ops[h][o] > 0 ? fsj + (size_t)(R.ops[h][o] - 1) * dd * dd
+                                                : fgh + (size_t)(-R.ops[h][o] - 1) * dd * dd;
+          if (!R.opk[h][o] && !R.mode1) {
+            tr_apply1<d>(L, R.D, R.stride[R.opi[h][o]], gt);
+          } else {
+            const int si = R.stride[R.opi[h][o]], sj = R.stride[R.opj[h][o]];
+            if (!R.opk[h][o])
+              tr_apply1_rows<d>(L, Lo, R.D, si, gt);
+            else if (R.mode2 == 2)
+              tr_apply2_rows<d, d>(L, Lo, R.D, si, sj, gt);
+            else
+              tr_apply2_rows<d, 1>(L, Lo, R.D, si, sj, gt);
+            double2* t = L;
+            L = Lo;
+            Lo = t;
+          }
+          __syncthreads();
+        }
+      }
+  }
+  for (int i = threadIdx.x; i < R.D; i += blockDim.x) carry[i] = L[i];
+}
+
+// n x n gates conjugate-transposed where they are
+__global__ void lc_adjoint_inplace_kernel(double2* __restrict__ G, int n, size_t count) {
+  const size_t nn = (size_t)n * n;
+  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < count * nn;
+       e += (size_t)gridDim.x * blockDim.x) {
+    const size_t b = e / nn, w = e % nn;
+    const int r = (int)(w / n), c = (int)(w % n);
+    if (r > c) continue;
+    double2* p = G + b * nn;
+    const double2 x = p[(size_t)r * n + c], y = p[(size_t)c * n + r];
+    p[(size_t)r * n + c] = make_double2(y.x, -y.y);
+    p[(size_t)c * n + r] = make_double2(x.x, -x.y);
+  }
+}
+
+template <int d>
+hipError_t run_lc_sweep(const TrRun& T, const LcRun& R, int n_top, int n_base, int first,
+                        const double2* psiT, const double2* lamT, double2* psi_c, double2* mu_c,
+                        double2* psi_st, double2* mu_st, const double2* fga, const double2* fsa,
+                        const double2* sga, hipStream_t st) {
+  const size_t sh = (size_t)2 * T.D * sizeof(double2);
+  hipError_t e = hipFuncSetAttribute((const void*)lc_sweep_kernel<d>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(lc_sweep_kernel<d>, dim3(2 * R.S), dim3(TR_THREADS), sh, st, T, R, n_top, n_base,
+                     first, psiT, lamT, psi_c, mu_c, psi_st, mu_st, fga, fsa, sga);
+  return hipGetLastError();
 }
 
 // Split walk, for columns small enough that LDS holds two buffers each of psi
@@ -1735,7 +1856,7 @@ __device__ __forceinline__ void lc_split_fold(const LcGate& G, int ch, const dou
 
 template <int d>
 __global__ void __launch_bounds__(LC_THREADS)
-lc_walk_split_kernel(LcRun R, int n_hi, int n_lo, int first, const double2* __restrict__ psiT,
+lc_walk_split_kernel(LcRun R, int n_top, int n_base, int first, const double2* __restrict__ psiT,
                      const double2* __restrict__ lamT, double2* __restrict__ psi_st,
                      double2* __restrict__ mu_st, const double2* __restrict__ sg_inv,
                      const double2* __restrict__ sg_adj, const double2* __restrict__ pg_inv,
@@ -1744,8 +1865,10 @@ lc_walk_split_kernel(LcRun R, int n_hi, int n_lo, int first, const double2* __re
   extern __shared__ double2 lds[];
   constexpr int dd = d * d, NN = dd * dd;
   static_assert(NN <= 2 * LC_THREADS, "a gate table is prefetched as two entries per thread");
-  const int col = blockIdx.x, D = R.D, tid = threadIdx.x, nft = D / d;
-  const size_t off = (size_t)col * D;
+  const int slot = blockIdx.x / R.S, col = blockIdx.x - slot * R.S;
+  const int n_hi = n_top - slot * R.len, n_lo = R.len ? max(n_base, n_hi - R.len) : n_base;
+  const int D = R.D, tid = threadIdx.x, nft = D / d;
+  const size_t off = (size_t)blockIdx.x * D;
   double2* P = lds;                  // psi: two buffers of D
   double2* U = lds + 2 * D;          // mu: two buffers of D
   double2* Gi = lds + 4 * D;         // inverse gates: two slots of NN
@@ -1753,22 +1876,24 @@ lc_walk_split_kernel(LcRun R, int n_hi, int n_lo, int first, const double2* __re
   double2* scr = Ga + 2 * NN;        // partial sums: two slots of LC_THREADS
   int* tab = reinterpret_cast<int*>(scr + 2 * LC_THREADS);   // fibre offsets: three slots of D/d
   const size_t np_col = (size_t)R.r * R.E * NN;
+  Mp += (size_t)slot * R.S * np_col;
   const int K = R.M + R.E, len = R.H == 2 ? 2 * K : K;
   const int ng = (n_hi - n_lo) * R.r * len;   // gates of this launch
   // launch constants of the two gate kinds: fibres and partial sums per entry
   const int nf1 = D / d, nf2 = D / dd;
   const int ch1 = lc_chunks(dd, nf1), ch2 = lc_chunks(NN, nf2);
   auto gate = [&](const LcPos& p) {
-    return lc_gate(R, p, n_lo, col, sg_inv, sg_adj, pg_inv, pg_adj, Ms, Mp, dd);
+    return lc_gate(R, p, n_base, col, sg_inv, sg_adj, pg_inv, pg_adj, Ms, Mp, dd);
   };
   auto nn_of = [&](const LcGate& G) { return G.s1 ? NN : dd; };
   auto chunks_of = [&](const LcGate& G) { return G.s1 ? ch2 : ch1; };
-  if (first) {
+  if (first)
+    for (size_t e = tid; e < np_col; e += LC_THREADS) Mp[col * np_col + e] = make_double2(0, 0);
+  if (first && !R.len) {
     for (int i = tid; i < D; i += LC_THREADS) {
       P[i] = unrotate(R, d, i, psiT[off + i]);
       U[i] = unrotate(R, d, i, lamT[off + i]);
     }
-    for (size_t e = tid; e < np_col; e += LC_THREADS) Mp[col * np_col + e] = make_double2(0, 0);
   } else {
     for (int i = tid; i < D; i += LC_THREADS) {
       P[i] = psi_st[off + i];
@@ -1862,7 +1987,7 @@ lc_walk_split_kernel(LcRun R, int n_hi, int n_lo, int first, const double2* __re
     }
     // C
     if (hasPP) lc_split_fold<d>(gpp, chunks_of(gpp), scr + (g & 1) * LC_THREADS, old, eF);
-    if (g == ng + 1) {
+    if (g == ng + 1 && !R.len) {
       for (int i = tid; i < D; i += LC_THREADS) {
         psi_st[off + i] = Pc[i];
         mu_st[off + i] = Uc[i];
@@ -2031,12 +2156,13 @@ hipError_t run_lc_walk(const LcRun& R, int n_hi, int n_lo, int first, const doub
                        const double2* lamT, double2* psi_st, double2* mu_st, const double2* sgi,
                        const double2* sga, const double2* pgi, const double2* pga, double2* Ms,
                        double2* Mp, hipStream_t st) {
+  const int nslot = R.len ? (n_hi - n_lo + R.len - 1) / R.len : 1;
   if (lc_split_fits(R.D, d)) {
     const size_t sh = lc_split_lds(R.D, d);
     hipError_t e = hipFuncSetAttribute((const void*)lc_walk_split_kernel<d>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(lc_walk_split_kernel<d>, dim3(R.S), dim3(LC_THREADS), sh, st, R, n_hi, n_lo,
+    hipLaunchKernelGGL(lc_walk_split_kernel<d>, dim3(nslot * R.S), dim3(LC_THREADS), sh, st, R, n_hi, n_lo,
                        first, psiT, lamT, psi_st, mu_st, sgi, sga, pgi, pga, Ms, Mp);
     return hipGetLastError();
   }
@@ -2044,15 +2170,16 @@ hipError_t run_lc_walk(const LcRun& R, int n_hi, int n_lo, int first, const doub
   hipError_t e = hipFuncSetAttribute((const void*)lc_walk_kernel<d>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lc_walk_kernel<d>, dim3(R.S), dim3(TR_THREADS), sh, st, R, n_hi, n_lo, first,
+  hipLaunchKernelGGL(lc_walk_kernel<d>, dim3(nslot * R.S), dim3(TR_THREADS), sh, st, R, n_hi, n_lo, first,
                      psiT, lamT, psi_st, mu_st, sgi, sga, pgi, pga, Ms, Mp);
   return hipGetLastError();
 }
 
 struct LcLayout {
   TrLayout F;              // the forward's layout (its tables are reused)
-  size_t psiT, psi_st, mu_st, sgi, sga, pgi, pga, ms, mp, z, zp, deps, dops, total;
-  int chunk;
+  size_t psiT, psi_st, mu_st, psi_c, mu_c, sgi, sga, pgi, pga, ms, mp, z, zp, deps, dops, total;
+  int chunk;               // steps of a launch of the walk
+  int nslot, len;          // walked side by side in slots of len steps (len 0: one walk)
 };
 
 LcLayout lc_layout(const scp_system* sys, int order, int S) {
@@ -2061,6 +2188,15 @@ LcLayout lc_layout(const scp_system* sys, int order, int S) {
   const size_t d = sys->d, dd = d * d, M = sys->n_modes, E = std::max<size_t>(1, sys->coup.size());
   const size_t N = sys->n_steps, r = L.F.r, D = sys->D;
   L.chunk = (int)std::min<size_t>(N, LC_CHUNK);
+  L.nslot = 1;
+  // slots where the gates are unitary, the sweep can use the split form of the
+  // fused operations, and one walk would fill less than half of the chip
+  if (order != SCP_TROTTER_Q4J && !L.F.phase && L.F.mode2 != 0 && S < 128 && N > 1) {
+    const int want = (256 + S - 1) / S;
+    L.len = (int)std::min<size_t>(64, (N + want - 1) / want);
+    L.nslot = (int)std::min<size_t>(want, (N + L.len - 1) / L.len);
+    L.chunk = (int)std::min<size_t>(N, (size_t)L.nslot * L.len);
+  }
   size_t o = L.F.total;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -2068,14 +2204,16 @@ LcLayout lc_layout(const scp_system* sys, int order, int S) {
     return at;
   };
   L.psiT = take((size_t)S * D * sizeof(double2));
-  L.psi_st = take((size_t)S * D * sizeof(double2));
-  L.mu_st = take((size_t)S * D * sizeof(double2));
+  L.psi_st = take((size_t)L.nslot * S * D * sizeof(double2));
+  L.mu_st = take((size_t)L.nslot * S * D * sizeof(double2));
+  L.psi_c = take((size_t)(L.len ? S : 0) * D * sizeof(double2));
+  L.mu_c = take((size_t)(L.len ? S : 0) * D * sizeof(double2));
   L.sgi = take(N * r * M * dd * sizeof(double2));
   L.sga = take(N * r * M * dd * sizeof(double2));
   L.pgi = take(r * E * dd * dd * sizeof(double2));
   L.pga = take(r * E * dd * dd * sizeof(double2));
   L.ms = take((size_t)L.chunk * r * M * (L.F.H == 2 ? 2 : 1) * S * dd * sizeof(double2));
-  L.mp = take((size_t)S * r * E * dd * dd * sizeof(double2));
+  L.mp = take((size_t)L.nslot * S * r * E * dd * dd * sizeof(double2));
   L.z = take(N * r * M * 5 * sizeof(double2));
   L.zp = take(r * E * 7 * sizeof(double2));
   L.deps = take(M * 3 * d * sizeof(double));
@@ -2112,7 +2250,7 @@ static scp_status lc_adjoint(scp_system* sys, int order, int S, void* ws, const 
   char* base = static_cast<char*>(ws);
   // the forward: only its final state is kept (its gate tables are reused)
   const double2* psiT = psi0 ? reinterpret_cast<double2*>(base + Y.psiT) : psiT_in;
-  scp_status s = launch_trotter(sys, order, S, ws, psi0, const_cast<double2*>(psiT), st);
+  scp_status s = tr_launch(sys, order, S, ws, psi0, const_cast<double2*>(psiT), Y.len != 0, st);
   if (s != SCP_OK) return s;
   // operator derivatives of every mode (FP64)
   std::vector<double> hdeps((size_t)M * 3 * d);
@@ -2173,6 +2311,7 @@ static scp_status lc_adjoint(scp_system* sys, int order, int S, void* ws, const 
   R.H = W.H;
   R.D = (int)sys->D;
   R.S = S;
+  R.len = Y.len;
   {
     int sd = 1;
     for (int m = M - 1; m >= 0; --m) {
@@ -2198,10 +2337,33 @@ static scp_status lc_adjoint(scp_system* sys, int order, int S, void* ws, const 
   // the split walk stores each visit of a single-mode gate in its own slot,
   // the in-place walk adds the visits of a step into one
   const int nvis = lc_split_fits(R.D, d) && W.H == 2 ? 2 : 1;
+  const TrRun T = make_run(sys, W);
+  double2* psi_c = reinterpret_cast<double2*>(base + Y.psi_c);
+  double2* mu_c = reinterpret_cast<double2*>(base + Y.mu_c);
+  double2* fga = reinterpret_cast<double2*>(base + W.fg);
+  double2* fsa = reinterpret_cast<double2*>(base + W.fs);
+  if (Y.len) {   // the fused operations, conjugate-transposed for the sweeps
+    auto adjoint = [&](double2* g, size_t count) {
+      const int blocks = (int)std::min<size_t>((count * dd * dd + 255) / 256, 65535);
+      if (count) hipLaunchKernelGGL(lc_adjoint_inplace_kernel, dim3(blocks), dim3(256), 0, st, g, dd, count);
+    };
+    adjoint(fga, (size_t)N * W.r * W.P.ndyn);
+    adjoint(fsa, (size_t)W.r * W.P.nslot);
+    HIPCHK(hipGetLastError());
+  }
   for (int n_hi = N; n_hi > 0; n_hi -= Y.chunk) {
     const int n_lo = std::max(0, n_hi - Y.chunk);
     const int first = n_hi == N ? 1 : 0;
     hipError_t e;
+    if (Y.len) {
+      switch (d) {
+        case 2: e = run_lc_sweep<2>(T, R, n_hi, n_lo, first, psiT, cot, psi_c, mu_c, psi_st, mu_st, fga, fsa, sga, st); break;
+        case 3: e = run_lc_sweep<3>(T, R, n_hi, n_lo, first, psiT, cot, psi_c, mu_c, psi_st, mu_st, fga, fsa, sga, st); break;
+        case 4: e = run_lc_sweep<4>(T, R, n_hi, n_lo, first, psiT, cot, psi_c, mu_c, psi_st, mu_st, fga, fsa, sga, st); break;
+        default: e = run_lc_sweep<5>(T, R, n_hi, n_lo, first, psiT, cot, psi_c, mu_c, psi_st, mu_st, fga, fsa, sga, st); break;
+      }
+      HIPCHK(e);
+    }
     switch (d) {
       case 2: e = run_lc_walk<2>(R, n_hi, n_lo, first, psiT, cot, psi_st, mu_st, sgi, sga, pgi, pga, Ms, Mp, st); break;
       case 3: e = run_lc_walk<3>(R, n_hi, n_lo, first, psiT, cot, psi_st, mu_st, sgi, sga, pgi, pga, Ms, Mp, st); break;
@@ -2220,7 +2382,8 @@ static scp_status lc_adjoint(scp_system* sys, int order, int S, void* ws, const 
     const size_t sh = 4 * (size_t)(2 * dd) * (2 * dd) * sizeof(double2);
     HIPCHK(hipFuncSetAttribute((const void*)lc_pair_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)sh));
-    hipLaunchKernelGGL(lc_pair_kernel, dim3(W.r * E), dim3(256), sh, st, G, S, dops, ddops, Mp, zp);
+    hipLaunchKernelGGL(lc_pair_kernel, dim3(W.r * E), dim3(256), sh, st, G, Y.nslot * S, dops, ddops, Mp,
+                       zp);
     HIPCHK(hipGetLastError());
   }
   std::vector<double2> hz((size_t)N * W.r * M * 5), hzp((size_t)std::max(1, W.r * E) * 7);
