@@ -845,10 +845,224 @@ bool couplings_commute(const scp_system* sys) {
   return true;
 }
 
+// ---------------------------------------------------------------------------
+// Matrix form, d = 4 and 5, where the couplings do not commute (fluxonium
+// chains) and every mode is coupled: a pair operation is a d^2 x d^2 complex
+// matrix times the column's D / d^2 fibres, and runs on the FP64 matrix
+// instruction (16 x 16 x 4).  A wave takes 16 fibres (and, d = 5, one of the
+// two tiles of 16 output rows): it reads each fibre element of its share from
+// LDS once and holds the gate as operands in registers, loaded one operation
+// ahead; the vector form read d^2 amplitudes and up to d^3 gate entries per
+// work item.  d = 4 in place (a wave owns whole fibres), d = 5 from one buffer
+// into the other.
+//
+// The sequence is also shorter: the last operation of a piece's first pass and
+// the first of its second act on the same pair and are one product, and so are
+// a piece's last and the next piece's first (2 k - 2 operations per piece for k
+// coupled pairs, and one at the end).
+//
+// Bound: the matrix instruction (64 cycles for 16 x 16 x 4 at 78.6 TFLOP/s):
+// 1.7 us per operation of a column of 4096 (d = 4), 0.75 us of one of 625
+// (d = 5, 25 rows and fibres padded to 32); around it one barrier and the LDS
+// latency.  6-fluxonium chain (d = 4, 64 columns), Q4: 222 -> 68 us per step
+// (2.8 us per operation); 4-fluxonium chain (d = 5, 16 columns), Q2 forward and
+// LCAM gradient (both sweep): 69 -> 40 us per step.
+// ---------------------------------------------------------------------------
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+struct TmRun {
+  int M, D, ns, nop;       // operations per piece; in all
+  int per_step;            // operations per step (sweep)
+  int si[2 * TR_MAXOPS], sj[2 * TR_MAXOPS];
+  double fT[SCP_MAX_MODES][SCP_MAX_TRUNC];   // frame energy times T, reduced mod 2 pi
+};
+static_assert(sizeof(TmRun) <= 4000, "TmRun is passed by value as a kernel argument");
+
+template <int d>
+struct TmShape {
+  static constexpr int n = d * d, KS = (n + 3) / 4, RT = (n + 15) / 16;
+  static constexpr bool INPLACE = RT == 1;
+  static constexpr int MAXT = d == 4 ? 1024 : 512;
+};
+
+// This lane's gate operands: rows rt 16 + l % 16, columns 4 s + l / 16.
+template <int d>
+__device__ __forceinline__ void tm_load(const double2* __restrict__ G, int rt, double2* A) {
+  using T = TmShape<d>;
+  const int lane = threadIdx.x & 63, row = rt * 16 + (lane & 15);
+#pragma unroll
+  for (int s = 0; s < T::KS; ++s) {
+    const int k = 4 * s + (lane >> 4);
+    const bool ok = row < T::n && k < T::n;
+    const double2 v = G[ok ? row * T::n + k : 0];
+    A[s] = ok ? v : make_double2(0.0, 0.0);
+  }
+}
+
+// out = gate times every fibre of modes (si, sj); in == out where INPLACE.
+template <int d>
+__device__ __forceinline__ void tm_apply(const double2* in, double2* out, int D, int si, int sj,
+                                         const double2* A) {
+  using T = TmShape<d>;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int rt = wave % T::RT, kq = lane >> 4;
+  const int nf = D / T::n;
+  const int sp = si > sj ? si : sj, sq = si > sj ? sj : si, w = sp / (sq * d);
+  const double isq = 1.0 / sq, iw = 1.0 / w;
+  const int pi = tp_at<d>(si), pj = tp_at<d>(sj);   // padded strides (additive, see tp_at)
+  for (int f0 = (wave / T::RT) * 16; f0 < nf; f0 += nw / T::RT * 16) {
+    const int f = f0 + (lane & 15);
+    const int base = tp_at<d>(fibre2<d>(f < nf ? f : nf - 1, sp, sq, w, isq, iw));
+    double2 x[T::KS];
+#pragma unroll
+    for (int s = 0; s < T::KS; ++s) {
+      const int k = 4 * s + kq < T::n ? 4 * s + kq : T::n - 1;   // beyond: the gate entry is zero
+      x[s] = in[base + (k / d) * pi + (k % d) * pj];
+    }
+    v4d cr = {0.0, 0.0, 0.0, 0.0}, ci = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < T::KS; ++s) {
+      cr = __builtin_amdgcn_mfma_f64_16x16x4f64(A[s].x, x[s].x, cr, 0, 0, 0);
+      ci = __builtin_amdgcn_mfma_f64_16x16x4f64(A[s].x, x[s].y, ci, 0, 0, 0);
+      cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-A[s].y, x[s].y, cr, 0, 0, 0);
+      ci = __builtin_amdgcn_mfma_f64_16x16x4f64(A[s].y, x[s].x, ci, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = rt * 16 + 4 * r + kq;   // the accumulator's rows
+      if (row < T::n && f < nf) out[base + (row / d) * pi + (row % d) * pj] = make_double2(cr[r], ci[r]);
+    }
+  }
+}
+
+// Workgroup = one column; gates: [nop][d^4] in the order they act.
+template <int d>
+__global__ void __launch_bounds__(TmShape<d>::MAXT)
+tr_mm_kernel(TmRun R, const double2* __restrict__ psi0, double2* __restrict__ psiT,
+             const double2* __restrict__ gates) {
+  using T = TmShape<d>;
+  extern __shared__ double2 lds[];
+  constexpr int nn = T::n * T::n;
+  const size_t off = (size_t)blockIdx.x * R.D;
+  const int rt = (threadIdx.x >> 6) % T::RT, bufs = tp_at<d>(R.D - 1) + 1;
+  double2 *L = lds, *Lo = T::INPLACE ? lds : lds + bufs;
+  for (int i = threadIdx.x; i < R.D; i += blockDim.x) L[tp_at<d>(i)] = psi0[off + i];
+  double2 A[T::KS], B[T::KS];
+  tm_load<d>(gates, rt, A);
+  __syncthreads();
+  int o = 0;
+  for (int t = 0; t < R.nop; ++t) {
+    tm_load<d>(gates + (size_t)(t + 1 < R.nop ? t + 1 : t) * nn, rt, B);
+    tm_apply<d>(L, Lo, R.D, R.si[o], R.sj[o], A);
+    __syncthreads();
+    double2* x = L;
+    L = Lo;
+    Lo = x;
+#pragma unroll
+    for (int s = 0; s < T::KS; ++s) A[s] = B[s];
+    o = o + 1 == R.ns ? 0 : o + 1;
+  }
+  for (int i = threadIdx.x; i < R.D; i += blockDim.x) {
+    int r = i;
+    double th = 0.0;
+    for (int m = R.M - 1; m >= 0; --m) {
+      th += R.fT[m][r % d];
+      r /= d;
+    }
+    double sn, cs;
+    sincos(wrap_2pi(th), &sn, &cs);
+    const double2 v = L[tp_at<d>(i)];
+    psiT[off + i] = make_double2(v.x * cs - v.y * sn, v.x * sn + v.y * cs);
+  }
+}
+
+// Merged operations: block b = (step r + j) * ns + slot (and one block behind
+// them with ``join``).  Slot 0 is the piece's first operation, with ``join``
+// after the last one of the piece before; slots 1 .. k - 2 the first pass's,
+// k - 1 the two that meet where the passes turn, the rest the second pass's
+// (its last one only without ``join``: with it, the next piece's slot 0 or the
+// block behind has it).  Q1 (H = 1): the k operations of its pass.
+__global__ void __launch_bounds__(256) tr_mm_gate_kernel(int d, int r, int H, int ns, int K, int join,
+                                                         int M, int E, const TrPlan* __restrict__ plan,
+                                                         const double2* __restrict__ sg,
+                                                         const double2* __restrict__ pg,
+                                                         double2* __restrict__ out) {
+  extern __shared__ double2 sh[];
+  const int b = blockIdx.x, q = b / ns, slot = b - q * ns, k = plan->nop[0];
+  const int dd = d * d, n = dd, nn = n * n;
+  double2 *A = sh, *W = sh + nn;
+  for (int e = threadIdx.x; e < nn; e += blockDim.x)
+    A[e] = make_double2((e / n == e % n) ? 1.0 : 0.0, 0.0);
+  __syncthreads();
+  // A <- (operation o of pass h of piece p) A
+  auto mult = [&](int p, int h, int o) {
+    const TrOp& op = plan->op[h][o];
+    const int j = p % r;
+    for (int c = 0; c < op.nc; ++c) {
+      const int ty = op.ctype[c], ix = op.cidx[c], dg = op.cdig[c];
+      const double2* S = sg + ((size_t)p * M + ix) * dd;
+      const double2* P = pg + ((size_t)j * E + ix) * dd * dd;
+      for (int e = threadIdx.x; e < nn; e += blockDim.x) {
+        const int row = e / n, col = e % n, ra = row / d, rb = row % d;
+        double re = 0.0, im = 0.0;
+        if (ty == 1) {
+          for (int x = 0; x < n; ++x) cmac(re, im, P[row * n + x], A[x * n + col]);
+        } else {
+          for (int x = 0; x < d; ++x)
+            cmac(re, im, dg == 0 ? S[ra * d + x] : S[rb * d + x],
+                 dg == 0 ? A[(x * d + rb) * n + col] : A[(ra * d + x) * n + col]);
+        }
+        W[e] = make_double2(re, im);
+      }
+      __syncthreads();
+      double2* t = A;
+      A = W;
+      W = t;
+    }
+  };
+  if (H == 1) {
+    mult(q, 0, slot);
+  } else if (slot == 0) {
+    if (join && q > 0) mult(q - 1, 1, k - 1);
+    if (q < K) mult(q, 0, 0);
+  } else if (slot < k - 1) {
+    mult(q, 0, slot);
+  } else if (slot == k - 1) {
+    mult(q, 0, k - 1);
+    mult(q, 1, 0);
+  } else {
+    mult(q, 1, slot - (k - 1));
+  }
+  for (int e = threadIdx.x; e < nn; e += blockDim.x) out[(size_t)b * nn + e] = A[e];
+}
+
+template <int d>
+int tm_threads(int D) {
+  using T = TmShape<d>;
+  const int tiles = (D / T::n + 15) / 16;
+  return std::min(T::MAXT, 64 * T::RT * tiles);
+}
+template <int d>
+size_t tm_lds(int D) {
+  return (size_t)(tp_at<d>(D - 1) + 1) * sizeof(double2) * (TmShape<d>::INPLACE ? 1 : 2);
+}
+
+template <int d>
+hipError_t run_mm(const TmRun& R, int S, const double2* psi0, double2* psiT, const double2* gates,
+                  hipStream_t st) {
+  const size_t sh = tm_lds<d>(R.D);
+  hipError_t e = hipFuncSetAttribute((const void*)tr_mm_kernel<d>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(tr_mm_kernel<d>, dim3(S), dim3(tm_threads<d>(R.D)), sh, st, R, psi0, psiT, gates);
+  return hipGetLastError();
+}
+
 struct TrLayout {
   size_t eps, ops, par, plan, V, alpha, in_end, pg, sg, fg, fs, gk, ph, total;
   int r, sym, npar, H, nopmax, mode1, mode2;
   bool phase;   // the phase form
+  bool mm;      // the matrix form: fg holds its merged operations
   TrPlan P;
 };
 
@@ -1000,6 +1214,12 @@ TrLayout tr_layout(const scp_system* sys, int order) {
     // are absorbed in registers instead, next to static pair products
     const bool regs = L.mode2 == 0 && E0 > 0 && dg <= 3;
     build_plan(sys, L.H, L.mode2 != 0 || regs, regs, L.P);
+    // the matrix form: every mode in a pair operation and two pairs or more
+    // (with one pair a piece has a single operation).  D <= 5120: two buffers
+    // of a d = 5 column, one padded buffer of a d = 4 column fit the LDS
+    L.mm = (dg == 4 || dg == 5) && L.mode2 != 0 && L.P.nop[0] >= 2;
+    for (int h = 0; h < L.H; ++h)
+      for (int o = 0; o < L.P.nop[h]; ++o) L.mm = L.mm && L.P.op[h][o].kind == 1;
     bool any_single = false;
     for (int h = 0; h < L.H; ++h)
       for (int o = 0; o < L.P.nop[h]; ++o) any_single |= L.P.op[h][o].kind == 0;
@@ -1041,7 +1261,9 @@ TrLayout tr_layout(const scp_system* sys, int order) {
     L.ph = o;
     o = align256(o + (size_t)L.r * sys->D * sizeof(double2));
   } else {
-    o = align256(o + (size_t)sys->n_steps * L.r * L.P.ndyn * d * d * d * d * sizeof(double2));
+    // (matrix form: at most 2 nop - 1 merged operations per piece, and one)
+    const size_t per = L.mm ? (L.H == 2 ? 2 * L.P.nop[0] - 1 : L.P.nop[0]) : L.P.ndyn;
+    o = align256(o + ((size_t)sys->n_steps * L.r * per + (L.mm ? 1 : 0)) * d * d * d * d * sizeof(double2));
     L.fs = o;
     o = align256(o + (size_t)L.r * std::max(1, L.P.nslot) * d * d * d * d * sizeof(double2));
   }
@@ -1153,6 +1375,39 @@ TrRun make_run(const scp_system* sys, const TrLayout& W) {
   return R;
 }
 
+// Matrix form: the operations' sequence; join: a piece's last operation and the
+// next one's first are one (the propagation; the sweep stops between them).
+TmRun make_mm(const scp_system* sys, const TrLayout& W, bool join) {
+  const TrRun T = make_run(sys, W);
+  TmRun R{};
+  const int k = W.P.nop[0];
+  R.M = T.M;
+  R.D = T.D;
+  R.ns = W.H == 1 ? k : (join ? 2 * k - 2 : 2 * k - 1);
+  for (int o = 0; o < R.ns; ++o) {
+    const int h = o < k ? 0 : 1, at = o < k ? o : o - (k - 1);
+    R.si[o] = T.stride[T.opi[h][at]];
+    R.sj[o] = T.stride[T.opj[h][at]];
+  }
+  R.per_step = R.ns * W.r;
+  R.nop = R.per_step * sys->n_steps + (W.H == 2 && join ? 1 : 0);
+  std::memcpy(R.fT, T.fT, sizeof(R.fT));
+  return R;
+}
+
+// The merged operations of that sequence into the workspace.
+hipError_t mm_gates(const scp_system* sys, const TrLayout& W, char* base, bool join, hipStream_t st) {
+  const int d = sys->d, n = d * d;
+  const TmRun R = make_mm(sys, W, join);
+  hipLaunchKernelGGL(tr_mm_gate_kernel, dim3((unsigned)R.nop), dim3(256), 2 * n * n * sizeof(double2), st,
+                     d, W.r, W.H, R.ns, sys->n_steps * W.r, W.H == 2 && join ? 1 : 0, sys->n_modes,
+                     (int)sys->coup.size(), reinterpret_cast<const TrPlan*>(base + W.plan),
+                     reinterpret_cast<const double2*>(base + W.sg),
+                     reinterpret_cast<const double2*>(base + W.pg),
+                     reinterpret_cast<double2*>(base + W.fg));
+  return hipGetLastError();
+}
+
 }  // namespace
 
 // psi0 == nullptr: the gate tables only (single-mode and pair gates, what
@@ -1258,6 +1513,13 @@ static scp_status tr_launch(scp_system* sys, int order, int S, void* ws, const d
   }
   double2* fg = reinterpret_cast<double2*>(base + W.fg);
   double2* fs = reinterpret_cast<double2*>(base + W.fs);
+  if (W.mm) {
+    if (psi0 == nullptr) return SCP_OK;   // the sweep forms its own (mm_gates)
+    TmRun R = make_mm(sys, W, true);
+    HIPCHK(mm_gates(sys, W, base, true, st));
+    HIPCHK(d == 4 ? run_mm<4>(R, S, psi0, psiT, fg, st) : run_mm<5>(R, S, psi0, psiT, fg, st));
+    return SCP_OK;
+  }
   {
     // every step only where some pair operation is re-formed per step; else
     // step 0, which forms the static operations
@@ -1595,6 +1857,67 @@ lc_sweep_kernel(TrRun R, LcRun R1, int n_top, int n_base, int first,
       }
   }
   for (int i = threadIdx.x; i < R.D; i += blockDim.x) carry[i] = L[i];
+}
+
+// The same in the matrix form (gates: the unjoined operations of tr_mm_kernel,
+// conjugate-transposed).
+template <int d>
+__global__ void __launch_bounds__(TmShape<d>::MAXT)
+lc_sweep_mm_kernel(TmRun R, LcRun R1, int n_top, int n_base, int first,
+                   const double2* __restrict__ psiT, const double2* __restrict__ lamT,
+                   double2* __restrict__ psi_c, double2* __restrict__ mu_c,
+                   double2* __restrict__ psi_st, double2* __restrict__ mu_st,
+                   const double2* __restrict__ gates) {
+  using T = TmShape<d>;
+  extern __shared__ double2 lds[];
+  constexpr int nn = T::n * T::n;
+  const int S = R1.S, col = blockIdx.x % S;
+  const bool mu = (int)blockIdx.x >= S;
+  const double2* src = (mu ? lamT : psiT) + (size_t)col * R.D;
+  double2* carry = (mu ? mu_c : psi_c) + (size_t)col * R.D;
+  double2* top = (mu ? mu_st : psi_st) + (size_t)col * R.D;
+  const int rt = (threadIdx.x >> 6) % T::RT, bufs = tp_at<d>(R.D - 1) + 1;
+  double2 *L = lds, *Lo = T::INPLACE ? lds : lds + bufs;
+  for (int i = threadIdx.x; i < R.D; i += blockDim.x)
+    L[tp_at<d>(i)] = first ? unrotate(R1, d, i, src[i]) : carry[i];
+  double2 A[T::KS], B[T::KS];
+  int t = n_top * R.per_step - 1;
+  tm_load<d>(gates + (size_t)t * nn, rt, A);
+  __syncthreads();
+  for (int n = n_top - 1; n >= n_base; --n) {
+    const int up = n_top - 1 - n;
+    if (up % R1.len == 0) {
+      double2* dst = top + (size_t)(up / R1.len) * S * R.D;
+      for (int i = threadIdx.x; i < R.D; i += blockDim.x) dst[i] = L[tp_at<d>(i)];
+      __syncthreads();
+    }
+    int o = R.ns - 1;
+    for (int c = 0; c < R.per_step; ++c, --t) {
+      tm_load<d>(gates + (size_t)(t > 0 ? t - 1 : 0) * nn, rt, B);
+      tm_apply<d>(L, Lo, R.D, R.si[o], R.sj[o], A);
+      __syncthreads();
+      double2* x = L;
+      L = Lo;
+      Lo = x;
+#pragma unroll
+      for (int s = 0; s < T::KS; ++s) A[s] = B[s];
+      o = o == 0 ? R.ns - 1 : o - 1;
+    }
+  }
+  for (int i = threadIdx.x; i < R.D; i += blockDim.x) carry[i] = L[tp_at<d>(i)];
+}
+
+template <int d>
+hipError_t run_lc_sweep_mm(const TmRun& T, const LcRun& R, int n_top, int n_base, int first,
+                           const double2* psiT, const double2* lamT, double2* psi_c, double2* mu_c,
+                           double2* psi_st, double2* mu_st, const double2* gates, hipStream_t st) {
+  const size_t sh = tm_lds<d>(T.D);
+  hipError_t e = hipFuncSetAttribute((const void*)lc_sweep_mm_kernel<d>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(lc_sweep_mm_kernel<d>, dim3(2 * R.S), dim3(tm_threads<d>(T.D)), sh, st, T, R, n_top,
+                     n_base, first, psiT, lamT, psi_c, mu_c, psi_st, mu_st, gates);
+  return hipGetLastError();
 }
 
 // n x n gates conjugate-transposed where they are
@@ -2338,6 +2661,8 @@ static scp_status lc_adjoint(scp_system* sys, int order, int S, void* ws, const 
   // the in-place walk adds the visits of a step into one
   const int nvis = lc_split_fits(R.D, d) && W.H == 2 ? 2 : 1;
   const TrRun T = make_run(sys, W);
+  TmRun Tm{};
+  if (W.mm) Tm = make_mm(sys, W, false);
   double2* psi_c = reinterpret_cast<double2*>(base + Y.psi_c);
   double2* mu_c = reinterpret_cast<double2*>(base + Y.mu_c);
   double2* fga = reinterpret_cast<double2*>(base + W.fg);
@@ -2347,15 +2672,23 @@ static scp_status lc_adjoint(scp_system* sys, int order, int S, void* ws, const 
       const int blocks = (int)std::min<size_t>((count * dd * dd + 255) / 256, 65535);
       if (count) hipLaunchKernelGGL(lc_adjoint_inplace_kernel, dim3(blocks), dim3(256), 0, st, g, dd, count);
     };
-    adjoint(fga, (size_t)N * W.r * W.P.ndyn);
-    adjoint(fsa, (size_t)W.r * W.P.nslot);
+    if (W.mm) {
+      HIPCHK(mm_gates(sys, W, base, false, st));
+      adjoint(fga, (size_t)Tm.nop);
+    } else {
+      adjoint(fga, (size_t)N * W.r * W.P.ndyn);
+      adjoint(fsa, (size_t)W.r * W.P.nslot);
+    }
     HIPCHK(hipGetLastError());
   }
   for (int n_hi = N; n_hi > 0; n_hi -= Y.chunk) {
     const int n_lo = std::max(0, n_hi - Y.chunk);
     const int first = n_hi == N ? 1 : 0;
     hipError_t e;
-    if (Y.len) {
+    if (Y.len && W.mm) {
+      HIPCHK(d == 4 ? run_lc_sweep_mm<4>(Tm, R, n_hi, n_lo, first, psiT, cot, psi_c, mu_c, psi_st, mu_st, fga, st)
+                    : run_lc_sweep_mm<5>(Tm, R, n_hi, n_lo, first, psiT, cot, psi_c, mu_c, psi_st, mu_st, fga, st));
+    } else if (Y.len) {
       switch (d) {
         case 2: e = run_lc_sweep<2>(T, R, n_hi, n_lo, first, psiT, cot, psi_c, mu_c, psi_st, mu_st, fga, fsa, sga, st); break;
         case 3: e = run_lc_sweep<3>(T, R, n_hi, n_lo, first, psiT, cot, psi_c, mu_c, psi_st, mu_st, fga, fsa, sga, st); break;
