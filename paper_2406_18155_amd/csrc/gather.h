@@ -66,7 +66,7 @@ struct GArgs {
   // first side << 20 | last of its own-slot group << 21)
   int me_beg[GA_MAXM + 1];
   int me[GA_MAXME];
-  // real form (gather_real.h): frame phases [2N+1][L], static rows, the coupled
+  // real form (gather_real.hip, open_real.hip): frame phases [2N+1][L], static rows, the coupled
   // neighbours (bit p: modes p, p + 1; bit N - 1: 0, N - 1), the driven modes
   // and their coefficient columns
   const float2* ph;
@@ -87,10 +87,11 @@ struct GAdj {
   const float2* cot;     // [S][L] cotangent of the final columns
   float2* seg;           // stage inputs, [ce][4][L] per column (open) or per slot (closed)
   const double* dctab;   // [3N][npulse] dc/dpar
-  double* part;          // open: [S][nacc] gradient partial sums
+  double* part;          // open, complex rows: [S][nacc] gradient partial sums
   float4* lam;           // costate (hi, lo): open [S][L] between reverse walks,
                          // closed [S][nck][L] at the end of every segment
-  double* gs;            // closed: [S][N][gw] sums of every step (see g_fold_kernel)
+  double* gs;            // closed, and the open real form: [S][N][gw] sums of
+                         // every step (see g_fold_kernel)
   int ce, nck, npulse, nacc, gw;
 };
 
@@ -193,6 +194,11 @@ hipError_t g_real_sweep(int d, int N, const GItem* items, const GArgs* dargs, co
                         int g_hi, int g_lo, hipStream_t s);
 hipError_t g_real_segments(int d, int N, const GItem* items, const GArgs* dargs, const GAdj* dadj,
                            int n, int gseg, hipStream_t s);
+// Open systems' real form (open_real.hip): forward (dadj != nullptr: with
+// checkpoints) and the whole reverse walk of S columns.
+bool l_real_supported(int d, int N);
+hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s);
+hipError_t l_real_adjoint(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s);
 hipError_t g_real_phases(int d, int N, int nsteps, double h, const double f[][8], float2* ph,
                          hipStream_t s);
 

@@ -1532,13 +1532,14 @@ hipError_t g_launch1(const GArgs* dargs, const GAdj* dadj, int S, int ntab, int 
   return hipGetLastError();
 }
 
-// Form of a launch: 0 general, 1 parity, 2 real (closed systems).
+// Form of a launch: 0 general, 1 parity, 2 real.
 int g_form(const GArgs& A) { return A.real ? 2 : (A.par ? 1 : 0); }
 
 template <int d, int N, bool OPEN>
 hipError_t g_launch(int form, const GArgs* dargs, const GAdj* dadj, int S, int ntab, int n_lo,
                     int n_hi, const float4* st_in, float4* st_out, hipStream_t s) {
   const bool par = form != 0;
+  if (OPEN && form == 2) return l_real_forward(d, N, dargs, dadj, S, s);
   if (!OPEN && form == 2)
     return g_real_forward(d, N, dadj != nullptr, nullptr, dargs, dadj, S, n_lo, n_hi, st_in, st_out, s);
   if (dadj != nullptr)
@@ -1591,6 +1592,7 @@ template <int d, int N, bool OPEN>
 hipError_t g_adj_launch(int form, const GArgs* dargs, const GAdj* dadj, int S, int ntabg, int nacc,
                         int gseg, int nseg, hipStream_t s) {
   using Sh = GShape<d, N, OPEN>;
+  if (OPEN && form == 2) return l_real_adjoint(d, N, dargs, dadj, S, s);
   if (!OPEN && form == 2) return g_real_segments(d, N, nullptr, dargs, dadj, nseg * S, gseg, s);
   const size_t sh = g_adj_lds_bytes<d, N, OPEN>(ntabg, nacc);
   if (sh > 163840) return hipErrorInvalidValue;
@@ -1761,7 +1763,7 @@ static scp_status g_args(const scp_system* sys, bool open, const double* gamma1,
   if ((3 * L + ((3 * L) & 1) + 2 * (size_t)A.ntab) * sizeof(float2) > 163840)
     return fail(SCP_EINVAL, "gather engine: column and stage tables exceed the LDS");
   A.ntabg = A.ntab;
-  if (!open && sys->d_rt != nullptr) {   // the real form (see build_gather_rows)
+  if (sys->d_rt != nullptr && (!open || l_real_supported(d, N))) {   // the real form (see build_gather_rows)
     A.real = P.real_frame != 0 ? 1 : 0;
     A.rt = sys->d_rt;
     A.rc = sys->d_rc;
@@ -1781,7 +1783,8 @@ static scp_status g_args(const scp_system* sys, bool open, const double* gamma1,
 // Empty where the form does not apply: an operator with even entries or a
 // complex term, a coupled pair that is no neighbour pair of the ring of modes
 // or has more than two couplings, two drive operators on a mode, or a shape
-// without a closed-system stepper.  Behind them the gradient's rows (RShape).
+// without a real stepper.  Behind them the gradient's rows (RShape), then the
+// rows of each pair's single couplings without their strength (LShape).
 // A drive operator is divided by its largest entry and c(t) multiplied by it in
 // FP64 (scale): a static coefficient repeats its rounding at every stage, which
 // for the resonant entry turns into an error of the rotation angle, while c(t)
@@ -1791,7 +1794,8 @@ std::vector<float> build_gather_rows(const scp_system* sys, double* scale) {
   std::vector<float> rt;
   const Plan& P = sys->plan;
   const int d = sys->d, N = sys->n_modes;
-  if (!P.parity || !sys->real_ok || !g_supported(d, N, false) || N < 3) return rt;
+  if (!P.parity || !sys->real_ok || N < 3 || !(g_supported(d, N, false) || l_real_supported(d, N)))
+    return rt;
   GArgs A;
   if (g_args(sys, false, nullptr, nullptr, A) != SCP_OK) {
     set_error("");
@@ -1861,15 +1865,37 @@ std::vector<float> build_gather_rows(const scp_system* sys, double* scale) {
       for (int th = 0; th < 3; ++th)
         rt[off_g + (size_t)N * 2 * d * gr + ((size_t)m * d + a) * 4 + th] = (float)M.deps[th][a];
   }
+  const size_t off_c = rt.size();
+  rt.resize(off_c + (size_t)N * 2 * d * d * pr, 0.f);
+  std::vector<int> seen(N, 0);
+  for (const Coupling& c : sys->coup) {
+    const int i = std::min(c.i, c.j), j = std::max(c.i, c.j), at = j == i + 1 ? i : N - 1;
+    const cplx* oi = sys->modes[i].ops[c.i == i ? c.op_i : c.op_j];
+    const cplx* oj = sys->modes[j].ops[c.i == i ? c.op_j : c.op_i];
+    float* rows = rt.data() + off_c + (size_t)(at * 2 + seen[at]++) * d * d * pr;
+    for (int a = 0; a < d; ++a)
+      for (int b = 0; b < d; ++b)
+        for (int x = 0; x < n; ++x)
+          for (int z = 0; z < n; ++z) {
+            const int la = nb_level(d, 1, x, a), lb = nb_level(d, 1, z, b);
+            if (la >= 0 && lb >= 0)
+              rows[(size_t)(a * d + b) * pr + x * n + z] = (float)(oi[a * d + la] * oj[b * d + lb]).real();
+          }
+  }
   return rt;
 }
 
-// Frame phases of the real form into the workspace.
-static scp_status g_phases(const scp_system* sys, float2* ph, hipStream_t st) {
+// Frame phases of the real form into the workspace (open: of the matrix
+// elements, A's modes before B's).
+static scp_status g_phases(const scp_system* sys, bool open, float2* ph, hipStream_t st) {
   double f[GA_MAXM][8] = {{0}};
-  for (int m = 0; m < sys->n_modes; ++m)
-    for (int a = 0; a < sys->d; ++a) f[m][a] = sys->modes[m].frame[a];
-  HIPCHK(g_real_phases(sys->d, sys->n_modes, sys->n_steps, sys->h, f, ph, st));
+  const int N = sys->n_modes;
+  for (int m = 0; m < N; ++m)
+    for (int a = 0; a < sys->d; ++a) {
+      f[m][a] = sys->modes[m].frame[a];
+      if (open) f[N + m][a] = -sys->modes[m].frame[a];
+    }
+  HIPCHK(g_real_phases(sys->d, open ? 2 * N : N, sys->n_steps, sys->h, f, ph, st));
   return SCP_OK;
 }
 
@@ -1920,6 +1946,26 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
     A.cp_sj[e] = tj;
     A.cp_g[e] = (float)sys->coup[e].g;
   }
+  if (A.rt != nullptr) {
+    // operator index on a mode: 0 for n, 1 for phi
+    for (int q = 0; q < A.ndm; ++q) {
+      const int m = A.dm_mode[q];
+      A.rd_u[m] = P.slot_op[A.dm_slot[q][0]];
+      for (int x = 0; x < A.nds; ++x)
+        if (A.ds_mode[x] == m) A.rd_k[m] = x;
+    }
+    for (int e = 0; e < P.ncoup; ++e) {
+      const Coupling& c = sys->coup[e];
+      const int i = std::min(c.i, c.j), j = std::max(c.i, c.j), p = j == i + 1 ? i : N - 1;
+      const int ui = c.i == i ? c.op_i : c.op_j, uj = c.i == i ? c.op_j : c.op_i;
+      const int q = A.rp_n[p]++;
+      const float sg = sys->slot_imag[P.coup_slot_i[e]] ? -1.f : 1.f;
+      A.rp_u[p][q] = ui | (uj << 1);
+      A.rp_c[p][q] = e;
+      A.rp_s[p][q] = sg;
+      A.rp_g[p][q] = sg * (float)c.g;
+    }
+  }
   A.off_s = A.ntab;
   if (open) {
     A.grad = 1;
@@ -1955,26 +2001,6 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
       }
     }
     A.me_beg[N] = k;
-    if (sys->d_rt != nullptr) {
-      // operator index on a mode: 0 for n, 1 for phi
-      for (int q = 0; q < A.ndm; ++q) {
-        const int m = A.dm_mode[q];
-        A.rd_u[m] = P.slot_op[A.dm_slot[q][0]];
-        for (int x = 0; x < A.nds; ++x)
-          if (A.ds_mode[x] == m) A.rd_k[m] = x;
-      }
-      for (int e = 0; e < P.ncoup; ++e) {
-        const Coupling& c = sys->coup[e];
-        const int i = std::min(c.i, c.j), j = std::max(c.i, c.j), p = j == i + 1 ? i : N - 1;
-        const int ui = c.i == i ? c.op_i : c.op_j, uj = c.i == i ? c.op_j : c.op_i;
-        const int q = A.rp_n[p]++;
-        const float sg = sys->slot_imag[P.coup_slot_i[e]] ? -1.f : 1.f;
-        A.rp_u[p][q] = ui | (uj << 1);
-        A.rp_c[p][q] = e;
-        A.rp_s[p][q] = sg;
-        A.rp_g[p][q] = sg * (float)c.g;
-      }
-    }
     A.off_m = A.off_s + A.nsl * d * A.srow;
     A.off_d = A.off_m + 3 * N * d * A.mrow;
     A.off_u = A.off_m;
@@ -1987,21 +2013,19 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
 
 // Bytes of the real form's frame phases (0 where it does not apply; the same
 // for either frame setting of a system that allows it).
-static size_t g_ph_bytes(const scp_system* sys) {
-  return sys->d_rt == nullptr
-             ? 0
-             : align256((2 * (size_t)sys->n_steps + 1) * (size_t)sys->D * sizeof(float2));
+static size_t g_ph_bytes(const scp_system* sys, bool open) {
+  if (sys->d_rt == nullptr || (open && !l_real_supported(sys->d, sys->n_modes))) return 0;
+  const size_t L = (size_t)sys->D * (open ? sys->D : 1);
+  return align256((2 * (size_t)sys->n_steps + 1) * L * sizeof(float2));
 }
 
 // Workspace: [GArgs][stage tables [3N][ntab], or the real form's frame phases
-// [2N+1][L]][open: jump bands [2N+1][N][d*d]].
+// [2N+1][L]; with the tables of an open system its jump bands [2N+1][N][d*d]].
 static size_t g_ws_bytes(const scp_system* sys, bool open, int ntab) {
   const size_t dd = (size_t)sys->d * sys->d;
   size_t t = align256(3 * (size_t)sys->n_steps * ntab * sizeof(float2));
-  if (!open) t = std::max(t, g_ph_bytes(sys));
-  size_t b = align256(sizeof(GArgs)) + t;
-  if (open) b += align256((2 * (size_t)sys->n_steps + 1) * sys->n_modes * dd * sizeof(float2));
-  return b;
+  if (open) t += align256((2 * (size_t)sys->n_steps + 1) * sys->n_modes * dd * sizeof(float2));
+  return align256(sizeof(GArgs)) + std::max(t, g_ph_bytes(sys, open));
 }
 
 static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const double* gammaphi,
@@ -2024,7 +2048,7 @@ static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const 
   A.xT = xT;
   A.S = S;
   const int N = sys->n_modes, d = sys->d;
-  if (A.has_jump) {
+  if (A.has_jump && !A.real) {
     JtabStatic js;
     std::memset(&js, 0, sizeof(js));
     js.d = d;
@@ -2040,7 +2064,7 @@ static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const 
   hipLaunchKernelGGL(store_args_kernel, dim3(1), dim3(64), 0, st, A, dargs);
   HIPCHK(hipGetLastError());
   if (A.real) {
-    SCP_TRY(g_phases(sys, gtab, st));
+    SCP_TRY(g_phases(sys, open, gtab, st));
   } else {
     hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
     HIPCHK(hipGetLastError());
@@ -2075,12 +2099,29 @@ scp_status launch_lindblad(scp_system* sys, const double* gamma1, const double* 
   return g_run(sys, true, gamma1, gammaphi, S, ws, ws_bytes, rho0, rhoT, st);
 }
 
-// Open-system gradient.  Workspace: [GArgs][GAdj][stage tables [3N][ntabg]]
-// [unit bands [2N+1][N][d*d]][checkpoints [S][nck][L] float4]
-// [stage inputs [S][ce][4][L]][partial sums [S][nacc] double][costate [S][L] float4].
+// The gradient from the steps' sums, copied to the host (synchronises st).
+static scp_status g_fold(scp_system* sys, int S, const GArgs* dargs, const GAdj* dadj, int nblk,
+                         int nacc, double* part, double* dgrad, double* grad, hipStream_t st) {
+  hipLaunchKernelGGL(g_fold_kernel, dim3(S * nblk), dim3(256), 0, st, dargs, dadj, nblk, part);
+  HIPCHK(hipGetLastError());
+  hipLaunchKernelGGL(g_fold_sum_kernel, dim3((nacc + 63) / 64), dim3(64), 0, st, part, S, nblk, nacc,
+                     dgrad);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipMemcpyAsync(grad, dgrad, nacc * sizeof(double), hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  return SCP_OK;
+}
+
+// Open-system gradient.  Workspace: [GArgs][GAdj][stage tables [3N][ntabg]
+// and unit bands [2N+1][N][d*d], or the real form's frame phases [2N+1][L]]
+// [checkpoints [S][nck][L] float4][stage inputs [S][ce][4][L]][costate [S][L]
+// float4][partial sums [S][nacc] double, or the real form's sums of the steps
+// [S][N][gw] double, their blocks [S][nblk][nacc] and the gradient [nacc]].
+// The size is the same for either frame setting of a system.
 struct LbAdjLayout {
   size_t args, adj, gtab, jtab, ck, seg, part, lam, total;
-  int ce, nck, nacc, ntabg;
+  size_t gs, blk, grad;   // real form
+  int ce, nck, nacc, ntabg, gw, nblk;
 };
 
 static scp_status lb_adj_layout(const scp_system* sys, int S, LbAdjLayout& w, GArgs* Aout) {
@@ -2101,17 +2142,28 @@ static scp_status lb_adj_layout(const scp_system* sys, int S, LbAdjLayout& w, GA
   w.adj = off;
   off += align256(sizeof(GAdj));
   w.gtab = off;
-  off += align256(3 * (size_t)N * A.ntabg * sizeof(float2));
-  w.jtab = off;
-  off += align256((2 * (size_t)N + 1) * sys->n_modes * dd * sizeof(float2));
+  w.jtab = off + align256(3 * (size_t)N * A.ntabg * sizeof(float2));
+  const size_t tabs = w.jtab + align256((2 * (size_t)N + 1) * sys->n_modes * dd * sizeof(float2));
+  off = std::max(tabs, off + g_ph_bytes(sys, true));
   w.ck = off;
   off += align256((size_t)S * w.nck * L * sizeof(float4));
   w.seg = off;
   off += align256((size_t)S * w.ce * 4 * L * sizeof(float2));
-  w.part = off;
-  off += align256((size_t)S * w.nacc * sizeof(double));
   w.lam = off;
   off += align256((size_t)S * L * sizeof(float4));
+  w.part = w.gs = off;
+  off += align256((size_t)S * w.nacc * sizeof(double));
+  w.gw = 4 * A.nds + P.ncoup + 2 * sys->n_modes;
+  w.nblk = (N + GF_STEPS - 1) / GF_STEPS;
+  w.blk = w.grad = 0;
+  if (A.rt != nullptr) {
+    size_t q = w.gs + align256((size_t)S * N * w.gw * sizeof(double));
+    w.blk = q;
+    q += align256((size_t)S * w.nblk * w.nacc * sizeof(double));
+    w.grad = q;
+    q += align256((size_t)w.nacc * sizeof(double));
+    off = std::max(off, q);
+  }
   w.total = off;
   if (g_adj_lds(sys->d, sys->n_modes, true, A.ntabg, w.nacc) > 163840)
     return fail(SCP_EINVAL, "open-system gradient: column and tables exceed the LDS");
@@ -2147,6 +2199,7 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
   A.ctab = sys->d_ctab;
   A.jtab = jtab;
   A.gtab = gtab;
+  A.ph = gtab;   // real form
   A.x0 = rho0;
   A.xT = nullptr;
   A.S = S;
@@ -2157,12 +2210,14 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
   B.seg = reinterpret_cast<float2*>(base + w.seg);
   B.dctab = sys->d_dctab64;
   B.part = reinterpret_cast<double*>(base + w.part);
+  B.gs = reinterpret_cast<double*>(base + w.gs);
+  B.gw = w.gw;
   B.lam = reinterpret_cast<float4*>(base + w.lam);
   B.ce = w.ce;
   B.nck = w.nck;
   B.npulse = sys->plan.npulse;
   B.nacc = w.nacc;
-  {
+  if (!A.real) {
     JtabStatic js;
     std::memset(&js, 0, sizeof(js));
     js.d = d;
@@ -2178,14 +2233,25 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
   HIPCHK(hipGetLastError());
   hipLaunchKernelGGL(store_adj_kernel, dim3(1), dim3(64), 0, st, B, dadj);
   HIPCHK(hipGetLastError());
-  hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
-  HIPCHK(hipGetLastError());
+  if (A.real) {
+    SCP_TRY(g_phases(sys, true, gtab, st));
+  } else {
+    hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
+    HIPCHK(hipGetLastError());
+  }
   hipEvent_t t0 = timing_start(sys, st);
   HIPCHK(g_dispatch(d, N, true, g_form(A), dargs, dadj, S, A.ntab, 0, sys->n_steps, nullptr, nullptr, st));
   timing_stop(sys, t0, 0, st);
   t0 = timing_start(sys, st);
   HIPCHK(g_adj_dispatch(d, N, true, g_form(A), dargs, dadj, S, A.ntabg, w.nacc, 0, 1, st));
   timing_stop(sys, t0, 2, st);
+  if (A.real) {
+    SCP_TRY(g_fold(sys, S, dargs, dadj, w.nblk, w.nacc, reinterpret_cast<double*>(base + w.blk),
+                   reinterpret_cast<double*>(base + w.grad), grad, st));
+    for (int k = 0; k < w.nacc; ++k)
+      if (!std::isfinite(grad[k])) return fail(SCP_ENONFINITE, "non-finite gradient");
+    return SCP_OK;
+  }
   std::vector<double> part((size_t)S * w.nacc);
   HIPCHK(hipMemcpyAsync(part.data(), base + w.part, part.size() * sizeof(double),
                         hipMemcpyDeviceToHost, st));
@@ -2284,7 +2350,7 @@ static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad
   off += align256(sizeof(GAdj));
   w.gtab = off;
   w.ph = off;
-  off += std::max(align256(3 * (size_t)N * A.ntabg * sizeof(float2)), g_ph_bytes(sys));
+  off += std::max(align256(3 * (size_t)N * A.ntabg * sizeof(float2)), g_ph_bytes(sys, false));
   w.ck = off;
   off += align256((size_t)S * w.nck * L * sizeof(float4));
   w.seg = w.gs = w.part = w.grad = w.lam = off;
@@ -2357,7 +2423,7 @@ static scp_status gc_prepare(scp_system* sys, int S, int ce, bool with_grad, cha
   hipLaunchKernelGGL(store_adj_kernel, dim3(1), dim3(64), 0, st, B, dadj);
   HIPCHK(hipGetLastError());
   if (tables) {
-    if (A.real) return g_phases(sys, reinterpret_cast<float2*>(base + w.ph), st);
+    if (A.real) return g_phases(sys, false, reinterpret_cast<float2*>(base + w.ph), st);
     hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, sys->d,
                        sys->n_modes, gtab);
     HIPCHK(hipGetLastError());
@@ -2379,20 +2445,11 @@ scp_status launch_gather_ckpt_forward(scp_system* sys, int S, int ce, void* ws, 
   return SCP_OK;
 }
 
-// The gradient from the steps' sums, copied to the host (synchronises st).
 static scp_status gc_fold(scp_system* sys, int S, char* base, const GcLayout& w, double* grad,
                           hipStream_t st) {
-  hipLaunchKernelGGL(g_fold_kernel, dim3(S * w.nblk), dim3(256), 0, st,
-                     reinterpret_cast<GArgs*>(base + w.args), reinterpret_cast<GAdj*>(base + w.adj),
-                     w.nblk, reinterpret_cast<double*>(base + w.part));
-  HIPCHK(hipGetLastError());
-  hipLaunchKernelGGL(g_fold_sum_kernel, dim3((w.nacc + 63) / 64), dim3(64), 0, st,
-                     reinterpret_cast<double*>(base + w.part), S, w.nblk, w.nacc,
-                     reinterpret_cast<double*>(base + w.grad));
-  HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(grad, base + w.grad, w.nacc * sizeof(double), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  return SCP_OK;
+  return g_fold(sys, S, reinterpret_cast<GArgs*>(base + w.args), reinterpret_cast<GAdj*>(base + w.adj),
+                w.nblk, w.nacc, reinterpret_cast<double*>(base + w.part),
+                reinterpret_cast<double*>(base + w.grad), grad, st);
 }
 
 // The reverse walk from the checkpoints (and stage tables) that
