@@ -198,6 +198,9 @@ hipError_t g_real_segments(int d, int N, const GItem* items, const GArgs* dargs,
 // checkpoints) and the whole reverse walk of S columns.
 bool l_real_supported(int d, int N);
 hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s);
+// Closed d = 3, N = 8 (D = 6561, above the gather engine's shapes): forward.
+bool l_column_supported(int d, int N);
+hipError_t l_real_column(int d, int N, const GArgs* dargs, int S, hipStream_t s);
 hipError_t l_real_adjoint(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s);
 hipError_t g_real_phases(int d, int N, int nsteps, double h, const double f[][8], float2* ph,
                          hipStream_t s);

@@ -1794,7 +1794,8 @@ std::vector<float> build_gather_rows(const scp_system* sys, double* scale) {
   std::vector<float> rt;
   const Plan& P = sys->plan;
   const int d = sys->d, N = sys->n_modes;
-  if (!P.parity || !sys->real_ok || N < 3 || !(g_supported(d, N, false) || l_real_supported(d, N)))
+  if (!P.parity || !sys->real_ok || N < 3 ||
+      !(g_supported(d, N, false) || l_real_supported(d, N) || l_column_supported(d, N)))
     return rt;
   GArgs A;
   if (g_args(sys, false, nullptr, nullptr, A) != SCP_OK) {
@@ -2099,6 +2100,35 @@ scp_status launch_lindblad(scp_system* sys, const double* gamma1, const double* 
   return g_run(sys, true, gamma1, gammaphi, S, ws, ws_bytes, rho0, rhoT, st);
 }
 
+// --- closed systems above the gather engine's shapes: forward -----------------
+// Workspace: [GArgs][frame phases [2N+1][D]].
+bool real_column_supported(const scp_system* sys) {
+  return sys->d_rt != nullptr && l_column_supported(sys->d, sys->n_modes);
+}
+
+size_t real_column_bytes(const scp_system* sys) {
+  return align256(sizeof(GArgs)) + g_ph_bytes(sys, false);
+}
+
+scp_status launch_real_column(scp_system* sys, int S, void* ws, const float2* x0, float2* xT,
+                              hipStream_t st) {
+  GArgs A;
+  SCP_TRY(g_args(sys, false, nullptr, nullptr, A));
+  GArgs* dargs = static_cast<GArgs*>(ws);
+  float2* ph = reinterpret_cast<float2*>(static_cast<char*>(ws) + align256(sizeof(GArgs)));
+  A.ph = ph;
+  A.x0 = x0;
+  A.xT = xT;
+  A.S = S;
+  hipLaunchKernelGGL(store_args_kernel, dim3(1), dim3(64), 0, st, A, dargs);
+  HIPCHK(hipGetLastError());
+  SCP_TRY(g_phases(sys, false, ph, st));
+  hipEvent_t t0 = timing_start(sys, st);
+  HIPCHK(l_real_column(sys->d, sys->n_modes, dargs, S, st));
+  timing_stop(sys, t0, 0, st);
+  return SCP_OK;
+}
+
 // The gradient from the steps' sums, copied to the host (synchronises st).
 static scp_status g_fold(scp_system* sys, int S, const GArgs* dargs, const GAdj* dadj, int nblk,
                          int nacc, double* part, double* dgrad, double* grad, hipStream_t st) {
@@ -2277,14 +2307,14 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
 //   4-transmon chain, d = 4, 256 columns       35 -> 2.8; 163 -> 17
 //   6-transmon ring, d = 3, 64 / 729 columns   33 -> 4 / 33 -> 12;  147 -> 20 / 150 -> 136
 //   9-mode ring, d = 2, 512 columns            34 -> 4.3; 181 -> 89
-bool gather_preferred(const scp_system* sys, int S) {
+bool gather_preferred(const scp_system* sys, int S, bool real) {
   if (!g_supported(sys->d, sys->n_modes, false)) return false;
   GArgs A;
   if (g_args(sys, false, nullptr, nullptr, A) != SCP_OK) {
     set_error("");
     return false;
   }
-  if (A.real) return S <= (sys->D <= 1024 ? 1024 : 256);
+  if (real && A.rt != nullptr) return S <= (sys->D <= 1024 ? 1024 : 256);
   if (S > 256) return false;
   const int fused_wg = (S + sys->plan.CPW - 1) / sys->plan.CPW;
   return fused_wg < 64;

@@ -281,7 +281,13 @@ scp_status lindblad_adjoint_workspace_bytes(const scp_system* sys, int S, size_t
 scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const double* gammaphi,
                                    int S, void* ws, size_t ws_bytes, const float2* rho0,
                                    const float2* cot, double* grad, hipStream_t st);
-bool gather_preferred(const scp_system* sys, int S);
+bool gather_preferred(const scp_system* sys, int S, bool real);
+// Forward of a closed system in the real form, one workgroup per column, for
+// shapes above the gather engine's (d = 3, N = 8).
+bool real_column_supported(const scp_system* sys);
+size_t real_column_bytes(const scp_system* sys);
+scp_status launch_real_column(scp_system* sys, int S, void* ws, const float2* psi0, float2* psiT,
+                              hipStream_t st);
 bool split_preferred(const scp_system* sys);
 size_t split_workspace_bytes(const scp_system* sys);
 scp_status launch_split_forward(scp_system* sys, int S, void* ws, const float2* psi0, float2* psiT,

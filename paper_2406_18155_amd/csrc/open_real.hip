@@ -1,4 +1,5 @@
-// Gather engine, real form of an open system's forward and adjoint.
+// Gather engine, real form of an open system's forward and adjoint, and of the
+// forward of closed systems above the other real form's shapes (d = 3, N = 8).
 //
 // Under the conditions of the closed systems' real form (real frame, odd
 // operators, neighbour couplings, one operator per driven mode) the density
@@ -24,16 +25,22 @@
 // and 46 -> 33; d = 2, N = 5 10.3 -> 8.6 and 61 -> 40; 16 matrices the same.
 // Elements dealt to 1024 threads in order, every element with its own digits and
 // rows, took 62 and 380: as many LDS reads of rows as of elements.
+//
+// A closed column of D = 6561 is the same element set with A's modes alone (no
+// B, no rates); two buffers and the low words fill the LDS, where the
+// register-layout stepper runs 256 threads of 27 amplitudes through four
+// layouts: 8-transmon ring 48 -> 33 us per step (256 columns), LDS-bound (36
+// reads of 8 bytes per element and stage, 6.5 of 8.2 us).
 #include "gather.h"
 
 namespace scp {
 
 namespace {
 
-template <int d, int N>
+template <int d, int N, bool OPEN>
 struct LShape {
-  static constexpr int D = cpow(d, N), L = D * D;
-  static constexpr int H = d == 3 && N == 4 ? 2 : 1;   // modes of A within a thread
+  static constexpr int D = cpow(d, N), L = OPEN ? D * D : D;
+  static constexpr int H = L == 6561 ? 2 : 1;          // modes of A within a thread
   static constexpr int E = cpow(d, H), T = L / E;      // elements tid + r T of a thread
   static constexpr int TB = (T + 63) / 64 * 64, NW = TB / 64;
   static constexpr int n = Nb<d, true>::n, nn = n * n, dd = d * d;
@@ -58,9 +65,9 @@ struct LShape {
   static constexpr size_t adj_bytes() {
     return sizeof(c32) * bufs + sizeof(float) * (size_t)(at_s + 2 * NW * NV);
   }
-  static_assert(adj_bytes() <= 163840, "a column fits the LDS");
+  static_assert((OPEN ? adj_bytes() : fwd_bytes()) <= 163840, "a column fits the LDS");
   static constexpr int ms(int m) { return cpow(d, N - 1 - m); }   // stride in A or B
-  static constexpr int st(int side, int m) { return (side ? 1 : D) * ms(m); }
+  static constexpr int st(int side, int m) { return (OPEN && !side ? D : 1) * ms(m); }
   static constexpr int pi(int p) { return p == N - 1 ? 0 : p; }
   static constexpr int pj(int p) { return p == N - 1 ? N - 1 : p + 1; }
   // digit of the thread's element r along one of the first H modes, the step of
@@ -112,9 +119,9 @@ __device__ __forceinline__ void l_mac(c32& z, float g, c32 v) {
 }
 
 // What a thread keeps of its elements and of the drives.
-template <int d, int N>
+template <int d, int N, bool OPEN>
 struct LThread {
-  using S = LShape<d, N>;
+  using S = LShape<d, N, OPEN>;
   static constexpr int E = S::E, T = S::T, L = S::L, H = S::H, n = S::n;
   bool on;            // threads past the last element only help with the copies
   unsigned tid;       // 0 where off
@@ -140,7 +147,7 @@ struct LThread {
       for (int t = threadIdx.x; t < S::nc; t += S::TB) lds_tab[S::at_c + t] = A->rt[S::off_c + t];
     // per mode and digit pair: decay -gamma1 (a + b) / 2 - gammaphi (a - b)^2,
     // and the jump's sqrt((a + 1)(b + 1)) (0 at the top level)
-    for (int t = threadIdx.x; t < N * S::dd; t += S::TB) {
+    for (int t = threadIdx.x; OPEN && t < N * S::dd; t += S::TB) {
       const int m = t / S::dd, a = t % S::dd / d, b = t % d;
       lds_tab[S::at_j + t] =
           (float)(A->kappa * (-0.5 * A->g1[m] * (a + b) - (double)A->gp[m] * ((a - b) * (a - b))));
@@ -155,18 +162,21 @@ struct LThread {
     }
     rates = false;
 #pragma unroll
-    for (int m = 0; m < N; ++m) rates |= A->g1[m] > 0.f || A->gp[m] > 0.f;
+    for (int m = 0; m < N; ++m) rates |= OPEN && (A->g1[m] > 0.f || A->gp[m] > 0.f);
     on = (int)threadIdx.x < T;
     tid = on ? threadIdx.x : 0;
-    const int Ai = tid / S::D, Bi = (int)tid - Ai * S::D;
+    const int Ai = OPEN ? tid / S::D : tid, Bi = OPEN ? (int)tid - Ai * S::D : 0;
     pk = 0;
     float g = 0.f;
 #pragma unroll
     for (int m = 0; m < N; ++m) {
-      const int a = m < H ? 0 : (Ai / S::ms(m)) % d, b = (Bi / S::ms(m)) % d;
-      pk |= (uint32_t)a << (3 * m) | (uint32_t)b << (3 * (N + m));
+      const int a = m < H ? 0 : (Ai / S::ms(m)) % d, b = OPEN ? (Bi / S::ms(m)) % d : 0;
+      pk |= (uint32_t)a << (3 * m);
       if (m >= H) g += A->delta[m][a];
-      g -= A->delta[m][b];
+      if (OPEN) {
+        pk |= (uint32_t)b << (3 * (N + m));
+        g -= A->delta[m][b];
+      }
     }
     dg = (float)(A->kappa * g);
   }
@@ -209,10 +219,11 @@ struct LThread {
   }
   // f(r, t): t[c] = sum over the neighbours of element r along the modes of
   // pair p, one side, of the rows of table c (C tables of dd rows at `rows`, in
-  // device memory at `urows`) times y; own: this thread's y
-  template <int p, int side, int C, typename F>
+  // device memory at `urows`) times y, t[0] with the start init(r), the rows of
+  // side 1 with the sign changed; own: this thread's y
+  template <int p, int side, int C, typename I, typename F>
   __device__ __forceinline__ void pair(const c32* yc, const c32 (&own)[E], const float* rows,
-                                       const float* urows, F f) const {
+                                       const float* urows, I init, F f) const {
     constexpr int i = S::pi(p), j = S::pj(p), cs = S::dd * S::pr;
     const Digits X = digits();
     if constexpr (side == 1 || i >= H) {   // both digits are the thread's
@@ -220,12 +231,19 @@ struct LThread {
 #pragma unroll
       for (int c = 0; c < C; ++c)
         l_row<S::nn, S::pr>(rows + c * cs + (X.dig(side, i) * d + X.dig(side, j)) * S::pr, g[c]);
+      if (side == 1) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int k = 0; k < S::nn; ++k) g[c][k] = -g[c][k];
+      }
       const c32* q = yc + tid + (X.o(side, i) + X.o(side, j));
 #pragma unroll
       for (int r = 0; r < E; ++r) {
         c32 t[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) t[c].x = t[c].y = 0.f;
+        t[0] = init(r);
 #pragma unroll
         for (int x = 0; x < n; ++x)
 #pragma unroll
@@ -258,6 +276,7 @@ struct LThread {
           c32 t[C];
 #pragma unroll
           for (int c = 0; c < C; ++c) t[c].x = t[c].y = 0.f;
+          t[0] = init(r0 + a * S::rs(i));
 #pragma unroll
           for (int b = (a & 1) ^ 1; b < d; b += 2)
 #pragma unroll
@@ -277,6 +296,7 @@ struct LThread {
         c32 t[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) t[c].x = t[c].y = 0.f;
+        t[0] = init(r);
 #pragma unroll
         for (int x = (a & 1) ^ 1; x < d; x += 2)
 #pragma unroll
@@ -290,18 +310,20 @@ struct LThread {
       }
     }
   }
-  // f(r, t): the same for the drive operator of mode m
-  template <int m, int side, typename F>
-  __device__ __forceinline__ void drive(const c32* yc, const c32 (&own)[E], F f) const {
+  // f(r, t): the same for the drive operator of mode m, times c
+  template <int m, int side, typename I, typename F>
+  __device__ __forceinline__ void drive(const c32* yc, const c32 (&own)[E], float c, I init,
+                                        F f) const {
     const Digits X = digits();
     if constexpr (side == 1 || m >= H) {
       float g[n];
       l_row<n, S::dr>(tab + S::off_d + (m * d + X.dig(side, m)) * S::dr, g);
+#pragma unroll
+      for (int x = 0; x < n; ++x) g[x] *= side == 1 ? -c : c;
       const c32* q = yc + tid + X.o(side, m);
 #pragma unroll
       for (int r = 0; r < E; ++r) {
-        c32 t;
-        t.x = t.y = 0.f;
+        c32 t = init(r);
 #pragma unroll
         for (int x = 0; x < n; ++x) l_mac(t, g[x], q[X.at(x, side, m) + r * T]);
         f(r, t);
@@ -317,7 +339,9 @@ struct LThread {
 #pragma unroll
         for (int x = (a & 1) ^ 1; x < d; x += 2)
           l_mac(t, u[a * S::dr + S::place(a, x)], own[r + (x - a) * S::rs(m)]);
-        f(r, t);
+        c32 k = init(r);
+        l_mac(k, c, t);
+        f(r, k);
         fence(r);
       }
     }
@@ -400,44 +424,43 @@ struct LThread {
       z[r].x = g * own[r].x;
       z[r].y = g * own[r].y;
     }
+    auto init = [&](int r) { return z[r]; };
     static_for<N>([&](auto P) {
       constexpr int p = decltype(P)::value;
       if (!((pmask >> p) & 1)) return;
       const float* rows = tab + p * S::dd * S::pr;
       const float* urows = rt + p * S::dd * S::pr;
-      pair<p, 0, 1>(yc, own, rows, urows, [&](int r, const c32(&t)[1]) {
-        z[r].x += t[0].x;
-        z[r].y += t[0].y;
-      });
-      pair<p, 1, 1>(yc, own, rows, urows, [&](int r, const c32(&t)[1]) {
-        z[r].x -= t[0].x;
-        z[r].y -= t[0].y;
-      });
+      auto keep = [&](int r, const c32(&t)[1]) { z[r] = t[0]; };
+      pair<p, 0, 1>(yc, own, rows, urows, init, keep);
+      if constexpr (OPEN) pair<p, 1, 1>(yc, own, rows, urows, init, keep);
       __builtin_amdgcn_sched_barrier(0);
     });
     static_for<N>([&](auto M) {
       constexpr int m = decltype(M)::value;
       if (!((dmask >> m) & 1)) return;
-      drive<m, 0>(yc, own, [&](int r, c32 t) { l_mac(z[r], c[m], t); });
-      drive<m, 1>(yc, own, [&](int r, c32 t) { l_mac(z[r], -c[m], t); });
+      auto keep = [&](int r, c32 t) { z[r] = t; };
+      drive<m, 0>(yc, own, c[m], init, keep);
+      if constexpr (OPEN) drive<m, 1>(yc, own, c[m], init, keep);
       __builtin_amdgcn_sched_barrier(0);
     });
     load();
-    if (rates) {
-      static_for<N>([&](auto M) {
-        constexpr int m = decltype(M)::value;
-        const float g1 = unif((float)(A->kappa * A->g1[m]));
-        jump<m, false>(yc, [&](int r, c32 v) {
-          z[r].y = fmaf(g1, v.x, z[r].y);
-          z[r].x = fmaf(-g1, v.y, z[r].x);
+    if constexpr (OPEN) {
+      if (rates) {
+        static_for<N>([&](auto M) {
+          constexpr int m = decltype(M)::value;
+          const float g1 = unif((float)(A->kappa * A->g1[m]));
+          jump<m, false>(yc, [&](int r, c32 v) {
+            z[r].y = fmaf(g1, v.x, z[r].y);
+            z[r].x = fmaf(-g1, v.y, z[r].x);
+          });
         });
-      });
-      const Decay D = decay();
+        const Decay D = decay();
 #pragma unroll
-      for (int r = 0; r < E; ++r) {
-        const float g = D.of(r);
-        z[r].y = fmaf(g, own[r].x, z[r].y);
-        z[r].x = fmaf(-g, own[r].y, z[r].x);
+        for (int r = 0; r < E; ++r) {
+          const float g = D.of(r);
+          z[r].y = fmaf(g, own[r].x, z[r].y);
+          z[r].x = fmaf(-g, own[r].y, z[r].x);
+        }
       }
     }
 #pragma unroll
@@ -450,12 +473,12 @@ struct LThread {
 
 // Steps [n0, n1) of one column from (hi, lo) at n0: CK keeps the state at every
 // ce-th step, SEG the stage inputs y'.
-template <int d, int N, bool CK, bool SEG>
+template <int d, int N, bool OPEN, bool CK, bool SEG>
 __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ Bg,
-                                        const LThread<d, N>& Th, c32* lds, c32* lo, int col, int n0,
+                                        const LThread<d, N, OPEN>& Th, c32* lds, c32* lo, int col, int n0,
                                         int n1, const float4* __restrict__ from,
                                         c32* __restrict__ segc) {
-  using S = LShape<d, N>;
+  using S = LShape<d, N, OPEN>;
   constexpr int L = S::L, T = S::T, E = S::E;
   const unsigned tid = Th.tid;
   const bool on = Th.on;
@@ -596,15 +619,16 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
   }
 }
 
-template <int d, int N, bool CK>
-__global__ void __launch_bounds__((LShape<d, N>::TB))
+template <int d, int N, bool OPEN, bool CK>
+__global__ void __launch_bounds__((LShape<d, N, OPEN>::TB))
 l_rk4_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
-  using S = LShape<d, N>;
+  using S = LShape<d, N, OPEN>;
   extern __shared__ __align__(16) c32 lds[];
   kptr<GArgs> A = kconst(Ag);
-  LThread<d, N> Th;
+  LThread<d, N, OPEN> Th;
   Th.init(A, reinterpret_cast<float*>(lds + S::bufs), false);
-  l_steps<d, N, CK, false>(A, Bg, Th, lds, lds + 2 * S::L, blockIdx.x, 0, A->nsteps, nullptr, nullptr);
+  l_steps<d, N, OPEN, CK, false>(A, Bg, Th, lds, lds + 2 * S::L, blockIdx.x, 0, A->nsteps, nullptr,
+                                 nullptr);
 }
 
 // The reverse walk of a column, segment by segment from the last: recompute the
@@ -614,9 +638,9 @@ l_rk4_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
 // K_c and 2 Re(conj(D_m) y') of the rates'; all use the neighbours that yb'
 // gathers.
 template <int d, int N>
-__global__ void __launch_bounds__((LShape<d, N>::TB))
+__global__ void __launch_bounds__((LShape<d, N, true>::TB))
 l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
-  using S = LShape<d, N>;
+  using S = LShape<d, N, true>;
   constexpr int L = S::L, T = S::T, E = S::E, H = S::H, NW = S::NW, NV = S::NV, dd = S::dd;
   extern __shared__ __align__(16) c32 lds[];
   kptr<GArgs> A = kconst(Ag);
@@ -628,7 +652,7 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
   float* tab = reinterpret_cast<float*>(lds + S::bufs);
   float* wsum = tab + S::at_s;
   c32* lo = lds + 2 * L;   // low words, where they lie in LDS
-  LThread<d, N> Th;
+  LThread<d, N, true> Th;
   Th.init(A, tab, true);
   const unsigned tid = Th.tid;
   const bool on = Th.on;
@@ -638,7 +662,7 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
 #pragma unroll 1
   for (int g = nck - 1; g >= 0; --g) {
     const int n0 = g * ce, n1 = min(nsteps, n0 + ce);
-    l_steps<d, N, false, true>(A, Bg, Th, lds, lo, col, n0, n1, B->ck + ((size_t)col * nck + g) * L,
+    l_steps<d, N, true, false, true>(A, Bg, Th, lds, lo, col, n0, n1, B->ck + ((size_t)col * nck + g) * L,
                                segc);
     // ---- back
     float lhr[E], lhm[E], llr[S::LO ? 1 : E], llm[S::LO ? 1 : E];
@@ -726,6 +750,11 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
           const float u = g_wave_sum(on ? 2.f * v : 0.f);
           if (lane == 0) wv[k] = u;
         };
+        auto zero = [](int) {
+          c32 v;
+          v.x = v.y = 0.f;
+          return v;
+        };
         c32 z[E];   // K, with D^dag turned by -i
 #pragma unroll
         for (int r = 0; r < E; ++r) {
@@ -742,27 +771,24 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
           const float* rows = tab + S::at_c + p * 2 * dd * S::pr;
           const float* urows = Th.rt + S::off_c + p * 2 * dd * S::pr;
           float v0 = 0.f, v1 = 0.f;
-          auto one = [&](int r, c32 t, float g, float& v, float sg) {
-            l_mac(z[r], sg * g, t);
-            v = fmaf(sg * t.x, y[r].y, fmaf(-sg * t.y, y[r].x, v));
+          auto one = [&](int r, c32 t, float g, float& v) {
+            l_mac(z[r], g, t);
+            v = fmaf(t.x, y[r].y, fmaf(-t.y, y[r].x, v));
             l_pin(z[r].x, z[r].y, v);
           };
           if (nc > 1) {
             const float g1 = unif((float)(A->kappa * A->cp_g[c1]));
-            Th.template pair<p, 0, 2>(kbw, kb, rows, urows, [&](int r, const c32(&t)[2]) {
-              one(r, t[0], g0, v0, 1.f);
-              one(r, t[1], g1, v1, 1.f);
-            });
-            Th.template pair<p, 1, 2>(kbw, kb, rows, urows, [&](int r, const c32(&t)[2]) {
-              one(r, t[0], g0, v0, -1.f);
-              one(r, t[1], g1, v1, -1.f);
-            });
+            auto two = [&](int r, const c32(&t)[2]) {
+              one(r, t[0], g0, v0);
+              one(r, t[1], g1, v1);
+            };
+            Th.template pair<p, 0, 2>(kbw, kb, rows, urows, zero, two);
+            Th.template pair<p, 1, 2>(kbw, kb, rows, urows, zero, two);
             sum(N + c1, v1);
           } else {
-            Th.template pair<p, 0, 1>(kbw, kb, rows, urows,
-                                      [&](int r, const c32(&t)[1]) { one(r, t[0], g0, v0, 1.f); });
-            Th.template pair<p, 1, 1>(kbw, kb, rows, urows,
-                                      [&](int r, const c32(&t)[1]) { one(r, t[0], g0, v0, -1.f); });
+            auto sole = [&](int r, const c32(&t)[1]) { one(r, t[0], g0, v0); };
+            Th.template pair<p, 0, 1>(kbw, kb, rows, urows, zero, sole);
+            Th.template pair<p, 1, 1>(kbw, kb, rows, urows, zero, sole);
           }
           sum(N + c0, v0);
           __builtin_amdgcn_sched_barrier(0);
@@ -771,13 +797,13 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
           constexpr int m = decltype(M)::value;
           if (!((Th.dmask >> m) & 1)) return;
           float v = 0.f;
-          auto one = [&](int r, c32 t, float sg) {
-            l_mac(z[r], sg * c[m], t);
-            v = fmaf(sg * t.x, y[r].y, fmaf(-sg * t.y, y[r].x, v));
+          auto one = [&](int r, c32 t) {
+            l_mac(z[r], c[m], t);
+            v = fmaf(t.x, y[r].y, fmaf(-t.y, y[r].x, v));
             l_pin(z[r].x, z[r].y, v);
           };
-          Th.template drive<m, 0>(kbw, kb, [&](int r, c32 t) { one(r, t, 1.f); });
-          Th.template drive<m, 1>(kbw, kb, [&](int r, c32 t) { one(r, t, -1.f); });
+          Th.template drive<m, 0>(kbw, kb, 1.f, zero, one);
+          Th.template drive<m, 1>(kbw, kb, 1.f, zero, one);
           // the row is the operator over its largest entry
           sum(uni(A->rd_k[m]), v / unif(A->rd_s[m]));
           __builtin_amdgcn_sched_barrier(0);
@@ -888,19 +914,27 @@ hipError_t l_launch(K* kernel, int S, int threads, size_t sh, const GArgs* dargs
 hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s) {
 #define L_FWD(dd_, nn_)                                                                            \
   if (d == dd_ && N == nn_) {                                                                      \
-    using Z = LShape<dd_, nn_>;                                                                    \
-    return dadj ? l_launch(l_rk4_kernel<dd_, nn_, true>, S, Z::TB, Z::fwd_bytes(), dargs, dadj, s)  \
-                : l_launch(l_rk4_kernel<dd_, nn_, false>, S, Z::TB, Z::fwd_bytes(), dargs, dadj, s); \
+    using Z = LShape<dd_, nn_, true>;                                                                    \
+    return dadj ? l_launch(l_rk4_kernel<dd_, nn_, true, true>, S, Z::TB, Z::fwd_bytes(), dargs, dadj, s)  \
+                : l_launch(l_rk4_kernel<dd_, nn_, true, false>, S, Z::TB, Z::fwd_bytes(), dargs, dadj, s); \
   }
   GA_OPEN_REAL(L_FWD)
 #undef L_FWD
   return hipErrorInvalidValue;
 }
 
+bool l_column_supported(int d, int N) { return d == 3 && N == 8; }
+
+hipError_t l_real_column(int d, int N, const GArgs* dargs, int S, hipStream_t s) {
+  using Z = LShape<3, 8, false>;
+  if (!l_column_supported(d, N)) return hipErrorInvalidValue;
+  return l_launch(l_rk4_kernel<3, 8, false, false>, S, Z::TB, Z::fwd_bytes(), dargs, nullptr, s);
+}
+
 hipError_t l_real_adjoint(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s) {
 #define L_ADJ(dd_, nn_)                                                                            \
   if (d == dd_ && N == nn_)                                                                        \
-    return l_launch(l_adj_kernel<dd_, nn_>, S, LShape<dd_, nn_>::TB, LShape<dd_, nn_>::adj_bytes(), \
+    return l_launch(l_adj_kernel<dd_, nn_>, S, LShape<dd_, nn_, true>::TB, LShape<dd_, nn_, true>::adj_bytes(), \
                     dargs, dadj, s);
   GA_OPEN_REAL(L_ADJ)
 #undef L_ADJ

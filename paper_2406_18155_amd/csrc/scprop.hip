@@ -886,13 +886,14 @@ struct WsLayout {
   bool gather = false;        // a forward-only FP32 solve on the gather engine (workspace from 0)
   bool gather_grad = false;   // checkpoints / adjoint on the gather engine (its own layout)
   bool split = false;         // a forward-only solve of a small device, split over time
+  bool column = false;        // a forward-only solve in the real form's column kernel
 };
 
 // Which engine runs an FP32 solve: the system's choice, else (automatic) the
 // gather engine when the register-layout stepper would leave most of the chip
 // idle.  allow_gather = false keeps the register-layout engine.
-WsLayout ws_layout(const scp_system* sys, const scp_solve_opts* o, int with_grad,
-                   bool allow_gather = true) {
+WsLayout ws_layout_in(const scp_system* sys, const scp_solve_opts* o, int with_grad,
+                      bool allow_gather, bool real) {
   WsLayout w;
   const int N = sys->n_steps;
   w.ce = o->ckpt_every > 0 ? o->ckpt_every : (int)std::ceil(std::sqrt((double)N));
@@ -903,7 +904,7 @@ WsLayout ws_layout(const scp_system* sys, const scp_solve_opts* o, int with_grad
   const int engine = allow_gather ? sys->engine : 1;
   bool want = false;
   if (o->precision == 0 && engine != 1)
-    want = engine == 2 ? gather_supported(sys) : gather_preferred(sys, (int)S);
+    want = engine == 2 ? gather_supported(sys) : gather_preferred(sys, (int)S, real);
   if (want && (o->with_ckpt || with_grad)) {
     want = gather_grad_check(sys) == SCP_OK;
     if (!want) set_error("");
@@ -920,6 +921,13 @@ WsLayout ws_layout(const scp_system* sys, const scp_solve_opts* o, int with_grad
     if (engine == 0 && !o->with_ckpt && !with_grad && split_preferred(sys)) {
       w.split = true;
       off = std::max(off, split_workspace_bytes(sys));
+    }
+    // one workgroup per column either way: 48 -> 33 us per step at any count of
+    // columns (8-transmon ring).  The forward alone: the adjoint's checkpoints
+    // are in the register layout
+    if (engine == 0 && !o->with_ckpt && !with_grad && real && real_column_supported(sys)) {
+      w.column = true;
+      off = std::max(off, real_column_bytes(sys));
     }
     if (o->with_ckpt || with_grad) {
       w.ckpt = off;
@@ -940,6 +948,16 @@ WsLayout ws_layout(const scp_system* sys, const scp_solve_opts* o, int with_grad
     off = align(4 * S * D * sizeof(double2));
   }
   w.total = std::max<size_t>(off, 256);
+  return w;
+}
+
+// The automatic choice depends on the frame; a workspace does for either.
+WsLayout ws_layout(const scp_system* sys, const scp_solve_opts* o, int with_grad,
+                   bool allow_gather = true) {
+  const bool real = sys->plan.real_frame != 0;
+  WsLayout w = ws_layout_in(sys, o, with_grad, allow_gather, real);
+  if (sys->real_ok && sys->engine == 0)
+    w.total = std::max(w.total, ws_layout_in(sys, o, with_grad, allow_gather, !real).total);
   return w;
 }
 
@@ -1127,6 +1145,10 @@ scp_status scp_propagate(scp_system* sys, const scp_solve_opts* opts, void* work
                                               (float2*)psiT, st);
     if (s == SCP_OK) ck_record(sys, workspace, opts->n_cols, w.ce);
     return s;
+  }
+  if (w.column) {
+    ck_clear(sys);
+    return launch_real_column(sys, opts->n_cols, workspace, (const float2*)psi0, (float2*)psiT, st);
   }
   if (w.split) {
     ck_clear(sys);

@@ -184,7 +184,8 @@ scp_status admit(scp_server* sv, Request* r) {
   // the gather engine where scp_propagate would take it and its tables fit
   // the budget beside what is admitted
   r->gather = false;
-  if (sv->engine != 1 && (sv->engine == 2 ? gather_supported(sys) : gather_preferred(sys, r->S))) {
+  if (sv->engine != 1 && (sv->engine == 2 ? gather_supported(sys)
+                                          : gather_preferred(sys, r->S, sys->plan.real_frame != 0))) {
     if (gather_grad_check(sys) == SCP_OK) {
       r->gws_bytes = gather_serve_bytes(sys, r->S, r->ce, r->want_grad != 0);
       r->gather = r->gws_bytes > 0 &&
