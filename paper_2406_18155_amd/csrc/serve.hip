@@ -11,14 +11,16 @@
 //      class (d, NR, MP) in which every workgroup reads its own work
 //      descriptor (its request's tables and states, its column block, its
 //      step range or segment): one forward launch, or per adjoint segment a
-//      recompute launch and a reverse launch;
+//      reverse launch, before it, where the segment's stage inputs are not
+//      there yet, a recompute launch of it and of the ones that follow;
 //   3. reduce the fidelity of requests whose forward completed (and seed the
 //      costate of gradient requests), finish gradients, release memory.
 // With the engine set to 0 or 2, requests that the gather engine runs (few
 // columns of a small device, as for scp_propagate) are batched per (d, modes)
 // on it instead: one launch per tick of every such request's step range of
-// the forward (its compensated state saved between chunks), and per round one
-// launch of the next segment of every such request's reverse walk.
+// the forward (its compensated state saved between chunks), or one launch of
+// the costate sweep over this tick's segments of every such request, then
+// rounds of several segments of each side by side.
 // The per-request state (psi hi/lo, costate, per-wave FP64 accumulators) is
 // carried between ticks exactly, so a request's result does not depend on
 // what else is in flight or on the chunk boundaries.  Every launch is bounded
@@ -95,6 +97,8 @@ struct Request {
   int state = RQ_QUEUED;
   int phase = 0;          // 0 forward, 1 adjoint
   int n_done = 0, seg_next = 0, ce = 1, nckpt = 1, nwg = 1;
+  int nbuf = 1;           // stage-input buffers: segment g in g % nbuf
+  int rec_next = 0;       // segments from here up have been recomputed
   size_t bytes = 0;
   scp_system* sys = nullptr;
   void* dmem = nullptr;
@@ -116,6 +120,11 @@ struct Request {
   void* gws = nullptr;      // its workspace (inside dmem)
   size_t gws_bytes = 0;
   GServeInfo gi{};          // its device descriptions, state buffer and LDS needs
+
+  float2* seg_buf(int g) const {
+    return (float2*)((char*)segbuf +
+                     (size_t)(g % nbuf) * (((size_t)ce * 4 * S * sys->D * 8 + 255) & ~(size_t)255));
+  }
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -209,7 +218,18 @@ scp_status admit(scp_server* sv, Request* r) {
     o_g = take(r->gws_bytes);
   } else if (r->want_grad) {
     o_ck = take((size_t)r->nckpt * S * D * 16);
-    o_seg = take((size_t)r->ce * 4 * S * D * 8);
+    // Several segments recomputed side by side, up to a workgroup per compute
+    // unit, cost the time of one: a request of few workgroups leaves most of
+    // the chip idle, and its recompute is a quarter of its reverse walk (16
+    // mixed requests, the longest of 32 workgroups: 786 -> 641 ms).  The buffers
+    // beyond the first come from the free half of the budget only.
+    const size_t seg = align256((size_t)r->ce * 4 * S * D * 8);
+    const size_t half = sv->budget / 2, in_use = sv->used + r->bytes;
+    r->nbuf = std::max(1, std::min({8, 256 / r->nwg, r->nckpt}));
+    if (in_use >= half) r->nbuf = 1;
+    else r->nbuf = (int)std::min<size_t>(r->nbuf, 1 + (half - in_use) / seg);
+    r->rec_next = r->nckpt;
+    o_seg = take(r->nbuf * seg);
     o_sum = take(S * D * 8);
     o_ls = take(S * D * 8);
     o_part = take((size_t)r->nwg * 4 * std::max(1, P.nacc) * 8);
@@ -397,7 +417,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
       size_t rounds = 1;
       for (auto& w : kv.second) {
         const size_t rw = std::get<0>(kv.first) == 0 ? 1 : (size_t)(w.s_hi - w.s_lo + 1);
-        need += rw * w.r->nwg * (sizeof(FwdItem) + sizeof(AdjItem));
+        need += rw * w.r->nwg * (w.r->nbuf * sizeof(FwdItem) + sizeof(AdjItem));
         rounds = std::max(rounds, rw);
       }
       need += 2 * 256 * rounds;   // alignment of every upload
@@ -459,18 +479,24 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
           for (auto& w : kv.second) {
             Request* r = w.r;
             const int seg = w.s_hi - j;
-            if (seg < w.s_lo) continue;
-            const int n0 = seg * r->ce, n1 = std::min(n0 + r->ce, r->sys->n_steps);
-            for (int cb = 0; cb < r->nwg; ++cb)
-              fi[nf++] = FwdItem{r->sys->d_plan, r->sys->d_ops, r->sys->d_ctab, nullptr, nullptr,
-                                 nullptr, r->lo, nullptr,
-                                 r->ckpt + (size_t)seg * r->S * r->sys->D, r->segbuf,
-                                 r->sys->d_ph, r->sys->d_rops, 1, r->S, cb, n0, n1, 0};
+            if (seg < w.s_lo || seg >= r->rec_next) continue;
+            r->rec_next = std::max(0, seg - r->nbuf + 1);
+            for (int g = seg; g >= r->rec_next; --g) {
+              const int n0 = g * r->ce, n1 = std::min(n0 + r->ce, r->sys->n_steps);
+              for (int cb = 0; cb < r->nwg; ++cb)
+                fi[nf++] = FwdItem{r->sys->d_plan, r->sys->d_ops, r->sys->d_ctab, nullptr, nullptr,
+                                   nullptr, r->lo, nullptr,
+                                   r->ckpt + (size_t)g * r->S * r->sys->D, r->seg_buf(g),
+                                   r->sys->d_ph, r->sys->d_rops, 1, r->S, cb, n0, n1, 0};
+            }
           }
           void* dptr = nullptr;
-          if (!stage(fi, (size_t)nf * sizeof(FwdItem), st, &dptr)) return fail(SCP_EHIP, "item upload");
-          s = launch_rk4_batched(d, NR, MP, ev, (const FwdItem*)dptr, nf, wg, sh_f, true, st);
-          if (s != SCP_OK) return s;
+          if (nf > 0) {
+            if (!stage(fi, (size_t)nf * sizeof(FwdItem), st, &dptr))
+              return fail(SCP_EHIP, "item upload");
+            s = launch_rk4_batched(d, NR, MP, ev, (const FwdItem*)dptr, nf, wg, sh_f, true, st);
+            if (s != SCP_OK) return s;
+          }
           AdjItem* ai = (AdjItem*)((char*)sv->h_items + off);
           int na = 0;
           for (auto& w : kv.second) {
@@ -479,7 +505,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
             if (seg < w.s_lo) continue;
             for (int cb = 0; cb < r->nwg; ++cb)
               ai[na++] = AdjItem{r->sys->d_plan, r->sys->d_ops, r->sys->d_ctab, r->sys->d_dctab,
-                                 r->ckpt, r->cot, r->segbuf, r->lo, r->sum, r->lamstate, r->part,
+                                 r->ckpt, r->cot, r->seg_buf(seg), r->lo, r->sum, r->lamstate, r->part,
                                  r->sys->d_ph, r->sys->d_rops, r->ce, r->nckpt, r->S, cb, seg, seg,
                                  seg == r->nckpt - 1 ? 1 : 0, 0};
           }
