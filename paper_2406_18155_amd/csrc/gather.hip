@@ -8,7 +8,9 @@
 // interaction-picture generator of Sec. 2.1's local decomposition,
 //   k_A = -i [ delta(A) y_A + sum (one- and two-mode contractions of V) ],
 // for devices whose columns are too few to fill the chip with the register-
-// layout stepper (the 4-fluxonium chain: 16 columns of 625).
+// layout stepper (the 4-fluxonium chain: 16 columns of 625).  This file has the
+// general form and the one for operators between levels of unlike parity (PAR);
+// gather_real.hip and open_real.hip have the forms for real terms.
 //
 // Open systems (OPEN = true): the vectorised Lindblad master equation (the
 // superoperator form of App. D's closing remark; the LindbladObj component of
@@ -2301,7 +2303,7 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
 // register-layout stepper; in its real form, whenever the columns fill no more
 // than one round of workgroups, four where a thread has one element.  Measured,
 // register -> real form, us per step (forward; forward + gradient):
-//   6-fluxonium chain, d = 4, 64 columns       56 -> 26;  302 -> 107
+//   6-fluxonium chain, d = 4, 64 columns       56 -> 17;  302 -> 76
 //   7-transmon ring, d = 3, 128 columns        47 -> 23;  244 -> 121
 //   5-fluxonium chain, d = 5, 32 columns       54 -> 40;  313 -> 111
 //   4-transmon chain, d = 4, 256 columns       35 -> 2.8; 163 -> 17

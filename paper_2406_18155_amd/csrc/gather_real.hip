@@ -2,8 +2,8 @@
 //
 // Where every term is real (the real frame), every operator is odd (parity),
 // the coupled pairs are neighbours on a chain or ring of the modes with two
-// couplings each at most, and a driven mode has one operator, the generator is V(t) = P(t) R(t) P(t)^dag with P the
-// diagonal of frame phases and R real.  The coefficients of R do not depend on
+// couplings each at most, and a driven mode has one operator, the generator is
+// V(t) = P(t) R(t) P(t)^dag with P the diagonal of frame phases and R real.  The coefficients of R do not depend on
 // time but for the drives' c_k(t): each thread holds those of its own elements
 // (in registers where a thread has one or few, else read from LDS rows), and a
 // stage needs no table but one phase per element and half step,
@@ -15,7 +15,9 @@
 // two multiply-adds instead of four and no coefficient read.
 // Measured, complex rows (g_apply, g_adj_body) -> here: 4-fluxonium chain
 // (d = 5, 16 columns) forward 8.4 -> 4.0 us per step, forward + gradient
-// 29 -> 19.5; 5-transmon ring (32 columns) forward + gradient 21 -> 8.4.
+// 29 -> 19.5; 5-transmon ring (32 columns) forward + gradient 21 -> 8.4.  Rows
+// shared by a thread's elements (SHARE), each element's own -> here: 6-fluxonium
+// chain (d = 4, 64 columns) forward 25 -> 17, sweep the same, segments 48 -> 41.
 // Error of the final states against FP64 over rings and chains of 3 to 5 modes:
 // 6e-8 to 1e-7 -> 2e-8 to 1e-7 (real_kappa in gather.hip has the reason).
 #include <cstring>
@@ -168,6 +170,11 @@ struct RThread {
   using Sh = GShape<d, N, false>;
   static constexpr int E = Sh::E, T = Sh::T, L = Sh::L;
   static constexpr bool REGC = RShape<d, N>::REGC;
+  // The thread's elements differ in mode 0's digit alone (element r has level
+  // r): the rows and offsets of the other modes are the same for all of them
+  // and are formed once per term, and what reads along mode 0 takes each
+  // neighbour once, or from the thread's own elements.
+  static constexpr bool SHARE = !REGC && E == d && E * T == L;
   uint32_t pk[E];
   float dg[E];
   RCoef<d, N> C[REGC ? E : 1];
@@ -225,6 +232,90 @@ struct RThread {
       Ee.set(p);
       r_apply<d, N>(yb + e, Ee, Cc, c, pmask, dmask, dg[r], y, kr, ki);
       __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // k = R y for all the thread's elements (y: their values of the stage input in
+  // yb), the sums of an element in the order of apply()
+  __device__ __forceinline__ void apply_all(const c32* yb, const float* c, const c32 (&y)[E],
+                                            c32 (&k)[E]) const {
+    if constexpr (SHARE) {
+      using R = RShape<d, N>;
+      constexpr int n = R::n;
+      uint32_t p0 = pk[0];
+      asm volatile("" : "+v"(p0));   // opaque per stage: offsets and rows are formed inside it
+      RElem<d, N> El;
+      El.set(p0);
+      const c32* ye = yb + threadIdx.x;
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        k[r].x = dg[r] * y[r].x;
+        k[r].y = dg[r] * y[r].y;
+      }
+      static_for<N>([&](auto P) {
+        constexpr int p = decltype(P)::value, i = R::pi(p), j = R::pj(p);
+        if (!((pmask >> p) & 1)) return;
+        if constexpr (i > 0) {
+          float g[R::nn];
+          r_row<d, N>(rt + (p * d * d + ket_digit(p0, i) * d + ket_digit(p0, j)) * R::pr, g, R::nn, R::pr);
+          const c32* q = ye + (El.o[i] + El.o[j]);
+#pragma unroll
+          for (int r = 0; r < E; ++r)
+#pragma unroll
+            for (int x = 0; x < n; ++x)
+#pragma unroll
+              for (int z = 0; z < n; ++z) {
+                const c32 v = q[El.at(x, i) + El.at(z, j) + r * T];
+                k[r].x = fmaf(g[x * n + z], v.x, k[r].x);
+                k[r].y = fmaf(g[x * n + z], v.y, k[r].y);
+              }
+        } else {
+          const c32* q = ye + El.o[j];
+          c32 v[d][n];
+#pragma unroll
+          for (int b = 0; b < d; ++b)
+#pragma unroll
+            for (int z = 0; z < n; ++z) v[b][z] = q[El.at(z, j) + b * T];
+#pragma unroll
+          for (int r = 0; r < E; ++r) {
+            float g[R::nn];
+            r_row<d, N>(rt + (p * d * d + r * d + ket_digit(p0, j)) * R::pr, g, R::nn, R::pr);
+#pragma unroll
+            for (int x = 0; x < n; ++x) {
+              const int b = ((r & 1) ^ 1) + 2 * x;
+              if (b >= d) continue;
+#pragma unroll
+              for (int z = 0; z < n; ++z) {
+                k[r].x = fmaf(g[x * n + z], v[b][z].x, k[r].x);
+                k[r].y = fmaf(g[x * n + z], v[b][z].y, k[r].y);
+              }
+            }
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      static_for<N>([&](auto M) {
+        constexpr int m = decltype(M)::value;
+        if (!((dmask >> m) & 1)) return;
+        float o[n];
+        if constexpr (m > 0) r_row<d, N>(rt + R::off_d + (m * d + ket_digit(p0, m)) * R::dr, o, n, R::dr);
+        const c32* q = ye + El.o[m];
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+          float sr = 0.f, si = 0.f;
+          if constexpr (m == 0) r_row<d, N>(rt + R::off_d + r * R::dr, o, n, R::dr);
+#pragma unroll
+          for (int x = 0; x < n; ++x) {
+            const int b = ((r & 1) ^ 1) + 2 * x;
+            if (m == 0 && b >= d) continue;
+            const c32 v = m == 0 ? y[b < d ? b : 0] : q[El.at(x, m) + r * T];
+            sr = fmaf(o[x], v.x, sr);
+            si = fmaf(o[x], v.y, si);
+          }
+          k[r].x = fmaf(c[m], sr, k[r].x);
+          k[r].y = fmaf(c[m], si, k[r].y);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
     }
   }
   __device__ __forceinline__ void phases(int q, c32 (&P)[E]) const {
@@ -313,15 +404,16 @@ __device__ __forceinline__ void g_real_rk4_body(const GArgs* __restrict__ Ag,
       const float ch = s == 2 ? h : 0.5f * h;
       const c32* yc = lds + cur * L;
       c32* yn = lds + (cur ^ 1) * L;
+      c32 ks[E];
+      if constexpr (RThread<d, N>::SHARE) Th.apply_all(yc, s == 0 ? c0 : (s == 3 ? c2 : c1), y, ks);
 #pragma unroll
       for (int r = 0; r < E; ++r) {
         const int e = tid + r * T;
         float kr, ki;
         if (e < L) {
-          Th.apply(r, yc, s == 0 ? c0 : (s == 3 ? c2 : c1), y[r], kr, ki);
           c32 u;
-          u.x = kr;
-          u.y = ki;
+          if constexpr (RThread<d, N>::SHARE) u = ks[r];
+          else Th.apply(r, yc, s == 0 ? c0 : (s == 3 ? c2 : c1), y[r], u.x, u.y);
           u = r_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
           kr = u.y;    // k = -i P R P^dag y
           ki = -u.x;
@@ -437,15 +529,15 @@ __device__ __forceinline__ void g_real_cos_body(const GArgs* __restrict__ Ag,
         if (e < L) kbw[e] = kb[r];
       }
       __syncthreads();
+      c32 ks[E];
+      if constexpr (RThread<d, N>::SHARE) Th.apply_all(kbw, s == 0 ? c0 : (s == 3 ? c2 : c1), kb, ks);
 #pragma unroll
       for (int r = 0; r < E; ++r) {
         const int e = tid + r * T;
         if (e < L) {
-          float kr, ki;
-          Th.apply(r, kbw, s == 0 ? c0 : (s == 3 ? c2 : c1), kb[r], kr, ki);
           c32 u;
-          u.x = kr;
-          u.y = ki;
+          if constexpr (RThread<d, N>::SHARE) u = ks[r];
+          else Th.apply(r, kbw, s == 0 ? c0 : (s == 3 ? c2 : c1), kb[r], u.x, u.y);
           u = r_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
           ybr[r] = -u.y;   // yb = i P R P^dag kb
           ybm[r] = u.x;
@@ -558,15 +650,16 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
         c32* yn = lds + (cur ^ 1) * L;
         c32* ys = segc + ((size_t)(n - n0) * 4 + s + 1) * L;   // the next stage's input
         const bool keep = s < 3 || n + 1 < n1;
+        c32 ks[E];
+        if constexpr (RThread<d, N>::SHARE) Th.apply_all(yc, s == 0 ? c0 : (s == 3 ? c2 : c1), y, ks);
 #pragma unroll
         for (int r = 0; r < E; ++r) {
           const int e = tid + r * T;
           float kr, ki;
           if (e < L) {
-            Th.apply(r, yc, s == 0 ? c0 : (s == 3 ? c2 : c1), y[r], kr, ki);
             c32 u;
-            u.x = kr;
-            u.y = ki;
+            if constexpr (RThread<d, N>::SHARE) u = ks[r];
+            else Th.apply(r, yc, s == 0 ? c0 : (s == 3 ? c2 : c1), y[r], u.x, u.y);
             u = r_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
             kr = u.y;
             ki = -u.x;
@@ -687,15 +780,15 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
         }
       }
       if (prev_n >= 0) fold_prev();
+      c32 ks[E];
+      if constexpr (RThread<d, N>::SHARE) Th.apply_all(kbw, c, kb, ks);
 #pragma unroll
       for (int r = 0; r < E; ++r) {
         const int e = tid + r * T;
         if (e < L) {
-          float kr, ki;
-          Th.apply(r, kbw, c, kb[r], kr, ki);
           c32 u;
-          u.x = kr;
-          u.y = ki;
+          if constexpr (RThread<d, N>::SHARE) u = ks[r];
+          else Th.apply(r, kbw, c, kb[r], u.x, u.y);
           u = r_mul(P[r], u);
           ybr[r] = -u.y;
           ybm[r] = u.x;
@@ -714,59 +807,120 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
         constexpr int MC = 2;
         const int i = R::pi(p), j = R::pj(p), nc = uni(A->rp_n[p]);
         float vc[MC] = {0.f, 0.f};
-#pragma unroll
-        for (int r = 0; r < E; ++r) {
-          const int e = tid + r * T;
-          if (e >= L) continue;
-          uint32_t pk = Th.pk[r];
-          asm volatile("" : "+v"(pk));
-          RElem<d, N> El;
-          El.set(pk);
-          const c32* q = kbw + e + (El.o[i] + El.o[j]);
-          c32 v[n_][n_];
-#pragma unroll
-          for (int x = 0; x < n_; ++x)
-#pragma unroll
-            for (int z = 0; z < n_; ++z) v[x][z] = q[El.at(x, i) + El.at(z, j)];
-          const c32 ye = y[r];
-          const int ri = ket_digit(pk, i) * R::gr, rj = ket_digit(pk, j) * R::gr;
+        if constexpr (RThread<d, N>::SHARE) {
+          // coupling by coupling: its rows once for all elements
 #pragma unroll
           for (int k = 0; k < MC; ++k) {
             if (k >= nc) continue;
             const int u = uni(A->rp_u[p][k]);
             const float g = A->rp_g[p][k], sg = A->rp_s[p][k];
+            uint32_t pk = Th.pk[0];
+            asm volatile("" : "+v"(pk));
+            RElem<d, N> El;
+            El.set(pk);
             float a[R::gr], b[R::gr];
-            r_row<d, N>(gt + (i * 2 + (u & 1)) * d * R::gr + ri, a, R::gr, R::gr);
-            r_row<d, N>(gt + (j * 2 + (u >> 1)) * d * R::gr + rj, b, R::gr, R::gr);
+            r_row<d, N>(gt + ((j * 2 + (u >> 1)) * d + ket_digit(pk, j)) * R::gr, b, R::gr, R::gr);
+            if (i > 0) r_row<d, N>(gt + ((i * 2 + (u & 1)) * d + ket_digit(pk, i)) * R::gr, a, R::gr, R::gr);
             float ta = 0.f, t0 = 0.f, t1 = 0.f, t2 = 0.f, u0 = 0.f, u1 = 0.f, u2 = 0.f;
 #pragma unroll
-            for (int x = 0; x < n_; ++x) {
-              float rr = 0.f, rm = 0.f, qr = 0.f, qm = 0.f;
+            for (int r = 0; r < E; ++r) {
+              if (i == 0) r_row<d, N>(gt + ((u & 1) * d + r) * R::gr, a, R::gr, R::gr);
+              const c32 ye = y[r];
+              c32 v[n_][n_];
 #pragma unroll
-              for (int z = 0; z < n_; ++z) {
-                rr = fmaf(b[z], v[x][z].x, rr);
-                rm = fmaf(b[z], v[x][z].y, rm);
-                qr = fmaf(a[z], v[z][x].x, qr);
-                qm = fmaf(a[z], v[z][x].y, qm);
+              for (int x = 0; x < n_; ++x)
+#pragma unroll
+                for (int z = 0; z < n_; ++z) {
+                  const int b0 = ((r & 1) ^ 1) + 2 * x;   // mode 0's level, in the thread
+                  v[x][z] = i == 0 ? kbw[tid + El.o[j] + El.at(z, j) + (b0 < d ? b0 : 1 - (r & 1)) * T]
+                                   : kbw[tid + El.o[i] + El.o[j] + El.at(x, i) + El.at(z, j) + r * T];
+                }
+#pragma unroll
+              for (int x = 0; x < n_; ++x) {
+                float rr = 0.f, rm = 0.f, qr = 0.f, qm = 0.f;
+#pragma unroll
+                for (int z = 0; z < n_; ++z) {
+                  rr = fmaf(b[z], v[x][z].x, rr);
+                  rm = fmaf(b[z], v[x][z].y, rm);
+                  qr = fmaf(a[z], v[z][x].x, qr);
+                  qm = fmaf(a[z], v[z][x].y, qm);
+                }
+                const float wi = fmaf(rr, ye.y, -rm * ye.x), wj = fmaf(qr, ye.y, -qm * ye.x);
+                ta = fmaf(a[x], wi, ta);
+                t0 = fmaf(a[n_ + x], wi, t0);
+                t1 = fmaf(a[2 * n_ + x], wi, t1);
+                t2 = fmaf(a[3 * n_ + x], wi, t2);
+                u0 = fmaf(b[n_ + x], wj, u0);
+                u1 = fmaf(b[2 * n_ + x], wj, u1);
+                u2 = fmaf(b[3 * n_ + x], wj, u2);
               }
-              const float wi = fmaf(rr, ye.y, -rm * ye.x), wj = fmaf(qr, ye.y, -qm * ye.x);
-              ta = fmaf(a[x], wi, ta);
-              t0 = fmaf(a[n_ + x], wi, t0);
-              t1 = fmaf(a[2 * n_ + x], wi, t1);
-              t2 = fmaf(a[3 * n_ + x], wi, t2);
-              u0 = fmaf(b[n_ + x], wj, u0);
-              u1 = fmaf(b[2 * n_ + x], wj, u1);
-              u2 = fmaf(b[3 * n_ + x], wj, u2);
+              // keeps the sums here: moved behind all reads they hold them all
+              asm volatile("" : "+v"(ta), "+v"(t0), "+v"(t1), "+v"(t2), "+v"(u0), "+v"(u1), "+v"(u2));
             }
-            vc[k] = fmaf(sg, ta, vc[k]);
+            vc[k] = sg * ta;
             t[i][0] = fmaf(g, t0, t[i][0]);
             t[i][1] = fmaf(g, t1, t[i][1]);
             t[i][2] = fmaf(g, t2, t[i][2]);
             t[j][0] = fmaf(g, u0, t[j][0]);
             t[j][1] = fmaf(g, u1, t[j][1]);
             t[j][2] = fmaf(g, u2, t[j][2]);
+            __builtin_amdgcn_sched_barrier(0);
           }
-          __builtin_amdgcn_sched_barrier(0);
+        } else {
+#pragma unroll
+          for (int r = 0; r < E; ++r) {
+            const int e = tid + r * T;
+            if (e >= L) continue;
+            uint32_t pk = Th.pk[r];
+            asm volatile("" : "+v"(pk));
+            RElem<d, N> El;
+            El.set(pk);
+            const c32* q = kbw + e + (El.o[i] + El.o[j]);
+            c32 v[n_][n_];
+#pragma unroll
+            for (int x = 0; x < n_; ++x)
+#pragma unroll
+              for (int z = 0; z < n_; ++z) v[x][z] = q[El.at(x, i) + El.at(z, j)];
+            const c32 ye = y[r];
+            const int ri = ket_digit(pk, i) * R::gr, rj = ket_digit(pk, j) * R::gr;
+#pragma unroll
+            for (int k = 0; k < MC; ++k) {
+              if (k >= nc) continue;
+              const int u = uni(A->rp_u[p][k]);
+              const float g = A->rp_g[p][k], sg = A->rp_s[p][k];
+              float a[R::gr], b[R::gr];
+              r_row<d, N>(gt + (i * 2 + (u & 1)) * d * R::gr + ri, a, R::gr, R::gr);
+              r_row<d, N>(gt + (j * 2 + (u >> 1)) * d * R::gr + rj, b, R::gr, R::gr);
+              float ta = 0.f, t0 = 0.f, t1 = 0.f, t2 = 0.f, u0 = 0.f, u1 = 0.f, u2 = 0.f;
+#pragma unroll
+              for (int x = 0; x < n_; ++x) {
+                float rr = 0.f, rm = 0.f, qr = 0.f, qm = 0.f;
+#pragma unroll
+                for (int z = 0; z < n_; ++z) {
+                  rr = fmaf(b[z], v[x][z].x, rr);
+                  rm = fmaf(b[z], v[x][z].y, rm);
+                  qr = fmaf(a[z], v[z][x].x, qr);
+                  qm = fmaf(a[z], v[z][x].y, qm);
+                }
+                const float wi = fmaf(rr, ye.y, -rm * ye.x), wj = fmaf(qr, ye.y, -qm * ye.x);
+                ta = fmaf(a[x], wi, ta);
+                t0 = fmaf(a[n_ + x], wi, t0);
+                t1 = fmaf(a[2 * n_ + x], wi, t1);
+                t2 = fmaf(a[3 * n_ + x], wi, t2);
+                u0 = fmaf(b[n_ + x], wj, u0);
+                u1 = fmaf(b[2 * n_ + x], wj, u1);
+                u2 = fmaf(b[3 * n_ + x], wj, u2);
+              }
+              vc[k] = fmaf(sg, ta, vc[k]);
+              t[i][0] = fmaf(g, t0, t[i][0]);
+              t[i][1] = fmaf(g, t1, t[i][1]);
+              t[i][2] = fmaf(g, t2, t[i][2]);
+              t[j][0] = fmaf(g, u0, t[j][0]);
+              t[j][1] = fmaf(g, u1, t[j][1]);
+              t[j][2] = fmaf(g, u2, t[j][2]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
 #pragma unroll
         for (int k = 0; k < MC; ++k) {
@@ -780,29 +934,34 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
         const bool drv = (Th.dmask >> m) & 1;
         const int u = uni(A->rd_u[m]);
         float vd = 0.f;
+        constexpr bool once = RThread<d, N>::SHARE;   // m > 0: the rows of element 0 are all's
+        float4 de;
+        float a[R::gr];
 #pragma unroll
         for (int r = 0; r < E; ++r) {
           const int e = tid + r * T;
           if (e >= L) continue;
-          uint32_t pk = Th.pk[r];
+          uint32_t pk = Th.pk[once ? 0 : r];
           asm volatile("" : "+v"(pk));
-          const int a_ = ket_digit(pk, m);
+          const int a_ = once && m == 0 ? r : ket_digit(pk, m);
           const c32 ye = y[r];
-          const float4 de = *reinterpret_cast<const float4*>(gt + R::off_e + (m * d + a_) * 4);
+          if (!once || m == 0 || r == 0) {
+            de = *reinterpret_cast<const float4*>(gt + R::off_e + (m * d + a_) * 4);
+            if (drv) r_row<d, N>(gt + ((m * 2 + u) * d + a_) * R::gr, a, R::gr, R::gr);
+          }
           const float w0 = fmaf(kb[r].x, ye.y, -kb[r].y * ye.x);
           t[m][0] = fmaf(de.x, w0, t[m][0]);
           t[m][1] = fmaf(de.y, w0, t[m][1]);
           t[m][2] = fmaf(de.z, w0, t[m][2]);
           if (drv) {
-            float a[R::gr];
-            r_row<d, N>(gt + ((m * 2 + u) * d + a_) * R::gr, a, R::gr, R::gr);
             RElem<d, N> El;
             El.set(pk);
             const c32* q = kbw + e + El.o[m];
             float t0 = 0.f, t1 = 0.f, t2 = 0.f;
 #pragma unroll
             for (int x = 0; x < n_; ++x) {
-              const c32 v = q[El.at(x, m)];
+              const int b0 = ((r & 1) ^ 1) + 2 * x;
+              const c32 v = once && m == 0 ? kb[b0 < d && b0 < E ? b0 : 0] : q[El.at(x, m)];
               const float w = fmaf(v.x, ye.y, -v.y * ye.x);
               vd = fmaf(a[x], w, vd);
               t0 = fmaf(a[n_ + x], w, t0);
