@@ -199,7 +199,11 @@ scp_status scp_system_set_frame(scp_system* sys, int32_t real_frame);
  * without checkpoints of a device with D < 64 and at least 64 steps is split
  * over time under engine 0: runs of steps propagate the identity side by side
  * on engine 1's stepper and are multiplied onto the columns in FP64
- * (scp_solve_engine reports 1).  Both engines compute the same RK4 steps and the same
+ * (scp_solve_engine reports 1).  A forward without checkpoints of eight
+ * three-level modes in the real frame, under the same conditions on operators
+ * and couplings, runs in the gather engine's manner, one workgroup per column,
+ * for any number of columns (scp_solve_engine reports 1).  A workspace size
+ * does for either frame setting of a system.  Both engines compute the same RK4 steps and the same
  * discrete adjoint in FP32 with a compensated state; results differ by
  * rounding.  scp_system_set_engine: SCP_EINVAL for engine 2 on a device the
  * gather engine cannot run; a change forgets the recorded checkpoints.
@@ -385,10 +389,11 @@ scp_status scp_fidelity_local(const void* U, int64_t D, int32_t S, int32_t preci
  * state (D x S complex64, device).  The discrete adjoint of Sec. 2.5 (the
  * per-step derivative sum and the costate chain rule) walks the checkpoint
  * segments back, recomputing each segment's states, on the engine
- * scp_solve_engine(opts, with_grad = 1) names.  The gather engine walks one
- * segment per launch while other workgroups of the same launch recompute the
- * next segment's states (two stage-input buffers); its per-stage sums are
- * folded in a fixed order, so both engines' gradients are deterministic.
+ * scp_solve_engine(opts, with_grad = 1) names.  The gather engine first
+ * sweeps the costate alone back over all segments, then recomputes and walks
+ * several segments side by side (a buffer of stage inputs each); its per-step
+ * sums are folded in a fixed order, so both engines' gradients are
+ * deterministic.
  *   psi0 != NULL: the checkpoints are first computed here by a forward
  *     propagation of psi0 (D x S complex64, device) into the workspace;
  *   psi0 == NULL: the checkpoints of the system's most recent scp_propagate

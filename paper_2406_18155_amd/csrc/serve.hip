@@ -213,28 +213,36 @@ scp_status admit(scp_server* sv, Request* r) {
   const size_t o_psi = take(S * D * 8), o_hi = take(S * D * 8), o_lo = take(S * D * 8),
                o_cot = take(S * D * 8), o_rows = take(r->d_c * 8), o_cols = take(r->d_c * 4),
                o_tgt = take((size_t)r->d_c * r->d_c * 16), o_tau = take(16);
-  size_t o_ck = 0, o_seg = 0, o_sum = 0, o_ls = 0, o_part = 0, o_g = 0;
+  size_t o_ck = 0, o_seg = 0, o_sum = 0, o_ls = 0, o_part = 0, o_g = 0, seg = 0;
   if (r->gather) {
     o_g = take(r->gws_bytes);
   } else if (r->want_grad) {
     o_ck = take((size_t)r->nckpt * S * D * 16);
+    o_sum = take(S * D * 8);
+    o_ls = take(S * D * 8);
+    o_part = take((size_t)r->nwg * 4 * std::max(1, P.nacc) * 8);
     // Several segments recomputed side by side, up to a workgroup per compute
     // unit, cost the time of one: a request of few workgroups leaves most of
-    // the chip idle, and its recompute is a quarter of its reverse walk (16
-    // mixed requests, the longest of 32 workgroups: 786 -> 641 ms).  The buffers
-    // beyond the first come from the free half of the budget only.
-    const size_t seg = align256((size_t)r->ce * 4 * S * D * 8);
+    // the chip idle, and its recompute takes a third of its reverse walk's time
+    // (16 mixed requests, the longest a 4-fluxonium gradient of two workgroups:
+    // 786 -> 641 ms).  The buffers beyond the first come from the free half of
+    // the budget only.
+    seg = align256((size_t)r->ce * 4 * S * D * 8);
     const size_t half = sv->budget / 2, in_use = sv->used + r->bytes;
     r->nbuf = std::max(1, std::min({8, 256 / r->nwg, r->nckpt}));
     if (in_use >= half) r->nbuf = 1;
     else r->nbuf = (int)std::min<size_t>(r->nbuf, 1 + (half - in_use) / seg);
     r->rec_next = r->nckpt;
-    o_seg = take(r->nbuf * seg);
-    o_sum = take(S * D * 8);
-    o_ls = take(S * D * 8);
-    o_part = take((size_t)r->nwg * 4 * std::max(1, P.nacc) * 8);
+    o_seg = take(r->nbuf * seg);   // last: the extra ones can be left out
   }
-  if (hipMalloc(&r->dmem, off) != hipSuccess) {
+  hipError_t got = hipMalloc(&r->dmem, off);
+  if (got != hipSuccess && r->nbuf > 1) {
+    (void)hipGetLastError();
+    off -= (r->nbuf - 1) * seg;
+    r->nbuf = 1;
+    got = hipMalloc(&r->dmem, off);
+  }
+  if (got != hipSuccess) {
     scp_destroy(sys);
     r->sys = nullptr;
     return fail(SCP_ENOMEM, "request allocation");
