@@ -593,6 +593,7 @@ scp_status make_plan(scp_system* sys) {
     for (int a = 0; a < d; ++a)
       for (int b = 0; b < d; ++b) {
         const double v = std::abs(o[a * d + b]);
+        if (!std::isfinite(v)) return false;   // reaches the result in the general kernels
         big = std::max(big, v);
         if (((a + b) & 1) == 0) even = std::max(even, v);
       }
