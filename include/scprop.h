@@ -121,6 +121,8 @@ typedef struct {
   const double* par;   /* n_par envelope parameters (host)                  */
 } scp_drive_desc;
 
+/* At most 256 drives and 256 pulse parameters in all, and four couplings on one
+ * operator pair of two modes. */
 typedef struct {
   int32_t n_modes, n_couplings, n_drives, n_steps;
   double T;            /* pulse length; step h = T / n_steps                */

@@ -18,8 +18,10 @@ constexpr int MAXL = 8;        // layouts per stage
 constexpr int MAXRB = 64;      // register block (complex amplitudes per thread per vector)
 constexpr int MAXSLOTS = 48;   // (mode, op) slots
 constexpr int MAXPAIRS = 48;   // (first slot, partner mode) pairs
-constexpr int MAXGROUPS = 48;
+constexpr int MAXGROUPS = 48;  // driven operators
 constexpr int MAXPULSE = 256;  // pulse parameters
+constexpr int MAXDRIVES = MAXPULSE;     // a drive has one parameter at least
+constexpr int MAXCOUP = 4 * MAXPAIRS;   // four couplings on a pair at most
 constexpr int WG_THREADS = 256;
 
 // Canonical per-layout term list: every pair term has its first factor at
@@ -52,9 +54,9 @@ struct Plan {
   float delta[17][8];          // eps - frame per mode (FP32); row 16 is zero
   int32_t slot_mode[MAXSLOTS];
   int32_t slot_op[MAXSLOTS];
-  float coup_g[MAXPAIRS];
-  int32_t coup_slot_i[MAXPAIRS], coup_slot_j[MAXPAIRS];
-  DriveDev drives[MAXGROUPS];
+  float coup_g[MAXCOUP];
+  int32_t coup_slot_i[MAXCOUP], coup_slot_j[MAXCOUP];
+  DriveDev drives[MAXDRIVES];
   int32_t layout_of_mode[16];  // a layout whose register modes contain the mode
   int32_t pos_of_mode[16];     // its register position there
   int32_t pair_ncoup[MAXPAIRS];
@@ -71,8 +73,8 @@ struct Plan {
   float deps[16][3][8];            // d eps / d(EJ, EC, EL) per mode
   int32_t lmode[MAXL][8];          // mode at each register position of each layout (-1: none)
   int32_t mdrv_off[17];            // drives of mode m: mdrv[mdrv_off[m] .. mdrv_off[m+1])
-  int32_t mdrv[MAXGROUPS];         // drive indices grouped by mode
-  int32_t mdrv_first[MAXGROUPS];   // 1: first drive on its operator slot
+  int32_t mdrv[MAXDRIVES];         // drive indices grouped by mode
+  int32_t mdrv_first[MAXDRIVES];   // 1: first drive on its operator slot
   int32_t nacc;                    // gradient accumulators: npulse + 3 N + ncoup
   // Real frame (every term a real operator: each operator is real or i times
   // real, both factors of a pair term of one kind, drives on real operators):

@@ -185,6 +185,7 @@ scp_status validate(const scp_system_desc* ds) {
       return fail(SCP_EINVAL, "transmon has no phase operator");
     if (!std::isfinite(C.g)) return fail(SCP_EINVAL, "non-finite coupling");
   }
+  if (ds->n_drives > MAXDRIVES) return fail(SCP_EINVAL, "too many drives");
   for (int k = 0; k < ds->n_drives; ++k) {
     const scp_drive_desc& R = ds->drives[k];
     if (R.mode < 0 || R.mode >= ds->n_modes) return fail(SCP_EINVAL, "drive mode invalid");

@@ -124,7 +124,7 @@ __global__ void ctable_kernel(TabStatic ts, const DriveStatic* __restrict__ dr,
 // out[p][m] = scale_m sum over mode m's drives of c(t_p), summed in FP64.
 struct RcStatic {
   int npt, ndrives, N;
-  int mode[MAXGROUPS];
+  int mode[MAXDRIVES];
   double scale[SCP_MAX_MODES];
 };
 __global__ void rc_kernel(RcStatic R, const double* __restrict__ ctab64, float* __restrict__ out) {
