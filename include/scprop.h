@@ -137,9 +137,9 @@ typedef struct {
                           1: complex FP64 plain path (one launch per term)  */
   int32_t ckpt_every;  /* checkpoint interval for the adjoint; 0 = ceil(sqrt(N)) */
   int32_t with_ckpt;   /* propagate: 1 = keep checkpoints in the workspace  */
-  size_t workspace_bytes;  /* size of the workspace passed with these opts; a
-                              call whose workspace_size exceeds it is refused
-                              (SCP_EINVAL) before any launch               */
+  size_t workspace_bytes;  /* size of the workspace passed with these opts (see
+                              scp_workspace_size); a call that has no path in
+                              it is refused (SCP_EINVAL) before any launch  */
 } scp_solve_opts;
 
 typedef struct scp_system scp_system;
@@ -210,8 +210,8 @@ scp_status scp_system_set_frame(scp_system* sys, int32_t real_frame);
  * rounding.  scp_system_set_engine: SCP_EINVAL for engine 2 on a device the
  * gather engine cannot run; a change forgets the recorded checkpoints.
  * scp_solve_engine writes (host) which engine a solve with opts (and the
- * adjoint if with_grad) runs on: 1 or 2 (0 for precision 1, the plain FP64
- * path).  Not while a call on the system is in flight. */
+ * adjoint if with_grad) runs on in a workspace of scp_workspace_size bytes: 1
+ * or 2 (0 for precision 1, the plain FP64 path).  Not while a call on the system is in flight. */
 scp_status scp_system_set_engine(scp_system* sys, int32_t engine);
 scp_status scp_solve_engine(const scp_system* sys, const scp_solve_opts* opts, int32_t with_grad,
                             int32_t* engine);
@@ -249,7 +249,17 @@ scp_status scp_energy_tensor(const scp_system* sys, double* E_out, void* stream)
 scp_status scp_static_zz(const scp_system* sys, int32_t qi, int32_t qj, double* zeta_out,
                          double* grad_out, void* stream);
 
-/* Workspace bytes a propagate (+ adjoint if with_grad) needs for opts. */
+/* Workspace bytes of a propagate (+ adjoint if with_grad) for opts: those of the
+ * path that scp_solve_engine describes.  In less (a workspace made for other
+ * opts, or all that the caller has) the gather engine's adjoint walks fewer
+ * segments side by side, down to one, and under engine 0 a call that still does
+ * not fit runs on the register-layout stepper alone, with the results of engine
+ * 1; that size is the smallest, and grows with the columns, the checkpoints and
+ * with_grad, so a workspace for the gradient of n columns always does for a
+ * forward, with or without checkpoints, of as many columns or fewer.  Below it,
+ * SCP_EINVAL.  An adjoint from checkpoints runs on the engine that wrote them:
+ * with_ckpt in a workspace of another size than its own takes the one whose
+ * adjoint fits it. */
 scp_status scp_workspace_size(const scp_system* sys, const scp_solve_opts* opts, int32_t with_grad,
                               size_t* bytes);
 
@@ -271,8 +281,8 @@ scp_status scp_apply_generator(const scp_system* sys, int32_t step, int32_t stag
  * register-layout stepper, or for few columns of a small device the gather
  * engine, one workgroup per column in LDS, with the same RK4 arithmetic:
  * compensated FP32 state, FP32 stage tables).  The workspace layout is the
- * engine's.  SCP_EINVAL if opts->workspace_bytes is below
- * scp_workspace_size(opts, with_grad = 0). */
+ * engine's.  SCP_EINVAL if opts->workspace_bytes holds no path (see
+ * scp_workspace_size). */
 scp_status scp_propagate(scp_system* sys, const scp_solve_opts* opts, void* workspace,
                          const void* psi0, void* psiT, void* stream);
 
@@ -405,8 +415,8 @@ scp_status scp_fidelity_local(const void* U, int64_t D, int32_t S, int32_t preci
  *     another system on this workspace pointer.  Otherwise SCP_EINVAL, before
  *     any launch.
  * The checkpoints stay valid, so several cotangents may follow one forward.
- * SCP_EINVAL if opts->workspace_bytes is below scp_workspace_size(opts,
- * with_grad = 1).  Synchronises ``stream``.  SCP_ENONFINITE if any gradient
+ * SCP_EINVAL if opts->workspace_bytes holds no path (see scp_workspace_size).
+ * Synchronises ``stream``.  SCP_ENONFINITE if any gradient
  * entry is not finite. */
 scp_status scp_propagate_adjoint(scp_system* sys, const scp_solve_opts* opts, void* workspace,
                                  const void* psi0, const void* cotangent, double* grad_out,

@@ -2358,8 +2358,9 @@ struct GcLayout {
   int nseg;   // segments walked side by side
 };
 
-static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad, GcLayout& w,
-                            GArgs* Aout) {
+// nseg > 0: that many segments side by side at most.
+static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad, int nseg,
+                            GcLayout& w, GArgs* Aout) {
   if (!g_supported(sys->d, sys->n_modes, false))
     return fail(SCP_EINVAL, "gather engine: no compiled stepper for this d and mode count");
   GArgs A;
@@ -2375,6 +2376,7 @@ static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad
   // (each holds a buffer of stage inputs); two segments at least, as many
   // buffers as a walk one segment after the other needs to hide its recompute
   w.nseg = std::min(w.nck, std::max(2, (512 + S - 1) / S));
+  if (nseg > 0) w.nseg = std::min(w.nseg, nseg);
   size_t off = 0;
   w.args = off;
   off += align256(sizeof(GArgs));
@@ -2407,24 +2409,40 @@ static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad
 
 scp_status gather_grad_check(const scp_system* sys) {
   GcLayout w;
-  return gc_layout(sys, 1, 1, true, w, nullptr);
+  return gc_layout(sys, 1, 1, true, 0, w, nullptr);
 }
 
 size_t gather_grad_workspace_bytes(const scp_system* sys, int S, int ce, bool with_grad) {
   GcLayout w;
-  if (gc_layout(sys, S, ce, with_grad, w, nullptr) != SCP_OK) {
+  if (gc_layout(sys, S, ce, with_grad, 0, w, nullptr) != SCP_OK) {
     set_error("");
     return 0;
   }
   return w.total;
 }
 
+// Segments side by side that a gradient's workspace of `bytes` has room for (0: none).
+int gather_grad_segments(const scp_system* sys, int S, int ce, size_t bytes) {
+  GcLayout w;
+  int n = 0;   // the most, then at most what the room left by the rest allows
+  for (;;) {
+    if (gc_layout(sys, S, ce, true, n, w, nullptr) != SCP_OK) {
+      set_error("");
+      return 0;
+    }
+    if (w.total <= bytes) return w.nseg;
+    const size_t seg = (size_t)S * std::min(ce, sys->n_steps) * 4 * sys->D * sizeof(float2);
+    n = w.nseg - (int)std::min<size_t>(w.nseg, (w.total - bytes + seg - 1) / seg);
+    if (n < 1) return 0;
+  }
+}
+
 // Args and adjoint description into the workspace (and the stage tables when
 // `tables`).
-static scp_status gc_prepare(scp_system* sys, int S, int ce, bool with_grad, char* base,
+static scp_status gc_prepare(scp_system* sys, int S, int ce, bool with_grad, int nseg, char* base,
                              size_t ws_bytes, const float2* x0, float2* xT, const float2* cot,
                              bool tables, GcLayout& w, GArgs& A, hipStream_t st) {
-  SCP_TRY(gc_layout(sys, S, ce, with_grad, w, &A));
+  SCP_TRY(gc_layout(sys, S, ce, with_grad, nseg, w, &A));
   if (ws_bytes < w.total) return fail(SCP_EINVAL, "workspace too small");
   GArgs* dargs = reinterpret_cast<GArgs*>(base + w.args);
   GAdj* dadj = reinterpret_cast<GAdj*>(base + w.adj);
@@ -2468,7 +2486,7 @@ scp_status launch_gather_ckpt_forward(scp_system* sys, int S, int ce, void* ws, 
   char* base = static_cast<char*>(ws);
   GcLayout w;
   GArgs A;
-  SCP_TRY(gc_prepare(sys, S, ce, false, base, ws_bytes, psi0, psiT, nullptr, true, w, A, st));
+  SCP_TRY(gc_prepare(sys, S, ce, false, 0, base, ws_bytes, psi0, psiT, nullptr, true, w, A, st));
   hipEvent_t t0 = timing_start(sys, st);
   HIPCHK(g_dispatch(sys->d, sys->n_modes, false, g_form(A), reinterpret_cast<GArgs*>(base + w.args),
                     reinterpret_cast<GAdj*>(base + w.adj), S, A.ntab, 0, sys->n_steps, nullptr,
@@ -2487,12 +2505,12 @@ static scp_status gc_fold(scp_system* sys, int S, char* base, const GcLayout& w,
 // The reverse walk from the checkpoints (and stage tables) that
 // launch_gather_ckpt_forward left in the same workspace: the costate sweep,
 // then the segments side by side.
-scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, void* ws, size_t ws_bytes,
+scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, int nseg, void* ws, size_t ws_bytes,
                                  const float2* cot, double* grad, hipStream_t st) {
   char* base = static_cast<char*>(ws);
   GcLayout w;
   GArgs A;
-  SCP_TRY(gc_prepare(sys, S, ce, true, base, ws_bytes, nullptr, nullptr, cot, false, w, A, st));
+  SCP_TRY(gc_prepare(sys, S, ce, true, nseg, base, ws_bytes, nullptr, nullptr, cot, false, w, A, st));
   const GArgs* dargs = reinterpret_cast<GArgs*>(base + w.args);
   const GAdj* dadj = reinterpret_cast<GAdj*>(base + w.adj);
   const int d = sys->d, N = sys->n_modes;
@@ -2513,7 +2531,7 @@ scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, void* ws, size_
 // wanted) followed by the compensated state [S][D] float4 between chunks.
 size_t gather_serve_bytes(const scp_system* sys, int S, int ce, bool grad) {
   GcLayout w;
-  if (gc_layout(sys, S, ce, grad, w, nullptr) != SCP_OK) {
+  if (gc_layout(sys, S, ce, grad, 0, w, nullptr) != SCP_OK) {
     set_error("");
     return 0;
   }
@@ -2524,7 +2542,7 @@ scp_status gather_serve_prepare(scp_system* sys, int S, int ce, bool grad, void*
                                 const float2* psi0, float2* psiT, const float2* cot, hipStream_t st) {
   GcLayout w;
   GArgs A;
-  return gc_prepare(sys, S, ce, grad, static_cast<char*>(ws), bytes, psi0, psiT, cot, true, w, A,
+  return gc_prepare(sys, S, ce, grad, 0, static_cast<char*>(ws), bytes, psi0, psiT, cot, true, w, A,
                     st);
 }
 
@@ -2534,7 +2552,7 @@ scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, vo
                              GServeInfo& out) {
   GcLayout w;
   GArgs A;
-  SCP_TRY(gc_layout(sys, S, ce, grad, w, &A));
+  SCP_TRY(gc_layout(sys, S, ce, grad, 0, w, &A));
   char* base = static_cast<char*>(ws);
   out.A = base + w.args;
   out.B = base + w.adj;
@@ -2642,7 +2660,7 @@ scp_status gather_launch_adj_batched(int d, int N, int form, const GItem* items,
 scp_status gather_serve_gradient(scp_system* sys, int S, int ce, void* ws, std::vector<double>& grad,
                                  hipStream_t st) {
   GcLayout w;
-  SCP_TRY(gc_layout(sys, S, ce, true, w, nullptr));
+  SCP_TRY(gc_layout(sys, S, ce, true, 0, w, nullptr));
   grad.assign(w.nacc, 0.0);
   return gc_fold(sys, S, static_cast<char*>(ws), w, grad.data(), st);
 }

@@ -208,6 +208,7 @@ struct scp_system {
   // adjoint called without psi0): where, for which opts, and its stamp
   const void* ck_ws = nullptr;
   int ck_S = 0, ck_ce = 0, ck_N = 0;
+  bool ck_gather = false;   // the gather engine wrote them (its layout)
   uint64_t ck_gen = 0;          // 0: no valid checkpoints
   // kernel timing (scp_system_set_timing): HIP events recorded on the launch
   // stream around each forward, recompute and reverse launch
@@ -301,9 +302,10 @@ scp_status launch_gather_forward(scp_system* sys, int S, void* ws, size_t ws_byt
                                  const float2* psi0, float2* psiT, hipStream_t st);
 scp_status gather_grad_check(const scp_system* sys);
 size_t gather_grad_workspace_bytes(const scp_system* sys, int S, int ce, bool with_grad);
+int gather_grad_segments(const scp_system* sys, int S, int ce, size_t bytes);
 scp_status launch_gather_ckpt_forward(scp_system* sys, int S, int ce, void* ws, size_t ws_bytes,
                                       const float2* psi0, float2* psiT, hipStream_t st);
-scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, void* ws, size_t ws_bytes,
+scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, int nseg, void* ws, size_t ws_bytes,
                                  const float2* cot, double* grad, hipStream_t st);
 // A workgroup's work item of a batched gather-engine launch (serving).
 struct GItem {

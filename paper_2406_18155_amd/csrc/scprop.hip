@@ -22,11 +22,12 @@ static std::mutex g_ck_mu;
 static std::map<const void*, std::pair<const scp_system*, uint64_t>> g_ck_owner;
 static uint64_t g_ck_next = 0;
 
-static void ck_record(scp_system* sys, const void* ws, int S, int ce) {
+static void ck_record(scp_system* sys, const void* ws, int S, int ce, bool gather) {
   std::lock_guard<std::mutex> lk(g_ck_mu);
   sys->ck_ws = ws;
   sys->ck_S = S;
   sys->ck_ce = ce;
+  sys->ck_gather = gather;
   sys->ck_N = sys->n_steps;
   sys->ck_gen = ++g_ck_next;
   g_ck_owner[ws] = std::make_pair((const scp_system*)sys, sys->ck_gen);
@@ -889,7 +890,12 @@ struct WsLayout {
   bool gather_grad = false;   // checkpoints / adjoint on the gather engine (its own layout)
   bool split = false;         // a forward-only solve of a small device, split over time
   bool column = false;        // a forward-only solve in the real form's column kernel
+  int nseg = 0;               // gather-engine adjoint: segments side by side (0: the most)
 };
+
+int ckpt_interval(const scp_system* sys, const scp_solve_opts* o) {
+  return o->ckpt_every > 0 ? o->ckpt_every : (int)std::ceil(std::sqrt((double)sys->n_steps));
+}
 
 // Which engine runs an FP32 solve: the system's choice, else (automatic) the
 // gather engine when the register-layout stepper would leave most of the chip
@@ -898,7 +904,7 @@ WsLayout ws_layout_in(const scp_system* sys, const scp_solve_opts* o, int with_g
                       bool allow_gather, bool real) {
   WsLayout w;
   const int N = sys->n_steps;
-  w.ce = o->ckpt_every > 0 ? o->ckpt_every : (int)std::ceil(std::sqrt((double)N));
+  w.ce = ckpt_interval(sys, o);
   w.nckpt = (N + w.ce - 1) / w.ce;
   const size_t S = (size_t)o->n_cols, D = (size_t)sys->D;
   size_t off = 0;
@@ -954,13 +960,50 @@ WsLayout ws_layout_in(const scp_system* sys, const scp_solve_opts* o, int with_g
 }
 
 // The automatic choice depends on the frame; a workspace does for either.
-WsLayout ws_layout(const scp_system* sys, const scp_solve_opts* o, int with_grad,
-                   bool allow_gather = true) {
+WsLayout ws_layout(const scp_system* sys, const scp_solve_opts* o, int with_grad) {
   const bool real = sys->plan.real_frame != 0;
-  WsLayout w = ws_layout_in(sys, o, with_grad, allow_gather, real);
+  WsLayout w = ws_layout_in(sys, o, with_grad, true, real);
   if (sys->real_ok && sys->engine == 0)
-    w.total = std::max(w.total, ws_layout_in(sys, o, with_grad, allow_gather, !real).total);
+    w.total = std::max(w.total, ws_layout_in(sys, o, with_grad, true, !real).total);
   return w;
+}
+
+// The layout of a call.  In a workspace below ws_layout's size (made for other
+// opts, or all that the caller has) a smaller one that fits: the gather
+// engine's adjoint with fewer segments side by side; under the automatic choice
+// the register-layout stepper, whose workspace is the smallest and grows with
+// the columns, the checkpoints and the gradient.  Checkpoints are written where
+// an adjoint in the same workspace can run (one of just the forward's size has
+// room for none).  from_ck: an adjoint from recorded checkpoints, whose layout
+// is that of the engine that wrote them.
+scp_status ws_fit(const scp_system* sys, const scp_solve_opts* o, int with_grad, bool from_ck,
+                  WsLayout& w) {
+  const size_t have = o->workspace_bytes;
+  w = ws_layout(sys, o, with_grad);
+  const size_t need = w.total;
+  const bool gather = w.gather_grad;
+  if (gather && !with_grad && sys->engine == 0 && have != need &&
+      gather_grad_segments(sys, o->n_cols, w.ce, have) == 0 &&
+      ws_layout_in(sys, o, 1, false, false).total <= have) {
+    w = ws_layout_in(sys, o, 0, false, false);
+    return SCP_OK;
+  }
+  if (!from_ck || sys->ck_gather == gather) {
+    if (have >= need) return SCP_OK;
+    w = ws_layout_in(sys, o, with_grad, true, sys->plan.real_frame != 0);
+    if (have >= w.total) return SCP_OK;
+    if (gather && with_grad) {
+      w.nseg = gather_grad_segments(sys, o->n_cols, w.ce, have);
+      if (w.nseg > 0) return SCP_OK;
+    }
+  }
+  if (sys->engine == 0 && o->precision == 0 && !(from_ck && sys->ck_gather)) {
+    w = ws_layout_in(sys, o, with_grad, false, false);
+    if (have >= w.total) return SCP_OK;
+  }
+  return fail(SCP_EINVAL, "workspace_bytes " + std::to_string(have) + " below the " +
+                              std::to_string(need) + " these opts need (scp_workspace_size" +
+                              (with_grad ? " with_grad = 1)" : ")"));
 }
 
 }  // namespace
@@ -1124,11 +1167,10 @@ scp_status scp_propagate(scp_system* sys, const scp_solve_opts* opts, void* work
   if (opts->n_cols < 1) return fail(SCP_EINVAL, "n_cols must be >= 1");
   if (opts->precision != 0 && opts->precision != 1) return fail(SCP_EINVAL, "precision must be 0 or 1");
   if (opts->ckpt_every < 0) return fail(SCP_EINVAL, "ckpt_every must be >= 0");
-  WsLayout w = ws_layout(sys, opts, 0);
   if (!workspace) return fail(SCP_EINVAL, "a workspace is needed (scp_workspace_size)");
-  if (opts->workspace_bytes < w.total)
-    return fail(SCP_EINVAL, "workspace_bytes " + std::to_string(opts->workspace_bytes) +
-                                " below the " + std::to_string(w.total) + " these opts need");
+  WsLayout w;
+  const scp_status fit = ws_fit(sys, opts, 0, false, w);
+  if (fit != SCP_OK) return fit;
   hipStream_t st = (hipStream_t)stream;
   ck_claim(sys, workspace);
   if (opts->precision == 1) {
@@ -1145,7 +1187,7 @@ scp_status scp_propagate(scp_system* sys, const scp_solve_opts* opts, void* work
     scp_status s = launch_gather_ckpt_forward(sys, opts->n_cols, w.ce, workspace,
                                               opts->workspace_bytes, (const float2*)psi0,
                                               (float2*)psiT, st);
-    if (s == SCP_OK) ck_record(sys, workspace, opts->n_cols, w.ce);
+    if (s == SCP_OK) ck_record(sys, workspace, opts->n_cols, w.ce, true);
     return s;
   }
   if (w.column) {
@@ -1160,7 +1202,7 @@ scp_status scp_propagate(scp_system* sys, const scp_solve_opts* opts, void* work
   ck_clear(sys);
   scp_status s = launch_rk4(sys, (const float2*)psi0, (float2*)psiT,
                             (float2*)((char*)workspace + w.lo), ck, w.ce, opts->n_cols, st);
-  if (s == SCP_OK && ck != nullptr) ck_record(sys, workspace, opts->n_cols, w.ce);
+  if (s == SCP_OK && ck != nullptr) ck_record(sys, workspace, opts->n_cols, w.ce, false);
   return s;
 }
 
@@ -1362,11 +1404,16 @@ scp_status scp_propagate_adjoint(scp_system* sys, const scp_solve_opts* opts, vo
   if (opts->precision != 0) return fail(SCP_EINVAL, "the adjoint runs on the FP32 path (precision 0)");
   if (opts->n_cols < 1) return fail(SCP_EINVAL, "n_cols must be >= 1");
   if (opts->ckpt_every < 0) return fail(SCP_EINVAL, "ckpt_every must be >= 0");
-  WsLayout w = ws_layout(sys, opts, 1);
-  if (opts->workspace_bytes < w.total)
-    return fail(SCP_EINVAL, "workspace_bytes " + std::to_string(opts->workspace_bytes) +
-                                " below the " + std::to_string(w.total) +
-                                " the adjoint needs (scp_workspace_size with_grad = 1)");
+  const bool from_ck =
+      psi0 == nullptr && ck_valid(sys, workspace, opts->n_cols, ckpt_interval(sys, opts));
+  WsLayout w;
+  const scp_status fit = ws_fit(sys, opts, 1, from_ck, w);
+  if (fit != SCP_OK) return fit;
+  if (psi0 == nullptr && !from_ck)
+    return fail(SCP_EINVAL,
+                "no checkpoints of this system for this workspace and opts: the last "
+                "scp_propagate must run with with_ckpt = 1 on the same workspace, n_cols and "
+                "ckpt_every (or pass psi0)");
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   if (w.gather_grad) {
@@ -1377,14 +1424,9 @@ scp_status scp_propagate_adjoint(scp_system* sys, const scp_solve_opts* opts, vo
                                                 opts->workspace_bytes, (const float2*)psi0,
                                                 nullptr, st);
       if (s != SCP_OK) return s;
-      ck_record(sys, workspace, opts->n_cols, w.ce);
-    } else if (!ck_valid(sys, workspace, opts->n_cols, w.ce)) {
-      return fail(SCP_EINVAL,
-                  "no checkpoints of this system for this workspace and opts: the last "
-                  "scp_propagate must run with with_ckpt = 1 on the same workspace, n_cols and "
-                  "ckpt_every (or pass psi0)");
+      ck_record(sys, workspace, opts->n_cols, w.ce, true);
     }
-    return launch_gather_adjoint(sys, opts->n_cols, w.ce, workspace, opts->workspace_bytes,
+    return launch_gather_adjoint(sys, opts->n_cols, w.ce, w.nseg, workspace, opts->workspace_bytes,
                                  (const float2*)cotangent, grad_out, st);
   }
   if (psi0 != nullptr) {
@@ -1393,12 +1435,7 @@ scp_status scp_propagate_adjoint(scp_system* sys, const scp_solve_opts* opts, vo
     scp_status s = launch_rk4(sys, (const float2*)psi0, nullptr, (float2*)(ws + w.lo),
                               (float4*)(ws + w.ckpt), w.ce, opts->n_cols, st);
     if (s != SCP_OK) return s;
-    ck_record(sys, workspace, opts->n_cols, w.ce);
-  } else if (!ck_valid(sys, workspace, opts->n_cols, w.ce)) {
-    return fail(SCP_EINVAL,
-                "no checkpoints of this system for this workspace and opts: the last "
-                "scp_propagate must run with with_ckpt = 1 on the same workspace, n_cols and "
-                "ckpt_every (or pass psi0)");
+    ck_record(sys, workspace, opts->n_cols, w.ce, false);
   }
   return finish_adjoint(sys, w, ws, cotangent, grad_out, opts->n_cols, st);
 }
@@ -1468,7 +1505,7 @@ scp_status scp_propagate_adjoint_noalloc(scp_system* sys, const scp_solve_opts* 
   if (opts->precision != 0) return fail(SCP_EINVAL, "the adjoint runs on the FP32 path (precision 0)");
   if (opts->n_cols < 1) return fail(SCP_EINVAL, "n_cols must be >= 1");
   if (opts->ckpt_every < 0) return fail(SCP_EINVAL, "ckpt_every must be >= 0");
-  WsLayout w = ws_layout(sys, opts, 1, false);
+  WsLayout w = ws_layout_in(sys, opts, 1, false, false);
   if (w.total > SCP_NOALLOC_SCRATCH_BYTES)
     return fail(SCP_EINVAL, "the adjoint needs " + std::to_string(w.total) +
                                 " bytes of workspace; the static scratch holds " +
