@@ -197,12 +197,16 @@ hipError_t g_real_segments(int d, int N, const GItem* items, const GArgs* dargs,
 // Open systems' real form (open_real.hip): forward (dadj != nullptr: with
 // checkpoints) and the whole reverse walk of S columns.
 bool l_real_supported(int d, int N);
-hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s);
-// Closed d = 3, N = 8 (D = 6561, above the gather engine's shapes): forward.
+hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, int nsteps,
+                          hipStream_t s);
+// Closed d = 3, N = 8 (D = 6561, above the gather engine's shapes): steps [n_lo, n_hi) of
+// a forward, the state from st_in / to st_out (nullable).
 bool l_column_supported(int d, int N);
-hipError_t l_real_column(int d, int N, const GArgs* dargs, int S, hipStream_t s);
+hipError_t l_real_column(int d, int N, const GArgs* dargs, int S, int n_lo, int n_hi,
+                         const float4* st_in, float4* st_out, hipStream_t s);
 hipError_t l_real_adjoint(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s);
-hipError_t g_real_phases(int d, int N, int nsteps, double h, const double f[][8], float2* ph,
+// Frame phases of the half steps [q_lo, q_lo + nq).
+hipError_t g_real_phases(int d, int N, int q_lo, int nq, double h, const double f[][8], float2* ph,
                          hipStream_t s);
 
 }  // namespace scp

@@ -1541,7 +1541,7 @@ template <int d, int N, bool OPEN>
 hipError_t g_launch(int form, const GArgs* dargs, const GAdj* dadj, int S, int ntab, int n_lo,
                     int n_hi, const float4* st_in, float4* st_out, hipStream_t s) {
   const bool par = form != 0;
-  if (OPEN && form == 2) return l_real_forward(d, N, dargs, dadj, S, s);
+  if (OPEN && form == 2) return l_real_forward(d, N, dargs, dadj, S, n_hi, s);
   if (!OPEN && form == 2)
     return g_real_forward(d, N, dadj != nullptr, nullptr, dargs, dadj, S, n_lo, n_hi, st_in, st_out, s);
   if (dadj != nullptr)
@@ -1888,9 +1888,10 @@ std::vector<float> build_gather_rows(const scp_system* sys, double* scale) {
   return rt;
 }
 
-// Frame phases of the real form into the workspace (open: of the matrix
-// elements, A's modes before B's).
-static scp_status g_phases(const scp_system* sys, bool open, float2* ph, hipStream_t st) {
+// Frame phases of the real form at the half steps [q_lo, q_lo + nq) into the
+// workspace (open: of the matrix elements, A's modes before B's).
+static scp_status g_phases(const scp_system* sys, bool open, int q_lo, int nq, float2* ph,
+                           hipStream_t st) {
   double f[GA_MAXM][8] = {{0}};
   const int N = sys->n_modes;
   for (int m = 0; m < N; ++m)
@@ -1898,7 +1899,7 @@ static scp_status g_phases(const scp_system* sys, bool open, float2* ph, hipStre
       f[m][a] = sys->modes[m].frame[a];
       if (open) f[N + m][a] = -sys->modes[m].frame[a];
     }
-  HIPCHK(g_real_phases(sys->d, open ? 2 * N : N, sys->n_steps, sys->h, f, ph, st));
+  HIPCHK(g_real_phases(sys->d, open ? 2 * N : N, q_lo, nq, sys->h, f, ph, st));
   return SCP_OK;
 }
 
@@ -2022,13 +2023,56 @@ static size_t g_ph_bytes(const scp_system* sys, bool open) {
   return align256((2 * (size_t)sys->n_steps + 1) * L * sizeof(float2));
 }
 
-// Workspace: [GArgs][stage tables [3N][ntab], or the real form's frame phases
-// [2N+1][L]; with the tables of an open system its jump bands [2N+1][N][d*d]].
-static size_t g_ws_bytes(const scp_system* sys, bool open, int ntab) {
+// A closed system's forward in the real form without checkpoints goes in runs of
+// steps, whose frame phases are formed before each: 256 MiB of them at most, so
+// that they do not grow with the steps (105 kB a step at D = 6561), the
+// compensated state carried between runs in the workspace: [phases
+// [2 run + 2][D]][state [S][D] float4].  A run is 70 ms or more at that size
+// (2557 steps of D = 6561); the launches between two cost 65 us.
+static int g_run_steps(const scp_system* sys) {
+  return (int)std::min<int64_t>(sys->n_steps, ((int64_t)256 << 20) / (2 * sys->D * sizeof(float2)));
+}
+static size_t g_run_ph_bytes(const scp_system* sys) {
+  return align256((2 * (size_t)g_run_steps(sys) + 2) * sys->D * sizeof(float2));
+}
+static size_t g_run_bytes(const scp_system* sys, int S) {
+  if (sys->d_rt == nullptr) return 0;
+  const bool one = sys->n_steps <= g_run_steps(sys);
+  return g_run_ph_bytes(sys) + (one ? 0 : align256((size_t)S * sys->D * sizeof(float4)));
+}
+
+// The runs: A's description at dargs, `at` the workspace behind it, step(n_lo,
+// n_hi, st_in, st_out) launches the stepper.
+template <typename F>
+static scp_status g_real_runs(scp_system* sys, GArgs A, GArgs* dargs, char* at, hipStream_t st, F step) {
+  const int N = sys->n_steps, run = g_run_steps(sys);
+  float2* ph = reinterpret_cast<float2*>(at);
+  float4* state = reinterpret_cast<float4*>(at + g_run_ph_bytes(sys));
+  for (int n = 0; n < N; n += run) {
+    const int n1 = std::min(N, n + run);
+    // the stepper counts half steps from the first one of all (an offset taken in
+    // the kernel cost 1 % of a step of D = 625)
+    A.ph = reinterpret_cast<const float2*>(reinterpret_cast<uintptr_t>(ph) -
+                                           (size_t)2 * n * sys->D * sizeof(float2));
+    hipLaunchKernelGGL(store_args_kernel, dim3(1), dim3(64), 0, st, A, dargs);
+    HIPCHK(hipGetLastError());
+    // the stepper reads one half step beyond the run's last, ahead of its use
+    SCP_TRY(g_phases(sys, false, 2 * n, std::min(2 * N, 2 * n1 + 1) - 2 * n + 1, ph, st));
+    hipEvent_t t0 = timing_start(sys, st);
+    HIPCHK(step(n, n1, n == 0 ? nullptr : state, n1 == N ? nullptr : state));
+    timing_stop(sys, t0, 0, st);
+  }
+  return SCP_OK;
+}
+
+// Workspace: [GArgs][stage tables [3N][ntab], with those of an open system its
+// jump bands [2N+1][N][d*d]; or, in the real form, the frame phases: of an open
+// system [2N+1][L], of a closed one as above].
+static size_t g_ws_bytes(const scp_system* sys, bool open, int S, int ntab) {
   const size_t dd = (size_t)sys->d * sys->d;
   size_t t = align256(3 * (size_t)sys->n_steps * ntab * sizeof(float2));
   if (open) t += align256((2 * (size_t)sys->n_steps + 1) * sys->n_modes * dd * sizeof(float2));
-  return align256(sizeof(GArgs)) + std::max(t, g_ph_bytes(sys, open));
+  return align256(sizeof(GArgs)) + std::max(t, open ? g_ph_bytes(sys, true) : g_run_bytes(sys, S));
 }
 
 static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const double* gammaphi,
@@ -2036,7 +2080,7 @@ static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const 
                         hipStream_t st) {
   GArgs A;
   SCP_TRY(g_args(sys, open, gamma1, gammaphi, A));
-  if (ws_bytes < g_ws_bytes(sys, open, A.ntab)) return fail(SCP_EINVAL, "workspace too small");
+  if (ws_bytes < g_ws_bytes(sys, open, S, A.ntab)) return fail(SCP_EINVAL, "workspace too small");
   char* w = static_cast<char*>(ws);
   GArgs* dargs = reinterpret_cast<GArgs*>(w);
   w += align256(sizeof(GArgs));
@@ -2063,11 +2107,17 @@ static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const 
     hipLaunchKernelGGL(jtab_kernel, dim3(js.nq), dim3(64), 0, st, js, jtab);
     HIPCHK(hipGetLastError());
   }
+  if (A.real && !open)
+    return g_real_runs(sys, A, dargs, reinterpret_cast<char*>(gtab), st,
+                       [&](int n_lo, int n_hi, const float4* st_in, float4* st_out) {
+                         return g_dispatch(d, N, false, g_form(A), dargs, nullptr, S, A.ntab, n_lo, n_hi,
+                                           st_in, st_out, st);
+                       });
   if (A.real) A.ph = gtab;
   hipLaunchKernelGGL(store_args_kernel, dim3(1), dim3(64), 0, st, A, dargs);
   HIPCHK(hipGetLastError());
   if (A.real) {
-    SCP_TRY(g_phases(sys, open, gtab, st));
+    SCP_TRY(g_phases(sys, true, 0, 2 * sys->n_steps + 1, gtab, st));
   } else {
     hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
     HIPCHK(hipGetLastError());
@@ -2092,7 +2142,7 @@ size_t lindblad_workspace_bytes(const scp_system* sys) {
   GArgs A;
   std::vector<double> one(sys->n_modes, 1.0);   // the largest table: relaxation on
   if (g_args(sys, true, one.data(), nullptr, A) != SCP_OK) return 0;
-  return g_ws_bytes(sys, true, A.ntab);
+  return g_ws_bytes(sys, true, 1, A.ntab);
 }
 
 scp_status launch_lindblad(scp_system* sys, const double* gamma1, const double* gammaphi, int S,
@@ -2103,13 +2153,12 @@ scp_status launch_lindblad(scp_system* sys, const double* gamma1, const double* 
 }
 
 // --- closed systems above the gather engine's shapes: forward -----------------
-// Workspace: [GArgs][frame phases [2N+1][D]].
 bool real_column_supported(const scp_system* sys) {
   return sys->d_rt != nullptr && l_column_supported(sys->d, sys->n_modes);
 }
 
-size_t real_column_bytes(const scp_system* sys) {
-  return align256(sizeof(GArgs)) + g_ph_bytes(sys, false);
+size_t real_column_bytes(const scp_system* sys, int S) {
+  return align256(sizeof(GArgs)) + g_run_bytes(sys, S);
 }
 
 scp_status launch_real_column(scp_system* sys, int S, void* ws, const float2* x0, float2* xT,
@@ -2117,18 +2166,13 @@ scp_status launch_real_column(scp_system* sys, int S, void* ws, const float2* x0
   GArgs A;
   SCP_TRY(g_args(sys, false, nullptr, nullptr, A));
   GArgs* dargs = static_cast<GArgs*>(ws);
-  float2* ph = reinterpret_cast<float2*>(static_cast<char*>(ws) + align256(sizeof(GArgs)));
-  A.ph = ph;
   A.x0 = x0;
   A.xT = xT;
   A.S = S;
-  hipLaunchKernelGGL(store_args_kernel, dim3(1), dim3(64), 0, st, A, dargs);
-  HIPCHK(hipGetLastError());
-  SCP_TRY(g_phases(sys, false, ph, st));
-  hipEvent_t t0 = timing_start(sys, st);
-  HIPCHK(l_real_column(sys->d, sys->n_modes, dargs, S, st));
-  timing_stop(sys, t0, 0, st);
-  return SCP_OK;
+  return g_real_runs(sys, A, dargs, static_cast<char*>(ws) + align256(sizeof(GArgs)), st,
+                     [&](int n_lo, int n_hi, const float4* st_in, float4* st_out) {
+                       return l_real_column(sys->d, sys->n_modes, dargs, S, n_lo, n_hi, st_in, st_out, st);
+                     });
 }
 
 // The gradient from the steps' sums, copied to the host (synchronises st).
@@ -2266,7 +2310,7 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
   hipLaunchKernelGGL(store_adj_kernel, dim3(1), dim3(64), 0, st, B, dadj);
   HIPCHK(hipGetLastError());
   if (A.real) {
-    SCP_TRY(g_phases(sys, true, gtab, st));
+    SCP_TRY(g_phases(sys, true, 0, 2 * sys->n_steps + 1, gtab, st));
   } else {
     hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, d, N, gtab);
     HIPCHK(hipGetLastError());
@@ -2332,13 +2376,13 @@ bool gather_supported(const scp_system* sys) {
   return true;
 }
 
-size_t gather_workspace_bytes(const scp_system* sys) {
+size_t gather_workspace_bytes(const scp_system* sys, int S) {
   GArgs A;
   if (g_args(sys, false, nullptr, nullptr, A) != SCP_OK) {
     set_error("");
     return 0;
   }
-  return g_ws_bytes(sys, false, A.ntab);
+  return g_ws_bytes(sys, false, S, A.ntab);
 }
 
 scp_status launch_gather_forward(scp_system* sys, int S, void* ws, size_t ws_bytes,
@@ -2473,7 +2517,8 @@ static scp_status gc_prepare(scp_system* sys, int S, int ce, bool with_grad, int
   hipLaunchKernelGGL(store_adj_kernel, dim3(1), dim3(64), 0, st, B, dadj);
   HIPCHK(hipGetLastError());
   if (tables) {
-    if (A.real) return g_phases(sys, false, reinterpret_cast<float2*>(base + w.ph), st);
+    if (A.real)
+      return g_phases(sys, false, 0, 2 * sys->n_steps + 1, reinterpret_cast<float2*>(base + w.ph), st);
     hipLaunchKernelGGL(gtab_kernel, dim3(3 * sys->n_steps), dim3(256), 0, st, dargs, sys->d,
                        sys->n_modes, gtab);
     HIPCHK(hipGetLastError());

@@ -1069,7 +1069,7 @@ g_real_seg_kernel(const GItem* __restrict__ items, const GArgs* __restrict__ Ag,
 // modes' phases from FP64 angles reduced modulo 2 pi, multiplied in FP64 and
 // rounded once.
 struct RPhase {
-  int d, N, L;
+  int d, N, L, q_lo;
   double h;
   double f[GA_MAXM][8];
 };
@@ -1078,7 +1078,7 @@ __global__ void __launch_bounds__(256) g_real_phase_kernel(RPhase S, float2* __r
   const int q = blockIdx.x;
   for (int t = threadIdx.x; t < S.N * S.d; t += blockDim.x) {
     const double twopi = 6.283185307179586476925286766559;
-    double x = S.f[t / S.d][t % S.d] * (q * (0.5 * S.h));
+    double x = S.f[t / S.d][t % S.d] * ((S.q_lo + q) * (0.5 * S.h));
     x -= twopi * rint(x / twopi);
     double sn, cs;
     sincos(x, &sn, &cs);
@@ -1156,16 +1156,17 @@ hipError_t g_real_segments(int d, int N, const GItem* items, const GArgs* dargs,
   return hipErrorInvalidValue;
 }
 
-hipError_t g_real_phases(int d, int N, int nsteps, double h, const double f[][8], float2* ph,
+hipError_t g_real_phases(int d, int N, int q_lo, int nq, double h, const double f[][8], float2* ph,
                          hipStream_t s) {
   RPhase R;
   std::memset(&R, 0, sizeof(R));
   R.d = d;
   R.N = N;
   R.L = cpow(d, N);
+  R.q_lo = q_lo;
   R.h = h;
   std::memcpy(R.f, f, sizeof(R.f));
-  hipLaunchKernelGGL(g_real_phase_kernel, dim3(2 * nsteps + 1), dim3(256), 0, s, R, ph);
+  hipLaunchKernelGGL(g_real_phase_kernel, dim3(nq), dim3(256), 0, s, R, ph);
   return hipGetLastError();
 }
 

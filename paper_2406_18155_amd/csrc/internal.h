@@ -288,7 +288,7 @@ bool gather_preferred(const scp_system* sys, int S, bool real);
 // Forward of a closed system in the real form, one workgroup per column, for
 // shapes above the gather engine's (d = 3, N = 8).
 bool real_column_supported(const scp_system* sys);
-size_t real_column_bytes(const scp_system* sys);
+size_t real_column_bytes(const scp_system* sys, int S);
 scp_status launch_real_column(scp_system* sys, int S, void* ws, const float2* psi0, float2* psiT,
                               hipStream_t st);
 bool split_preferred(const scp_system* sys);
@@ -297,7 +297,7 @@ scp_status launch_split_forward(scp_system* sys, int S, void* ws, const float2* 
                                 hipStream_t st);
 bool gather_supported(const scp_system* sys);
 std::vector<float> build_gather_rows(const scp_system* sys, double* scale);
-size_t gather_workspace_bytes(const scp_system* sys);
+size_t gather_workspace_bytes(const scp_system* sys, int S);
 scp_status launch_gather_forward(scp_system* sys, int S, void* ws, size_t ws_bytes,
                                  const float2* psi0, float2* psiT, hipStream_t st);
 scp_status gather_grad_check(const scp_system* sys);

@@ -471,13 +471,14 @@ struct LThread {
   }
 };
 
-// Steps [n0, n1) of one column from (hi, lo) at n0: CK keeps the state at every
-// ce-th step, SEG the stage inputs y'.
+// Steps [n0, n1) of one column from (hi, lo) at n0 in `from` (null: from the
+// input column) to `to` (nullable): CK keeps the state at every ce-th step, SEG
+// the stage inputs y'.
 template <int d, int N, bool OPEN, bool CK, bool SEG>
 __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ Bg,
                                         const LThread<d, N, OPEN>& Th, c32* lds, c32* lo, int col, int n0,
                                         int n1, const float4* __restrict__ from,
-                                        c32* __restrict__ segc) {
+                                        float4* __restrict__ to, c32* __restrict__ segc) {
   using S = LShape<d, N, OPEN>;
   constexpr int L = S::L, T = S::T, E = S::E;
   const unsigned tid = Th.tid;
@@ -513,7 +514,7 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
   for (int r = 0; r < E; ++r) {
     const int e = tid + r * T;
     float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (SEG) {
+    if (SEG || from != nullptr) {
       q = from[e];
     } else {
       const c32 v = ((const c32*)A->x0)[(size_t)col * L + e];
@@ -609,7 +610,15 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
       cur ^= 1;
     }
   }
-  if (SEG || A->xT == nullptr) return;
+  if (SEG) return;
+  if (to != nullptr) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const c32 l = low(r);
+      if (on) to[tid + r * T] = make_float4(hr[r], hm[r], l.x, l.y);
+    }
+  }
+  if (A->xT == nullptr || n1 < A->nsteps) return;
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     c32 l = low(r);
@@ -621,14 +630,16 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
 
 template <int d, int N, bool OPEN, bool CK>
 __global__ void __launch_bounds__((LShape<d, N, OPEN>::TB))
-l_rk4_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
+l_rk4_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg, int n_lo, int n_hi,
+             const float4* __restrict__ st_in, float4* __restrict__ st_out) {
   using S = LShape<d, N, OPEN>;
   extern __shared__ __align__(16) c32 lds[];
   kptr<GArgs> A = kconst(Ag);
   LThread<d, N, OPEN> Th;
   Th.init(A, reinterpret_cast<float*>(lds + S::bufs), false);
-  l_steps<d, N, OPEN, CK, false>(A, Bg, Th, lds, lds + 2 * S::L, blockIdx.x, 0, A->nsteps, nullptr,
-                                 nullptr);
+  const size_t at = (size_t)blockIdx.x * S::L;
+  l_steps<d, N, OPEN, CK, false>(A, Bg, Th, lds, lds + 2 * S::L, blockIdx.x, n_lo, n_hi,
+                                 st_in ? st_in + at : nullptr, st_out ? st_out + at : nullptr, nullptr);
 }
 
 // The reverse walk of a column, segment by segment from the last: recompute the
@@ -663,7 +674,7 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
   for (int g = nck - 1; g >= 0; --g) {
     const int n0 = g * ce, n1 = min(nsteps, n0 + ce);
     l_steps<d, N, true, false, true>(A, Bg, Th, lds, lo, col, n0, n1, B->ck + ((size_t)col * nck + g) * L,
-                               segc);
+                               nullptr, segc);
     // ---- back
     float lhr[E], lhm[E], llr[S::LO ? 1 : E], llm[S::LO ? 1 : E];
     auto low = [&](int r) {
@@ -897,12 +908,19 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
   }
 }
 
-template <typename K>
-hipError_t l_launch(K* kernel, int S, int threads, size_t sh, const GArgs* dargs, const GAdj* dadj,
-                    hipStream_t s) {
+template <typename K, typename... Args>
+hipError_t l_launch(K* kernel, int S, int threads, size_t sh, hipStream_t s, Args... args) {
   (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-  hipLaunchKernelGGL(kernel, dim3(S), dim3(threads), sh, s, dargs, dadj);
+  hipLaunchKernelGGL(kernel, dim3(S), dim3(threads), sh, s, args...);
   return hipGetLastError();
+}
+
+template <int d, int N, bool OPEN, bool CK>
+hipError_t l_forward(const GArgs* dargs, const GAdj* dadj, int S, int n_lo, int n_hi,
+                     const float4* st_in, float4* st_out, hipStream_t s) {
+  using Z = LShape<d, N, OPEN>;
+  return l_launch(l_rk4_kernel<d, N, OPEN, CK>, S, Z::TB, Z::fwd_bytes(), s, dargs, dadj, n_lo, n_hi,
+                  st_in, st_out);
 }
 
 }  // namespace
@@ -911,13 +929,12 @@ hipError_t l_launch(K* kernel, int S, int threads, size_t sh, const GArgs* dargs
 // of modes would count twice).
 #define GA_OPEN_REAL(X) X(2, 3) X(2, 4) X(2, 5) X(3, 3) X(3, 4) X(4, 3)
 
-hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s) {
-#define L_FWD(dd_, nn_)                                                                            \
-  if (d == dd_ && N == nn_) {                                                                      \
-    using Z = LShape<dd_, nn_, true>;                                                                    \
-    return dadj ? l_launch(l_rk4_kernel<dd_, nn_, true, true>, S, Z::TB, Z::fwd_bytes(), dargs, dadj, s)  \
-                : l_launch(l_rk4_kernel<dd_, nn_, true, false>, S, Z::TB, Z::fwd_bytes(), dargs, dadj, s); \
-  }
+hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, int nsteps,
+                          hipStream_t s) {
+#define L_FWD(dd_, nn_)                                                                              \
+  if (d == dd_ && N == nn_)                                                                          \
+    return dadj ? l_forward<dd_, nn_, true, true>(dargs, dadj, S, 0, nsteps, nullptr, nullptr, s)    \
+                : l_forward<dd_, nn_, true, false>(dargs, dadj, S, 0, nsteps, nullptr, nullptr, s);
   GA_OPEN_REAL(L_FWD)
 #undef L_FWD
   return hipErrorInvalidValue;
@@ -925,17 +942,17 @@ hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, in
 
 bool l_column_supported(int d, int N) { return d == 3 && N == 8; }
 
-hipError_t l_real_column(int d, int N, const GArgs* dargs, int S, hipStream_t s) {
-  using Z = LShape<3, 8, false>;
+hipError_t l_real_column(int d, int N, const GArgs* dargs, int S, int n_lo, int n_hi,
+                         const float4* st_in, float4* st_out, hipStream_t s) {
   if (!l_column_supported(d, N)) return hipErrorInvalidValue;
-  return l_launch(l_rk4_kernel<3, 8, false, false>, S, Z::TB, Z::fwd_bytes(), dargs, nullptr, s);
+  return l_forward<3, 8, false, false>(dargs, nullptr, S, n_lo, n_hi, st_in, st_out, s);
 }
 
 hipError_t l_real_adjoint(int d, int N, const GArgs* dargs, const GAdj* dadj, int S, hipStream_t s) {
 #define L_ADJ(dd_, nn_)                                                                            \
   if (d == dd_ && N == nn_)                                                                        \
-    return l_launch(l_adj_kernel<dd_, nn_>, S, LShape<dd_, nn_, true>::TB, LShape<dd_, nn_, true>::adj_bytes(), \
-                    dargs, dadj, s);
+    return l_launch(l_adj_kernel<dd_, nn_>, S, LShape<dd_, nn_, true>::TB,                         \
+                    LShape<dd_, nn_, true>::adj_bytes(), s, dargs, dadj);
   GA_OPEN_REAL(L_ADJ)
 #undef L_ADJ
   return hipErrorInvalidValue;

@@ -919,7 +919,7 @@ WsLayout ws_layout_in(const scp_system* sys, const scp_solve_opts* o, int with_g
   }
   if (want && !o->with_ckpt && !with_grad) {
     w.gather = true;
-    off = gather_workspace_bytes(sys);
+    off = gather_workspace_bytes(sys, (int)S);
   } else if (want) {
     w.gather_grad = true;
     off = gather_grad_workspace_bytes(sys, (int)S, w.ce, with_grad != 0);
@@ -935,7 +935,7 @@ WsLayout ws_layout_in(const scp_system* sys, const scp_solve_opts* o, int with_g
     // are in the register layout
     if (engine == 0 && !o->with_ckpt && !with_grad && real && real_column_supported(sys)) {
       w.column = true;
-      off = std::max(off, real_column_bytes(sys));
+      off = std::max(off, real_column_bytes(sys, (int)S));
     }
     if (o->with_ckpt || with_grad) {
       w.ckpt = off;

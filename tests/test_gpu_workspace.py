@@ -114,3 +114,38 @@ def test_adjoint_with_fewer_segments(scp, d, n, S, ng):
     with pytest.raises(scp.ScpError, match="EINVAL.*workspace_bytes"):
         g.adjoint(cot, opts, ws[:full - 6 * seg], psi0=x)
     g.close()
+
+
+def test_forward_workspace_of_the_column_kernel_is_bounded(scp):
+    sizes = []
+    for n_steps in (4000, 20000):
+        g = _device(scp, 3, 8, n_steps)
+        sizes.append(g.workspace_bytes(g.opts(3)))
+        g.close()
+    assert sizes[0] == sizes[1]
+
+
+# the real form's forward goes in runs of steps, 4096 of them at D = 4096: one
+# step in the last run, a run and a remainder, three runs
+@pytest.mark.parametrize("n_steps", [4096, 4097, 5000, 8193])
+def test_runs_of_steps_leave_no_trace(scp, n_steps):
+    g = _device(scp, 4, 6, n_steps)
+    S = 3
+    x = _columns(g, S)
+    opts = g.opts(S, with_ckpt=1)
+    assert g.engine(opts) == "gather"
+    U = g.propagate(x, opts=opts)                     # checkpoints: one run
+    V = g.propagate(x, opts=g.opts(S))
+    assert torch.equal(U, V) and torch.equal(V, g.propagate(x, psiT=x, opts=g.opts(S)))
+    g.close()
+
+
+def test_runs_of_steps_of_the_column_kernel(scp):
+    g = _device(scp, 3, 8, 2700)                      # a run of 2557 steps and the rest
+    x = _columns(g, 3)
+    U = g.propagate(x)
+    ref = g.propagate(x.to(torch.complex128)).to(torch.complex64)
+    # amplitudes of about 0.01 (random columns of 6561), |V| T below 50, a few rounded
+    # FP32 operations (6e-8) per evaluation: 0.01 * 50 * 10 * 6e-8
+    assert (U - ref).abs().max().item() <= 3e-7
+    g.close()
