@@ -622,8 +622,10 @@ void scp_server_destroy(scp_server* sv);
  * scp_mode_desc).
  * ------------------------------------------------------------------------ */
 
-/* Device workspace bytes of scp_propagate_lindblad (a small argument block
- * and the relaxation phases of every half-step). */
+/* Device workspace bytes of scp_propagate_lindblad: a small argument block and
+ * the stage tables or, where every term is real (as scp_system_set_engine has
+ * it for closed systems), the frame phases of every half-step (16 D^2 bytes a
+ * step).  In less, as long as the tables fit, the complex rows run. */
 scp_status scp_lindblad_workspace_size(const scp_system* sys, size_t* bytes);
 
 /* Propagate n_cols density matrices rho0 (device, complex64, n_cols x D x D,
@@ -638,8 +640,10 @@ scp_status scp_propagate_lindblad(scp_system* sys, const double* gamma1, const d
                                   const void* rho0, void* rhoT, void* stream);
 
 /* Device workspace bytes of scp_lindblad_adjoint for n_cols matrices: the
- * stage tables, checkpoints (hi and lo words) every ceil(sqrt(n_steps))
- * steps, one segment of stage inputs and the costate, per matrix. */
+ * stage tables or the frame phases, checkpoints (hi and lo words) every
+ * ceil(sqrt(n_steps)) steps, one segment of stage inputs, the costate and the
+ * sums of every step, per matrix.  In less, as long as the tables fit, the
+ * complex rows run. */
 scp_status scp_lindblad_adjoint_workspace_size(const scp_system* sys, int32_t n_cols,
                                                size_t* bytes);
 

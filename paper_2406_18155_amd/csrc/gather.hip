@@ -2068,11 +2068,15 @@ static scp_status g_real_runs(scp_system* sys, GArgs A, GArgs* dargs, char* at, 
 // Workspace: [GArgs][stage tables [3N][ntab], with those of an open system its
 // jump bands [2N+1][N][d*d]; or, in the real form, the frame phases: of an open
 // system [2N+1][L], of a closed one as above].
-static size_t g_ws_bytes(const scp_system* sys, bool open, int S, int ntab) {
+static size_t g_tab_bytes(const scp_system* sys, bool open, int ntab) {
   const size_t dd = (size_t)sys->d * sys->d;
-  size_t t = align256(3 * (size_t)sys->n_steps * ntab * sizeof(float2));
+  size_t t = align256(sizeof(GArgs)) + align256(3 * (size_t)sys->n_steps * ntab * sizeof(float2));
   if (open) t += align256((2 * (size_t)sys->n_steps + 1) * sys->n_modes * dd * sizeof(float2));
-  return align256(sizeof(GArgs)) + std::max(t, open ? g_ph_bytes(sys, true) : g_run_bytes(sys, S));
+  return t;
+}
+static size_t g_ws_bytes(const scp_system* sys, bool open, int S, int ntab) {
+  return std::max(g_tab_bytes(sys, open, ntab),
+                  align256(sizeof(GArgs)) + (open ? g_ph_bytes(sys, true) : g_run_bytes(sys, S)));
 }
 
 static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const double* gammaphi,
@@ -2080,7 +2084,12 @@ static scp_status g_run(scp_system* sys, bool open, const double* gamma1, const 
                         hipStream_t st) {
   GArgs A;
   SCP_TRY(g_args(sys, open, gamma1, gammaphi, A));
-  if (ws_bytes < g_ws_bytes(sys, open, S, A.ntab)) return fail(SCP_EINVAL, "workspace too small");
+  if (ws_bytes < g_ws_bytes(sys, open, S, A.ntab)) {
+    // an open system's phases are five times its tables (d = 3, N = 4): where only
+    // the tables fit, the complex rows run
+    if (!open || ws_bytes < g_tab_bytes(sys, true, A.ntab)) return fail(SCP_EINVAL, "workspace too small");
+    A.real = 0;
+  }
   char* w = static_cast<char*>(ws);
   GArgs* dargs = reinterpret_cast<GArgs*>(w);
   w += align256(sizeof(GArgs));
@@ -2193,14 +2202,15 @@ static scp_status g_fold(scp_system* sys, int S, const GArgs* dargs, const GAdj*
 // [checkpoints [S][nck][L] float4][stage inputs [S][ce][4][L]][costate [S][L]
 // float4][partial sums [S][nacc] double, or the real form's sums of the steps
 // [S][N][gw] double, their blocks [S][nblk][nacc] and the gradient [nacc]].
-// The size is the same for either frame setting of a system.
+// The size is the same for either frame setting of a system; without `real`, that
+// of the tables alone.
 struct LbAdjLayout {
   size_t args, adj, gtab, jtab, ck, seg, part, lam, total;
   size_t gs, blk, grad;   // real form
   int ce, nck, nacc, ntabg, gw, nblk;
 };
 
-static scp_status lb_adj_layout(const scp_system* sys, int S, LbAdjLayout& w, GArgs* Aout) {
+static scp_status lb_adj_layout(const scp_system* sys, int S, bool real, LbAdjLayout& w, GArgs* Aout) {
   GArgs A;
   std::vector<double> one(sys->n_modes, 1.0);   // the widest table: relaxation on
   SCP_TRY(g_args(sys, true, one.data(), nullptr, A));
@@ -2220,7 +2230,7 @@ static scp_status lb_adj_layout(const scp_system* sys, int S, LbAdjLayout& w, GA
   w.gtab = off;
   w.jtab = off + align256(3 * (size_t)N * A.ntabg * sizeof(float2));
   const size_t tabs = w.jtab + align256((2 * (size_t)N + 1) * sys->n_modes * dd * sizeof(float2));
-  off = std::max(tabs, off + g_ph_bytes(sys, true));
+  off = std::max(tabs, off + (real ? g_ph_bytes(sys, true) : 0));
   w.ck = off;
   off += align256((size_t)S * w.nck * L * sizeof(float4));
   w.seg = off;
@@ -2232,7 +2242,7 @@ static scp_status lb_adj_layout(const scp_system* sys, int S, LbAdjLayout& w, GA
   w.gw = 4 * A.nds + P.ncoup + 2 * sys->n_modes;
   w.nblk = (N + GF_STEPS - 1) / GF_STEPS;
   w.blk = w.grad = 0;
-  if (A.rt != nullptr) {
+  if (real && A.rt != nullptr) {
     size_t q = w.gs + align256((size_t)S * N * w.gw * sizeof(double));
     w.blk = q;
     q += align256((size_t)S * w.nblk * w.nacc * sizeof(double));
@@ -2250,7 +2260,7 @@ static scp_status lb_adj_layout(const scp_system* sys, int S, LbAdjLayout& w, GA
 scp_status lindblad_adjoint_workspace_bytes(const scp_system* sys, int S, size_t* bytes) {
   SCP_TRY(lindblad_check(sys));
   LbAdjLayout w;
-  SCP_TRY(lb_adj_layout(sys, S, w, nullptr));
+  SCP_TRY(lb_adj_layout(sys, S, true, w, nullptr));
   *bytes = w.total;
   return SCP_OK;
 }
@@ -2260,11 +2270,14 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
                                    const float2* cot, double* grad, hipStream_t st) {
   SCP_TRY(lindblad_check(sys));
   LbAdjLayout w;
-  SCP_TRY(lb_adj_layout(sys, S, w, nullptr));
+  SCP_TRY(lb_adj_layout(sys, S, true, w, nullptr));
+  const bool room = ws_bytes >= w.total;   // else the complex rows, if those fit
+  if (!room) SCP_TRY(lb_adj_layout(sys, S, false, w, nullptr));
   if (ws_bytes < w.total) return fail(SCP_EINVAL, "workspace too small");
   GArgs A;
   SCP_TRY(g_args(sys, true, gamma1, gammaphi, A));
   SCP_TRY(g_args_grad(sys, true, A));
+  if (!room) A.real = 0;
   char* base = static_cast<char*>(ws);
   GArgs* dargs = reinterpret_cast<GArgs*>(base + w.args);
   GAdj* dadj = reinterpret_cast<GAdj*>(base + w.adj);

@@ -149,3 +149,29 @@ def test_runs_of_steps_of_the_column_kernel(scp):
     # FP32 operations (6e-8) per evaluation: 0.01 * 50 * 10 * 6e-8
     assert (U - ref).abs().max().item() <= 3e-7
     g.close()
+
+
+def _open_device(scp):
+    s = si.transmon_ring(si.rng_for(7, 3), 3, 3, 1.0, 50)
+    s = si.with_rates(s, si.open_rates(si.rng_for(9, 1), 3))
+    return scp.System(si._finish(s, [3] * 3, target=si.cz_target(3)))
+
+
+def test_open_system_in_the_size_of_the_tables(scp):
+    g = _open_device(scp)
+    x = scp.matrix_units(g.D, [0, 1])
+    cot = torch.randn(x.shape, dtype=torch.complex64, generator=torch.Generator().manual_seed(3)).cuda()
+    # |V| T below 10; at most 30 rounded FP32 terms per evaluation (6e-8 each)
+    full = g.lindblad_workspace_bytes()
+    R = g.propagate_lindblad(x)
+    Q = g.propagate_lindblad(x, workspace=_bytes(full // 2))
+    assert (R - Q).abs().max().item() <= 2e-5
+    with pytest.raises(scp.ScpError, match="workspace"):
+        g.propagate_lindblad(x, workspace=_bytes(full // 50))
+    full = g.lindblad_adjoint_workspace_bytes(x.shape[0])
+    ref = g.lindblad_adjoint(x, cot)
+    grad = g.lindblad_adjoint(x, cot, workspace=_bytes(full - 256))
+    assert abs(grad - ref).max() <= 1e-4 * abs(ref).max()
+    with pytest.raises(scp.ScpError, match="workspace"):
+        g.lindblad_adjoint(x, cot, workspace=_bytes(full // 3))
+    g.close()
