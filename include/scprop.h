@@ -512,9 +512,11 @@ scp_status scp_propagate_trotter(scp_system* sys, int32_t order, int32_t n_cols,
  * exponential.  Complex FP64 throughout; the frame and the carriers are held
  * fixed.  The result is bitwise reproducible (no atomics).
  * workspace: device, scp_trotter_adjoint_workspace_size(order, n_cols) bytes
- * (the forward's gate tables, one column state and costate per column, the
- * inverse and adjoint gate tables, per-column local sums for a chunk of 128
- * steps); workspace_bytes is its size.  Synchronises the stream.
+ * (the forward's gate tables, one column state and costate per column and slot,
+ * the inverse and adjoint gate tables, per-column local sums for a round of the
+ * walk); workspace_bytes is its size, which grows with n_cols.  Fewer than 128
+ * columns are walked in slots of steps side by side where the gates are unitary
+ * and do not commute.  Synchronises the stream.
  * SCP_EINVAL (as scp_trotter_workspace_size, and for 16 (2 D + 512) bytes >
  * 160 KiB: a column and its costate live in LDS), SCP_ENONFINITE, SCP_EHIP. */
 scp_status scp_trotter_adjoint_workspace_size(const scp_system* sys, int32_t order, int32_t n_cols,

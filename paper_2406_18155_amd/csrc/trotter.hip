@@ -2512,13 +2512,27 @@ LcLayout lc_layout(const scp_system* sys, int order, int S) {
   const size_t N = sys->n_steps, r = L.F.r, D = sys->D;
   L.chunk = (int)std::min<size_t>(N, LC_CHUNK);
   L.nslot = 1;
+  // columns times slots and steps times columns of a round: the most that this
+  // or a smaller count of columns takes, so that a workspace for S columns does
+  // for fewer
+  size_t cols = S, steps = (size_t)L.chunk * S, carry = 0;
   // slots where the gates are unitary, the sweep can use the split form of the
   // fused operations, and one walk would fill less than half of the chip
-  if (order != SCP_TROTTER_Q4J && !L.F.phase && L.F.mode2 != 0 && S < 128 && N > 1) {
-    const int want = (256 + S - 1) / S;
-    L.len = (int)std::min<size_t>(64, (N + want - 1) / want);
-    L.nslot = (int)std::min<size_t>(want, (N + L.len - 1) / L.len);
-    L.chunk = (int)std::min<size_t>(N, (size_t)L.nslot * L.len);
+  if (order != SCP_TROTTER_Q4J && !L.F.phase && L.F.mode2 != 0 && N > 1) {
+    for (int s = 1; s <= std::min(S, 127); ++s) {
+      const int want = (256 + s - 1) / s;
+      const int len = (int)std::min<size_t>(64, (N + want - 1) / want);
+      const int nslot = (int)std::min<size_t>(want, (N + len - 1) / len);
+      const int chunk = (int)std::min<size_t>(N, (size_t)nslot * len);
+      cols = std::max(cols, (size_t)nslot * s);
+      steps = std::max(steps, (size_t)chunk * s);
+      carry = s;
+      if (s == S) {
+        L.len = len;
+        L.nslot = nslot;
+        L.chunk = chunk;
+      }
+    }
   }
   size_t o = L.F.total;
   auto take = [&](size_t bytes) {
@@ -2527,16 +2541,16 @@ LcLayout lc_layout(const scp_system* sys, int order, int S) {
     return at;
   };
   L.psiT = take((size_t)S * D * sizeof(double2));
-  L.psi_st = take((size_t)L.nslot * S * D * sizeof(double2));
-  L.mu_st = take((size_t)L.nslot * S * D * sizeof(double2));
-  L.psi_c = take((size_t)(L.len ? S : 0) * D * sizeof(double2));
-  L.mu_c = take((size_t)(L.len ? S : 0) * D * sizeof(double2));
+  L.psi_st = take(cols * D * sizeof(double2));
+  L.mu_st = take(cols * D * sizeof(double2));
+  L.psi_c = take(carry * D * sizeof(double2));
+  L.mu_c = take(carry * D * sizeof(double2));
   L.sgi = take(N * r * M * dd * sizeof(double2));
   L.sga = take(N * r * M * dd * sizeof(double2));
   L.pgi = take(r * E * dd * dd * sizeof(double2));
   L.pga = take(r * E * dd * dd * sizeof(double2));
-  L.ms = take((size_t)L.chunk * r * M * (L.F.H == 2 ? 2 : 1) * S * dd * sizeof(double2));
-  L.mp = take((size_t)L.nslot * S * r * E * dd * dd * sizeof(double2));
+  L.ms = take(steps * r * M * (L.F.H == 2 ? 2 : 1) * dd * sizeof(double2));
+  L.mp = take(cols * r * E * dd * dd * sizeof(double2));
   L.z = take(N * r * M * 5 * sizeof(double2));
   L.zp = take(r * E * 7 * sizeof(double2));
   L.deps = take(M * 3 * d * sizeof(double));

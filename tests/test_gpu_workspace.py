@@ -175,3 +175,19 @@ def test_open_system_in_the_size_of_the_tables(scp):
     with pytest.raises(scp.ScpError, match="workspace"):
         g.lindblad_adjoint(x, cot, workspace=_bytes(full // 3))
     g.close()
+
+
+# either side of the columns that are walked in slots, one step and many rounds;
+# fused operations in the split form and in the matrix form
+@pytest.mark.parametrize("d,n,n_steps", [(3, 3, 1), (3, 3, 70), (4, 3, 400)])
+def test_lcam_workspace_grows_with_the_columns(scp, d, n, n_steps):
+    s = si.fluxonium_chain(si.rng_for(8, d), n, d, 0.01 * n_steps, n_steps, n_basis_gauss=3)
+    g = scp.System(si._finish(s, [d] * n, target=si.cz_target(n)))
+    for order in ("q1", "q2", "q4", "q4j"):
+        sizes = [g.trotter_adjoint_workspace_bytes(order, k) for k in range(1, 300)]
+        assert sizes == sorted(sizes)
+    x, cot = (_columns(g, 86, k).to(torch.complex128) for k in (1, 2))
+    ref = g.trotter_adjoint(x, cot, "q2")
+    ws = _bytes(g.trotter_adjoint_workspace_bytes("q2", 130))
+    assert (ref == g.trotter_adjoint(x, cot, "q2", workspace=ws)).all()
+    g.close()
