@@ -2587,9 +2587,11 @@ scp_status launch_gather_adjoint(scp_system* sys, int S, int ce, int nseg, void*
 // --- serving: a closed-system request on the gather engine, in chunks --------
 // Workspace: the layout of gc_layout (the adjoint's when the gradient is
 // wanted) followed by the compensated state [S][D] float4 between chunks.
+// It has stage inputs for one segment; the server lends room for more (see
+// gather_serve_buffers).
 size_t gather_serve_bytes(const scp_system* sys, int S, int ce, bool grad) {
   GcLayout w;
-  if (gc_layout(sys, S, ce, grad, 0, w, nullptr) != SCP_OK) {
+  if (gc_layout(sys, S, ce, grad, 1, w, nullptr) != SCP_OK) {
     set_error("");
     return 0;
   }
@@ -2600,7 +2602,7 @@ scp_status gather_serve_prepare(scp_system* sys, int S, int ce, bool grad, void*
                                 const float2* psi0, float2* psiT, const float2* cot, hipStream_t st) {
   GcLayout w;
   GArgs A;
-  return gc_prepare(sys, S, ce, grad, 0, static_cast<char*>(ws), bytes, psi0, psiT, cot, true, w, A,
+  return gc_prepare(sys, S, ce, grad, 1, static_cast<char*>(ws), bytes, psi0, psiT, cot, true, w, A,
                     st);
 }
 
@@ -2608,9 +2610,10 @@ int gather_serve_nckpt(const scp_system* sys, int ce) { return (sys->n_steps + c
 
 scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, void* ws,
                              GServeInfo& out) {
-  GcLayout w;
+  GcLayout w, full;
   GArgs A;
-  SCP_TRY(gc_layout(sys, S, ce, grad, 0, w, &A));
+  SCP_TRY(gc_layout(sys, S, ce, grad, 0, full, nullptr));
+  SCP_TRY(gc_layout(sys, S, ce, grad, 1, w, &A));
   char* base = static_cast<char*>(ws);
   out.A = base + w.args;
   out.B = base + w.adj;
@@ -2624,7 +2627,16 @@ scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, vo
     out.lds_adj = g_real_lds(sys->d, sys->n_modes, true);
   }
   out.nck = w.nck;
-  out.nseg = w.nseg;
+  out.seg = reinterpret_cast<float2*>(base + w.seg);
+  out.most = full.nseg;
+  return SCP_OK;
+}
+
+// The request's stage inputs lie at seg from now on (room for as many segments as
+// the launches that follow name).  Not while one of its launches is in flight.
+scp_status gather_serve_buffers(const GServeInfo& gi, const float2* seg) {
+  const GAdj* B = static_cast<const GAdj*>(gi.B);
+  HIPCHK(hipMemcpy(const_cast<float2**>(&B->seg), &seg, sizeof(seg), hipMemcpyHostToDevice));
   return SCP_OK;
 }
 
@@ -2718,7 +2730,7 @@ scp_status gather_launch_adj_batched(int d, int N, int form, const GItem* items,
 scp_status gather_serve_gradient(scp_system* sys, int S, int ce, void* ws, std::vector<double>& grad,
                                  hipStream_t st) {
   GcLayout w;
-  SCP_TRY(gc_layout(sys, S, ce, true, 0, w, nullptr));
+  SCP_TRY(gc_layout(sys, S, ce, true, 1, w, nullptr));
   grad.assign(w.nacc, 0.0);
   return gc_fold(sys, S, static_cast<char*>(ws), w, grad.data(), st);
 }

@@ -325,7 +325,8 @@ struct GServeInfo {
   size_t lds_fwd, lds_adj, lds_cos;
   int form;   // 0 general, 1 parity, 2 real (batched launches are of one form)
   int nck;
-  int nseg;   // segments walked side by side (stage-input buffers: nseg per column)
+  float2* seg;   // its stage-input buffers, room for one segment
+  int most;      // the most segments walked side by side
 };
 scp_status gather_serve_info(const scp_system* sys, int S, int ce, bool grad, void* ws,
                              GServeInfo& out);
@@ -336,6 +337,7 @@ scp_status gather_launch_adj_batched(int d, int N, int form, const GItem* items,
 scp_status gather_launch_cos_batched(int d, int N, int form, const GItem* items, int n, size_t lds,
                                      hipStream_t st);
 size_t gather_serve_bytes(const scp_system* sys, int S, int ce, bool grad);
+scp_status gather_serve_buffers(const GServeInfo& gi, const float2* seg);
 scp_status gather_serve_prepare(scp_system* sys, int S, int ce, bool grad, void* ws, size_t bytes,
                                 const float2* psi0, float2* psiT, const float2* cot, hipStream_t st);
 int gather_serve_nckpt(const scp_system* sys, int ce);

@@ -97,8 +97,10 @@ struct Request {
   int state = RQ_QUEUED;
   int phase = 0;          // 0 forward, 1 adjoint
   int n_done = 0, seg_next = 0, ce = 1, nckpt = 1, nwg = 1;
-  int nbuf = 1;           // stage-input buffers: segment g in g % nbuf
+  int nbuf = 1;           // stage-input buffers (register kernels: segment g in g % nbuf)
   int rec_next = 0;       // segments from here up have been recomputed
+  void* xmem = nullptr;   // lent ones (see lend_buffers)
+  size_t xbytes = 0;
   size_t bytes = 0;
   scp_system* sys = nullptr;
   void* dmem = nullptr;
@@ -121,9 +123,10 @@ struct Request {
   size_t gws_bytes = 0;
   GServeInfo gi{};          // its device descriptions, state buffer and LDS needs
 
+  size_t seg_bytes() const { return ((size_t)ce * 4 * S * sys->D * 8 + 255) & ~(size_t)255; }
   float2* seg_buf(int g) const {
-    return (float2*)((char*)segbuf +
-                     (size_t)(g % nbuf) * (((size_t)ce * 4 * S * sys->D * 8 + 255) & ~(size_t)255));
+    const int i = g % nbuf;
+    return i == 0 ? segbuf : (float2*)((char*)xmem + (size_t)(i - 1) * seg_bytes());
   }
 };
 
@@ -180,6 +183,63 @@ size_t estimate_bytes(const scp_system_desc* d, int S, int want_grad) {
   return b + (1 << 20);
 }
 
+// A gradient request holds stage inputs of one segment.  Several recomputed (and,
+// on the gather engine, walked) side by side, up to a workgroup or two per compute
+// unit, cost the time of one: a request of few workgroups leaves most of the chip
+// idle (16 mixed requests, the longest a 4-fluxonium gradient of two workgroups on
+// the register kernels: 786 -> 641 ms).  Room for more is lent between ticks, from
+// the free half of the budget (a second segment of the gather engine from all that
+// is free) and while nothing waits for memory, and taken back as soon as a queued
+// request needs it; the next segment is then recomputed once more.
+void lend_buffers(scp_server* sv) {
+  for (Request* r : sv->active) {
+    if (r->phase != 1 || r->nbuf > 1 || r->seg_next < 1) continue;
+    const size_t seg = r->seg_bytes(), half = sv->budget / 2;
+    const size_t room = sv->used < half ? (half - sv->used) / seg : 0;
+    const size_t all = sv->used < sv->budget ? (sv->budget - sv->used) / seg : 0;
+    // the gather engine's buffers are one array, the register kernels' the first and the rest
+    const int most = std::min(r->gather ? r->gi.most : std::min(8, 256 / r->nwg), r->seg_next + 1);
+    const int n = r->gather ? (int)std::min<size_t>(most, std::max(room, std::min<size_t>(all, 2)))
+                            : (int)std::min<size_t>(most, 1 + room);
+    if (n < 2) continue;
+    const size_t bytes = (r->gather ? n : n - 1) * seg;
+    if (hipMalloc(&r->xmem, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      r->xmem = nullptr;
+      return;
+    }
+    if (r->gather && gather_serve_buffers(r->gi, (float2*)r->xmem) != SCP_OK) {
+      (void)hipFree(r->xmem);
+      r->xmem = nullptr;
+      continue;
+    }
+    r->xbytes = bytes;
+    sv->used += bytes;
+    r->nbuf = n;
+    r->rec_next = r->seg_next + 1;   // segments move to other buffers
+  }
+}
+
+// Lent buffers back until `need` more bytes fit the budget; false if none was lent
+// or they do not amount to that.
+bool reclaim_buffers(scp_server* sv, size_t need) {
+  size_t lent = 0;
+  for (Request* r : sv->active) lent += r->xbytes;
+  const bool all = need == ~(size_t)0;
+  if (lent == 0 || (!all && sv->used - lent + need > sv->budget)) return false;
+  for (Request* r : sv->active) {
+    if (!all && sv->used + need <= sv->budget) break;
+    if (!r->xmem || (r->gather && gather_serve_buffers(r->gi, r->gi.seg) != SCP_OK)) continue;
+    (void)hipFree(r->xmem);
+    sv->used -= r->xbytes;
+    r->xmem = nullptr;
+    r->xbytes = 0;
+    r->nbuf = 1;
+    r->rec_next = r->seg_next + 1;
+  }
+  return all || sv->used + need <= sv->budget;
+}
+
 scp_status admit(scp_server* sv, Request* r) {
   scp_system* sys = nullptr;
   scp_status st = scp_build_system(&r->dc.desc, sv->stream, &sys);
@@ -197,9 +257,8 @@ scp_status admit(scp_server* sv, Request* r) {
                                           : gather_preferred(sys, r->S, sys->plan.real_frame != 0))) {
     if (gather_grad_check(sys) == SCP_OK) {
       r->gws_bytes = gather_serve_bytes(sys, r->S, r->ce, r->want_grad != 0);
-      r->gather = r->gws_bytes > 0 &&
-                  sv->used + r->gws_bytes + (size_t)(4 << 20) + 2 * (size_t)r->S * sys->D * 8 <=
-                      sv->budget;
+      const size_t need = r->gws_bytes + (size_t)(4 << 20) + 2 * (size_t)r->S * sys->D * 8;
+      r->gather = r->gws_bytes > 0 && (sv->used + need <= sv->budget || reclaim_buffers(sv, need));
     } else {
       set_error("");
     }
@@ -213,7 +272,7 @@ scp_status admit(scp_server* sv, Request* r) {
   const size_t o_psi = take(S * D * 8), o_hi = take(S * D * 8), o_lo = take(S * D * 8),
                o_cot = take(S * D * 8), o_rows = take(r->d_c * 8), o_cols = take(r->d_c * 4),
                o_tgt = take((size_t)r->d_c * r->d_c * 16), o_tau = take(16);
-  size_t o_ck = 0, o_seg = 0, o_sum = 0, o_ls = 0, o_part = 0, o_g = 0, seg = 0;
+  size_t o_ck = 0, o_seg = 0, o_sum = 0, o_ls = 0, o_part = 0, o_g = 0;
   if (r->gather) {
     o_g = take(r->gws_bytes);
   } else if (r->want_grad) {
@@ -221,25 +280,12 @@ scp_status admit(scp_server* sv, Request* r) {
     o_sum = take(S * D * 8);
     o_ls = take(S * D * 8);
     o_part = take((size_t)r->nwg * 4 * std::max(1, P.nacc) * 8);
-    // Several segments recomputed side by side, up to a workgroup per compute
-    // unit, cost the time of one: a request of few workgroups leaves most of
-    // the chip idle, and its recompute takes a third of its reverse walk's time
-    // (16 mixed requests, the longest a 4-fluxonium gradient of two workgroups:
-    // 786 -> 641 ms).  The buffers beyond the first come from the free half of
-    // the budget only.
-    seg = align256((size_t)r->ce * 4 * S * D * 8);
-    const size_t half = sv->budget / 2, in_use = sv->used + r->bytes;
-    r->nbuf = std::max(1, std::min({8, 256 / r->nwg, r->nckpt}));
-    if (in_use >= half) r->nbuf = 1;
-    else r->nbuf = (int)std::min<size_t>(r->nbuf, 1 + (half - in_use) / seg);
+    o_seg = take((size_t)r->ce * 4 * S * D * 8);
     r->rec_next = r->nckpt;
-    o_seg = take(r->nbuf * seg);   // last: the extra ones can be left out
   }
   hipError_t got = hipMalloc(&r->dmem, off);
-  if (got != hipSuccess && r->nbuf > 1) {
+  if (got != hipSuccess && reclaim_buffers(sv, ~(size_t)0)) {
     (void)hipGetLastError();
-    off -= (r->nbuf - 1) * seg;
-    r->nbuf = 1;
     got = hipMalloc(&r->dmem, off);
   }
   if (got != hipSuccess) {
@@ -291,6 +337,10 @@ scp_status admit(scp_server* sv, Request* r) {
 void release(scp_server* sv, Request* r) {
   if (r->dmem) (void)hipFree(r->dmem);
   r->dmem = nullptr;
+  if (r->xmem) (void)hipFree(r->xmem);
+  r->xmem = nullptr;
+  sv->used -= std::min(sv->used, r->xbytes);
+  r->xbytes = 0;
   if (r->sys) scp_destroy(r->sys);
   r->sys = nullptr;
   sv->used -= std::min(sv->used, r->bytes);
@@ -386,7 +436,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
   while (!sv->queue.empty() && (int)sv->active.size() < sv->max_active) {
     Request* r = sv->queue.front();
     const size_t est = r->bytes;
-    if (sv->used + est > sv->budget) break;
+    if (sv->used + est > sv->budget && !reclaim_buffers(sv, est)) break;
     sv->queue.pop_front();
     scp_status s = admit(sv, r);
     if (s != SCP_OK) {
@@ -399,10 +449,11 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
     r->bytes = std::max(est, r->bytes);
     sv->active.push_back(r);
   }
+  if (sv->queue.empty() || (int)sv->active.size() >= sv->max_active) lend_buffers(sv);
   if (!sv->active.empty()) {
     // 2. one chunk for everyone, one launch per (kind, size class)
     struct Work { Request* r; int n0, n1, s_hi, s_lo; };
-    // (kind, d, NR, MP, real frame)
+    // (kind, d, NR, MP, evaluation)
     std::map<std::tuple<int, int, int, int, int>, std::vector<Work>> classes;
     for (Request* r : sv->active) {
       if (r->gather) continue;
@@ -571,7 +622,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
             const int steps = std::max(8, (int)(sv->chunk_work / r->cost_step));
             const int segs = std::max(1, steps / r->ce);
             g_lo[q] = std::max(0, r->seg_next - segs + 1);
-            rounds = std::max(rounds, (r->seg_next - g_lo[q]) / r->gi.nseg + 1);
+            rounds = std::max(rounds, (r->seg_next - g_lo[q]) / r->nbuf + 1);
             for (int c = 0; c < r->S; ++c)
               it[nit++] = GItem{r->gi.A, r->gi.B, nullptr, nullptr, c, g_lo[q], 0, r->seg_next};
             lds = std::max(lds, r->gi.lds_cos);
@@ -586,8 +637,8 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
             lds = 0;
             for (size_t q = 0; q < kv.second.size(); ++q) {
               Request* r = kv.second[q];
-              for (int k = 0; k < r->gi.nseg; ++k) {
-                const int gs = r->seg_next - j * r->gi.nseg - k;
+              for (int k = 0; k < r->nbuf; ++k) {
+                const int gs = r->seg_next - j * r->nbuf - k;
                 if (gs < g_lo[q]) break;
                 for (int c = 0; c < r->S; ++c)
                   it[nit++] = GItem{r->gi.A, r->gi.B, nullptr, nullptr, c, k * r->S + c, 0, gs};
