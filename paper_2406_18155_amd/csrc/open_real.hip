@@ -618,7 +618,7 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
       if (on) to[tid + r * T] = make_float4(hr[r], hm[r], l.x, l.y);
     }
   }
-  if (A->xT == nullptr || n1 < A->nsteps) return;
+  if (A->xT == nullptr || (!OPEN && n1 < A->nsteps)) return;
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     c32 l = low(r);
@@ -637,9 +637,14 @@ l_rk4_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg, int n_lo
   kptr<GArgs> A = kconst(Ag);
   LThread<d, N, OPEN> Th;
   Th.init(A, reinterpret_cast<float*>(lds + S::bufs), false);
-  const size_t at = (size_t)blockIdx.x * S::L;
-  l_steps<d, N, OPEN, CK, false>(A, Bg, Th, lds, lds + 2 * S::L, blockIdx.x, n_lo, n_hi,
-                                 st_in ? st_in + at : nullptr, st_out ? st_out + at : nullptr, nullptr);
+  if constexpr (OPEN) {   // in one run (the range as arguments: 1 to 4 % of a step)
+    l_steps<d, N, OPEN, CK, false>(A, Bg, Th, lds, lds + 2 * S::L, blockIdx.x, 0, A->nsteps, nullptr,
+                                   nullptr, nullptr);
+  } else {
+    const size_t at = (size_t)blockIdx.x * S::L;
+    l_steps<d, N, OPEN, CK, false>(A, Bg, Th, lds, lds + 2 * S::L, blockIdx.x, n_lo, n_hi,
+                                   st_in ? st_in + at : nullptr, st_out ? st_out + at : nullptr, nullptr);
+  }
 }
 
 // The reverse walk of a column, segment by segment from the last: recompute the
