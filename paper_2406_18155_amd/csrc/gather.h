@@ -123,12 +123,14 @@ struct Nb {
   static constexpr int prow = n * n + ((n * n) & 1);
   static constexpr int srow = PAR ? orow : d;
   static constexpr int mrow = PAR ? (n + 1) + ((n + 1) & 1) : d;
-  // offset of entry k's element from the row's own (digit a, stride st)
-  static __device__ __forceinline__ int off(int k, int a, int st) {
-    if (!PAR) return (k - a) * st;
-    const int b0 = (a & 1) ^ 1;
-    const int b = ((d & 1) && k == n - 1 && b0) ? b0 : b0 + 2 * k;
-    return (b - a) * st;
+  // offset of the first entry's element from the row's own (digit a, stride st),
+  // and of entry k's from that (uniform but for the padding)
+  static __device__ __forceinline__ int first(int a, int st) {
+    return PAR ? (((a & 1) ^ 1) - a) * st : -a * st;
+  }
+  static __device__ __forceinline__ int step(int k, int a, int st) {
+    if (!PAR) return k * st;
+    return (d & 1) && k == n - 1 && !(a & 1) ? 0 : 2 * k * st;
   }
 };
 // Level of entry k of row a (-1: padding), as Nb<d, par> has it.

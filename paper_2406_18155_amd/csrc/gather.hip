@@ -161,6 +161,7 @@ __device__ __forceinline__ void one_dot(const c32* __restrict__ row, const c32* 
                                         int a, int st, float& sr, float& si) {
   using B = Nb<d, PAR>;
   const float4* r4 = reinterpret_cast<const float4*>(row);
+  y += B::first(a, st);
 #pragma unroll
   for (int k = 0; k < (B::n + 1) / 2; ++k) {
     const float4 q = r4[k];
@@ -171,9 +172,9 @@ __device__ __forceinline__ void one_dot(const c32* __restrict__ row, const c32* 
       o.x = u ? q.z : q.x;
       o.y = u ? q.w : q.y;
       if (CONJ)
-        cmac_conj(sr, si, o, y[B::off(2 * k + u, a, st)]);
+        cmac_conj(sr, si, o, y[B::step(2 * k + u, a, st)]);
       else
-        cmac(sr, si, o, y[B::off(2 * k + u, a, st)]);
+        cmac(sr, si, o, y[B::step(2 * k + u, a, st)]);
     }
   }
 }
@@ -185,21 +186,27 @@ __device__ __forceinline__ void pair_dot(const c32* __restrict__ row, const c32*
   using B = Nb<d, PAR>;
   constexpr int nn = B::n * B::n;
   const float4* r4 = reinterpret_cast<const float4*>(row);
+  const c32* y0 = y + (PAR ? B::first(ai, si_) + B::first(aj, sj_) : -(ai * si_ + aj * sj_));
 #pragma unroll
   for (int k = 0; k < (nn + 1) / 2; ++k) {
     const float4 q = r4[k];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int t = 2 * k + u;
-      if (t >= nn) continue;
-      c32 o;
-      o.x = u ? q.z : q.x;
-      o.y = u ? q.w : q.y;
-      const c32 v = y[B::off(t / B::n, ai, si_) + B::off(t % B::n, aj, sj_)];
+    c32 a;
+    a.x = q.x;
+    a.y = q.y;
+    const c32 ya = y0[B::step((2 * k) / B::n, ai, si_) + B::step((2 * k) % B::n, aj, sj_)];
+    if (CONJ)
+      cmac_conj(sr, si, a, ya);
+    else
+      cmac(sr, si, a, ya);
+    if (2 * k + 1 < nn) {
+      c32 b;
+      b.x = q.z;
+      b.y = q.w;
+      const c32 yb_ = y0[B::step((2 * k + 1) / B::n, ai, si_) + B::step((2 * k + 1) % B::n, aj, sj_)];
       if (CONJ)
-        cmac_conj(sr, si, o, v);
+        cmac_conj(sr, si, b, yb_);
       else
-        cmac(sr, si, o, v);
+        cmac(sr, si, b, yb_);
     }
   }
 }
@@ -234,7 +241,7 @@ __device__ __forceinline__ void g_apply(kptr<GArgs> A, const c32* __restrict__ y
     {
       const int sm = uni(A->kst[m]);
       const int am = ket_digit(pk, m);
-      const c32* row = tab + (dm * d + am) * Nb<d, PAR>::orow;
+      const c32* row = tab + dm * d * Nb<d, PAR>::orow + am * Nb<d, PAR>::orow;
       float sr = 0.f, si = 0.f;
       one_dot<d, PAR, false>(row, yb + e, am, sm, sr, si);
       kr += si;
@@ -243,7 +250,7 @@ __device__ __forceinline__ void g_apply(kptr<GArgs> A, const c32* __restrict__ y
     if (OPEN) {
       const int sm = uni(A->bst[m]);
       const int bm = bra_digit(pk, m, N);
-      const c32* row = tab + (dm * d + bm) * Nb<d, PAR>::orow;
+      const c32* row = tab + dm * d * Nb<d, PAR>::orow + bm * Nb<d, PAR>::orow;
       float sr = 0.f, si = 0.f;
       one_dot<d, PAR, true>(row, yb + e, bm, sm, sr, si);
       kr -= si;
@@ -543,7 +550,7 @@ __device__ __forceinline__ void g_apply_adj(kptr<GArgs> A, const c32* __restrict
     {
       const int sm = uni(A->kst[m]);
       const int am = ket_digit(pk, m);
-      const c32* row = tab + (dm * d + am) * Nb<d, PAR>::orow;
+      const c32* row = tab + dm * d * Nb<d, PAR>::orow + am * Nb<d, PAR>::orow;
       float sr = 0.f, si = 0.f;
       one_dot<d, PAR, false>(row, xb + e, am, sm, sr, si);
       yr -= si;
@@ -552,7 +559,7 @@ __device__ __forceinline__ void g_apply_adj(kptr<GArgs> A, const c32* __restrict
     if (OPEN) {
       const int sm = uni(A->bst[m]);
       const int bm = bra_digit(pk, m, N);
-      const c32* row = tab + (dm * d + bm) * Nb<d, PAR>::orow;
+      const c32* row = tab + dm * d * Nb<d, PAR>::orow + bm * Nb<d, PAR>::orow;
       float sr = 0.f, si = 0.f;
       one_dot<d, PAR, true>(row, xb + e, bm, sm, sr, si);
       yr += si;
@@ -593,10 +600,12 @@ __device__ __forceinline__ c32 comm1(const c32* __restrict__ kb, const c32* __re
                                      int e, int am, int bm, int ks, int bs) {
   using B = Nb<d, PAR>;
   float kr = 0.f, ki = 0.f, br = 0.f, bi = 0.f;
+  const c32* k0 = kb + e + B::first(am, ks);
+  const c32* b0 = kb + e + B::first(bm, bs);
 #pragma unroll
   for (int x = 0; x < B::n; ++x) {
-    cmac(kr, ki, rows[am * B::srow + x], kb[e + B::off(x, am, ks)]);
-    cmac_conj(br, bi, rows[bm * B::srow + x], kb[e + B::off(x, bm, bs)]);
+    cmac(kr, ki, rows[am * B::srow + x], k0[B::step(x, am, ks)]);
+    cmac_conj(br, bi, rows[bm * B::srow + x], b0[B::step(x, bm, bs)]);
   }
   c32 z;
   z.x = kr - br;
@@ -611,13 +620,15 @@ __device__ __forceinline__ c32 comm2(const c32* __restrict__ kb, const c32* __re
                                      int bj, int ksi, int ksj, int bsi, int bsj) {
   using B = Nb<d, PAR>;
   float kr = 0.f, ki = 0.f, br = 0.f, bim = 0.f;
+  const c32* k0 = kb + e + B::first(ai, ksi) + B::first(aj, ksj);
+  const c32* b0 = kb + e + B::first(bi, bsi) + B::first(bj, bsj);
 #pragma unroll
   for (int x = 0; x < B::n; ++x) {
     float ir = 0.f, ii = 0.f, jr = 0.f, ji = 0.f;
 #pragma unroll
     for (int z = 0; z < B::n; ++z) {
-      cmac(ir, ii, Rj[aj * B::srow + z], kb[e + B::off(x, ai, ksi) + B::off(z, aj, ksj)]);
-      cmac_conj(jr, ji, Rj[bj * B::srow + z], kb[e + B::off(x, bi, bsi) + B::off(z, bj, bsj)]);
+      cmac(ir, ii, Rj[aj * B::srow + z], k0[B::step(x, ai, ksi) + B::step(z, aj, ksj)]);
+      cmac_conj(jr, ji, Rj[bj * B::srow + z], b0[B::step(x, bi, bsi) + B::step(z, bj, bsj)]);
     }
     c32 u, w;
     u.x = ir;
@@ -1298,7 +1309,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                 const int am = ket_digit(pk[r], m);
                 c32 kt[nb];
 #pragma unroll
-                for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::off(x, am, ks)];
+                for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::first(am, ks) + B_::step(x, am, ks)];
                 if constexpr (KC) {
 #pragma unroll
                   for (int x = 0; x < nb; ++x) kv[r][x] = kt[x];
@@ -1325,7 +1336,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                 for (int x = 0; x < nb; ++x) kt[x] = kv[KC ? r : 0][x];
               } else {
 #pragma unroll
-                for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::off(x, am, ks)];
+                for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::first(am, ks) + B_::step(x, am, ks)];
               }
             };
             // drive slots on this mode: 2 Im <O kb, y>, one sum per wave (the
@@ -1368,7 +1379,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                   const int am = ket_digit(pk[r], m), ap = ket_digit(pk[r], pm);
                   c32 yv[nb];
 #pragma unroll
-                  for (int z = 0; z < nb; ++z) yv[z] = ybw[e + B_::off(z, ap, ps)];
+                  for (int z = 0; z < nb; ++z) yv[z] = ybw[e + B_::first(ap, ps) + B_::step(z, ap, ps)];
                   const c32 cp = rowdot<nb>(Rp + ap * SR, yv);
                   C[r].x = fmaf(gc, cp.x, C[r].x);
                   C[r].y = fmaf(gc, cp.y, C[r].y);
@@ -1417,7 +1428,7 @@ __device__ __forceinline__ void g_adj_body(const GArgs* __restrict__ Ag, const G
                   const int am = ket_digit(pk[r], m);
                   c32 kt[nb];
 #pragma unroll
-                  for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::off(x, am, ks)];
+                  for (int x = 0; x < nb; ++x) kt[x] = kbw[e + B_::first(am, ks) + B_::step(x, am, ks)];
                   v += 2.f * im_conj(rowdot<nb>(rows + am * SR, kt), ybw[e]);
                 }
               }
