@@ -2368,23 +2368,32 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
 // --- closed systems ----------------------------------------------------------
 // The gather engine (one workgroup per column) takes a closed system of a
 // compiled shape when its columns would leave most of the chip idle in the
-// register-layout stepper; in its real form, whenever the columns fill no more
-// than one round of workgroups, four where a thread has one element.  Measured,
-// register -> real form, us per step (forward; forward + gradient):
-//   6-fluxonium chain, d = 4, 64 columns       56 -> 17;  302 -> 76
-//   7-transmon ring, d = 3, 128 columns        47 -> 23;  244 -> 121
-//   5-fluxonium chain, d = 5, 32 columns       54 -> 40;  313 -> 111
-//   4-transmon chain, d = 4, 256 columns       35 -> 2.8; 163 -> 17
-//   6-transmon ring, d = 3, 64 / 729 columns   33 -> 4 / 33 -> 12;  147 -> 20 / 150 -> 136
-//   9-mode ring, d = 2, 512 columns            34 -> 4.3; 181 -> 89
-bool gather_preferred(const scp_system* sys, int S, bool real) {
+// register-layout stepper; in its real form, for as many columns as it wins with.
+// Measured, register -> real form, us per step (forward; forward + gradient):
+//   6-fluxonium chain, d = 4, 64 / 256 columns   54 -> 14;  252 -> 71 / 258 -> 160
+//   7-transmon ring, d = 3, 128 / 256 columns    47 -> 23;  245 -> 119 / 249 -> 194
+//   5-fluxonium chain, d = 5, 128 / 256 columns  51 -> 34;  266 -> 165 / 272 -> 266
+//   5-transmon ring, d = 5, 128 / 160 / 256      48 -> 45;  247 -> 195 / 249 -> 258 / 253 -> 312
+//   4-transmon ring, d = 4, 256 / 1024 columns   44 -> 3.5; 186 -> 18 / 186 -> 43
+//   6-transmon ring, d = 3, 768 / 900 / 1024     33 -> 12;  151 -> 138 / 168 -> 182 / 169 -> 183
+//   5-transmon ring, d = 4, 768 / 1024           48 -> 14;  219 -> 152 / 221 -> 202
+//   9-mode ring, d = 2, 512 / 1024 columns       34 -> 4.2; 182 -> 89 / 183 -> 176
+//   10-mode ring, d = 2, 512 / 600 / 1024        47 -> 9.1; 232 -> 197 / 234 -> 242 / 237 -> 389
+// A gradient's time grows with the rounds of workgroups (256 of 1024 threads): up
+// to three of them above D = 512 (two at d = 2, whose rows have one entry for the
+// same sums per wave), one above D = 1024, half of one with five levels there
+// (four elements a thread, the last one's threads nearly idle).
+bool gather_preferred(const scp_system* sys, int S, bool real, bool grad) {
   if (!g_supported(sys->d, sys->n_modes, false)) return false;
   GArgs A;
   if (g_args(sys, false, nullptr, nullptr, A) != SCP_OK) {
     set_error("");
     return false;
   }
-  if (real && A.rt != nullptr) return S <= (sys->D <= 1024 ? 1024 : 256);
+  if (real && A.rt != nullptr) {
+    if (sys->D > 1024) return S <= (grad && sys->d == 5 ? 128 : 256);
+    return S <= (!grad || sys->D <= 512 ? 1024 : (sys->d == 2 ? 512 : 768));
+  }
   if (S > 256) return false;
   const int fused_wg = (S + sys->plan.CPW - 1) / sys->plan.CPW;
   return fused_wg < 64;

@@ -284,7 +284,7 @@ scp_status lindblad_adjoint_workspace_bytes(const scp_system* sys, int S, size_t
 scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const double* gammaphi,
                                    int S, void* ws, size_t ws_bytes, const float2* rho0,
                                    const float2* cot, double* grad, hipStream_t st);
-bool gather_preferred(const scp_system* sys, int S, bool real);
+bool gather_preferred(const scp_system* sys, int S, bool real, bool grad);
 // Forward of a closed system in the real form, one workgroup per column, for
 // shapes above the gather engine's (d = 3, N = 8).
 bool real_column_supported(const scp_system* sys);

@@ -912,7 +912,8 @@ WsLayout ws_layout_in(const scp_system* sys, const scp_solve_opts* o, int with_g
   const int engine = allow_gather ? sys->engine : 1;
   bool want = false;
   if (o->precision == 0 && engine != 1)
-    want = engine == 2 ? gather_supported(sys) : gather_preferred(sys, (int)S, real);
+    want = engine == 2 ? gather_supported(sys)
+                       : gather_preferred(sys, (int)S, real, o->with_ckpt || with_grad);
   if (want && (o->with_ckpt || with_grad)) {
     want = gather_grad_check(sys) == SCP_OK;
     if (!want) set_error("");

@@ -254,7 +254,8 @@ scp_status admit(scp_server* sv, Request* r) {
   // the budget beside what is admitted
   r->gather = false;
   if (sv->engine != 1 && (sv->engine == 2 ? gather_supported(sys)
-                                          : gather_preferred(sys, r->S, sys->plan.real_frame != 0))) {
+                                          : gather_preferred(sys, r->S, sys->plan.real_frame != 0,
+                                                             r->want_grad != 0))) {
     if (gather_grad_check(sys) == SCP_OK) {
       r->gws_bytes = gather_serve_bytes(sys, r->S, r->ce, r->want_grad != 0);
       const size_t need = r->gws_bytes + (size_t)(4 << 20) + 2 * (size_t)r->S * sys->D * 8;
