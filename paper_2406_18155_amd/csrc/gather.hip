@@ -2449,10 +2449,14 @@ static scp_status gc_layout(const scp_system* sys, int S, int ce, bool with_grad
   w.nacc = sys->plan.npulse + 3 * sys->n_modes + sys->plan.ncoup;
   w.gw = 4 * A.nds + 3 * sys->n_modes + A.ncp;
   w.nblk = (N + GF_STEPS - 1) / GF_STEPS;
-  // two workgroups for every compute unit, where there are that many segments
-  // (each holds a buffer of stage inputs); two segments at least, as many
-  // buffers as a walk one segment after the other needs to hide its recompute
-  w.nseg = std::min(w.nck, std::max(2, (512 + S - 1) / S));
+  // two workgroups for every compute unit (four of at most 256 threads), where
+  // there are that many segments (each holds a buffer of stage inputs); two
+  // segments at least, as many buffers as a walk one segment after the other needs
+  // to hide its recompute.  4-transmon ring, d = 4, n_g = 0.2, 256 columns, forward
+  // and gradient: two of 256 threads 55 us per step, four 47 (53 with one segment
+  // after the other, which needs no sweep)
+  const int most = sys->D <= 256 ? 1024 : 512;
+  w.nseg = std::min(w.nck, std::max(2, (most + S - 1) / S));
   if (nseg > 0) w.nseg = std::min(w.nseg, nseg);
   size_t off = 0;
   w.args = off;
