@@ -37,6 +37,7 @@
 //      computes d output rows (pair operations, when that fills the block)
 //      or one output row of one fibre from one buffer into the other, which
 //      keeps up to d^2 times more threads busy; the buffers then swap.
+#include <climits>
 #include <cmath>
 #include <cstring>
 
@@ -599,17 +600,22 @@ struct TpRun {
   double fT[SCP_MAX_MODES][SCP_MAX_TRUNC];   // frame energy times T, reduced mod 2 pi
 };
 
-// modes per pass: d^Q amplitudes of a thread in registers
-constexpr int tp_q(int d) { return d == 2 ? 4 : (d == 5 ? 1 : 2); }
+// Modes per pass: d^Q amplitudes of a thread in registers, eight or nine of them
+// (d = 4 and 5: one mode's).  With 16 the passes are fewer, but a small column
+// has a lane or two at work and a large one spills: us per step at Q2, 256
+// columns, 16 amplitudes -> 8 (d = 2) or 4 (d = 4): 4 modes 5.1 -> 2.6, 12 modes
+// 14.9 -> 7.9; d = 4, 2 modes 6.7 -> 2.9, 6 modes 19.2 -> 11.1.
+constexpr int tp_q(int d) { return d == 2 ? 3 : (d == 3 ? 2 : 1); }
 constexpr int tp_pow(int b, int e) { return e == 0 ? 1 : b * tp_pow(b, e - 1); }
 
 // Place of element i in LDS.  Even d: a thread's amplitudes of the fastest
-// group are 16 in a row, which would put every lane on the same banks; one
-// element of padding per 16 spreads them.  Strides of at least 16 are
-// multiples of 16 there, so the map is additive along a group.
+// group are 8 in a row (d = 2; d = 4: a pair operation's 16), which would put
+// every lane on the same banks; one element of padding per 8 (16) spreads them.
+// The strides of the other groups (operations) are multiples of 8 (4 within a
+// block of 16, or multiples of 16), so the map is additive along a group.
 template <int d>
 __host__ __device__ __forceinline__ int tp_at(int i) {
-  return d % 2 == 0 ? i + (i >> 4) : i;
+  return d == 2 ? i + (i >> 3) : (d == 4 ? i + (i >> 4) : i);
 }
 
 // One pass: the gates G[k] (d x d each, k = 0 the most significant mode) of
@@ -684,7 +690,6 @@ __global__ void __launch_bounds__(1024) tr_phase_kernel(TpRun R, const double2* 
         if (R.nq[g] == 1) tp_group<d, 1>(lds, R.D, R.s[g], G, pj);
         if constexpr (Q > 2) {
           if (R.nq[g] == 2) tp_group<d, 2>(lds, R.D, R.s[g], G, pj);
-          if (R.nq[g] == 3) tp_group<d, 3>(lds, R.D, R.s[g], G, pj);
         }
       }
       __syncthreads();
@@ -1194,14 +1199,23 @@ void build_plan(const scp_system* sys, int H, bool absorb, bool regs, TrPlan& P)
     }
 }
 
+// Q1 on two modes is one fused operation per step where the phase form has two
+// passes, and few columns wait for it: us per step, phase form -> fused, 256
+// columns: d = 3 1.48 -> 1.22, d = 5 2.54 -> 1.73 (d = 2, 0.82, and d = 4, 1.54,
+// are the faster in the phase form with one or two passes).  1024 columns, d = 5:
+// the phase form is twice as fast.
+bool one_operation(const scp_system* sys, int order, int S) {
+  return order == SCP_TROTTER_Q1 && sys->n_modes == 2 && (sys->d == 3 || sys->d == 5) && S <= 512;
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-TrLayout tr_layout(const scp_system* sys, int order) {
+TrLayout tr_layout(const scp_system* sys, int order, int S) {
   TrLayout L{};
   L.r = order == SCP_TROTTER_Q4 ? 3 : (order == SCP_TROTTER_Q4J ? 2 : 1);
   L.sym = order != SCP_TROTTER_Q1;
   L.H = L.sym ? 2 : 1;
-  L.phase = couplings_commute(sys);
+  L.phase = couplings_commute(sys) && !one_operation(sys, order, S);
   L.P = TrPlan{};
   if (!L.phase) {
     // split forms need a second column buffer; single-mode gates are
@@ -1284,7 +1298,10 @@ scp_status trotter_check(const scp_system* sys, int order) {
   return SCP_OK;
 }
 
-size_t trotter_workspace_bytes(const scp_system* sys, int order) { return tr_layout(sys, order).total; }
+// the same for any number of columns
+size_t trotter_workspace_bytes(const scp_system* sys, int order) {
+  return std::max(tr_layout(sys, order, 1).total, tr_layout(sys, order, INT_MAX).total);
+}
 
 namespace {
 
@@ -1411,12 +1428,14 @@ hipError_t mm_gates(const scp_system* sys, const TrLayout& W, char* base, bool j
 }  // namespace
 
 // psi0 == nullptr: the gate tables only (single-mode and pair gates, what
-// the adjoint reuses; with ``fuse`` the fused operations too), no propagation
+// the adjoint reuses; with ``fuse`` the fused operations too), no propagation.
+// The phase form has the pair gates only for that (``adjoint``): its own pair terms
+// are the phases.
 static scp_status tr_launch(scp_system* sys, int order, int S, void* ws, const double2* psi0,
-                            double2* psiT, bool fuse, hipStream_t st) {
+                            double2* psiT, bool adjoint, bool fuse, hipStream_t st) {
   scp_status chk = trotter_check(sys, order);
   if (chk != SCP_OK) return chk;
-  const TrLayout W = tr_layout(sys, order);
+  const TrLayout W = tr_layout(sys, order, S);
   const int d = sys->d, M = sys->n_modes, E = (int)sys->coup.size(), N = sys->n_steps;
   char* base = static_cast<char*>(ws);
   // inputs: energies, dressed operators, pulse parameters
@@ -1461,7 +1480,7 @@ static scp_status tr_launch(scp_system* sys, int order, int S, void* ws, const d
   const double* dpar = reinterpret_cast<const double*>(base + W.par);
   double2* pg = reinterpret_cast<double2*>(base + W.pg);
   double2* sg = reinterpret_cast<double2*>(base + W.sg);
-  if (E > 0) {
+  if (E > 0 && (adjoint || !W.phase)) {
     const int n = d * d;
     hipLaunchKernelGGL(tr_pair_gate_kernel, dim3(W.r * E), dim3(256), 4 * n * n * sizeof(double2), st,
                        G, dops, pg);
@@ -1545,7 +1564,7 @@ static scp_status tr_launch(scp_system* sys, int order, int S, void* ws, const d
 
 scp_status launch_trotter(scp_system* sys, int order, int S, void* ws, const double2* psi0,
                           double2* psiT, hipStream_t st) {
-  return tr_launch(sys, order, S, ws, psi0, psiT, false, st);
+  return tr_launch(sys, order, S, ws, psi0, psiT, false, false, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -2507,7 +2526,7 @@ struct LcLayout {
 
 LcLayout lc_layout(const scp_system* sys, int order, int S) {
   LcLayout L{};
-  L.F = tr_layout(sys, order);
+  L.F = tr_layout(sys, order, S);
   const size_t d = sys->d, dd = d * d, M = sys->n_modes, E = std::max<size_t>(1, sys->coup.size());
   const size_t N = sys->n_steps, r = L.F.r, D = sys->D;
   L.chunk = (int)std::min<size_t>(N, LC_CHUNK);
@@ -2534,7 +2553,7 @@ LcLayout lc_layout(const scp_system* sys, int order, int S) {
       }
     }
   }
-  size_t o = L.F.total;
+  size_t o = trotter_workspace_bytes(sys, order);
   auto take = [&](size_t bytes) {
     const size_t at = o;
     o = align256(o + bytes);
@@ -2587,7 +2606,7 @@ static scp_status lc_adjoint(scp_system* sys, int order, int S, void* ws, const 
   char* base = static_cast<char*>(ws);
   // the forward: only its final state is kept (its gate tables are reused)
   const double2* psiT = psi0 ? reinterpret_cast<double2*>(base + Y.psiT) : psiT_in;
-  scp_status s = tr_launch(sys, order, S, ws, psi0, const_cast<double2*>(psiT), Y.len != 0, st);
+  scp_status s = tr_launch(sys, order, S, ws, psi0, const_cast<double2*>(psiT), true, Y.len != 0, st);
   if (s != SCP_OK) return s;
   // operator derivatives of every mode (FP64)
   std::vector<double> hdeps((size_t)M * 3 * d);
