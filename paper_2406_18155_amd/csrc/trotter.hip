@@ -1675,9 +1675,9 @@ lc_walk_kernel(LcRun R, int n_top, int n_base, int first, const double2* __restr
                double2* __restrict__ Mp) {
   extern __shared__ double2 lds[];
   constexpr int dd = d * d;
-  const int slot = blockIdx.x / R.S, col = blockIdx.x - slot * R.S;
+  const int slot = blockIdx.y, col = blockIdx.x;
   const int n_hi = n_top - slot * R.len, n_lo = R.len ? max(n_base, n_hi - R.len) : n_base;
-  const size_t off = (size_t)blockIdx.x * R.D;
+  const size_t off = ((size_t)slot * R.S + col) * R.D;
   double2* L = lds;                   // psi (the state)
   double2* Lm = lds + R.D;            // mu (the costate)
   double2* scr = lds + 2 * R.D;       // TR_THREADS partial sums
@@ -2207,10 +2207,10 @@ lc_walk_split_kernel(LcRun R, int n_top, int n_base, int first, const double2* _
   extern __shared__ double2 lds[];
   constexpr int dd = d * d, NN = dd * dd;
   static_assert(NN <= 2 * LC_THREADS, "a gate table is prefetched as two entries per thread");
-  const int slot = blockIdx.x / R.S, col = blockIdx.x - slot * R.S;
+  const int slot = blockIdx.y, col = blockIdx.x;
   const int n_hi = n_top - slot * R.len, n_lo = R.len ? max(n_base, n_hi - R.len) : n_base;
   const int D = R.D, tid = threadIdx.x, nft = D / d;
-  const size_t off = (size_t)blockIdx.x * D;
+  const size_t off = ((size_t)slot * R.S + col) * D;
   double2* P = lds;                  // psi: two buffers of D
   double2* U = lds + 2 * D;          // mu: two buffers of D
   double2* Gi = lds + 4 * D;         // inverse gates: two slots of NN
@@ -2504,7 +2504,7 @@ hipError_t run_lc_walk(const LcRun& R, int n_hi, int n_lo, int first, const doub
     hipError_t e = hipFuncSetAttribute((const void*)lc_walk_split_kernel<d>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(lc_walk_split_kernel<d>, dim3(nslot * R.S), dim3(LC_THREADS), sh, st, R, n_hi, n_lo,
+    hipLaunchKernelGGL(lc_walk_split_kernel<d>, dim3(R.S, nslot), dim3(LC_THREADS), sh, st, R, n_hi, n_lo,
                        first, psiT, lamT, psi_st, mu_st, sgi, sga, pgi, pga, Ms, Mp);
     return hipGetLastError();
   }
@@ -2512,7 +2512,7 @@ hipError_t run_lc_walk(const LcRun& R, int n_hi, int n_lo, int first, const doub
   hipError_t e = hipFuncSetAttribute((const void*)lc_walk_kernel<d>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lc_walk_kernel<d>, dim3(nslot * R.S), dim3(TR_THREADS), sh, st, R, n_hi, n_lo, first,
+  hipLaunchKernelGGL(lc_walk_kernel<d>, dim3(R.S, nslot), dim3(TR_THREADS), sh, st, R, n_hi, n_lo, first,
                      psiT, lamT, psi_st, mu_st, sgi, sga, pgi, pga, Ms, Mp);
   return hipGetLastError();
 }
@@ -2536,9 +2536,13 @@ LcLayout lc_layout(const scp_system* sys, int order, int S) {
   // for fewer
   size_t cols = S, steps = (size_t)L.chunk * S, carry = 0;
   // slots where the gates are unitary, the sweep can use the split form of the
-  // fused operations, and one walk would fill less than half of the chip
+  // fused operations, and one walk would fill less than half of the chip (a
+  // quarter for two modes of five levels, whose one operation per pass costs the
+  // sweep what it costs the walk: Q1, 127 columns 23.5 us per step in one walk,
+  // 24.2 in three slots)
+  const int most = d == 5 && M == 2 ? 64 : 127;
   if (order != SCP_TROTTER_Q4J && !L.F.phase && L.F.mode2 != 0 && N > 1) {
-    for (int s = 1; s <= std::min(S, 127); ++s) {
+    for (int s = 1; s <= std::min(S, most); ++s) {
       const int want = (256 + s - 1) / s;
       const int len = (int)std::min<size_t>(64, (N + want - 1) / want);
       const int nslot = (int)std::min<size_t>(want, (N + len - 1) / len);
