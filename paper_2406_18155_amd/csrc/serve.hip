@@ -443,6 +443,7 @@ scp_status scp_server_step(scp_server* sv, int32_t* n_active, int32_t* n_queued)
     if (s != SCP_OK) {
       r->state = RQ_FAILED;
       r->err = scp_last_error();
+      r->bytes = 0;   // never counted
       release(sv, r);
       continue;
     }

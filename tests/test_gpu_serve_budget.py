@@ -59,3 +59,21 @@ def test_lent_buffers_are_taken_back_for_a_queued_request(scp, engine):  # noqa:
     assert srv.step() == (3, 0)
     _check(scp, scp.serve.drain(srv, ids), reqs, ids, engine)
     srv.close()
+
+
+def test_a_refused_request_leaves_the_budget_alone(scp):  # noqa: F811
+    # six levels: queued, refused when it is built
+    good, bad = _request(0), _request(1)
+    bad["modes"] = [dict(m, trunc=6) for m in bad["modes"][:2]]
+    bad["couplings"], bad["drives"] = bad["couplings"][:1], bad["drives"][:2]
+    bad["columns"], bad["comp_rows"], bad["comp_cols"] = [0, 1], [0, 1], [0, 1]
+    bad["target"], bad["n_steps"] = np.eye(2), 300
+    need = scp.serve.request_bytes(good, False)
+    srv = scp.serve.Server(need + scp.serve.request_bytes(bad, False), max_active=8, chunk_work=1e4,
+                           engine="register")
+    ids = [srv.submit(q, False) for q in (good, bad, good)]
+    assert srv.step() == (1, 1)              # the third waits for the first's memory
+    assert srv.result(ids[0])["state"] == "running" and srv.result(ids[2])["state"] == "queued"
+    with pytest.raises(scp.ScpError, match="d in"):
+        srv.result(ids[1])
+    srv.close()
