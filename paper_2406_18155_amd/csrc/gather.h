@@ -78,7 +78,8 @@ struct GArgs {
   // mode, signed strength, sign of the product of two imaginary operators,
   // index), per driven mode its operator and drive slot
   int rp_n[GA_MAXM], rp_u[GA_MAXM][2], rp_c[GA_MAXM][2], rd_u[GA_MAXM], rd_k[GA_MAXM];
-  float rp_g[GA_MAXM][2], rp_s[GA_MAXM][2], rd_s[GA_MAXM];   // rd_s: 1 / the scale of rc
+  // 1 / the operator's largest entry (that of its static row), 1 / the scale of rc
+  float rp_g[GA_MAXM][2], rp_s[GA_MAXM][2], rd_s[GA_MAXM], rd_c[GA_MAXM];
 };
 
 // Checkpoints, costate and gradient buffers of an adjoint.

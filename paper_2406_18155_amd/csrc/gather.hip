@@ -1786,6 +1786,7 @@ static scp_status g_args(const scp_system* sys, bool open, const double* gamma1,
     for (int q = 0; q < A.ndm; ++q) {
       A.dmask |= 1 << A.dm_mode[q];
       A.rd_s[A.dm_mode[q]] = (float)(A.kappa / sys->rc_scale[A.dm_mode[q]]);
+      A.rd_c[A.dm_mode[q]] = (float)(1.0 / sys->rc_scale[A.dm_mode[q]]);
     }
   }
   return SCP_OK;

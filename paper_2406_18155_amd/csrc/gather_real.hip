@@ -968,7 +968,7 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
               t1 = fmaf(a[2 * n_ + x], w, t1);
               t2 = fmaf(a[3 * n_ + x], w, t2);
             }
-            const float cm = c[m] * unif(A->rd_s[m]);
+            const float cm = c[m] * unif(A->rd_c[m]);   // c(t) itself: kappa comes with the fold
             t[m][0] = fmaf(cm, t0, t[m][0]);
             t[m][1] = fmaf(cm, t1, t[m][1]);
             t[m][2] = fmaf(cm, t2, t[m][2]);
