@@ -521,7 +521,7 @@ __device__ __forceinline__ void adj_stage(kptr<Plan> P, c32* lds, int cbase,
             const int par0 = uni(R.par0), npar = uni(R.npar);
             for (int q = 0; q < npar; ++q)
               acc_add(A, accw, par0 + q, (double)dcq[par0 + q] * (double)s_im, lane);
-            if (uni(P->mdrv_first[kk])) {   // one c(t) per slot: count the slot once
+            if ((uni(P->mdrv_first[kk >> 5]) >> (kk & 31)) & 1) {   // one c(t) per slot: count the slot once
               const float c = cq[uni(R.cidx)];
 #pragma unroll
               for (int th = 0; th < 3; ++th)

@@ -1738,7 +1738,7 @@ static scp_status g_args(const scp_system* sys, bool open, const double* gamma1,
   }
   // coupled pairs (i < j)
   for (int e = 0; e < P.ncoup; ++e) {
-    const int si = P.coup_slot_i[e], sj = P.coup_slot_j[e];
+    const int si = sys->coup_slot_i[e], sj = sys->coup_slot_j[e];
     int i = P.slot_mode[si], j = P.slot_mode[sj];
     int ssi = si, ssj = sj;
     if (i > j) {
@@ -1953,7 +1953,7 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
   }
   A.ncp = P.ncoup;
   for (int e = 0; e < P.ncoup; ++e) {
-    const int si = P.coup_slot_i[e], sj = P.coup_slot_j[e];
+    const int si = sys->coup_slot_i[e], sj = sys->coup_slot_j[e];
     const int ti = tslot(si), tj = tslot(sj);
     if (ti < 0 || tj < 0) return fail(SCP_EINVAL, "gather-engine gradient: too many operator slots");
     A.cp_i[e] = P.slot_mode[si];
@@ -1975,7 +1975,7 @@ static scp_status g_args_grad(const scp_system* sys, bool open, GArgs& A) {
       const int i = std::min(c.i, c.j), j = std::max(c.i, c.j), p = j == i + 1 ? i : N - 1;
       const int ui = c.i == i ? c.op_i : c.op_j, uj = c.i == i ? c.op_j : c.op_i;
       const int q = A.rp_n[p]++;
-      const float sg = sys->slot_imag[P.coup_slot_i[e]] ? -1.f : 1.f;
+      const float sg = sys->slot_imag[sys->coup_slot_i[e]] ? -1.f : 1.f;
       A.rp_u[p][q] = ui | (uj << 1);
       A.rp_c[p][q] = e;
       A.rp_s[p][q] = sg;

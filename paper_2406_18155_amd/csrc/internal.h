@@ -55,7 +55,6 @@ struct Plan {
   int32_t slot_mode[MAXSLOTS];
   int32_t slot_op[MAXSLOTS];
   float coup_g[MAXCOUP];
-  int32_t coup_slot_i[MAXCOUP], coup_slot_j[MAXCOUP];
   DriveDev drives[MAXDRIVES];
   int32_t layout_of_mode[16];  // a layout whose register modes contain the mode
   int32_t pos_of_mode[16];     // its register position there
@@ -74,7 +73,7 @@ struct Plan {
   int32_t lmode[MAXL][8];          // mode at each register position of each layout (-1: none)
   int32_t mdrv_off[17];            // drives of mode m: mdrv[mdrv_off[m] .. mdrv_off[m+1])
   int32_t mdrv[MAXDRIVES];         // drive indices grouped by mode
-  int32_t mdrv_first[MAXDRIVES];   // 1: first drive on its operator slot
+  uint32_t mdrv_first[MAXDRIVES / 32];   // bit: first drive on its operator slot
   int32_t nacc;                    // gradient accumulators: npulse + 3 N + ncoup
   // Real frame (every term a real operator: each operator is real or i times
   // real, both factors of a pair term of one kind, drives on real operators):
@@ -182,6 +181,7 @@ struct scp_system {
   std::vector<scp::Drive> drives;
   int n_params = 0, n_pulse = 0;
   // slots / pairs / groups (host copies used by gradient assembly)
+  std::vector<int> coup_slot_i, coup_slot_j;   // operator slots of every coupling
   std::vector<int> slot_mode, slot_op;
   std::vector<scp::cplx> pairW_host;   // static pair operators sum g O_j (d*d each)
   std::vector<int> pair_mode_host;

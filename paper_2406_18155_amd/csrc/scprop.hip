@@ -498,7 +498,7 @@ scp_status make_plan(scp_system* sys) {
         bool first = true;
         for (int k2 = 0; k2 < k; ++k2) first &= P.drives[k2].slot != P.drives[k].slot;
         P.mdrv[q] = (int32_t)k;
-        P.mdrv_first[q] = first ? 1 : 0;
+        P.mdrv_first[q >> 5] |= (uint32_t)first << (q & 31);
         ++q;
       }
     }
@@ -512,8 +512,8 @@ scp_status make_plan(scp_system* sys) {
   P.ncoup = (int)sys->coup.size();
   for (int e = 0; e < P.ncoup; ++e) {
     P.coup_g[e] = (float)sys->coup[e].g;
-    P.coup_slot_i[e] = slot(sys->coup[e].i, sys->coup[e].op_i);
-    P.coup_slot_j[e] = slot(sys->coup[e].j, sys->coup[e].op_j);
+    sys->coup_slot_i.push_back(slot(sys->coup[e].i, sys->coup[e].op_i));
+    sys->coup_slot_j.push_back(slot(sys->coup[e].j, sys->coup[e].op_j));
   }
   P.nacc = P.npulse + 3 * N + P.ncoup;
   P.off_pair = P.nslots * d * d;
