@@ -198,7 +198,8 @@ scp_status scp_system_set_frame(scp_system* sys, int32_t real_frame);
  * workgroups, or the device is in the real frame with operators between levels
  * of unlike parity only, coupled neighbours on a chain or ring of its modes
  * and at most 256 columns (1024 for D <= 1024; with checkpoints or a gradient
- * 768 for D > 512, 512 there with d = 2, 128 for D > 1024 with d = 5); else engine 1.  A forward
+ * for D > 512 512 with d = 2 and 768 with d = 3, for D > 1024 128 with d = 5);
+ * else engine 1.  A forward
  * without checkpoints of a device with D < 64 and at least 64 steps is split
  * over time under engine 0: runs of steps propagate the identity side by side
  * on engine 1's stepper and are multiplied onto the columns in FP64

@@ -2380,10 +2380,11 @@ scp_status launch_lindblad_adjoint(scp_system* sys, const double* gamma1, const 
 //   5-transmon ring, d = 4, 768 / 1024           48 -> 14;  219 -> 152 / 221 -> 202
 //   9-mode ring, d = 2, 512 / 1024 columns       34 -> 4.2; 182 -> 89 / 183 -> 176
 //   10-mode ring, d = 2, 512 / 600 / 1024        47 -> 9.1; 232 -> 197 / 234 -> 242 / 237 -> 389
-// A gradient's time grows with the rounds of workgroups (256 of 1024 threads): up
-// to three of them above D = 512 (two at d = 2, whose rows have one entry for the
-// same sums per wave), one above D = 1024, half of one with five levels there
-// (four elements a thread, the last one's threads nearly idle).
+// A gradient's time grows with the rounds of workgroups (256 of 1024 threads).
+// Above D = 512 it wins for four of them, three at d = 3 and two at d = 2 (rows of
+// fewer entries for the same sums per wave); above D = 1024 for one, half of one
+// with five levels there (four elements a thread, the last one's threads nearly
+// idle).
 bool gather_preferred(const scp_system* sys, int S, bool real, bool grad) {
   if (!g_supported(sys->d, sys->n_modes, false)) return false;
   GArgs A;
@@ -2393,7 +2394,7 @@ bool gather_preferred(const scp_system* sys, int S, bool real, bool grad) {
   }
   if (real && A.rt != nullptr) {
     if (sys->D > 1024) return S <= (grad && sys->d == 5 ? 128 : 256);
-    return S <= (!grad || sys->D <= 512 ? 1024 : (sys->d == 2 ? 512 : 768));
+    return S <= (!grad || sys->D <= 512 || sys->d > 3 ? 1024 : (sys->d == 2 ? 512 : 768));
   }
   if (S > 256) return false;
   const int fused_wg = (S + sys->plan.CPW - 1) / sys->plan.CPW;

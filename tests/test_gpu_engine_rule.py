@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,n,fwd,grad", [(3, 4, 1024, 1024), (2, 9, 1024, 1024), (2, 10, 1024, 512),
-                                          (3, 6, 1024, 768), (4, 5, 1024, 768), (4, 6, 256, 256),
+                                          (3, 6, 1024, 768), (4, 5, 1024, 1024), (4, 6, 256, 256),
                                           (5, 5, 256, 128)])
 def test_columns_of_the_gather_engine(d, n, fwd, grad):
     if not torch.cuda.is_available():
