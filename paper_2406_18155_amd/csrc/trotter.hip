@@ -2537,10 +2537,10 @@ LcLayout lc_layout(const scp_system* sys, int order, int S) {
   size_t cols = S, steps = (size_t)L.chunk * S, carry = 0;
   // slots where the gates are unitary, the sweep can use the split form of the
   // fused operations, and one walk would fill less than half of the chip (a
-  // quarter for two modes of five levels, whose one operation per pass costs the
-  // sweep what it costs the walk: Q1, 127 columns 23.5 us per step in one walk,
+  // quarter for Q1 on two modes of five levels, whose one operation per step costs
+  // the sweep what it costs the walk: 127 columns 23.5 us per step in one walk,
   // 24.2 in three slots)
-  const int most = d == 5 && M == 2 ? 64 : 127;
+  const int most = order == SCP_TROTTER_Q1 && d == 5 && M == 2 ? 64 : 127;
   if (order != SCP_TROTTER_Q4J && !L.F.phase && L.F.mode2 != 0 && N > 1) {
     for (int s = 1; s <= std::min(S, most); ++s) {
       const int want = (256 + s - 1) / s;
