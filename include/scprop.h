@@ -557,14 +557,21 @@ void scp_destroy(scp_system* sys);
  * scp_system_set_engine) are batched per (d, modes) on the gather engine
  * instead, when their workspace fits the budget beside what is admitted: per
  * tick one launch of every such request's step range of the forward (its
- * compensated state saved between chunks) and per round one launch of the
- * next segment of every such request's reverse walk.  The server starts with
- * engine 1 (the register-layout kernels), which gives the higher throughput
- * on a saturated mix.  Work per tick
- * per workgroup is about chunk_work cost units (0 = default).  A request's
- * result is bitwise the same whether it runs alone or among others, and the
- * same as scp_propagate / scp_propagate_adjoint on the same engine.  The server allocates device memory
- * (at admission); it is not for callers that cannot allocate.
+ * compensated state saved between chunks); for the reverse walk one launch of
+ * the costate sweep over every such request's segments of this tick, then
+ * rounds of one launch, up to eight segments of each request side by side
+ * (n_cols workgroups a segment).  A request holds the stage inputs of one
+ * segment; while nothing waits for admission, buffers for more are lent to it
+ * within the budget, and taken back when a request needs the room.  The server
+ * starts with engine 1 (the register-layout kernels); on a saturated mix of
+ * 128 requests of 2 to 6 modes engine 0 serves more (19.8 against 16.5
+ * requests/s).  Work per tick per workgroup is about chunk_work cost units
+ * (0 = default).  A request's result is bitwise the same whether it runs alone
+ * or among others, and the same as scp_propagate / scp_propagate_adjoint on
+ * the same engine (under engine 0 a forward that scp_propagate would split over
+ * time, or run a column per workgroup at eight three-level modes, has engine
+ * 1's results here).  The server allocates device memory (at admission); it is
+ * not for callers that cannot allocate.
  * ------------------------------------------------------------------------ */
 typedef struct scp_server scp_server;
 

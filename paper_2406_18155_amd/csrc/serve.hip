@@ -139,8 +139,10 @@ struct scp_server {
   size_t budget = 0, used = 0;
   int max_active = 64;
   // engine of admissions, as scp_system_set_engine (0 automatic, 1 register,
-  // 2 gather); the register-layout kernels by default: batched, they give the
-  // higher throughput under load
+  // 2 gather); the register-layout kernels by default, whose results a request
+  // without the choice has always had.  Not the faster ones since the gather
+  // engine's real form: 16.5 requests/s against 19.8 with engine 0 (128 requests
+  // of 2 to 6 modes at once)
   int engine = 1;
   double chunk_work = 2.0e7;   // per-tick work budget per workgroup (cost units)
   hipStream_t stream = nullptr;        // admission (builds and uploads)
