@@ -158,6 +158,36 @@ __device__ __forceinline__ void cmac_conj(float& sr, float& si, c32 a, c32 b) {
   si = fmaf(a.x, b.y, si);
   si = fmaf(-a.y, b.x, si);
 }
+__device__ __forceinline__ c32 c_mul(c32 a, c32 b) {
+  c32 z;
+  z.x = fmaf(-a.y, b.y, a.x * b.x);
+  z.y = fmaf(a.x, b.y, a.y * b.x);
+  return z;
+}
+__device__ __forceinline__ c32 c_mul_conj(c32 a, c32 b) {   // conj(a) b
+  c32 z;
+  z.x = fmaf(a.y, b.y, a.x * b.x);
+  z.y = fmaf(a.x, b.y, -a.y * b.x);
+  return z;
+}
+
+// One row of a static table (cnt entries, stride str) to registers.
+template <int cnt, int str>
+__device__ __forceinline__ void g_row(const float* __restrict__ row, float (&v)[cnt]) {
+  if constexpr (str % 4 == 0) {
+#pragma unroll
+    for (int k = 0; k < str / 4; ++k) {
+      const float4 q = reinterpret_cast<const float4*>(row)[k];
+      if (4 * k < cnt) v[4 * k] = q.x;
+      if (4 * k + 1 < cnt) v[4 * k + 1] = q.y;
+      if (4 * k + 2 < cnt) v[4 * k + 2] = q.z;
+      if (4 * k + 3 < cnt) v[4 * k + 3] = q.w;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < cnt; ++k) v[k] = row[k];
+  }
+}
 
 template <int CTRL>
 __device__ __forceinline__ float g_dpp(float v) {

@@ -86,30 +86,13 @@ struct RCoef {
 };
 
 template <int d, int N>
-__device__ __forceinline__ void r_row(const float* __restrict__ row, float* v, int cnt, int str) {
-  if (str % 4 == 0) {
-#pragma unroll
-    for (int k = 0; k < str / 4; ++k) {
-      const float4 q = reinterpret_cast<const float4*>(row)[k];
-      if (4 * k < cnt) v[4 * k] = q.x;
-      if (4 * k + 1 < cnt) v[4 * k + 1] = q.y;
-      if (4 * k + 2 < cnt) v[4 * k + 2] = q.z;
-      if (4 * k + 3 < cnt) v[4 * k + 3] = q.w;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < cnt; ++k) v[k] = row[k];
-  }
-}
-
-template <int d, int N>
 __device__ __forceinline__ void r_coef(const float* __restrict__ tab, uint32_t pk, RCoef<d, N>& C) {
   using R = RShape<d, N>;
 #pragma unroll
   for (int p = 0; p < N; ++p) {
     const int row = ket_digit(pk, R::pi(p)) * d + ket_digit(pk, R::pj(p));
-    r_row<d, N>(tab + (p * d * d + row) * R::pr, C.g[p], R::nn, R::pr);
-    r_row<d, N>(tab + R::off_d + (p * d + ket_digit(pk, p)) * R::dr, C.o[p], R::n, R::dr);
+    g_row<R::nn, R::pr>(tab + (p * d * d + row) * R::pr, C.g[p]);
+    g_row<R::n, R::dr>(tab + R::off_d + (p * d + ket_digit(pk, p)) * R::dr, C.o[p]);
   }
 }
 
@@ -149,19 +132,6 @@ __device__ __forceinline__ void r_apply(const c32* __restrict__ ye, const RElem<
     kr = fmaf(c[m], sr, kr);
     ki = fmaf(c[m], si, ki);
   }
-}
-
-__device__ __forceinline__ c32 r_mul(c32 a, c32 b) {
-  c32 z;
-  z.x = fmaf(-a.y, b.y, a.x * b.x);
-  z.y = fmaf(a.x, b.y, a.y * b.x);
-  return z;
-}
-__device__ __forceinline__ c32 r_mul_conj(c32 a, c32 b) {   // conj(a) b
-  c32 z;
-  z.x = fmaf(a.y, b.y, a.x * b.x);
-  z.y = fmaf(a.x, b.y, -a.y * b.x);
-  return z;
 }
 
 // What a thread keeps of its elements and of the drives.
@@ -256,7 +226,7 @@ struct RThread {
         if (!((pmask >> p) & 1)) return;
         if constexpr (i > 0) {
           float g[R::nn];
-          r_row<d, N>(rt + (p * d * d + ket_digit(p0, i) * d + ket_digit(p0, j)) * R::pr, g, R::nn, R::pr);
+          g_row<R::nn, R::pr>(rt + (p * d * d + ket_digit(p0, i) * d + ket_digit(p0, j)) * R::pr, g);
           const c32* q = ye + (El.o[i] + El.o[j]);
 #pragma unroll
           for (int r = 0; r < E; ++r)
@@ -278,7 +248,7 @@ struct RThread {
 #pragma unroll
           for (int r = 0; r < E; ++r) {
             float g[R::nn];
-            r_row<d, N>(rt + (p * d * d + r * d + ket_digit(p0, j)) * R::pr, g, R::nn, R::pr);
+            g_row<R::nn, R::pr>(rt + (p * d * d + r * d + ket_digit(p0, j)) * R::pr, g);
 #pragma unroll
             for (int x = 0; x < n; ++x) {
               const int b = ((r & 1) ^ 1) + 2 * x;
@@ -297,12 +267,12 @@ struct RThread {
         constexpr int m = decltype(M)::value;
         if (!((dmask >> m) & 1)) return;
         float o[n];
-        if constexpr (m > 0) r_row<d, N>(rt + R::off_d + (m * d + ket_digit(p0, m)) * R::dr, o, n, R::dr);
+        if constexpr (m > 0) g_row<n, R::dr>(rt + R::off_d + (m * d + ket_digit(p0, m)) * R::dr, o);
         const c32* q = ye + El.o[m];
 #pragma unroll
         for (int r = 0; r < E; ++r) {
           float sr = 0.f, si = 0.f;
-          if constexpr (m == 0) r_row<d, N>(rt + R::off_d + r * R::dr, o, n, R::dr);
+          if constexpr (m == 0) g_row<n, R::dr>(rt + R::off_d + r * R::dr, o);
 #pragma unroll
           for (int x = 0; x < n; ++x) {
             const int b = ((r & 1) ^ 1) + 2 * x;
@@ -376,7 +346,7 @@ __device__ __forceinline__ void g_real_rk4_body(const GArgs* __restrict__ Ag,
     c32 v;
     v.x = hr[r];
     v.y = hm[r];
-    y[r] = r_mul_conj(P0[r], v);
+    y[r] = c_mul_conj(P0[r], v);
     if (e < L) lds[e] = y[r];
   }
   __syncthreads();
@@ -414,7 +384,7 @@ __device__ __forceinline__ void g_real_rk4_body(const GArgs* __restrict__ Ag,
           c32 u;
           if constexpr (RThread<d, N>::SHARE) u = ks[r];
           else Th.apply(r, yc, s == 0 ? c0 : (s == 3 ? c2 : c1), y[r], u.x, u.y);
-          u = r_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
+          u = c_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
           kr = u.y;    // k = -i P R P^dag y
           ki = -u.x;
           ar[r] = s == 0 ? kr : fmaf(w, kr, ar[r]);
@@ -430,7 +400,7 @@ __device__ __forceinline__ void g_real_rk4_body(const GArgs* __restrict__ Ag,
             v.x = hr[r];
             v.y = hm[r];
           }
-          y[r] = r_mul_conj(s < 2 ? P1[r] : P2[r], v);
+          y[r] = c_mul_conj(s < 2 ? P1[r] : P2[r], v);
           yn[e] = y[r];
         }
       }
@@ -525,7 +495,7 @@ __device__ __forceinline__ void g_real_cos_body(const GArgs* __restrict__ Ag,
         c32 v;
         v.x = s == 3 ? cs * lhr[r] : fmaf(cs, lhr[r], cy * ybr[r]);
         v.y = s == 3 ? cs * lhm[r] : fmaf(cs, lhm[r], cy * ybm[r]);
-        kb[r] = r_mul_conj(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), v);
+        kb[r] = c_mul_conj(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), v);
         if (e < L) kbw[e] = kb[r];
       }
       __syncthreads();
@@ -538,7 +508,7 @@ __device__ __forceinline__ void g_real_cos_body(const GArgs* __restrict__ Ag,
           c32 u;
           if constexpr (RThread<d, N>::SHARE) u = ks[r];
           else Th.apply(r, kbw, s == 0 ? c0 : (s == 3 ? c2 : c1), kb[r], u.x, u.y);
-          u = r_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
+          u = c_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
           ybr[r] = -u.y;   // yb = i P R P^dag kb
           ybm[r] = u.x;
           llr[r] -= u.y;
@@ -629,7 +599,7 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
       c32 v;
       v.x = q.x;
       v.y = q.y;
-      y[r] = r_mul_conj(P0[r], v);
+      y[r] = c_mul_conj(P0[r], v);
       if (e < L) {
         lds[e] = y[r];
         segc[e] = y[r];
@@ -660,7 +630,7 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
             c32 u;
             if constexpr (RThread<d, N>::SHARE) u = ks[r];
             else Th.apply(r, yc, s == 0 ? c0 : (s == 3 ? c2 : c1), y[r], u.x, u.y);
-            u = r_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
+            u = c_mul(s == 0 ? P0[r] : (s == 3 ? P2[r] : P1[r]), u);
             kr = u.y;
             ki = -u.x;
             ar[r] = s == 0 ? kr : fmaf(w, kr, ar[r]);
@@ -676,7 +646,7 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
               v.x = hr[r];
               v.y = hm[r];
             }
-            y[r] = r_mul_conj(s < 2 ? P1[r] : P2[r], v);
+            y[r] = c_mul_conj(s < 2 ? P1[r] : P2[r], v);
             yn[e] = y[r];
             if (keep) ys[e] = y[r];
           }
@@ -764,7 +734,7 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
         c32 v;
         v.x = s == 3 ? cs * lhr[r] : fmaf(cs, lhr[r], cy * ybr[r]);
         v.y = s == 3 ? cs * lhm[r] : fmaf(cs, lhm[r], cy * ybm[r]);
-        kb[r] = r_mul_conj(P[r], v);
+        kb[r] = c_mul_conj(P[r], v);
         if (e < L) kbw[e] = kb[r];
       }
       __syncthreads();
@@ -789,7 +759,7 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
           c32 u;
           if constexpr (RThread<d, N>::SHARE) u = ks[r];
           else Th.apply(r, kbw, c, kb[r], u.x, u.y);
-          u = r_mul(P[r], u);
+          u = c_mul(P[r], u);
           ybr[r] = -u.y;
           ybm[r] = u.x;
           llr[r] -= u.y;
@@ -819,12 +789,12 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
             RElem<d, N> El;
             El.set(pk);
             float a[R::gr], b[R::gr];
-            r_row<d, N>(gt + ((j * 2 + (u >> 1)) * d + ket_digit(pk, j)) * R::gr, b, R::gr, R::gr);
-            if (i > 0) r_row<d, N>(gt + ((i * 2 + (u & 1)) * d + ket_digit(pk, i)) * R::gr, a, R::gr, R::gr);
+            g_row<R::gr, R::gr>(gt + ((j * 2 + (u >> 1)) * d + ket_digit(pk, j)) * R::gr, b);
+            if (i > 0) g_row<R::gr, R::gr>(gt + ((i * 2 + (u & 1)) * d + ket_digit(pk, i)) * R::gr, a);
             float ta = 0.f, t0 = 0.f, t1 = 0.f, t2 = 0.f, u0 = 0.f, u1 = 0.f, u2 = 0.f;
 #pragma unroll
             for (int r = 0; r < E; ++r) {
-              if (i == 0) r_row<d, N>(gt + ((u & 1) * d + r) * R::gr, a, R::gr, R::gr);
+              if (i == 0) g_row<R::gr, R::gr>(gt + ((u & 1) * d + r) * R::gr, a);
               const c32 ye = y[r];
               c32 v[n_][n_];
 #pragma unroll
@@ -889,8 +859,8 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
               const int u = uni(A->rp_u[p][k]);
               const float g = A->rp_g[p][k], sg = A->rp_s[p][k];
               float a[R::gr], b[R::gr];
-              r_row<d, N>(gt + (i * 2 + (u & 1)) * d * R::gr + ri, a, R::gr, R::gr);
-              r_row<d, N>(gt + (j * 2 + (u >> 1)) * d * R::gr + rj, b, R::gr, R::gr);
+              g_row<R::gr, R::gr>(gt + (i * 2 + (u & 1)) * d * R::gr + ri, a);
+              g_row<R::gr, R::gr>(gt + (j * 2 + (u >> 1)) * d * R::gr + rj, b);
               float ta = 0.f, t0 = 0.f, t1 = 0.f, t2 = 0.f, u0 = 0.f, u1 = 0.f, u2 = 0.f;
 #pragma unroll
               for (int x = 0; x < n_; ++x) {
@@ -947,7 +917,7 @@ __device__ __forceinline__ void g_real_seg_body(const GArgs* __restrict__ Ag,
           const c32 ye = y[r];
           if (!once || m == 0 || r == 0) {
             de = *reinterpret_cast<const float4*>(gt + R::off_e + (m * d + a_) * 4);
-            if (drv) r_row<d, N>(gt + ((m * 2 + u) * d + a_) * R::gr, a, R::gr, R::gr);
+            if (drv) g_row<R::gr, R::gr>(gt + ((m * 2 + u) * d + a_) * R::gr, a);
           }
           const float w0 = fmaf(kb[r].x, ye.y, -kb[r].y * ye.x);
           t[m][0] = fmaf(de.x, w0, t[m][0]);

@@ -40,7 +40,7 @@ namespace {
 template <int d, int N, bool OPEN>
 struct LShape {
   static constexpr int D = cpow(d, N), L = OPEN ? D * D : D;
-  static constexpr int H = L == 6561 ? 2 : 1;          // modes of A within a thread
+  static constexpr int H = L / d > 1024 ? 2 : 1;       // modes of A within a thread
   static constexpr int E = cpow(d, H), T = L / E;      // elements tid + r T of a thread
   static constexpr int TB = (T + 63) / 64 * 64, NW = TB / 64;
   static constexpr int n = Nb<d, true>::n, nn = n * n, dd = d * d;
@@ -76,36 +76,6 @@ struct LShape {
   static constexpr int rd(int r, int m) { return r / rs(m) % d; }
   static constexpr int place(int a, int b) { return (b - ((a & 1) ^ 1)) / 2; }
 };
-
-__device__ __forceinline__ c32 l_mul(c32 a, c32 b) {
-  c32 z;
-  z.x = fmaf(-a.y, b.y, a.x * b.x);
-  z.y = fmaf(a.x, b.y, a.y * b.x);
-  return z;
-}
-__device__ __forceinline__ c32 l_mul_conj(c32 a, c32 b) {   // conj(a) b
-  c32 z;
-  z.x = fmaf(a.y, b.y, a.x * b.x);
-  z.y = fmaf(a.x, b.y, -a.y * b.x);
-  return z;
-}
-
-template <int cnt, int str>
-__device__ __forceinline__ void l_row(const float* __restrict__ row, float (&v)[cnt]) {
-  if constexpr (str % 4 == 0) {
-#pragma unroll
-    for (int k = 0; k < str / 4; ++k) {
-      const float4 q = reinterpret_cast<const float4*>(row)[k];
-      if (4 * k < cnt) v[4 * k] = q.x;
-      if (4 * k + 1 < cnt) v[4 * k + 1] = q.y;
-      if (4 * k + 2 < cnt) v[4 * k + 2] = q.z;
-      if (4 * k + 3 < cnt) v[4 * k + 3] = q.w;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < cnt; ++k) v[k] = row[k];
-  }
-}
 
 // Keeps the sums of an element where its neighbours are read: moved behind all
 // elements' reads they would hold every read value in a register.
@@ -230,7 +200,7 @@ struct LThread {
       float g[C][S::nn];
 #pragma unroll
       for (int c = 0; c < C; ++c)
-        l_row<S::nn, S::pr>(rows + c * cs + (X.dig(side, i) * d + X.dig(side, j)) * S::pr, g[c]);
+        g_row<S::nn, S::pr>(rows + c * cs + (X.dig(side, i) * d + X.dig(side, j)) * S::pr, g[c]);
       if (side == 1) {
 #pragma unroll
         for (int c = 0; c < C; ++c)
@@ -261,7 +231,7 @@ struct LThread {
       for (int c = 0; c < C; ++c)
 #pragma unroll
         for (int a = 0; a < d; ++a)
-          l_row<S::nn, S::pr>(rows + c * cs + (a * d + X.dig(0, j)) * S::pr, g[c][a]);
+          g_row<S::nn, S::pr>(rows + c * cs + (a * d + X.dig(0, j)) * S::pr, g[c][a]);
       const c32* q = yc + tid + X.o(0, j);
 #pragma unroll
       for (int r0 = 0; r0 < E; ++r0) {
@@ -317,7 +287,7 @@ struct LThread {
     const Digits X = digits();
     if constexpr (side == 1 || m >= H) {
       float g[n];
-      l_row<n, S::dr>(tab + S::off_d + (m * d + X.dig(side, m)) * S::dr, g);
+      g_row<n, S::dr>(tab + S::off_d + (m * d + X.dig(side, m)) * S::dr, g);
 #pragma unroll
       for (int x = 0; x < n; ++x) g[x] *= side == 1 ? -c : c;
       const c32* q = yc + tid + X.o(side, m);
@@ -530,7 +500,7 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
     v.x = q.x;
     v.y = q.y;
     set_low(r, l);
-    y[r] = l_mul_conj(P0[r], v);
+    y[r] = c_mul_conj(P0[r], v);
     if (on) {
       lds[e] = y[r];
       if (SEG) segc[e] = y[r];
@@ -571,7 +541,7 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
       const float w0 = s == 0 ? 0.f : 1.f;
 #pragma unroll
       for (int r = 0; r < E; ++r) {
-        x[r] = l_mul(P[r], x[r]);
+        x[r] = c_mul(P[r], x[r]);
         ar[r] = fmaf(w, x[r].x, w0 * ar[r]);
         ai[r] = fmaf(w, x[r].y, w0 * ai[r]);
       }
@@ -581,7 +551,7 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
           c32 v;
           v.x = fmaf(ch, x[r].x, hr[r]);
           v.y = fmaf(ch, x[r].y, hm[r]);
-          y[r] = l_mul_conj(Q[r], v);
+          y[r] = c_mul_conj(Q[r], v);
         }
       } else {
         const float h6 = h * (1.0f / 6.0f);
@@ -593,7 +563,7 @@ __device__ __forceinline__ void l_steps(kptr<GArgs> A, const GAdj* __restrict__ 
           set_low(r, l);
           v.x = hr[r];
           v.y = hm[r];
-          y[r] = l_mul_conj(Q[r], v);
+          y[r] = c_mul_conj(Q[r], v);
         }
       }
       if (on) {
@@ -726,7 +696,7 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
       l.x = v.z;
       l.y = v.w;
       set_low(r, l);
-      kb[r] = l_mul_conj(P1[r], k);
+      kb[r] = c_mul_conj(P1[r], k);
       if (on) lds[e] = kb[r];
     }
     __syncthreads();
@@ -868,7 +838,7 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
           c32 x;
           x.x = fmaf(f, kb[r].x, -z[r].y);
           x.y = fmaf(f, kb[r].y, z[r].x);
-          z[r] = l_mul(P[r], x);
+          z[r] = c_mul(P[r], x);
         }
         // the step's increments yb gather in the low word; at its end they go
         // into hi (fast two-sum), which the next stage's kb starts from
@@ -886,7 +856,7 @@ l_adj_kernel(const GArgs* __restrict__ Ag, const GAdj* __restrict__ Bg) {
           c32 k;
           k.x = fmaf(cs, u, cy * z[r].x);
           k.y = fmaf(cs, v, cy * z[r].y);
-          kb[r] = l_mul_conj(Q[r], k);
+          kb[r] = c_mul_conj(Q[r], k);
         }
         if (on) {
 #pragma unroll
@@ -945,6 +915,8 @@ hipError_t l_real_forward(int d, int N, const GArgs* dargs, const GAdj* dadj, in
   return hipErrorInvalidValue;
 }
 
+// The one shape above the gather engine's D <= 4096 whose two buffers and low words
+// (24 D bytes) fit the 160 KB of LDS with rows of more than one entry.
 bool l_column_supported(int d, int N) { return d == 3 && N == 8; }
 
 hipError_t l_real_column(int d, int N, const GArgs* dargs, int S, int n_lo, int n_hi,
