@@ -100,8 +100,8 @@ KERNEL_SOURCES = {
     "rk4": ("rk4.hip", "kernel_common.h", "internal.h"),
     "recompute": ("rk4.hip", "kernel_common.h", "internal.h"),
     "adjoint": ("adjoint.hip", "kernel_common.h", "internal.h"),
-    "lindblad": ("gather.hip", "kernel_common.h", "internal.h"),
-    "gather": ("gather.hip", "kernel_common.h", "internal.h"),
+    "lindblad": ("open_real.hip", "gather.hip", "gather.h", "kernel_common.h", "internal.h"),
+    "gather": ("gather.hip", "gather_real.hip", "gather.h", "kernel_common.h", "internal.h"),
 }
 
 
@@ -889,15 +889,15 @@ def main():
                 "share_of_step": ms / args.steps / (dt * 1e3), "note": bound_note}
         return line
 
-    rf = "true" if args.frame == "real" else "false"
+    ev = 3 if args.frame == "real" else 2   # evaluation: real frame (1) and parity (2)
     sfx = "" if args.frame == "real" else "_complex"
     kernels = {
-        "reverse": kernel_line("reverse", f"adjoint_kernel<3,3,1,{rf}>", "adjoint_ring8_d3" + sfx,
+        "reverse": kernel_line("reverse", f"adjoint_kernel<3,3,1,{ev}>", "adjoint_ring8_d3" + sfx,
                                "reverse walk of one checkpoint segment: per stage C reverse "
                                "contractions + (3 per pair + 1 per mode) sensitivity contractions"),
-        "forward": kernel_line("forward", f"rk4_kernel<3,3,1,false,{rf}>", "rk4_ring8_d3" + sfx,
+        "forward": kernel_line("forward", f"rk4_kernel<3,3,1,false,{ev}>", "rk4_ring8_d3" + sfx,
                                "the whole 3000-step forward in one launch, C contractions per stage"),
-        "recompute": kernel_line("recompute", f"rk4_kernel<3,3,1,true,{rf}>",
+        "recompute": kernel_line("recompute", f"rk4_kernel<3,3,1,true,{ev}>",
                                  "recompute_ring8_d3" + sfx,
                                  "one checkpoint segment forward, stage inputs stored"),
     }
