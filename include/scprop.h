@@ -564,7 +564,7 @@ void scp_destroy(scp_system* sys);
  * segment; while nothing waits for admission, buffers for more are lent to it
  * within the budget, and taken back when a request needs the room.  The server
  * starts with engine 1 (the register-layout kernels); on a saturated mix of
- * 128 requests of 2 to 6 modes engine 0 serves more (19.8 against 16.5
+ * 128 requests of 2 to 6 modes engine 0 serves more (19.4 against 16.4
  * requests/s).  Work per tick per workgroup is about chunk_work cost units
  * (0 = default).  A request's result is bitwise the same whether it runs alone
  * or among others, and the same as scp_propagate / scp_propagate_adjoint on

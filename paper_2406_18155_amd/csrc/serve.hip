@@ -141,7 +141,7 @@ struct scp_server {
   // engine of admissions, as scp_system_set_engine (0 automatic, 1 register,
   // 2 gather); the register-layout kernels by default, whose results a request
   // without the choice has always had.  Not the faster ones since the gather
-  // engine's real form: 16.5 requests/s against 19.8 with engine 0 (128 requests
+  // engine's real form: 16.4 requests/s against 19.4 with engine 0 (128 requests
   // of 2 to 6 modes at once)
   int engine = 1;
   double chunk_work = 2.0e7;   // per-tick work budget per workgroup (cost units)
